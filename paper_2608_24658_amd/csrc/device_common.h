@@ -36,7 +36,10 @@ constexpr int LOADS = SEG_VEC / WAVE;    /* vector loads per lane per segment */
  * bytes in all. */
 constexpr int GATHER_SLOTS = 4;
 constexpr int POOL_PER_SEG = 8;
-constexpr int64_t POOL_MIN = (int64_t)1 << 20;
+#ifndef PARASON_POOL_MIN
+#define PARASON_POOL_MIN ((int64_t)1 << 20)
+#endif
+constexpr int64_t POOL_MIN = PARASON_POOL_MIN;
 /* A segment's event list (or, in its first segment, a compact row's): its
  * length and its first slot.  Slot indices fit 32 bits for any batch one GPU
  * holds (the host refuses larger ones). */

@@ -34,7 +34,14 @@ constexpr int64_t MAX_SEGMENTS =
     (((int64_t)1 << 32) - 1 - pk::POOL_MIN) / (pk::GATHER_SLOTS + pk::POOL_PER_SEG);
 constexpr int MID_BLOCKS_PER_CU = 2; /* rows_mid blocks hold 64 KB of LDS frames each */
 constexpr int GATHER_BLOCKS_PER_CU = 8; /* 4-wave blocks of gather_rows */
-constexpr int ROWS_WAVES_PER_CU = 20;   /* rows_fast waves a CU holds (8 KB of LDS frames each) */
+#ifndef PARASON_PAR_ROWS_PER_CU
+#define PARASON_PAR_ROWS_PER_CU 40
+#endif
+#ifndef PARASON_FAST_WAVES_PER_CU
+#define PARASON_FAST_WAVES_PER_CU 20
+#endif
+constexpr int PAR_ROWS_PER_CU = PARASON_PAR_ROWS_PER_CU;     /* rows_par below this many rows per CU */
+constexpr int FAST_WAVES_PER_CU = PARASON_FAST_WAVES_PER_CU; /* rows_fast waves a CU holds (8 KB of LDS frames each) */
 
 /* Byte offsets of the workspace sections for n rows. */
 struct Layout {
@@ -160,32 +167,30 @@ void find_tag_hash(pk::TagMatch &tm)
  * The deep tier is a launch of its own only when deep_launch is set (the
  * batch-wide statistics need every row first); otherwise group_reward runs
  * it. */
-/* A small batch (fewer rows than ROWS_WAVES_PER_CU waves on every CU, with
- * two rows per wave) takes rows_par, one wave per row. */
-bool rows_par_batch(int64_t n, int cus) { return n / 2 < (int64_t)cus * ROWS_WAVES_PER_CU; }
+/* A small batch takes rows_par, one wave per row. */
+bool rows_par_batch(int64_t n, int cus) { return n < (int64_t)cus * PAR_ROWS_PER_CU; }
 
 template <bool LENIENT>
 void launch_rows(const pk::RowArgs &ra, const pk::GatherArgs &ga, int cus, uint8_t *mode, int32_t *counters,
                  int32_t *mid_rows, int32_t *deep_rows, int32_t *deep_frames, uint32_t *deep_bits, bool deep_launch,
                  hipStream_t stream)
 {
-    /* A small batch (fewer rows than ROWS_WAVES_PER_CU waves on every CU):
-     * rows_par, one wave per row, its lanes over the row's events.  A larger
-     * one: rows_fast, one row per lane, with as many rows per wave as keep
-     * ROWS_WAVES_PER_CU waves on every CU (64 once the batch is large). */
-    int64_t per_wave = 1;
-    int32_t lane_shift = 6; /* log2(64 / per_wave) */
-    /* per_wave stays 1 exactly when rows_par_batch(ra.n, cus) */
-    while (per_wave < 64 && ra.n / (per_wave * 2) >= (int64_t)cus * ROWS_WAVES_PER_CU) {
-        per_wave *= 2;
-        --lane_shift;
-    }
-    const unsigned row_blocks = (unsigned)((ra.n + per_wave - 1) / per_wave);
-    if (per_wave == 1) {
+    /* A small batch: rows_par, one wave per row, its lanes over the row's
+     * events.  A larger one: rows_fast, one row per lane, with as many rows
+     * per wave as keep FAST_WAVES_PER_CU waves on every CU (64 once the batch
+     * is large). */
+    if (rows_par_batch(ra.n, cus)) {
         /* rows_par runs the rows it does not hold through the automaton
          * itself (the second tier), so rows_mid has nothing to do */
-        hipLaunchKernelGGL(pk::rows_par<LENIENT>, dim3(row_blocks), dim3(64), 0, stream, ra, mode, counters, deep_rows);
+        hipLaunchKernelGGL(pk::rows_par<LENIENT>, dim3((unsigned)ra.n), dim3(64), 0, stream, ra, mode, counters, deep_rows);
     } else {
+        int64_t per_wave = 1;
+        int32_t lane_shift = 6; /* log2(64 / per_wave) */
+        while (per_wave < 64 && ra.n / (per_wave * 2) >= (int64_t)cus * FAST_WAVES_PER_CU) {
+            per_wave *= 2;
+            --lane_shift;
+        }
+        const unsigned row_blocks = (unsigned)((ra.n + per_wave - 1) / per_wave);
         /* the per-lane automaton reads split rows best as compact lists */
         hipLaunchKernelGGL(pk::gather_rows, dim3((unsigned)(cus * GATHER_BLOCKS_PER_CU)), dim3(256), 0, stream, ga);
         hipLaunchKernelGGL(pk::rows_fast<LENIENT>, dim3(row_blocks), dim3(64), 0, stream, ra, mode, counters, mid_rows,
@@ -371,8 +376,10 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     sa.seg_cap = cap;
     sa.seg = seg;
     sa.slots = slots;
-    sa.pool_base = (uint32_t)q.pool_base;
-    sa.pool_slots = (uint32_t)q.pool_slots;
+    /* only the row tiers after gather_rows use the gather slots */
+    const bool par = rows_par_batch(n_traj, cus);
+    sa.pool_base = par ? 0u : (uint32_t)q.pool_base;
+    sa.pool_slots = (uint32_t)(par ? q.pool_base + q.pool_slots : q.pool_slots);
     sa.mode = mode;
     sa.tm = h->tm;
     sa.split_count = counters + 2;

@@ -24,13 +24,14 @@
  *        list with row positions in the row's gather slots (mode[i] = 1).
  *   rows_par  (small batches: one wave per row, four events per lane)
  *        Validity from local checks and a depth prefix sum; latency and branch
- *        tokens level by level with segmented scans (DPP).  A row it cannot
- *        hold runs through the automaton on one lane, with MID_DEPTH frames in
+ *        tokens level by level with segmented scans (DPP).  A segment whose
+ *        events the scan could not store (marked DENSE) is read again by the
+ *        wave.  A row it cannot hold runs through the automaton on one lane, with MID_DEPTH frames in
  *        LDS, as in rows_mid.
  *   rows_fast  (larger batches: one thread per row)
  *        The grammar's pushdown automaton over the row's events; Text runs are
- *        the gaps between event positions.  A segment whose events the scan
- *        could not store (marked DENSE) is classified again token by token.
+ *        the gaps between event positions.  Rows with a DENSE segment are
+ *        evaluated by their wave as in rows_par.
  *        Frames of open blocks in LDS (FAST_DEPTH per row, 64 outline entries
  *        per block); a row that needs more is handed to rows_mid.
  *   rows_mid  (after rows_fast: one thread per handed-over row, MID_DEPTH
@@ -512,7 +513,8 @@ struct RowArgs {
     RowOut out;
 };
 
-/* Feed row r's events to A.  Returns false when A stopped early.
+/* Feed row r's events to A.  Returns false when A stopped early, or (STOP_DENSE)
+ * at a segment marked DENSE, which sets *dense.
  *
  * Three sources, all feeding the one call of A.event below: a compact list
  * (the whole row: seg[first], row positions), or per segment
@@ -522,9 +524,9 @@ struct RowArgs {
  * gfx950 build returned wrong results for dense segments although the same
  * source is correct when compiled for the CPU, so the sources are merged into
  * one fetch loop. */
-template <class Store, bool LENIENT>
+template <bool STOP_DENSE, class Store, bool LENIENT>
 __device__ bool drive_row(const RowArgs &a, int64_t r, int64_t g, int32_t len, bool compact,
-                          Automaton<Store, LENIENT> &A)
+                          Automaton<Store, LENIENT> &A, bool *dense_out = nullptr)
 {
     const int64_t s0 = a.seg_off[r], s1 = a.seg_off[r + 1];
     const int64_t vrow0 = row_first_vec(g), vend = row_end_vec(g, len);
@@ -556,7 +558,7 @@ __device__ bool drive_row(const RowArgs &a, int64_t r, int64_t g, int32_t len, b
                 c = w & 15u;
                 break;
             }
-            if (dense) {
+            if (!STOP_DENSE && dense) {
                 while (q < q_end) {
                     const int32_t t = a.tok_base[q];
                     const int64_t pp = q - g;
@@ -581,6 +583,9 @@ __device__ bool drive_row(const RowArgs &a, int64_t r, int64_t g, int32_t len, b
             if (n_s != DENSE) {
                 cnt = n_s;
                 ev = a.slots + rec.list; /* not read when n_s is 0 */
+            } else if (STOP_DENSE) {
+                *dense_out = true;
+                return false;
             } else {
                 cnt = 0;
                 dense = true;
@@ -593,44 +598,6 @@ __device__ bool drive_row(const RowArgs &a, int64_t r, int64_t g, int32_t len, b
         if (!A.event(p, c)) return false;
     }
     return true;
-}
-
-/* One thread per row.  mode[r] == MODE_COMPACT: the scan left the row's events as one
- * compact list; 0: per-segment lists.  A row that needs more than FAST_DEPTH
- * frames (or more than 64 entries in an open block) is listed for rows_mid.
- * Few frames keep the LDS per block small, so that many waves hide the
- * latency of the branchy automaton. */
-template <bool LENIENT>
-__global__ void __launch_bounds__(64) rows_fast(RowArgs a, const uint8_t *__restrict__ mode,
-                                                int32_t *__restrict__ counters, int32_t *__restrict__ mid_rows,
-                                                int32_t lane_shift)
-{
-    __shared__ int32_t lds[FAST_DEPTH * FRAME_WORDS * 64];
-    /* every (1 << lane_shift)-th lane takes a row (64 >> lane_shift rows per wave) */
-    if ((threadIdx.x & ((1u << lane_shift) - 1u)) != 0) return;
-    const int64_t r = (int64_t)blockIdx.x * (blockDim.x >> lane_shift) + (threadIdx.x >> lane_shift);
-    if (r >= a.n) return;
-    const int64_t start = a.starts[r];
-    const int32_t len = a.lengths[r];
-    if (start < 0 || len < 0) {
-        write_row(a.out, r, 0, 0, 0, 0, 0, 0, 0, PARASON_FLAG_BAD_ROW);
-        return;
-    }
-    if (a.seg_off[a.n] > a.seg_cap) {
-        write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_WS_OVERFLOW);
-        return;
-    }
-    Automaton<LdsStore<FAST_DEPTH>, LENIENT> A;
-    A.st.lds = lds;
-    A.st.tid = threadIdx.x;
-    A.st.nt = blockDim.x;
-    A.init();
-    if (drive_row(a, r, start + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
-    if (A.overflow) {
-        mid_rows[atomicAdd(&counters[0], 1)] = (int32_t)r;
-        return; /* rows_mid writes this row */
-    }
-    write_result(a.out, r, len, A);
 }
 
 /* The rows rows_fast listed, one thread each (grid-stride over the list), with
@@ -652,7 +619,7 @@ __global__ void __launch_bounds__(64) rows_mid(RowArgs a, uint8_t *__restrict__ 
         A.st.tid = threadIdx.x;
         A.st.nt = blockDim.x;
         A.init();
-        if (drive_row(a, r, a.starts[r] + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
+        if (drive_row<false>(a, r, a.starts[r] + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
         if (A.overflow) {
             mode[r] |= MODE_DEEP;
             int32_t slot = atomicAdd(&counters[1], 1);
@@ -680,7 +647,7 @@ __device__ void run_deep_rows(const RowArgs &a, const uint8_t *__restrict__ mode
         A.st.max_bits = a.deep_bits;
         A.st.esp = 0;
         A.init();
-        if (drive_row(a, r, a.starts[r] + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
+        if (drive_row<false>(a, r, a.starts[r] + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
         if (A.overflow)
             write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_DEPTH_LIMIT);
         else
@@ -871,8 +838,79 @@ __device__ __forceinline__ void par_seg_scan(int32_t (&v)[PAR_K], const bool (&h
     }
 }
 
-/* One wave per row, its lanes over the row's events, four consecutive events
- * per lane (a small batch).  The same results as the automaton, from the
+/* The LDS of a wave that evaluates a row with its lanes over the row's events:
+ * per event its position, its class with the depth and the open threads before
+ * it (one word), and, while the levels are evaluated, a thread's tokens and a
+ * block's saved tokens.  Until phase A the last two hold the map from event to
+ * segment of the split-row gather.  8 KB per wave, so that 20 waves (rows) fit
+ * a compute unit; with a word per quantity (16 KB) it was 10. */
+struct ParLds {
+    int32_t P[PAR_EVENTS];
+    int32_t X[PAR_EVENTS]; /* class | depth before << 4 | threads before << 16 */
+    int32_t TOK[PAR_EVENTS];
+    int32_t SAV[PAR_EVENTS];
+};
+constexpr int PAR_LDS = 4 * PAR_EVENTS; /* words */
+static_assert(PAR_EVENTS < (1 << 12), "depths and thread counts of a held row fit their fields");
+static_assert(PAR_EVENTS >= 2 * PAR_PASS, "the gather keeps two words per segment of a chunk in SAV");
+static_assert(MID_DEPTH * FRAME_WORDS <= PAR_EVENTS, "the automaton's frames fit TOK");
+
+__device__ __forceinline__ int32_t par_class(int32_t x) { return x & 15; }
+__device__ __forceinline__ int32_t par_depth(int32_t x) { return (x >> 4) & 0xfff; }
+__device__ __forceinline__ int32_t par_threads(int32_t x) { return x >> 16; }
+
+/* The tags of one segment of the row at g, read again by the whole wave: the
+ * vectors x (vector v0 + i * WAVE + lane), of which the positions inside the
+ * row count, appended to sP and sX from event m on.  Returns the new count;
+ * events past PAR_EVENTS are counted and not stored. */
+__device__ __forceinline__ int32_t par_classify(const RowArgs &a, const int4 (&x)[LOADS], int32_t bias, int32_t len,
+                                                ParLds &l, int32_t m, int lane)
+{
+    const bool contig = a.tm.contiguous != 0;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int32_t t[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
+        const int32_t p0 = bias + 4 * (i * WAVE + lane); /* row position of the vector's first token */
+        uint32_t c[4];
+        uint64_t b[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            c[j] = (uint32_t)(p0 + j) < (uint32_t)len ? classify(a.tm, t[j], contig) : (uint32_t)C_TEXT;
+            b[j] = __ballot(c[j] != C_TEXT);
+        }
+        if ((b[0] | b[1] | b[2] | b[3]) == 0) continue; /* wave-uniform */
+        uint32_t at = (uint32_t)m;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            at = __builtin_amdgcn_mbcnt_hi((uint32_t)(b[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[j], at));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (c[j] != C_TEXT) {
+                if (at < (uint32_t)PAR_EVENTS) {
+                    l.P[at] = p0 + j;
+                    l.X[at] = (int32_t)c[j];
+                }
+                ++at;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m += __popcll(b[j]);
+    }
+    return m;
+}
+
+/* The vectors of the row's k-th segment; lanes past the row's end get the
+ * row's last vector (par_classify drops positions outside the row). */
+__device__ __forceinline__ void par_load_segment(const RowArgs &a, int64_t vrow0, int64_t vend, int64_t k,
+                                                 int4 (&x)[LOADS], int lane)
+{
+    const int4 *src = reinterpret_cast<const int4 *>(a.tok_base);
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) x[i] = src[min(vrow0 + k * SEG_VEC + i * WAVE + lane, vend - 1)];
+}
+
+/* One row by one wave, its lanes over the row's events, four consecutive
+ * events per lane.  The same results as the automaton, from the
  * structure of the grammar:
  *   - the state before a tag is fixed by the class of the tag before it, and
  *     the nesting depth before it is a prefix sum, so every check of the
@@ -886,39 +924,24 @@ __device__ __forceinline__ void par_seg_scan(int32_t (&v)[PAR_K], const bool (&h
  *     type of the outline entry it pairs with.  Evaluated level by level,
  *     deepest first, with segmented scans, one pass over the events per
  *     level (phase B).
- * Rows holding more than PAR_EVENTS events, nested deeper than PAR_LEVELS,
- * or with a dense segment, run through the automaton on lane 0 (the single
- * automaton call site of this kernel).  Split rows are read from their
- * segments' lists directly (no gather_rows launch for a small batch). */
+ * Returns false, with nothing written, for a row of more than PAR_EVENTS
+ * events or nested deeper than PAR_LEVELS.  Split rows are read from their
+ * segments' lists directly, and a segment whose list the scan could not store
+ * is read again by the wave (par_classify): for one lane alone those rows'
+ * tokens are a chain of loads that held up a whole batch (the row kernel of
+ * 8,192 rows of 3,500 tokens, whose outlines overflow a few of the scan's pool
+ * regions: 372 us, 24 us read by the wave). */
 template <bool LENIENT>
-__global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ mode,
-                                               int32_t *__restrict__ counters, int32_t *__restrict__ deep_rows)
+__device__ bool par_row(const RowArgs &a, ParLds &l, int64_t r, int64_t start, int32_t len, int64_t s0, int64_t s1,
+                        bool compact, int lane)
 {
-    __shared__ __align__(16) int32_t sP[PAR_EVENTS], sC[PAR_EVENTS], sD[PAR_EVENTS], sT[PAR_EVENTS];
-    __shared__ __align__(16) int32_t sTOK[PAR_EVENTS], sLAT[PAR_EVENTS], sOWN[PAR_EVENTS], sSAV[PAR_EVENTS];
-    const int lane = threadIdx.x;
-    const int64_t r = blockIdx.x;
-    if (r >= a.n) return;
-    /* the row's records in one round of loads, before any branch */
-    const int64_t start = a.starts[r];
-    const int32_t len = a.lengths[r];
-    const int64_t S = a.seg_off[a.n], s0 = a.seg_off[r], s1 = a.seg_off[r + 1];
-    const uint8_t md = mode[r];
-    if (start < 0 || len < 0) {
-        if (lane == 0) write_row(a.out, r, 0, 0, 0, 0, 0, 0, 0, PARASON_FLAG_BAD_ROW);
-        return;
-    }
-    if (S > a.seg_cap) {
-        if (lane == 0) write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_WS_OVERFLOW);
-        return;
-    }
     /* the row's events into LDS, in position order: from its compact list (row
      * positions), or from its segments' lists (segment positions), gathered
      * here as gather_rows does for the per-lane kernel */
     const int64_t g = start + a.mis;
     int32_t m = 0;
     bool held = true;
-    if (md & MODE_COMPACT) {
+    if (compact) {
         const SegRec rec = a.seg[s0];
         m = rec.count;
         held = m <= PAR_EVENTS;
@@ -934,8 +957,8 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
             for (int u = 0; u < 4; ++u) {
                 const int32_t i = i0 + u * WAVE + lane;
                 if (i < m) {
-                    sP[i] = (int32_t)(w[u] >> 4);
-                    sC[i] = (int32_t)(w[u] & 15u);
+                    l.P[i] = (int32_t)(w[u] >> 4);
+                    l.X[i] = (int32_t)(w[u] & 15u);
                 }
             }
         }
@@ -944,36 +967,59 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
          * round of loads and an exclusive scan of their counts; then an LDS
          * map from event to segment (each segment that holds events marks its
          * first event, a running maximum spreads the marks) and the events'
-         * loads in one round per PAR_PASS events.  Until phase A, sD holds the
-         * map and sLAT, sOWN each segment's first slot and first event. */
-        const int64_t vrow0 = row_first_vec(g);
-        for (int64_t c0 = s0; held && c0 < s1; c0 += PAR_PASS) {
+         * loads in one round per PAR_PASS events.  A chunk ends at the first
+         * DENSE segment; a run of DENSE segments at its start is read again. */
+        const int64_t vrow0 = row_first_vec(g), vend = row_end_vec(g, len);
+        int32_t *map = l.TOK, *seg_list = l.SAV, *seg_first = l.SAV + PAR_PASS;
+        for (int64_t c0 = s0; held && c0 < s1;) {
             const int32_t jb = PAR_K * lane; /* the chunk's segment of element 0 */
+            const int32_t n_c = (int32_t)min((int64_t)PAR_PASS, s1 - c0);
             int32_t cnt[PAR_K], lst[PAR_K], incl[PAR_K];
-            bool dense = false;
+            int32_t dense0 = n_c, stored0 = n_c; /* the lane's first DENSE segment, and its first other one */
 #pragma unroll
             for (int k = 0; k < PAR_K; ++k) {
                 const int64_t s = c0 + jb + k;
                 const SegRec rec = s < s1 ? a.seg[s] : SegRec{0, 0u};
                 cnt[k] = rec.count;
                 lst[k] = (int32_t)rec.list; /* meaningless for a segment without events */
-                incl[k] = cnt[k];
-                dense = dense || cnt[k] == DENSE;
             }
-            par_incl_scan<OpAdd>(incl, 0, lane); /* DENSE counts cannot overflow it */
+#pragma unroll
+            for (int k = PAR_K - 1; k >= 0; --k) {
+                if (cnt[k] == DENSE) dense0 = min(dense0, jb + k);
+                else stored0 = min(stored0, jb + k);
+            }
+            const int32_t n_stored = wave_min32(dense0);
+            if (n_stored == 0) {
+                const int32_t n_dense = wave_min32(stored0);
+                for (int32_t k = 0; k < n_dense; ++k) {
+                    int4 x[LOADS];
+                    par_load_segment(a, vrow0, vend, c0 - s0 + k, x, lane);
+                    m = par_classify(a, x, (int32_t)(4 * (vrow0 + (c0 - s0 + k) * SEG_VEC) - g), len, l, m, lane);
+                }
+                held = m <= PAR_EVENTS;
+                c0 += n_dense;
+                continue;
+            }
+#pragma unroll
+            for (int k = 0; k < PAR_K; ++k) {
+                if (jb + k >= n_stored) cnt[k] = 0;
+                incl[k] = cnt[k];
+            }
+            par_incl_scan<OpAdd>(incl, 0, lane);
             const int32_t total = lane63(incl[PAR_K - 1]);
-            /* a dense segment or too many events: the automaton below */
-            held = __ballot(dense) == 0 && m + total <= PAR_EVENTS;
+            const int64_t chunk = c0;
+            c0 += n_stored;
+            held = m + total <= PAR_EVENTS;
             if (!held || total == 0) continue;
-            for (int32_t f0 = 0; f0 < total; f0 += PAR_PASS) par_store(sD, f0 + jb, {-1, -1, -1, -1});
+            for (int32_t f0 = 0; f0 < total; f0 += PAR_PASS) par_store(map, f0 + jb, {-1, -1, -1, -1});
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < PAR_K; ++k) {
                 if (cnt[k] > 0) {
                     const int32_t e0 = incl[k] - cnt[k];
-                    sD[e0] = jb + k;
-                    sLAT[jb + k] = lst[k];
-                    sOWN[jb + k] = e0;
+                    map[e0] = jb + k;
+                    seg_list[jb + k] = lst[k];
+                    seg_first[jb + k] = e0;
                 }
             }
             __syncthreads();
@@ -981,20 +1027,20 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
             for (int32_t f0 = 0; f0 < total; f0 += PAR_PASS) {
                 int32_t j[PAR_K];
                 uint32_t w[PAR_K];
-                par_load(sD, f0 + jb, j);
+                par_load(map, f0 + jb, j);
                 par_incl_scan<OpMax>(j, carry, lane); /* every event's segment (position 0 is marked) */
 #pragma unroll
                 for (int k = 0; k < PAR_K; ++k) {
                     const int32_t f = f0 + jb + k, jj = max(j[k], 0);
-                    w[k] = f < total ? a.slots[(int64_t)(uint32_t)sLAT[jj] + (f - sOWN[jj])] : 0u;
+                    w[k] = f < total ? a.slots[(int64_t)(uint32_t)seg_list[jj] + (f - seg_first[jj])] : 0u;
                 }
 #pragma unroll
                 for (int k = 0; k < PAR_K; ++k) {
                     const int32_t f = f0 + jb + k;
                     if (f < total) {
-                        const int64_t seg = c0 + j[k];
-                        sP[m + f] = (int32_t)(4 * (vrow0 + (seg - s0) * SEG_VEC) - g + (int64_t)(w[k] >> 4));
-                        sC[m + f] = (int32_t)(w[k] & 15u);
+                        const int64_t seg = chunk + j[k];
+                        l.P[m + f] = (int32_t)(4 * (vrow0 + (seg - s0) * SEG_VEC) - g + (int64_t)(w[k] >> 4));
+                        l.X[m + f] = (int32_t)(w[k] & 15u);
                     }
                 }
                 carry = lane63(j[PAR_K - 1]);
@@ -1003,103 +1049,79 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
             m += total;
         }
     }
+    if (!held) return false;
+    __syncthreads();
     /* phase A: validity, first error, depth and open threads before each event */
     int32_t prev_c = -1, prev_p = -1, depth = 0, threads = 0, err = INT32_MAX, max_depth = 0, n_blocks = 0;
-    bool fallback = !held; /* the row goes to the automaton below */
-    do {
-        if (fallback) break;
-        __syncthreads();
-        for (int32_t i0 = 0; i0 < m && err == INT32_MAX; i0 += PAR_PASS) {
-            const int32_t ib = i0 + PAR_K * lane;
-            int32_t c[PAR_K], p[PAR_K], dd[PAR_K], dt[PAR_K];
-            par_load(sC, ib, c);
-            par_load(sP, ib, p);
+    for (int32_t i0 = 0; i0 < m && err == INT32_MAX; i0 += PAR_PASS) {
+        const int32_t ib = i0 + PAR_K * lane;
+        int32_t c[PAR_K], p[PAR_K], dd[PAR_K], dt[PAR_K];
+        par_load(l.X, ib, c);
+        par_load(l.P, ib, p);
 #pragma unroll
-            for (int k = 0; k < PAR_K; ++k) {
-                if (ib + k >= m) c[k] = p[k] = 0;
-                dd[k] = ib + k < m ? (c[k] == C_PAR) - (c[k] == C_END_PAR) : 0;
-                dt[k] = ib + k < m ? (c[k] == C_THR) - (c[k] == C_END_THR) : 0;
-            }
-            int32_t d_in[PAR_K], t_in[PAR_K]; /* depth and open threads after each event */
+        for (int k = 0; k < PAR_K; ++k) {
+            if (ib + k >= m) c[k] = p[k] = 0;
+            dd[k] = ib + k < m ? (c[k] == C_PAR) - (c[k] == C_END_PAR) : 0;
+            dt[k] = ib + k < m ? (c[k] == C_THR) - (c[k] == C_END_THR) : 0;
+        }
+        int32_t d_in[PAR_K], t_in[PAR_K]; /* depth and open threads after each event */
 #pragma unroll
-            for (int k = 0; k < PAR_K; ++k) {
-                d_in[k] = dd[k];
-                t_in[k] = dt[k];
-            }
-            par_incl_scan<OpAdd>(d_in, depth, lane);
-            par_incl_scan<OpAdd>(t_in, threads, lane);
-            int32_t pc = lane_before(c[PAR_K - 1], prev_c), pp = lane_before(p[PAR_K - 1], prev_p);
-            int32_t e = INT32_MAX, open_depth = 0, pars = 0;
-            int32_t dbv[PAR_K], tbv[PAR_K];
+        for (int k = 0; k < PAR_K; ++k) {
+            d_in[k] = dd[k];
+            t_in[k] = dt[k];
+        }
+        par_incl_scan<OpAdd>(d_in, depth, lane);
+        par_incl_scan<OpAdd>(t_in, threads, lane);
+        int32_t pc = lane_before(c[PAR_K - 1], prev_c), pp = lane_before(p[PAR_K - 1], prev_p);
+        int32_t e = INT32_MAX, open_depth = 0, pars = 0;
+        int32_t xv[PAR_K];
 #pragma unroll
-            for (int k = 0; k < PAR_K; ++k) {
-                /* the checks of one event, without branches (bitwise, not
-                 * short-circuit: lanes hold different classes) */
-                const int32_t db = d_in[k] - dd[k], tb = t_in[k] - dt[k];
-                const int32_t ck = c[k];
-                const bool act = ib + k < m;
-                const uint32_t st = state_at(pc);
-                const int32_t gap = p[k] - pp - 1;
-                const bool text_ok = (gap == 0) | text_allowed(st) | (LENIENT & (st != S_START));
-                const bool closes_entry = (ck == C_END_SUB) | (ck == C_END_TRI);
-                const bool tag_ok = class_allowed(st, ck) & !((ck == C_END_THINK) & (db != 0)) &
-                                    !((ck == C_END_THR) & (db == 0)) & !(closes_entry & ((ck != pc + 1) | (gap == 0)));
-                const int32_t ek = text_ok ? (tag_ok ? INT32_MAX : p[k]) : pp + 1;
-                const bool opens = act & (ck == C_PAR);
-                e = min(e, act ? ek : INT32_MAX);
-                open_depth = max(open_depth, opens ? db + 1 : 0);
-                pars += opens ? 1 : 0;
-                dbv[k] = db;
-                tbv[k] = tb;
-                pc = c[k];
-                pp = p[k];
-            }
-            par_store(sD, ib, dbv);
-            par_store(sT, ib, tbv);
-            err = wave_min32(e);
-            max_depth = max(max_depth, wave_max32(open_depth));
-            n_blocks += wave_sum32(pars);
-            /* the pass's last event: the one before the next pass's first */
-            const int32_t last = min(m - i0, PAR_PASS) - 1;
-            prev_c = __builtin_amdgcn_readlane(par_pick(c, last % PAR_K), last / PAR_K);
-            prev_p = __builtin_amdgcn_readlane(par_pick(p, last % PAR_K), last / PAR_K);
-            depth = lane63(d_in[PAR_K - 1]);
-            threads = lane63(t_in[PAR_K - 1]);
+        for (int k = 0; k < PAR_K; ++k) {
+            /* the checks of one event, without branches (bitwise, not
+             * short-circuit: lanes hold different classes) */
+            const int32_t db = d_in[k] - dd[k], tb = t_in[k] - dt[k];
+            const int32_t ck = c[k];
+            const bool act = ib + k < m;
+            const uint32_t st = state_at(pc);
+            const int32_t gap = p[k] - pp - 1;
+            const bool text_ok = (gap == 0) | text_allowed(st) | (LENIENT & (st != S_START));
+            const bool closes_entry = (ck == C_END_SUB) | (ck == C_END_TRI);
+            const bool tag_ok = class_allowed(st, ck) & !((ck == C_END_THINK) & (db != 0)) &
+                                !((ck == C_END_THR) & (db == 0)) & !(closes_entry & ((ck != pc + 1) | (gap == 0)));
+            const int32_t ek = text_ok ? (tag_ok ? INT32_MAX : p[k]) : pp + 1;
+            const bool opens = act & (ck == C_PAR);
+            e = min(e, act ? ek : INT32_MAX);
+            open_depth = max(open_depth, opens ? db + 1 : 0);
+            pars += opens ? 1 : 0;
+            /* counts of a row that goes on to phase B are not negative */
+            xv[k] = (int32_t)((uint32_t)ck | ((uint32_t)db & 0xfffu) << 4 | (uint32_t)tb << 16);
+            pc = c[k];
+            pp = p[k];
         }
-        if (err == INT32_MAX) {
-            /* the end of the row: the text after the last tag, then </think> must have come */
-            const uint32_t st = state_at(prev_c);
-            const int32_t gap = len - prev_p - 1;
-            const bool text_ok = gap == 0 || text_allowed(st) || (LENIENT && st != S_START);
-            if (!text_ok) err = prev_p + 1;
-            else if (st != S_TRAIL) err = len;
-        }
-        if (err != INT32_MAX) {
-            if (lane == 0) write_row(a.out, r, len, len, 0, 0, 0, 0, err, err == len ? PARASON_FLAG_TRUNCATED : 0u);
-            return;
-        }
-        fallback = max_depth > PAR_LEVELS;
-    } while (0);
-    if (fallback) {
-        /* a row this kernel does not hold (more than PAR_EVENTS events, a dense
-         * segment, nesting deeper than PAR_LEVELS): the automaton on one lane
-         * with MID_DEPTH frames in LDS (sTOK, unused on this path), as rows_mid
-         * would; a row that needs still more is listed for rows_deep */
-        if (lane == 0) {
-            Automaton<LdsStore<MID_DEPTH>, LENIENT> A;
-            A.st.lds = sTOK;
-            A.st.tid = 0;
-            A.st.nt = 1;
-            A.init();
-            if (drive_row(a, r, g, len, (md & MODE_COMPACT) != 0, A)) A.finish(len);
-            if (A.overflow) {
-                mode[r] = md | MODE_DEEP;
-                deep_rows[atomicAdd(&counters[1], 1)] = (int32_t)r;
-            }
-            else write_result(a.out, r, len, A);
-        }
-        return;
+        par_store(l.X, ib, xv);
+        err = wave_min32(e);
+        max_depth = max(max_depth, wave_max32(open_depth));
+        n_blocks += wave_sum32(pars);
+        /* the pass's last event: the one before the next pass's first */
+        const int32_t last = min(m - i0, PAR_PASS) - 1;
+        prev_c = __builtin_amdgcn_readlane(par_pick(c, last % PAR_K), last / PAR_K);
+        prev_p = __builtin_amdgcn_readlane(par_pick(p, last % PAR_K), last / PAR_K);
+        depth = lane63(d_in[PAR_K - 1]);
+        threads = lane63(t_in[PAR_K - 1]);
     }
+    if (err == INT32_MAX) {
+        /* the end of the row: the text after the last tag, then </think> must have come */
+        const uint32_t st = state_at(prev_c);
+        const int32_t gap = len - prev_p - 1;
+        const bool text_ok = gap == 0 || text_allowed(st) || (LENIENT && st != S_START);
+        if (!text_ok) err = prev_p + 1;
+        else if (st != S_TRAIL) err = len;
+    }
+    if (err != INT32_MAX) {
+        if (lane == 0) write_row(a.out, r, len, len, 0, 0, 0, 0, err, err == len ? PARASON_FLAG_TRUNCATED : 0u);
+        return true;
+    }
+    if (max_depth > PAR_LEVELS) return false;
     __syncthreads();
 
     /* phase B: level by level, deepest first */
@@ -1113,24 +1135,23 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
         int32_t c_sum = 0, c_max = 0, c_n = 0, c_par = -1, c_eout = -1;
         for (int32_t i0 = 0; i0 < m; i0 += PAR_PASS) {
             const int32_t ib = i0 + PAR_K * lane;
-            int32_t c[PAR_K], db[PAR_K], tb[PAR_K], sav[PAR_K], tk[PAR_K];
-            par_load(sC, ib, c);
-            par_load(sD, ib, db);
-            par_load(sT, ib, tb);
-            par_load(sSAV, ib, sav);
-            par_load(sTOK, ib, tk);
+            int32_t x[PAR_K], sav[PAR_K], tk[PAR_K];
+            par_load(l.X, ib, x);
+            par_load(l.SAV, ib, sav);
+            par_load(l.TOK, ib, tk);
             bool thr[PAR_K], ethr[PAR_K], par[PAR_K], epar[PAR_K];
             int32_t ti[PAR_K], S[PAR_K], CH[PAR_K], pi[PAR_K], oi[PAR_K];
 #pragma unroll
             for (int k = 0; k < PAR_K; ++k) {
                 const bool act = ib + k < m;
-                thr[k] = act & (c[k] == C_THR) & (tb[k] == lev - 1);
-                ethr[k] = act & (c[k] == C_END_THR) & (tb[k] == lev);
-                const bool epar_in = act & (c[k] == C_END_PAR) & (db[k] == lev + 1);
-                const bool ethr_in = act & (c[k] == C_END_THR) & (tb[k] == lev + 1);
-                par[k] = act & (c[k] == C_PAR) & (db[k] == lev - 1);
-                epar[k] = act & (c[k] == C_END_PAR) & (db[k] == lev);
-                const bool eout = act & (c[k] == C_END_OUT) & (db[k] == lev) & (tb[k] == lev - 1);
+                const int32_t c = par_class(x[k]), db = par_depth(x[k]), tb = par_threads(x[k]);
+                thr[k] = act & (c == C_THR) & (tb == lev - 1);
+                ethr[k] = act & (c == C_END_THR) & (tb == lev);
+                const bool epar_in = act & (c == C_END_PAR) & (db == lev + 1);
+                const bool ethr_in = act & (c == C_END_THR) & (tb == lev + 1);
+                par[k] = act & (c == C_PAR) & (db == lev - 1);
+                epar[k] = act & (c == C_END_PAR) & (db == lev);
+                const bool eout = act & (c == C_END_OUT) & (db == lev) & (tb == lev - 1);
                 ti[k] = thr[k] ? ib + k : -1;
                 S[k] = epar_in ? sav[k] : 0;
                 CH[k] = ethr_in ? tk[k] : 0;
@@ -1145,8 +1166,8 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
             int32_t sum[PAR_K], mx[PAR_K], nt[PAR_K], own[PAR_K];
 #pragma unroll
             for (int k = 0; k < PAR_K; ++k) {
-                const int32_t tok = ethr[k] ? sP[ib + k] - sP[max(ti[k], 0)] + 1 : 0;
-                if (ethr[k]) sTOK[ib + k] = tok; /* read by the next level's threads */
+                const int32_t tok = ethr[k] ? l.P[ib + k] - l.P[max(ti[k], 0)] + 1 : 0;
+                if (ethr[k]) l.TOK[ib + k] = tok; /* read by the next level's threads */
                 sum[k] = tok;
                 mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
                 own[k] = tok - CH[k];
@@ -1161,14 +1182,14 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
                 if (ethr[k]) {
                     const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
                     if (kk < n_e) {
-                        const int32_t t = sC[pi[k] + 2 + 2 * kk];
+                        const int32_t t = par_class(l.X[pi[k] + 2 + 2 * kk]);
                         my_sub += t == C_SUB ? own[k] : 0;
                         my_tri += t == C_TRI ? own[k] : 0;
                     }
                 }
                 if (epar[k]) {
                     const int32_t saved = sum[k] - mx[k];
-                    sSAV[ib + k] = saved;
+                    l.SAV[ib + k] = saved;
                     my_mismatch = my_mismatch || nt[k] != n_e;
                     my_saved += lev == 1 ? saved : 0;
                 }
@@ -1191,6 +1212,101 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
         if (mismatch) fl |= PARASON_FLAG_COUNT_MISMATCH;
         if (n_blocks > 0) fl |= PARASON_FLAG_TRIGGERED;
         write_row(a.out, r, len, len - saved, n_sub, n_tri, n_blocks, max_depth, -1, fl);
+    }
+    return true;
+}
+
+/* One wave per row (a small batch).  A row par_row does not hold runs through
+ * the automaton on lane 0 (the single automaton call site of this kernel),
+ * with MID_DEPTH frames in LDS, as rows_mid would; one that needs still more
+ * is listed for the deep tier. */
+template <bool LENIENT>
+__global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ mode,
+                                               int32_t *__restrict__ counters, int32_t *__restrict__ deep_rows)
+{
+    __shared__ __align__(16) ParLds l;
+    const int lane = threadIdx.x;
+    const int64_t r = blockIdx.x;
+    if (r >= a.n) return;
+    /* the row's records in one round of loads, before any branch */
+    const int64_t start = a.starts[r];
+    const int32_t len = a.lengths[r];
+    const int64_t S = a.seg_off[a.n], s0 = a.seg_off[r], s1 = a.seg_off[r + 1];
+    const uint8_t md = mode[r];
+    if (start < 0 || len < 0) {
+        if (lane == 0) write_row(a.out, r, 0, 0, 0, 0, 0, 0, 0, PARASON_FLAG_BAD_ROW);
+        return;
+    }
+    if (S > a.seg_cap) {
+        if (lane == 0) write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_WS_OVERFLOW);
+        return;
+    }
+    if (par_row<LENIENT>(a, l, r, start, len, s0, s1, (md & MODE_COMPACT) != 0, lane)) return;
+    if (lane == 0) {
+        Automaton<LdsStore<MID_DEPTH>, LENIENT> A;
+        A.st.lds = l.TOK; /* unused on this path */
+        A.st.tid = 0;
+        A.st.nt = 1;
+        A.init();
+        if (drive_row<false>(a, r, start + a.mis, len, (md & MODE_COMPACT) != 0, A)) A.finish(len);
+        if (A.overflow) {
+            mode[r] = md | MODE_DEEP;
+            deep_rows[atomicAdd(&counters[1], 1)] = (int32_t)r;
+        } else {
+            write_result(a.out, r, len, A);
+        }
+    }
+}
+
+/* One thread per row.  mode[r] == MODE_COMPACT: the scan left the row's events as one
+ * compact list; 0: per-segment lists.  A row that needs more than FAST_DEPTH
+ * frames (or more than 64 entries in an open block) is listed for rows_mid.
+ * Few frames keep the LDS per block small, so that many waves hide the
+ * latency of the branchy automaton.  Rows with a segment whose list the scan
+ * could not store are left by their lanes and evaluated one after the other by
+ * the whole wave (par_row, in the frames' LDS); one that par_row does not hold
+ * is listed for rows_mid. */
+template <bool LENIENT>
+__global__ void __launch_bounds__(64) rows_fast(RowArgs a, const uint8_t *__restrict__ mode,
+                                                int32_t *__restrict__ counters, int32_t *__restrict__ mid_rows,
+                                                int32_t lane_shift)
+{
+    static_assert(FAST_DEPTH * FRAME_WORDS * 64 <= PAR_LDS, "the frames and par_row share the LDS");
+    __shared__ __align__(16) ParLds l;
+    const int lane = threadIdx.x;
+    /* every (1 << lane_shift)-th lane takes a row (64 >> lane_shift rows per wave) */
+    const int64_t r0 = (int64_t)blockIdx.x * (blockDim.x >> lane_shift);
+    const int64_t r = r0 + (lane >> lane_shift);
+    const bool mine = (lane & ((1 << lane_shift) - 1)) == 0 && r < a.n;
+    const bool fits = a.seg_off[a.n] <= a.seg_cap;
+    bool dense = false;
+    if (mine) {
+        const int64_t start = a.starts[r];
+        const int32_t len = a.lengths[r];
+        if (start < 0 || len < 0) {
+            write_row(a.out, r, 0, 0, 0, 0, 0, 0, 0, PARASON_FLAG_BAD_ROW);
+        } else if (!fits) {
+            write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_WS_OVERFLOW);
+        } else {
+            Automaton<LdsStore<FAST_DEPTH>, LENIENT> A;
+            A.st.lds = reinterpret_cast<int32_t *>(&l);
+            A.st.tid = lane;
+            A.st.nt = blockDim.x;
+            A.init();
+            if (drive_row<true>(a, r, start + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A, &dense)) A.finish(len);
+            if (A.overflow) mid_rows[atomicAdd(&counters[0], 1)] = (int32_t)r; /* rows_mid writes this row */
+            else if (!dense) write_result(a.out, r, len, A);
+        }
+    }
+    uint64_t todo = __ballot(dense);
+    while (todo != 0) {
+        __syncthreads(); /* the LDS of the row before (or the frames) is rewritten */
+        const int64_t rd = r0 + (__builtin_ctzll(todo) >> lane_shift);
+        todo &= todo - 1;
+        const int64_t start = uniform64(a.starts[rd]), s0 = uniform64(a.seg_off[rd]), s1 = uniform64(a.seg_off[rd + 1]);
+        const int32_t len = __builtin_amdgcn_readfirstlane(a.lengths[rd]);
+        if (!par_row<LENIENT>(a, l, rd, start, len, s0, s1, false, lane) && lane == 0)
+            mid_rows[atomicAdd(&counters[0], 1)] = (int32_t)rd;
     }
 }
 

@@ -1,0 +1,82 @@
+"""The row kernels where the scan cannot store a segment's events: outlines so
+dense that a scan wave's pool region runs out (rows are then read again by the
+wave that evaluates them), at the batch sizes where the kernels change, against
+the oracle.  On the CPU the emulated build gets a small pool, on the GPU the
+batches are large enough to use the real one up."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from adversarial import adversarial_streams, pack
+from gpu_util import DEFAULT_COEF, compare, insert_gaps, oracle_expect
+from paper_2608_24658_amd import parason as PX
+from paper_2608_24658_amd.synth import synth as S
+from test_simt_emulation import CLANG, CSRC, FEW, MANY, ROOT, SIMT, TAGS, check
+
+G = 8
+
+
+def short_rows(n, lo, hi, seed, tags=TAGS, len_kind=0, **kw):
+    P = S.make_params(dict(seed=seed, len_kind=len_kind, len_lo=lo, len_hi=hi, **kw), tag_ids=tags)
+    return S.host_batch(P, n)
+
+
+@pytest.fixture(scope="module")
+def emu_small_pool(tmp_path_factory):
+    """Four slots per segment and 512 in all: most ranges run out."""
+    if not os.path.exists(CLANG):
+        pytest.skip("no host clang++ with the sanitizers")
+    out = str(tmp_path_factory.mktemp("rows") / "emu")
+    subprocess.check_call([CLANG, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined",
+                           "-fno-sanitize-recover=undefined", "-ffp-contract=off", "-DPARASON_POOL_MIN=512", "-I", SIMT,
+                           "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-x", "c++",
+                           os.path.join(CSRC, "parason.hip"), os.path.join(SIMT, "emu_main.cpp"), "-o", out])
+    return out
+
+
+@pytest.mark.parametrize("cus", [MANY, FEW])
+@pytest.mark.parametrize("tags", ["contiguous", "scattered"])
+def test_unstored_segments(emu_small_pool, cus, tags):
+    """Rows of 1 to 3,000 tokens (one to four segments each, some cut off),
+    on every kind of batch: the scan's own plan and the larger ones."""
+    ids = TAGS if tags == "contiguous" else S.SCATTERED_TAGS
+    tok, st, ln, co = short_rows(320, 1, 3000, 11, ids, len_kind=1, p_trunc=0.1, p_trigger=1.0)
+    for shift in (0, 3):
+        check(emu_small_pool, tok, st, ln, co, ids, cus=cus, shift=shift, what="unstored cus %d shift %d" % (cus, shift))
+    P = S.make_params("small", tag_ids=ids)
+    t2, s2, l2, c2 = S.host_batch(P, 64)
+    rng = np.random.default_rng(5)
+    rows = [insert_gaps(t2[s2[i]: s2[i] + l2[i]], ids, rng) for i in range(64)]
+    lengths = np.array([r.size for r in rows], np.int32)
+    starts = np.concatenate([[0], np.cumsum(lengths[:-1])]).astype(np.int64)
+    check(emu_small_pool, np.concatenate(rows), starts, lengths, c2, ids, flags=PX.CFG_LENIENT_GAPS, cus=cus,
+          what="unstored, lenient")
+
+
+@pytest.mark.parametrize("cus", [16, FEW])
+def test_unstored_segments_adversarial(emu_small_pool, cus):
+    """Strings the row kernels hand on (too many events, too deep) next to
+    ones they hold, with most lists unstored."""
+    tokens, starts, lengths = pack(adversarial_streams(), TAGS)
+    correct = (np.arange(lengths.size) % 3 != 0).astype(np.uint8)
+    check(emu_small_pool, tokens, starts, lengths, correct, cus=cus, what="unstored adversarial")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,lo,hi,kind", [(2048, 1750, 5250, 0), (2056, 350, 1050, 0), (8192, 1, 2100, 1),
+                                          (12000, 350, 1050, 0), (40000, 300, 900, 0)])
+def test_rows_on_the_gpu(n, lo, hi, kind):
+    """Outline-heavy batches over the sizes where the row kernels change."""
+    import torch
+
+    P = S.make_params(dict(seed=n, len_kind=kind, len_lo=lo, len_hi=hi, p_trigger=1.0, p_trunc=0.02))
+    tok, st, ln, co = S.host_batch(P, n)
+    dev = [torch.as_tensor(x).cuda() for x in (tok, st, ln, co)]
+    for flags in (0, PX.CFG_LENIENT_GAPS):
+        px = PX.Parason(S.CONTIGUOUS_TAGS, group_size=G, flags=flags, **DEFAULT_COEF)
+        got = {k: v.cpu().numpy() for k, v in px.run(*dev, total_tokens=tok.size).items()}
+        got["flags"] = got["flags"].view(np.uint32)
+        compare(got, *oracle_expect(tok, st, ln, co, S.CONTIGUOUS_TAGS, G, DEFAULT_COEF, flags),
+                what="rows %d flags %d" % (n, flags))
