@@ -27,25 +27,21 @@ namespace {
 #define PARASON_SCAN_BLOCKS_PER_CU 4
 #endif
 constexpr int SCAN_BLOCKS_PER_CU = PARASON_SCAN_BLOCKS_PER_CU; /* persistent grid of 4-wave blocks */
-/* slot indices are 32-bit: GATHER_SLOTS + POOL_PER_SEG slots per segment and
- * POOL_MIN more must stay below 2^32 (about 3.6e11 tokens, far beyond what
+/* slot indices are 32-bit: POOL_PER_SEG + POOL_SPARE_PER_SEG slots per segment
+ * and POOL_MIN more must stay below 2^32 (about 3.6e11 tokens, far beyond what
  * one GPU holds) */
 constexpr int64_t MAX_SEGMENTS =
-    (((int64_t)1 << 32) - 1 - pk::POOL_MIN) / (pk::GATHER_SLOTS + pk::POOL_PER_SEG);
-constexpr int MID_BLOCKS_PER_CU = 2; /* rows_mid blocks hold 64 KB of LDS frames each */
-constexpr int GATHER_BLOCKS_PER_CU = 8; /* 4-wave blocks of gather_rows */
+    (((int64_t)1 << 32) - 1 - pk::POOL_MIN) / (pk::POOL_PER_SEG + pk::POOL_SPARE_PER_SEG);
 #ifndef PARASON_PAR_ROWS_PER_CU
-#define PARASON_PAR_ROWS_PER_CU 40
+#define PARASON_PAR_ROWS_PER_CU 64
 #endif
-#ifndef PARASON_FAST_WAVES_PER_CU
-#define PARASON_FAST_WAVES_PER_CU 20
-#endif
-constexpr int PAR_ROWS_PER_CU = PARASON_PAR_ROWS_PER_CU;     /* rows_par below this many rows per CU */
-constexpr int FAST_WAVES_PER_CU = PARASON_FAST_WAVES_PER_CU; /* rows_fast waves a CU holds (8 KB of LDS frames each) */
+constexpr int PAR_ROWS_PER_CU = PARASON_PAR_ROWS_PER_CU; /* rows_par up to this many rows per CU */
+constexpr int PLAN_ROWS_PER_CU = 40;  /* the scan plans batches of fewer rows per CU itself */
+constexpr int LISTED_WAVES_PER_CU = 20; /* rows_listed waves a CU holds (8 KB of LDS frames each) */
 
 /* Byte offsets of the workspace sections for n rows. */
 struct Layout {
-    size_t seg_off, tile_sum, tile_off, counters, mode, mid_rows, deep_rows, split_rows;
+    size_t seg_off, tile_sum, tile_off, counters, mode, listed, deep_rows, spare;
     size_t red_d, red_i, stats;
     size_t fixed;  /* bytes before the per-segment sections */
     int64_t n_tiles;
@@ -66,11 +62,11 @@ Layout layout_for(int64_t n)
     o = align_up(o + 4 * sizeof(int32_t));
     L.mode = o;
     o = align_up(o + (size_t)(n > 0 ? n : 1));
-    L.mid_rows = o;
+    L.listed = o;
     o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
     L.deep_rows = o;
     o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
-    L.split_rows = o;
+    L.spare = o; /* kept, so that workspaces keep their sizes */
     o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
     /* partial sums of the batch reductions (one record per 4096 rows) */
     L.red_d = o;
@@ -85,13 +81,12 @@ Layout layout_for(int64_t n)
 
 /* The sections after the fixed ones, for a capacity of cap segments: the
  * deep tier's frames and entry bits (sized for any row that fits in cap
- * segments), one SegRec per segment, then the event slots: GATHER_SLOTS per
- * segment, then the pool (POOL_PER_SEG slots per segment, at least
- * POOL_MIN).  About 56 bytes per 1024-token segment once the deep store
+ * segments), one SegRec per segment, then the pool's event slots (POOL_PER_SEG
+ * per segment, at least POOL_MIN, and POOL_SPARE_PER_SEG per segment).  About 56 bytes per 1024-token segment once the deep store
  * reaches its maximum (2^20 frames, 32 MiB, from about 6,100 segments on). */
 struct CapSections {
     size_t frames, bits, seg, slots, end;            /* byte offsets; end = bytes needed */
-    int64_t n_frames, n_bits, pool_base, pool_slots; /* the pool in slots */
+    int64_t n_frames, n_bits, pool_slots;
 };
 
 CapSections cap_sections(const Layout &L, int64_t cap)
@@ -99,7 +94,7 @@ CapSections cap_sections(const Layout &L, int64_t cap)
     CapSections q;
     q.n_frames = std::min(pk::DEEP_FRAMES, pk::DEEP_FRAMES_PER_SEG * cap + 1);
     q.n_bits = std::min(pk::DEEP_ENTRY_BITS, (pk::DEEP_BITS_PER_SEG * cap + 32 + 31) / 32 * 32);
-    q.pool_slots = std::max((int64_t)pk::POOL_PER_SEG * cap, pk::POOL_MIN);
+    q.pool_slots = std::max((int64_t)pk::POOL_PER_SEG * cap, pk::POOL_MIN) + pk::POOL_SPARE_PER_SEG * cap;
     size_t o = L.fixed;
     q.frames = o;
     o = align_up(o + (size_t)q.n_frames * pk::FRAME_WORDS * sizeof(int32_t));
@@ -108,8 +103,7 @@ CapSections cap_sections(const Layout &L, int64_t cap)
     q.seg = o;
     o = align_up(o + (size_t)cap * sizeof(pk::SegRec));
     q.slots = o;
-    q.pool_base = (int64_t)pk::GATHER_SLOTS * cap;
-    q.end = o + (size_t)(q.pool_base + q.pool_slots) * sizeof(uint32_t);
+    q.end = o + (size_t)q.pool_slots * sizeof(uint32_t);
     return q;
 }
 
@@ -167,36 +161,28 @@ void find_tag_hash(pk::TagMatch &tm)
  * The deep tier is a launch of its own only when deep_launch is set (the
  * batch-wide statistics need every row first); otherwise group_reward runs
  * it. */
-/* A small batch takes rows_par, one wave per row. */
-bool rows_par_batch(int64_t n, int cus) { return n < (int64_t)cus * PAR_ROWS_PER_CU; }
+/* A small batch takes rows_par, one wave per row: its waves are done in one or
+ * two rounds of the chip, and a row's own chain of steps, shorter over 64 lanes
+ * than over 16, sets the time.  A larger one takes rows_quad, four rows per
+ * wave, where the instructions set it (rows of 3,500 tokens, a call: 8,192 rows
+ * 75 us with rows_par and 80 with rows_quad, 24,000 rows 154 and 151, 64,000
+ * rows of 20,000 tokens 980 and 935). */
+bool rows_par_batch(int64_t n, int cus) { return n <= (int64_t)cus * PAR_ROWS_PER_CU; }
 
 template <bool LENIENT>
-void launch_rows(const pk::RowArgs &ra, const pk::GatherArgs &ga, int cus, uint8_t *mode, int32_t *counters,
-                 int32_t *mid_rows, int32_t *deep_rows, int32_t *deep_frames, uint32_t *deep_bits, bool deep_launch,
+void launch_rows(const pk::RowArgs &ra, int cus, uint8_t *mode, int32_t *counters, int32_t *listed,
+                 int32_t *deep_rows, int32_t *deep_frames, uint32_t *deep_bits, bool deep_launch,
                  hipStream_t stream)
 {
-    /* A small batch: rows_par, one wave per row, its lanes over the row's
-     * events.  A larger one: rows_fast, one row per lane, with as many rows
-     * per wave as keep FAST_WAVES_PER_CU waves on every CU (64 once the batch
-     * is large). */
     if (rows_par_batch(ra.n, cus)) {
         /* rows_par runs the rows it does not hold through the automaton
-         * itself (the second tier), so rows_mid has nothing to do */
+         * itself */
         hipLaunchKernelGGL(pk::rows_par<LENIENT>, dim3((unsigned)ra.n), dim3(64), 0, stream, ra, mode, counters, deep_rows);
     } else {
-        int64_t per_wave = 1;
-        int32_t lane_shift = 6; /* log2(64 / per_wave) */
-        while (per_wave < 64 && ra.n / (per_wave * 2) >= (int64_t)cus * FAST_WAVES_PER_CU) {
-            per_wave *= 2;
-            --lane_shift;
-        }
-        const unsigned row_blocks = (unsigned)((ra.n + per_wave - 1) / per_wave);
-        /* the per-lane automaton reads split rows best as compact lists */
-        hipLaunchKernelGGL(pk::gather_rows, dim3((unsigned)(cus * GATHER_BLOCKS_PER_CU)), dim3(256), 0, stream, ga);
-        hipLaunchKernelGGL(pk::rows_fast<LENIENT>, dim3(row_blocks), dim3(64), 0, stream, ra, mode, counters, mid_rows,
-                           lane_shift);
-        hipLaunchKernelGGL(pk::rows_mid<LENIENT>, dim3((unsigned)(cus * MID_BLOCKS_PER_CU)), dim3(64), 0, stream, ra,
-                           mode, counters, mid_rows, deep_rows);
+        hipLaunchKernelGGL(pk::rows_quad<LENIENT>, dim3((unsigned)((ra.n + pk::QUAD_ROWS - 1) / pk::QUAD_ROWS)),
+                           dim3(64), 0, stream, ra, mode, counters, listed);
+        hipLaunchKernelGGL(pk::rows_listed<LENIENT>, dim3((unsigned)(cus * LISTED_WAVES_PER_CU)), dim3(64), 0, stream,
+                           ra, mode, counters, listed, deep_rows);
     }
     if (deep_launch)
         hipLaunchKernelGGL(pk::rows_deep<LENIENT>, dim3(1), dim3(64), 0, stream, ra, mode, counters, deep_rows,
@@ -344,9 +330,8 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     int64_t *tile_off = (int64_t *)(ws + L.tile_off);
     int32_t *counters = (int32_t *)(ws + L.counters);
     uint8_t *mode = (uint8_t *)(ws + L.mode);
-    int32_t *mid_rows = (int32_t *)(ws + L.mid_rows);
+    int32_t *listed = (int32_t *)(ws + L.listed);
     int32_t *deep_rows = (int32_t *)(ws + L.deep_rows);
-    int32_t *split_rows = (int32_t *)(ws + L.split_rows);
     double *red_d = (double *)(ws + L.red_d);
     int64_t *red_i = (int64_t *)(ws + L.red_i);
     pk::BatchStats *stats = (pk::BatchStats *)(ws + L.stats);
@@ -357,10 +342,10 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     uint32_t *slots = (uint32_t *)(ws + q.slots);
 
     const unsigned tiles = (unsigned)L.n_tiles;
-    /* a batch that takes rows_par and fits one scan block's plan is planned
-     * by the scan blocks themselves (one launch less, and the scan waves find
-     * their rows in LDS) */
-    const bool plan_in_scan = n_traj <= pk::SCAN_PLAN_ROWS && rows_par_batch(n_traj, cus);
+    /* a batch that fits one scan block's plan is planned by the scan blocks
+     * themselves (one launch less, and the scan waves find their rows in LDS),
+     * unless each block would plan many more rows than it scans */
+    const bool plan_in_scan = n_traj <= pk::SCAN_PLAN_ROWS && n_traj < (int64_t)cus * PLAN_ROWS_PER_CU;
     if (!plan_in_scan)
         abi::launch_plan(starts, lengths, n_traj, mis, L.n_tiles, tile_sum, tile_off, seg_off, counters, mode, stream);
 
@@ -376,14 +361,9 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     sa.seg_cap = cap;
     sa.seg = seg;
     sa.slots = slots;
-    /* only the row tiers after gather_rows use the gather slots */
-    const bool par = rows_par_batch(n_traj, cus);
-    sa.pool_base = par ? 0u : (uint32_t)q.pool_base;
-    sa.pool_slots = (uint32_t)(par ? q.pool_base + q.pool_slots : q.pool_slots);
+    sa.pool_slots = (uint32_t)q.pool_slots;
     sa.mode = mode;
     sa.tm = h->tm;
-    sa.split_count = counters + 2;
-    sa.split_rows = split_rows;
     sa.counters = counters;
     if (scan_events && hipEventRecord((hipEvent_t)scan_events[0], stream) != hipSuccess) return PARASON_ERR_HIP;
     if (plan_in_scan)
@@ -406,15 +386,14 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     ra.deep_bits = q.n_bits;
     ra.tm = h->tm;
     ra.out = row_out;
-    const pk::GatherArgs ga{starts, n_traj, mis, seg_off, cap, seg, slots, mode, counters + 2, split_rows};
     const bool lenient = (h->cfg.flags & PARASON_CFG_LENIENT_GAPS) != 0;
     const bool batch_stats = (h->cfg.flags & PARASON_CFG_BATCH_STATS) != 0;
     if (lenient)
-        launch_rows<true>(ra, ga, cus, mode, counters, mid_rows, deep_rows, deep_frames, deep_bits, batch_stats,
-                          stream);
+        launch_rows<true>(ra, cus, mode, counters, listed, deep_rows, deep_frames, deep_bits,
+                          batch_stats, stream);
     else
-        launch_rows<false>(ra, ga, cus, mode, counters, mid_rows, deep_rows, deep_frames, deep_bits, batch_stats,
-                           stream);
+        launch_rows<false>(ra, cus, mode, counters, listed, deep_rows, deep_frames, deep_bits,
+                           batch_stats, stream);
 
     pk::RewardArgs rw;
     rw.total = out->total;

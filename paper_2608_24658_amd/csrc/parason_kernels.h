@@ -7,38 +7,32 @@
  *        Each row is cut into segments of SEG_VEC 16-byte vectors, starting at
  *        the 128-byte line that holds its first token.  A three-pass exclusive
  *        scan gives seg_off[i] (first segment of row i) and the segment count
- *        seg_off[n]; mode[i] is cleared.  A batch that takes rows_par and has
- *        at most SCAN_PLAN_ROWS rows skips these launches: every scan block
- *        makes the plan in LDS itself (scan_plan).
+ *        seg_off[n]; mode[i] is cleared.  A batch of at most SCAN_PLAN_ROWS
+ *        rows skips these launches: every scan block makes the plan in LDS
+ *        itself (scan_plan).
  *   scan_rows  (HBM-bound; one wave per segment, persistent grid)
  *        Streams every token once with 16-byte loads, tests it against the
  *        twelve tag ids with a wave ballot and compacts the rare tags (about
  *        0.1-1% of tokens) in position order.  A row whose segments all fall in
  *        one wave's range collects its events in that wave's LDS buffer and is
  *        written out, coalesced, as one compact list (mode[i] = 1).  Other rows
- *        leave their events in per-segment lists (mode[i] = 0) and are listed
- *        as split.  Every list the scan writes is in the wave's region of the
+ *        leave their events in per-segment lists (mode[i] = 0).  Every list the scan writes is in the wave's region of the
  *        slot pool; seg[s] holds its length and first slot.
- *   gather_rows  (one wave per split row)
- *        Gathers a split row's per-segment events through LDS into one compact
- *        list with row positions in the row's gather slots (mode[i] = 1).
  *   rows_par  (small batches: one wave per row, four events per lane)
  *        Validity from local checks and a depth prefix sum; latency and branch
  *        tokens level by level with segmented scans (DPP).  A segment whose
  *        events the scan could not store (marked DENSE) is read again by the
- *        wave.  A row it cannot hold runs through the automaton on one lane, with MID_DEPTH frames in
- *        LDS, as in rows_mid.
- *   rows_fast  (larger batches: one thread per row)
- *        The grammar's pushdown automaton over the row's events; Text runs are
- *        the gaps between event positions.  Rows with a DENSE segment are
- *        evaluated by their wave as in rows_par.
- *        Frames of open blocks in LDS (FAST_DEPTH per row, 64 outline entries
- *        per block); a row that needs more is handed to rows_mid.
- *   rows_mid  (after rows_fast: one thread per handed-over row, MID_DEPTH
- *        frames in LDS)
- *        The same automaton for deeper rows; a row that needs more still is
- *        handed to rows_deep.
- *   rows_deep  (one thread, only rows rows_mid or rows_par handed over)
+ *        wave.  A row it cannot hold runs through the grammar's pushdown
+ *        automaton on one lane, with MID_DEPTH frames in LDS: Text runs are the
+ *        gaps between event positions.
+ *   rows_quad  (larger batches: four rows per wave, eight events per lane)
+ *        The same, for rows of up to QUAD_EVENTS events; others by the whole
+ *        wave as in rows_par.  A row that does not fit that either is listed.
+ *   rows_listed  (after rows_quad: one thread per listed row)
+ *        The automaton with frames of open blocks in LDS (FAST_DEPTH per row,
+ *        64 outline entries per block; MID_DEPTH for the rows that need more);
+ *        a row that needs more still is handed to the deep tier.
+ *   rows_deep  (one thread, only rows rows_listed or rows_par handed over)
  *        The same automaton with frames and entry types in global workspace.
  *        Only with batch-wide statistics is this a launch of its own; with
  *        per-group statistics the first block of group_reward runs these rows
@@ -171,15 +165,15 @@ struct Top {
     uint64_t ent;       /* fast store: entry-type bits; deep store: first bit index */
 };
 
-/* LDS store: DEPTH frames per thread in LDS, entry types as a 64-bit mask. */
-template <int DEPTH>
+/* LDS store: depth frames for each of nt rows in LDS, entry types as a 64-bit
+ * mask. */
 struct LdsStore {
-    int32_t *lds; /* [DEPTH][FRAME_WORDS][blockDim] */
-    int tid, nt;
+    int32_t *lds; /* [depth][FRAME_WORDS][nt] */
+    int tid, nt, depth;
     __device__ int32_t &at(int d, int f) { return lds[(d * FRAME_WORDS + f) * nt + tid]; }
     __device__ bool push(const Top &t, int d)
     {
-        if (d > DEPTH) return false;
+        if (d > depth) return false;
         at(d - 1, 0) = t.saved_acc;
         at(d - 1, 1) = t.block_main;
         at(d - 1, 2) = t.max_w;
@@ -513,8 +507,7 @@ struct RowArgs {
     RowOut out;
 };
 
-/* Feed row r's events to A.  Returns false when A stopped early, or (STOP_DENSE)
- * at a segment marked DENSE, which sets *dense.
+/* Feed row r's events to A.  Returns false when A stopped early.
  *
  * Three sources, all feeding the one call of A.event below: a compact list
  * (the whole row: seg[first], row positions), or per segment
@@ -524,9 +517,9 @@ struct RowArgs {
  * gfx950 build returned wrong results for dense segments although the same
  * source is correct when compiled for the CPU, so the sources are merged into
  * one fetch loop. */
-template <bool STOP_DENSE, class Store, bool LENIENT>
+template <class Store, bool LENIENT>
 __device__ bool drive_row(const RowArgs &a, int64_t r, int64_t g, int32_t len, bool compact,
-                          Automaton<Store, LENIENT> &A, bool *dense_out = nullptr)
+                          Automaton<Store, LENIENT> &A)
 {
     const int64_t s0 = a.seg_off[r], s1 = a.seg_off[r + 1];
     const int64_t vrow0 = row_first_vec(g), vend = row_end_vec(g, len);
@@ -558,7 +551,7 @@ __device__ bool drive_row(const RowArgs &a, int64_t r, int64_t g, int32_t len, b
                 c = w & 15u;
                 break;
             }
-            if (!STOP_DENSE && dense) {
+            if (dense) {
                 while (q < q_end) {
                     const int32_t t = a.tok_base[q];
                     const int64_t pp = q - g;
@@ -583,9 +576,6 @@ __device__ bool drive_row(const RowArgs &a, int64_t r, int64_t g, int32_t len, b
             if (n_s != DENSE) {
                 cnt = n_s;
                 ev = a.slots + rec.list; /* not read when n_s is 0 */
-            } else if (STOP_DENSE) {
-                *dense_out = true;
-                return false;
             } else {
                 cnt = 0;
                 dense = true;
@@ -598,36 +588,6 @@ __device__ bool drive_row(const RowArgs &a, int64_t r, int64_t g, int32_t len, b
         if (!A.event(p, c)) return false;
     }
     return true;
-}
-
-/* The rows rows_fast listed, one thread each (grid-stride over the list), with
- * MID_DEPTH frames per row in LDS; rows that need still more are listed for
- * rows_deep. */
-template <bool LENIENT>
-__global__ void __launch_bounds__(64) rows_mid(RowArgs a, uint8_t *__restrict__ mode,
-                                               int32_t *__restrict__ counters, const int32_t *__restrict__ mid_rows,
-                                               int32_t *__restrict__ deep_rows)
-{
-    __shared__ int32_t lds[MID_DEPTH * FRAME_WORDS * 64];
-    const int32_t n_mid = counters[0];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_mid;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = mid_rows[i];
-        const int32_t len = a.lengths[r];
-        Automaton<LdsStore<MID_DEPTH>, LENIENT> A;
-        A.st.lds = lds;
-        A.st.tid = threadIdx.x;
-        A.st.nt = blockDim.x;
-        A.init();
-        if (drive_row<false>(a, r, a.starts[r] + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
-        if (A.overflow) {
-            mode[r] |= MODE_DEEP;
-            int32_t slot = atomicAdd(&counters[1], 1);
-            deep_rows[slot] = (int32_t)r;
-        } else {
-            write_result(a.out, r, len, A);
-        }
-    }
 }
 
 /* Rows whose nesting or entry count exceeded the LDS stores, one after the
@@ -647,7 +607,7 @@ __device__ void run_deep_rows(const RowArgs &a, const uint8_t *__restrict__ mode
         A.st.max_bits = a.deep_bits;
         A.st.esp = 0;
         A.init();
-        if (drive_row<false>(a, r, a.starts[r] + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
+        if (drive_row(a, r, a.starts[r] + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
         if (A.overflow)
             write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_DEPTH_LIMIT);
         else
@@ -767,19 +727,6 @@ __device__ __forceinline__ int32_t wave_max32(int32_t v)
     return lane63(dpp_incl_scan<OpMax>(v, (int)(threadIdx.x & (WAVE - 1))));
 }
 
-/* The largest lane j with x (held by lane j) <= f, for x non-decreasing over
- * the lanes and x of lane 0 <= f (every lane must call it). */
-__device__ __forceinline__ int32_t last_lane_at_most(int32_t x, int32_t f)
-{
-    int32_t lo = 0;
-#pragma unroll
-    for (int step = WAVE / 2; step > 0; step >>= 1) {
-        const int32_t cand = lo + step;
-        lo = __shfl(x, cand, WAVE) <= f ? cand : lo;
-    }
-    return lo;
-}
-
 /* Events in passes of PAR_PASS: event i0 + PAR_K * lane + k is element k of
  * the lane, so a row of up to PAR_PASS events takes one wave scan per
  * quantity instead of one per 64 events (the scans are latency: a chain of
@@ -852,12 +799,17 @@ struct ParLds {
 };
 constexpr int PAR_LDS = 4 * PAR_EVENTS; /* words */
 static_assert(PAR_EVENTS < (1 << 12), "depths and thread counts of a held row fit their fields");
-static_assert(PAR_EVENTS >= 2 * PAR_PASS, "the gather keeps two words per segment of a chunk in SAV");
+static_assert(PAR_EVENTS >= 2 * PAR_PASS, "the gather of a split row keeps two words per segment of a chunk in SAV");
 static_assert(MID_DEPTH * FRAME_WORDS <= PAR_EVENTS, "the automaton's frames fit TOK");
 
-__device__ __forceinline__ int32_t par_class(int32_t x) { return x & 15; }
-__device__ __forceinline__ int32_t par_depth(int32_t x) { return (x >> 4) & 0xfff; }
-__device__ __forceinline__ int32_t par_threads(int32_t x) { return x >> 16; }
+/* The word of X.  In a valid row the depth and the open threads before a
+ * structural tag of level lev are fixed (an outline and a <Thread> of a block
+ * of level lev stand in lev blocks and lev - 1 threads, a </Thread> in lev of
+ * both), so one compare with such a word finds the tags of a level. */
+__device__ __forceinline__ int32_t par_key(uint32_t c, int32_t depth, int32_t threads)
+{
+    return (int32_t)(c | ((uint32_t)depth & 0xfffu) << 4 | (uint32_t)threads << 16);
+}
 
 /* The tags of one segment of the row at g, read again by the whole wave: the
  * vectors x (vector v0 + i * WAVE + lane), of which the positions inside the
@@ -936,8 +888,7 @@ __device__ bool par_row(const RowArgs &a, ParLds &l, int64_t r, int64_t start, i
                         bool compact, int lane)
 {
     /* the row's events into LDS, in position order: from its compact list (row
-     * positions), or from its segments' lists (segment positions), gathered
-     * here as gather_rows does for the per-lane kernel */
+     * positions), or gathered from its segments' lists (segment positions) */
     const int64_t g = start + a.mis;
     int32_t m = 0;
     bool held = true;
@@ -1094,7 +1045,7 @@ __device__ bool par_row(const RowArgs &a, ParLds &l, int64_t r, int64_t start, i
             open_depth = max(open_depth, opens ? db + 1 : 0);
             pars += opens ? 1 : 0;
             /* counts of a row that goes on to phase B are not negative */
-            xv[k] = (int32_t)((uint32_t)ck | ((uint32_t)db & 0xfffu) << 4 | (uint32_t)tb << 16);
+            xv[k] = par_key((uint32_t)ck, db, tb);
             pc = c[k];
             pp = p[k];
         }
@@ -1143,20 +1094,16 @@ __device__ bool par_row(const RowArgs &a, ParLds &l, int64_t r, int64_t start, i
             int32_t ti[PAR_K], S[PAR_K], CH[PAR_K], pi[PAR_K], oi[PAR_K];
 #pragma unroll
             for (int k = 0; k < PAR_K; ++k) {
-                const bool act = ib + k < m;
-                const int32_t c = par_class(x[k]), db = par_depth(x[k]), tb = par_threads(x[k]);
-                thr[k] = act & (c == C_THR) & (tb == lev - 1);
-                ethr[k] = act & (c == C_END_THR) & (tb == lev);
-                const bool epar_in = act & (c == C_END_PAR) & (db == lev + 1);
-                const bool ethr_in = act & (c == C_END_THR) & (tb == lev + 1);
-                par[k] = act & (c == C_PAR) & (db == lev - 1);
-                epar[k] = act & (c == C_END_PAR) & (db == lev);
-                const bool eout = act & (c == C_END_OUT) & (db == lev) & (tb == lev - 1);
+                /* phase A left class 0 in the places of the last pass past m */
+                thr[k] = x[k] == par_key(C_THR, lev, lev - 1);
+                ethr[k] = x[k] == par_key(C_END_THR, lev, lev);
+                par[k] = x[k] == par_key(C_PAR, lev - 1, lev - 1);
+                epar[k] = x[k] == par_key(C_END_PAR, lev, lev - 1);
                 ti[k] = thr[k] ? ib + k : -1;
-                S[k] = epar_in ? sav[k] : 0;
-                CH[k] = ethr_in ? tk[k] : 0;
+                S[k] = x[k] == par_key(C_END_PAR, lev + 1, lev) ? sav[k] : 0;
+                CH[k] = x[k] == par_key(C_END_THR, lev + 1, lev + 1) ? tk[k] : 0;
                 pi[k] = par[k] ? ib + k : -1;
-                oi[k] = eout ? ib + k : -1;
+                oi[k] = x[k] == par_key(C_END_OUT, lev, lev - 1) ? ib + k : -1;
             }
             par_incl_scan<OpMax>(ti, c_thr, lane);  /* the thread each event is in */
             par_seg_scan<OpAdd>(S, thr, c_S, lane);
@@ -1182,7 +1129,7 @@ __device__ bool par_row(const RowArgs &a, ParLds &l, int64_t r, int64_t start, i
                 if (ethr[k]) {
                     const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
                     if (kk < n_e) {
-                        const int32_t t = par_class(l.X[pi[k] + 2 + 2 * kk]);
+                        const int32_t t = l.X[pi[k] + 2 + 2 * kk] & 15;
                         my_sub += t == C_SUB ? own[k] : 0;
                         my_tri += t == C_TRI ? own[k] : 0;
                     }
@@ -1218,8 +1165,8 @@ __device__ bool par_row(const RowArgs &a, ParLds &l, int64_t r, int64_t start, i
 
 /* One wave per row (a small batch).  A row par_row does not hold runs through
  * the automaton on lane 0 (the single automaton call site of this kernel),
- * with MID_DEPTH frames in LDS, as rows_mid would; one that needs still more
- * is listed for the deep tier. */
+ * with MID_DEPTH frames in LDS; one that needs still more is listed for the deep
+ * tier. */
 template <bool LENIENT>
 __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ mode,
                                                int32_t *__restrict__ counters, int32_t *__restrict__ deep_rows)
@@ -1243,12 +1190,13 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
     }
     if (par_row<LENIENT>(a, l, r, start, len, s0, s1, (md & MODE_COMPACT) != 0, lane)) return;
     if (lane == 0) {
-        Automaton<LdsStore<MID_DEPTH>, LENIENT> A;
+        Automaton<LdsStore, LENIENT> A;
         A.st.lds = l.TOK; /* unused on this path */
         A.st.tid = 0;
         A.st.nt = 1;
+        A.st.depth = MID_DEPTH;
         A.init();
-        if (drive_row<false>(a, r, start + a.mis, len, (md & MODE_COMPACT) != 0, A)) A.finish(len);
+        if (drive_row(a, r, start + a.mis, len, (md & MODE_COMPACT) != 0, A)) A.finish(len);
         if (A.overflow) {
             mode[r] = md | MODE_DEEP;
             deep_rows[atomicAdd(&counters[1], 1)] = (int32_t)r;
@@ -1258,55 +1206,390 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
     }
 }
 
-/* One thread per row.  mode[r] == MODE_COMPACT: the scan left the row's events as one
- * compact list; 0: per-segment lists.  A row that needs more than FAST_DEPTH
- * frames (or more than 64 entries in an open block) is listed for rows_mid.
- * Few frames keep the LDS per block small, so that many waves hide the
- * latency of the branchy automaton.  Rows with a segment whose list the scan
- * could not store are left by their lanes and evaluated one after the other by
- * the whole wave (par_row, in the frames' LDS); one that par_row does not hold
- * is listed for rows_mid. */
-template <bool LENIENT>
-__global__ void __launch_bounds__(64) rows_fast(RowArgs a, const uint8_t *__restrict__ mode,
-                                                int32_t *__restrict__ counters, int32_t *__restrict__ mid_rows,
-                                                int32_t lane_shift)
+/* ------------------------------------------------------------------ rows_quad */
+
+/* The widths of rows_quad: QUAD_W lanes (one DPP row) per row, QUAD_K
+ * consecutive events per lane. */
+constexpr int QUAD_W = 16;
+constexpr int QUAD_K = 8;
+constexpr int QUAD_ROWS = WAVE / QUAD_W;
+constexpr int QUAD_EVENTS = QUAD_W * QUAD_K;
+static_assert(QUAD_ROWS * QUAD_EVENTS <= PAR_LDS, "rows_quad keeps its events in par_row's LDS");
+
+/* Scans over the QUAD_W lanes of a row stay inside a DPP row: four shifts and
+ * no carries between rows of lanes. */
+template <class Op>
+__device__ __forceinline__ int32_t quad_lane_scan(int32_t v)
 {
-    static_assert(FAST_DEPTH * FRAME_WORDS * 64 <= PAR_LDS, "the frames and par_row share the LDS");
+    v = Op::f(v, row_shr<1>(v, Op::ident));
+    v = Op::f(v, row_shr<2>(v, Op::ident));
+    v = Op::f(v, row_shr<4>(v, Op::ident));
+    return Op::f(v, row_shr<8>(v, Op::ident));
+}
+
+/* Value of the row's last lane, in all of its lanes. */
+__device__ __forceinline__ int32_t quad_last(int32_t v, int lane) { return __shfl(v, lane | (QUAD_W - 1), WAVE); }
+
+/* Inclusive scan over a row's events in order. */
+template <class Op>
+__device__ __forceinline__ void quad_incl_scan(int32_t (&v)[QUAD_K])
+{
+#pragma unroll
+    for (int k = 1; k < QUAD_K; ++k) v[k] = Op::f(v[k - 1], v[k]);
+    const int32_t before = row_shr<1>(quad_lane_scan<Op>(v[QUAD_K - 1]), Op::ident);
+#pragma unroll
+    for (int k = 0; k < QUAD_K; ++k) v[k] = Op::f(before, v[k]);
+}
+
+/* Segment heads of a row's events, shared by the segmented scans over the
+ * same heads: seen[k], a head among the lane's events 0 .. k; at[i], a head in
+ * the 2^i lanes up to this one. */
+struct QuadHeads {
+    bool seen[QUAD_K];
+    bool at[4];
+};
+
+__device__ __forceinline__ QuadHeads quad_heads(const bool (&head)[QUAD_K])
+{
+    QuadHeads h;
+    h.seen[0] = head[0];
+#pragma unroll
+    for (int k = 1; k < QUAD_K; ++k) h.seen[k] = h.seen[k - 1] | head[k];
+    int32_t f = h.seen[QUAD_K - 1] ? 1 : 0;
+    h.at[0] = f != 0;
+    f |= row_shr<1>(f, 0);
+    h.at[1] = f != 0;
+    f |= row_shr<2>(f, 0);
+    h.at[2] = f != 0;
+    f |= row_shr<4>(f, 0);
+    h.at[3] = f != 0;
+    return h;
+}
+
+/* Segmented inclusive scan: restarts at heads; events before the first head
+ * hold what precedes it (unused).  Op::ident must be Op's identity on v. */
+template <class Op>
+__device__ __forceinline__ void quad_seg_scan(int32_t (&v)[QUAD_K], const bool (&head)[QUAD_K], const QuadHeads &h)
+{
+#pragma unroll
+    for (int k = 1; k < QUAD_K; ++k) v[k] = head[k] ? v[k] : Op::f(v[k - 1], v[k]);
+    int32_t t = v[QUAD_K - 1];
+    int32_t o = Op::f(row_shr<1>(t, Op::ident), t);
+    t = h.at[0] ? t : o;
+    o = Op::f(row_shr<2>(t, Op::ident), t);
+    t = h.at[1] ? t : o;
+    o = Op::f(row_shr<4>(t, Op::ident), t);
+    t = h.at[2] ? t : o;
+    o = Op::f(row_shr<8>(t, Op::ident), t);
+    t = h.at[3] ? t : o;
+    const int32_t in = row_shr<1>(t, Op::ident);
+#pragma unroll
+    for (int k = 0; k < QUAD_K; ++k) v[k] = h.seen[k] ? v[k] : Op::f(in, v[k]);
+}
+
+/* A larger batch: four rows per wave, sixteen lanes per row, eight consecutive
+ * events per lane, so that a row of up to QUAD_EVENTS events (99 of 100 of the
+ * generator's; the median row holds 38) stays in registers from its list to its
+ * outputs.  The same two phases as par_row, without its passes and carries.
+ * It is bound by instructions: par_row spends a wave's on one row, whose events
+ * fill a sixth of its 256 places, and the per-lane automaton's lanes wait for
+ * each other in most of its states.  64,000 rows of 20,000 tokens: 67 us, one
+ * wave per row 124, one lane per row 219; 712,000 rows: 569 us, 1,266, 644.
+ * Rows it does not hold (more events, a segment the scan could not store) are
+ * evaluated one after the other by the whole wave (par_row); one that par_row
+ * does not hold either is listed for rows_listed. */
+template <bool LENIENT>
+__global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__restrict__ mode,
+                                                int32_t *__restrict__ counters, int32_t *__restrict__ listed)
+{
     __shared__ __align__(16) ParLds l;
-    const int lane = threadIdx.x;
-    /* every (1 << lane_shift)-th lane takes a row (64 >> lane_shift rows per wave) */
-    const int64_t r0 = (int64_t)blockIdx.x * (blockDim.x >> lane_shift);
-    const int64_t r = r0 + (lane >> lane_shift);
-    const bool mine = (lane & ((1 << lane_shift) - 1)) == 0 && r < a.n;
-    const bool fits = a.seg_off[a.n] <= a.seg_cap;
-    bool dense = false;
-    if (mine) {
-        const int64_t start = a.starts[r];
-        const int32_t len = a.lengths[r];
-        if (start < 0 || len < 0) {
-            write_row(a.out, r, 0, 0, 0, 0, 0, 0, 0, PARASON_FLAG_BAD_ROW);
-        } else if (!fits) {
-            write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_WS_OVERFLOW);
-        } else {
-            Automaton<LdsStore<FAST_DEPTH>, LENIENT> A;
-            A.st.lds = reinterpret_cast<int32_t *>(&l);
-            A.st.tid = lane;
-            A.st.nt = blockDim.x;
-            A.init();
-            if (drive_row<true>(a, r, start + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A, &dense)) A.finish(len);
-            if (A.overflow) mid_rows[atomicAdd(&counters[0], 1)] = (int32_t)r; /* rows_mid writes this row */
-            else if (!dense) write_result(a.out, r, len, A);
+    const int lane = threadIdx.x, l16 = lane & (QUAD_W - 1);
+    uint32_t *ev = reinterpret_cast<uint32_t *>(&l) + (lane / QUAD_W) * QUAD_EVENTS; /* the row's events */
+    const int64_t r0 = (int64_t)blockIdx.x * QUAD_ROWS;
+    const int64_t r = min(r0 + lane / QUAD_W, a.n - 1);
+    /* the row's records in one round of loads, before any branch */
+    const int64_t start = a.starts[r];
+    const int32_t len = a.lengths[r];
+    const int64_t S = a.seg_off[a.n], s0 = a.seg_off[r], s1 = a.seg_off[r + 1];
+    const bool compact = (mode[r] & MODE_COMPACT) != 0;
+    const bool bad = start < 0 || len < 0;
+    const bool over = S > a.seg_cap;
+    const bool mine = r0 + lane / QUAD_W < a.n; /* the last wave's lanes past the batch repeat its last row */
+    const bool eval = mine && !bad && !over;
+    if (mine && !eval && l16 == 0) {
+        if (bad) write_row(a.out, r, 0, 0, 0, 0, 0, 0, 0, PARASON_FLAG_BAD_ROW);
+        else write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_WS_OVERFLOW);
+    }
+    /* the row's events (row position << 4 | class): lane l16 holds events
+     * QUAD_K l16 .. QUAD_K l16 + 7 of the m */
+    const int64_t g = start + a.mis;
+    int32_t m = 0;
+    bool held = eval;
+    const bool has_list = eval && compact;
+    uint32_t first_slot = 0;
+    if (has_list) {
+        const SegRec rec = a.seg[s0];
+        m = rec.count;
+        held = m <= QUAD_EVENTS;
+        first_slot = held && m > 0 ? rec.list : 0u;
+    }
+    uint32_t e[QUAD_K];
+    {
+        /* whole quads of four slots, as they are stored; lanes past the list
+         * read its last quad again */
+        const int32_t last_quad = held && m > 0 ? (m - 1) / 4 : 0;
+        const uint4 *list = reinterpret_cast<const uint4 *>(a.slots + first_slot);
+        const uint4 q0 = list[min(2 * l16, last_quad)], q1 = list[min(2 * l16 + 1, last_quad)];
+        e[0] = q0.x, e[1] = q0.y, e[2] = q0.z, e[3] = q0.w;
+        e[4] = q1.x, e[5] = q1.y, e[6] = q1.z, e[7] = q1.w;
+    }
+    const bool split = eval && !compact;
+    held = held && (!split || len < (1 << 27));
+    if (__ballot(split && held) != 0) {
+        /* sixteen segments at a time: their records, an exclusive scan of
+         * their counts, then every lane copies its segment's list */
+        const int64_t vrow0 = row_first_vec(g);
+        for (int64_t c0 = s0; __ballot(split && held && c0 < s1) != 0; c0 += QUAD_W) {
+            const int64_t s = c0 + l16;
+            const bool in = split && held && s < s1;
+            const SegRec rec = in ? a.seg[s] : SegRec{0, 0u};
+            const uint32_t dense = (uint32_t)(__ballot(rec.count == DENSE) >> (lane & ~(QUAD_W - 1))) & 0xffffu;
+            const int32_t cnt = dense != 0 ? 0 : rec.count;
+            const int32_t incl = quad_lane_scan<OpAdd>(cnt);
+            const int32_t total = quad_last(incl, lane);
+            held = held && dense == 0 && m + total <= QUAD_EVENTS;
+            if (held && cnt > 0) {
+                const int32_t base = (int32_t)(4 * (vrow0 + (s - s0) * SEG_VEC) - g);
+                const uint4 *list = reinterpret_cast<const uint4 *>(a.slots + rec.list);
+                uint32_t *dst = ev + m + incl - cnt;
+                const int32_t last = (cnt - 1) / 4;
+                for (int32_t q = 0; q <= last; q += 2) { /* two quads in flight */
+                    const uint4 x = list[q], y = list[min(q + 1, last)];
+                    const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (4 * q + u < cnt)
+                            dst[4 * q + u] = (uint32_t)(base + (int32_t)(w[u] >> 4)) << 4 | (w[u] & 15u);
+                }
+            }
+            m += held ? total : 0;
+        }
+        __syncthreads();
+        if (split) {
+            const uint4 q0 = reinterpret_cast<const uint4 *>(ev)[2 * l16], q1 = reinterpret_cast<const uint4 *>(ev)[2 * l16 + 1];
+            e[0] = q0.x, e[1] = q0.y, e[2] = q0.z, e[3] = q0.w;
+            e[4] = q1.x, e[5] = q1.y, e[6] = q1.z, e[7] = q1.w;
         }
     }
-    uint64_t todo = __ballot(dense);
+    if (!held) m = 0;
+    if (has_list) { /* the types of outline entries are looked up here */
+        reinterpret_cast<uint4 *>(ev)[2 * l16] = make_uint4(e[0], e[1], e[2], e[3]);
+        reinterpret_cast<uint4 *>(ev)[2 * l16 + 1] = make_uint4(e[4], e[5], e[6], e[7]);
+    }
+    __syncthreads();
+
+    /* phase A: validity, first error, depth and open threads before each event */
+    const int32_t ib = QUAD_K * l16;
+    int32_t key[QUAD_K], d_in[QUAD_K];
+#pragma unroll
+    for (int k = 0; k < QUAD_K; ++k) {
+        if (ib + k >= m) e[k] = 0;
+        const uint32_t c = e[k] & 15u;
+        /* depth in the low half, open threads in the high half */
+        d_in[k] = (c == C_PAR ? 1 : 0) - (c == C_END_PAR ? 1 : 0) + (c == C_THR ? 0x10000 : 0) - (c == C_END_THR ? 0x10000 : 0);
+        key[k] = d_in[k];
+    }
+    quad_incl_scan<OpAdd>(d_in);
+    int32_t err = INT32_MAX, max_depth = 0, n_blocks = 0;
+    {
+        /* -1 before the first event: a class before </think> and a position */
+        const uint32_t e_prev = (uint32_t)row_shr<1>((int32_t)e[QUAD_K - 1], -1);
+        int32_t pc = l16 == 0 ? -1 : (int32_t)(e_prev & 15u), pp = l16 == 0 ? -1 : (int32_t)(e_prev >> 4);
+#pragma unroll
+        for (int k = 0; k < QUAD_K; ++k) {
+            const int32_t before = d_in[k] - key[k];
+            const int32_t db = (int32_t)(int16_t)before, tb = (before - db) >> 16;
+            const int32_t ck = (int32_t)(e[k] & 15u), p = (int32_t)(e[k] >> 4);
+            const bool act = ib + k < m;
+            const uint32_t st = state_at(pc);
+            const int32_t gap = p - pp - 1;
+            const bool text_ok = (gap == 0) | text_allowed(st) | (LENIENT & (st != S_START));
+            const bool closes_entry = (ck == C_END_SUB) | (ck == C_END_TRI);
+            const bool tag_ok = class_allowed(st, ck) & !((ck == C_END_THINK) & (db != 0)) &
+                                !((ck == C_END_THR) & (db == 0)) & !(closes_entry & ((ck != pc + 1) | (gap == 0)));
+            const int32_t ek = text_ok ? (tag_ok ? INT32_MAX : p) : pp + 1;
+            const bool opens = act & (ck == C_PAR);
+            err = min(err, act ? ek : INT32_MAX);
+            max_depth = max(max_depth, opens ? db + 1 : 0);
+            n_blocks += opens ? 1 : 0;
+            key[k] = par_key((uint32_t)ck, db, tb);
+            pc = ck;
+            pp = p;
+        }
+    }
+    err = quad_last(quad_lane_scan<OpMin>(err), lane);
+    max_depth = quad_last(quad_lane_scan<OpMax>(max_depth), lane);
+    n_blocks = quad_last(quad_lane_scan<OpAdd>(n_blocks), lane);
+    if (held && err == INT32_MAX) {
+        /* the end of the row: the text after the last tag, then </think> must have come */
+        const uint32_t e_last = m > 0 ? ev[m - 1] : 0u;
+        const int32_t pc = m > 0 ? (int32_t)(e_last & 15u) : -1, pp = m > 0 ? (int32_t)(e_last >> 4) : -1;
+        const uint32_t st = state_at(pc);
+        const int32_t gap = len - pp - 1;
+        const bool text_ok = gap == 0 || text_allowed(st) || (LENIENT && st != S_START);
+        if (!text_ok) err = pp + 1;
+        else if (st != S_TRAIL) err = len;
+    }
+    const bool valid = held && err == INT32_MAX;
+    if (!valid) {
+#pragma unroll
+        for (int k = 0; k < QUAD_K; ++k) key[k] = 0; /* no structural tag of any level */
+        max_depth = 0;
+    }
+
+    /* phase B: level by level, deepest first, as many as the wave's deepest row has */
+    int32_t my_sub = 0, my_tri = 0, my_saved = 0;
+    bool my_mismatch = false;
+    int32_t val[QUAD_K]; /* at a </Thread> its thread's tokens, at a </Parallel> its block's saved tokens */
+#pragma unroll
+    for (int k = 0; k < QUAD_K; ++k) val[k] = 0;
+    for (int32_t lev = wave_max32(max_depth); lev >= 1; --lev) {
+        bool thr[QUAD_K], par[QUAD_K];
+        int32_t at[QUAD_K], S[QUAD_K], CH[QUAD_K], pi[QUAD_K], oi[QUAD_K];
+#pragma unroll
+        for (int k = 0; k < QUAD_K; ++k) {
+            thr[k] = key[k] == par_key(C_THR, lev, lev - 1);
+            par[k] = key[k] == par_key(C_PAR, lev - 1, lev - 1);
+            at[k] = thr[k] ? (int32_t)(e[k] >> 4) : -1;
+            S[k] = key[k] == par_key(C_END_PAR, lev + 1, lev) ? val[k] : 0;
+            CH[k] = key[k] == par_key(C_END_THR, lev + 1, lev + 1) ? val[k] : 0;
+            pi[k] = par[k] ? ib + k : -1;
+            oi[k] = key[k] == par_key(C_END_OUT, lev, lev - 1) ? ib + k : -1;
+        }
+        quad_incl_scan<OpMax>(at); /* where the thread each event is in begins */
+        const QuadHeads ht = quad_heads(thr);
+        quad_seg_scan<OpAdd>(S, thr, ht);
+        quad_seg_scan<OpAdd>(CH, thr, ht);
+        quad_incl_scan<OpMax>(pi); /* the block each event is in ... */
+        quad_incl_scan<OpMax>(oi); /* ... and its outline's end */
+        int32_t sum[QUAD_K], mx[QUAD_K], nt[QUAD_K];
+#pragma unroll
+        for (int k = 0; k < QUAD_K; ++k) {
+            const bool ethr = key[k] == par_key(C_END_THR, lev, lev);
+            const int32_t tok = ethr ? (int32_t)(e[k] >> 4) - at[k] + 1 : 0;
+            if (ethr) val[k] = tok; /* read by the next level's threads */
+            sum[k] = tok;
+            mx[k] = ethr ? tok - S[k] : 0; /* the thread's latency */
+            CH[k] = tok - CH[k];           /* its own tokens */
+            nt[k] = ethr ? 1 : 0;
+        }
+        const QuadHeads hp = quad_heads(par);
+        quad_seg_scan<OpAdd>(sum, par, hp);
+        quad_seg_scan<OpMax>(mx, par, hp);
+        quad_seg_scan<OpAdd>(nt, par, hp);
+#pragma unroll
+        for (int k = 0; k < QUAD_K; ++k) {
+            const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
+            if (key[k] == par_key(C_END_THR, lev, lev)) {
+                const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
+                if (kk < n_e) {
+                    const uint32_t t = ev[pi[k] + 2 + 2 * kk] & 15u;
+                    my_sub += t == C_SUB ? CH[k] : 0;
+                    my_tri += t == C_TRI ? CH[k] : 0;
+                }
+            }
+            if (key[k] == par_key(C_END_PAR, lev, lev - 1)) {
+                val[k] = sum[k] - mx[k];
+                my_mismatch = my_mismatch || nt[k] != n_e;
+                my_saved += lev == 1 ? val[k] : 0;
+            }
+        }
+    }
+    const int32_t n_sub = quad_last(quad_lane_scan<OpAdd>(my_sub), lane);
+    const int32_t n_tri = quad_last(quad_lane_scan<OpAdd>(my_tri), lane);
+    const int32_t saved = quad_last(quad_lane_scan<OpAdd>(my_saved), lane);
+    const bool mismatch = ((uint32_t)(__ballot(my_mismatch) >> (lane & ~(QUAD_W - 1))) & 0xffffu) != 0;
+    if (held && l16 == 0) {
+        if (valid) {
+            uint32_t fl = PARASON_FLAG_VALID;
+            if (mismatch) fl |= PARASON_FLAG_COUNT_MISMATCH;
+            if (n_blocks > 0) fl |= PARASON_FLAG_TRIGGERED;
+            write_row(a.out, r, len, len - saved, n_sub, n_tri, n_blocks, max_depth, -1, fl);
+        } else {
+            write_row(a.out, r, len, len, 0, 0, 0, 0, err, err == len ? PARASON_FLAG_TRUNCATED : 0u);
+        }
+    }
+    uint64_t todo = __ballot(eval && !held && l16 == 0);
     while (todo != 0) {
-        __syncthreads(); /* the LDS of the row before (or the frames) is rewritten */
-        const int64_t rd = r0 + (__builtin_ctzll(todo) >> lane_shift);
+        __syncthreads(); /* the LDS is rewritten */
+        const int src = __builtin_ctzll(todo);
         todo &= todo - 1;
-        const int64_t start = uniform64(a.starts[rd]), s0 = uniform64(a.seg_off[rd]), s1 = uniform64(a.seg_off[rd + 1]);
-        const int32_t len = __builtin_amdgcn_readfirstlane(a.lengths[rd]);
-        if (!par_row<LENIENT>(a, l, rd, start, len, s0, s1, false, lane) && lane == 0)
-            mid_rows[atomicAdd(&counters[0], 1)] = (int32_t)rd;
+        const int64_t rd = r0 + src / QUAD_W;
+        const int64_t st = uniform64(a.starts[rd]), f0 = uniform64(a.seg_off[rd]), f1 = uniform64(a.seg_off[rd + 1]);
+        const int32_t ln = __builtin_amdgcn_readfirstlane(a.lengths[rd]);
+        const bool cp = __builtin_amdgcn_readfirstlane(mode[rd] & MODE_COMPACT) != 0;
+        if (!par_row<LENIENT>(a, l, rd, st, ln, f0, f1, cp, lane) && lane == 0)
+            listed[atomicAdd(&counters[0], 1)] = (int32_t)rd;
+    }
+}
+
+/* The rows rows_quad listed (more than PAR_EVENTS events, or nested deeper than
+ * PAR_LEVELS), by the automaton, one thread each, 64 at a time per wave: with
+ * FAST_DEPTH frames per row, so that the LDS leaves room for the waves that
+ * hide the latency of the branchy automaton; then those that need more frames
+ * (or more than 64 entries in an open block), MID_ROWS at a time with
+ * MID_DEPTH frames in the same LDS.  A row that needs still more is listed for
+ * the deep tier. */
+constexpr int MID_ROWS = FAST_DEPTH * WAVE / MID_DEPTH;
+static_assert(MID_ROWS >= 1, "a deeper row fits the frames of a wave's rows");
+
+template <bool LENIENT>
+__global__ void __launch_bounds__(64) rows_listed(RowArgs a, uint8_t *__restrict__ mode, int32_t *__restrict__ counters,
+                                                  const int32_t *__restrict__ listed, int32_t *__restrict__ deep_rows)
+{
+    __shared__ int32_t lds[FAST_DEPTH * FRAME_WORDS * WAVE];
+    const int lane = threadIdx.x;
+    const int32_t n_listed = counters[0];
+    for (int32_t i0 = (int32_t)blockIdx.x * WAVE; i0 < n_listed; i0 += (int32_t)gridDim.x * WAVE) {
+        uint64_t todo = ~0ull; /* the rows of this turn's lanes still to evaluate */
+        bool deeper = false;
+        while (todo != 0) {
+            __syncthreads(); /* the frames' layout changes */
+            /* every lane's row, or the next MID_ROWS of those that need more frames, in lanes 0, 1, ... */
+            int src = lane;
+            bool mine = i0 + lane < n_listed;
+            if (deeper) {
+                uint64_t t = todo;
+                for (int k = 0; k < lane && k < MID_ROWS; ++k) t &= t - 1;
+                mine = lane < MID_ROWS && t != 0;
+                src = mine ? __builtin_ctzll(t) : 0;
+                for (int k = 0; k < MID_ROWS; ++k) todo &= todo - 1;
+            }
+            bool again = false;
+            if (mine) {
+                const int64_t r = listed[i0 + src];
+                const int32_t len = a.lengths[r];
+                Automaton<LdsStore, LENIENT> A;
+                A.st.lds = lds;
+                A.st.tid = lane;
+                A.st.nt = deeper ? MID_ROWS : WAVE;
+                A.st.depth = deeper ? MID_DEPTH : FAST_DEPTH;
+                A.init();
+                if (drive_row(a, r, a.starts[r] + a.mis, len, (mode[r] & MODE_COMPACT) != 0, A)) A.finish(len);
+                if (!A.overflow) {
+                    write_result(a.out, r, len, A);
+                } else if (deeper) {
+                    mode[r] |= MODE_DEEP;
+                    deep_rows[atomicAdd(&counters[1], 1)] = (int32_t)r;
+                } else {
+                    again = true;
+                }
+            }
+            if (!deeper) {
+                todo = __ballot(again);
+                deeper = true;
+            }
+        }
     }
 }
 
@@ -1429,14 +1712,11 @@ struct ScanArgs {
     int64_t seg_cap;
     SegRec *seg;
     uint32_t *slots;
-    uint32_t pool_base;  /* the pool: slots [pool_base, pool_base + pool_slots); wave w's */
-    uint32_t pool_slots; /* region starts at pool_base + POOL_PER_SEG * s_begin + x * w and ends at
-                            pool_base + POOL_PER_SEG * s_end + x * (w + 1), with
-                            x = (pool_slots - POOL_PER_SEG * S) / W rounded down to 4 */
+    uint32_t pool_slots; /* the pool: slots [0, pool_slots); wave w's region starts at
+                            POOL_PER_SEG * s_begin + x * w and ends at POOL_PER_SEG * s_end + x * (w + 1),
+                            with x = (pool_slots - POOL_PER_SEG * S) / W rounded down to 4 */
     uint8_t *mode;
     TagMatch tm;
-    int32_t *split_count; /* rows of more than one segment that no scan wave owns ... */
-    int32_t *split_rows;  /* ... listed here for gather_rows */
     int32_t *counters;    /* cleared by a scan that plans the batch itself */
 };
 
@@ -1500,10 +1780,6 @@ __device__ __forceinline__ bool collect_segment(const ScanArgs &a, const int4 (&
             /* the scan planned the batch itself: the wave holding a row's first
              * segment clears its mode (flush_row may set it again below) */
             if (lane == 0) a.mode[w.row] = 0;
-        } else if (!w.owned && w.last > w.first && w.len < (1 << 27) && lane == 0) {
-            /* the wave holding the first segment of a split row lists it for
-             * gather_rows (rows of 2^27 tokens or more stay per segment) */
-            a.split_rows[atomicAdd(a.split_count, 1)] = (int32_t)w.row;
         }
     }
     uint32_t cnt = 0; /* wave-uniform */
@@ -1611,7 +1887,7 @@ __device__ __forceinline__ void scan_plan(const ScanArgs &a, int64_t *off, int64
  * boundary.  Every range (share or chunk) has its own region of the slot pool:
  * range q (shares 0 .. W-1, then chunk i as W + i) covering segments [b, e)
  * owns slots [POOL_PER_SEG * b + x * q, POOL_PER_SEG * e + x * (q + 1)) past
- * pool_base, x = (pool_slots - POOL_PER_SEG * S) / (W + chunks) rounded down
+ * the pool's start, x = (pool_slots - POOL_PER_SEG * S) / (W + chunks) rounded down
  * to 4, so regions are disjoint and in segment order. */
 constexpr int64_t DYN_MIN_PER_WAVE = 256;
 constexpr int64_t DYN_NUM = 3, DYN_DEN = 16;
@@ -1783,9 +2059,9 @@ __global__ void __launch_bounds__(WAVE * scan_waves<PLAN>(), PARASON_SCAN_WAVES_
     }
     while (true) {
         if (b < e) {
-            const uint32_t pc = __builtin_amdgcn_readfirstlane(a.pool_base + POOL_PER_SEG * (uint32_t)b + extra * (uint32_t)q);
+            const uint32_t pc = __builtin_amdgcn_readfirstlane(POOL_PER_SEG * (uint32_t)b + extra * (uint32_t)q);
             const uint32_t p_end =
-                __builtin_amdgcn_readfirstlane(a.pool_base + POOL_PER_SEG * (uint32_t)e + extra * (uint32_t)(q + 1));
+                __builtin_amdgcn_readfirstlane(POOL_PER_SEG * (uint32_t)e + extra * (uint32_t)(q + 1));
             scan_range<MODE, PLAN>(a, seg_off, PLAN ? plan_st : a.starts, PLAN ? plan_ln : a.lengths, b, e, pc, p_end,
                                    lev, tab, lane);
         }
@@ -1877,91 +2153,6 @@ __global__ void __launch_bounds__(WAVE * SCAN_WAVES) read_probe(const int4 *__re
                        (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 31) ^
                        (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 47) ^ (uint32_t)lane63((int32_t)v);
     if (lane == 0) sink[wave % sink_len] = w;
-}
-
-/* ------------------------------------------------------------------ gather */
-
-struct GatherArgs {
-    const int64_t *starts;
-    int64_t n, mis;
-    const int64_t *seg_off;
-    int64_t seg_cap;
-    SegRec *seg;
-    uint32_t *slots;
-    uint8_t *mode;
-    const int32_t *split_count;
-    const int32_t *split_rows;
-};
-
-constexpr int GATHER_EVENTS = 1024; /* LDS events per gather wave */
-
-/* Gather the events of row `row` (split between scan waves: one list per
- * segment, segment positions) into one list in the row's gather slots
- * (GATHER_SLOTS per segment of the row, from slot GATHER_SLOTS * seg_off[row]),
- * in position order, with row positions (the compact form, mode 1), through
- * the wave's LDS buffer lds[0 .. GATHER_EVENTS).  A row with a DENSE segment,
- * or with more events than its gather slots or the buffer hold, is left as it
- * is; the whole wave calls this. */
-__device__ __forceinline__ void gather_row(const GatherArgs &a, int64_t row, uint32_t *lds, int lane)
-{
-    const int64_t s0 = uniform64(a.seg_off[row]), s1 = uniform64(a.seg_off[row + 1]);
-    const int64_t g = uniform64(a.starts[row] + a.mis);
-    const int64_t vrow0 = row_first_vec(g);
-    bool dense = false;
-    int64_t total = 0;
-    for (int64_t c0 = s0; c0 < s1; c0 += WAVE) {
-        const int64_t s = c0 + lane;
-        const int32_t cnt = s < s1 ? a.seg[s].count : 0;
-        dense = dense || cnt == DENSE;
-        total += lane63(wave_incl_scan32(cnt, lane)); /* DENSE counts cannot overflow it */
-    }
-    if (__ballot(dense) != 0 || total > GATHER_EVENTS || total > (s1 - s0) * GATHER_SLOTS) return;
-    int64_t carry = 0; /* events of the segments before this chunk */
-    for (int64_t c0 = s0; c0 < s1; c0 += WAVE) {
-        const int64_t s = c0 + lane;
-        const SegRec rec = s < s1 ? a.seg[s] : SegRec{0, 0u};
-        const int32_t cnt = rec.count;
-        const uint32_t list = rec.list; /* meaningless for a segment without events */
-        const int32_t incl = wave_incl_scan32(cnt, lane);
-        const int32_t excl = incl - cnt;
-        const int32_t n_c = lane63(incl);
-        for (int32_t f0 = 0; f0 < n_c; f0 += WAVE) {
-            const int32_t f = f0 + lane; /* the chunk's f-th event, of segment c0 + j */
-            const int32_t j = last_lane_at_most(excl, f);
-            const int32_t first = __shfl(excl, j, WAVE);
-            const uint32_t lj = __shfl(list, j, WAVE);
-            if (f < n_c) {
-                const int64_t seg = c0 + j;
-                const uint32_t w = a.slots[(int64_t)lj + (f - first)];
-                /* row position of segment position 0 */
-                const int64_t base = 4 * (vrow0 + (seg - s0) * SEG_VEC) - g;
-                lds[carry + f] = ((uint32_t)(base + (int64_t)(w >> 4)) << 4) | (w & 15u);
-            }
-        }
-        carry += n_c;
-    }
-    /* lanes store what other lanes loaded: every load above first */
-    __builtin_amdgcn_wave_barrier();
-    uint32_t *dst = a.slots + s0 * GATHER_SLOTS;
-    for (int64_t i = lane; i < carry; i += WAVE) dst[i] = lds[i];
-    if (lane == 0) {
-        a.seg[s0] = SegRec{(int32_t)carry, (uint32_t)(s0 * GATHER_SLOTS)};
-        a.mode[row] = MODE_COMPACT;
-    }
-}
-
-/* The rows the scan listed as split between its waves, for the per-lane row
- * kernel: one wave per listed row (grid-stride over the list). */
-__global__ void __launch_bounds__(256) gather_rows(GatherArgs a)
-{
-    __shared__ uint32_t lds[256 / WAVE][GATHER_EVENTS];
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-    const int64_t wave = uniform64(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE);
-    const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    if (a.seg_off[a.n] > a.seg_cap) return; /* the scan wrote nothing: the row kernel reports it */
-    const int32_t n_split = __builtin_amdgcn_readfirstlane(*a.split_count);
-    for (int64_t i = wave; i < n_split; i += n_waves) gather_row(a, uniform64(a.split_rows[i]), lds[wib], lane);
 }
 
 /* ------------------------------------------------------------------ reward */
@@ -2137,7 +2328,7 @@ __device__ __forceinline__ void group_reward_memory(const RewardArgs &a, int64_t
                  xs(i), xr(i));
 }
 
-/* The deep tier's rows (listed by rows_par or rows_mid), run by the first
+/* The deep tier's rows (listed by rows_par or rows_listed), run by the first
  * block of group_reward instead of a launch of their own. */
 struct DeepArgs {
     RowArgs rows;

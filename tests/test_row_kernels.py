@@ -66,7 +66,7 @@ def test_unstored_segments_adversarial(emu_small_pool, cus):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,lo,hi,kind", [(2048, 1750, 5250, 0), (2056, 350, 1050, 0), (8192, 1, 2100, 1),
-                                          (12000, 350, 1050, 0), (40000, 300, 900, 0)])
+                                          (16384, 350, 1050, 0), (16392, 350, 1050, 0), (40000, 300, 900, 0)])
 def test_rows_on_the_gpu(n, lo, hi, kind):
     """Outline-heavy batches over the sizes where the row kernels change."""
     import torch
@@ -80,3 +80,21 @@ def test_rows_on_the_gpu(n, lo, hi, kind):
         got["flags"] = got["flags"].view(np.uint32)
         compare(got, *oracle_expect(tok, st, ln, co, S.CONTIGUOUS_TAGS, G, DEFAULT_COEF, flags),
                 what="rows %d flags %d" % (n, flags))
+
+
+@pytest.mark.gpu
+def test_adversarial_rows_in_a_large_batch_on_the_gpu():
+    """17,000 rows (four per wave): strings of every kind the row kernels hand
+    on, next to ones they hold, down to the deep tier."""
+    import torch
+
+    streams = adversarial_streams()
+    tokens, starts, lengths = pack([streams[i % len(streams)] for i in range(17000)], S.CONTIGUOUS_TAGS)
+    correct = (np.arange(lengths.size) % 3 != 0).astype(np.uint8)
+    dev = [torch.as_tensor(x).cuda() for x in (tokens, starts, lengths, correct)]
+    px = PX.Parason(S.CONTIGUOUS_TAGS, group_size=G, **DEFAULT_COEF)
+    got = {k: v.cpu().numpy() for k, v in px.run(*dev, total_tokens=tokens.size).items()}
+    got["flags"] = got["flags"].view(np.uint32)
+    compare(got, *oracle_expect(tokens, starts, lengths, correct, S.CONTIGUOUS_TAGS, G, DEFAULT_COEF),
+            what="adversarial, large batch")
+    assert got["max_depth"].max() >= 1000
