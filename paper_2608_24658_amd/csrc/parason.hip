@@ -42,7 +42,7 @@ constexpr int LISTED_WAVES_PER_CU = 20; /* rows_listed waves a CU holds (8 KB of
 /* Byte offsets of the workspace sections for n rows. */
 struct Layout {
     size_t seg_off, tile_sum, tile_off, counters, mode, listed, deep_rows, spare;
-    size_t red_d, red_i, stats;
+    size_t moments, metrics; /* the batch reductions' records */
     size_t fixed;  /* bytes before the per-segment sections */
     int64_t n_tiles;
 };
@@ -66,15 +66,16 @@ Layout layout_for(int64_t n)
     o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
     L.deep_rows = o;
     o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
-    L.spare = o; /* kept, so that workspaces keep their sizes */
+    L.spare = o;
     o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
-    /* partial sums of the batch reductions (one record per 4096 rows) */
-    L.red_d = o;
+    /* no longer used; kept so that workspaces keep their sizes */
     o = align_up(o + (size_t)L.n_tiles * 3 * sizeof(double));
-    L.red_i = o;
-    o = align_up(o + (size_t)L.n_tiles * pk::NMI * sizeof(int64_t));
-    L.stats = o;
-    o = align_up(o + sizeof(pk::BatchStats));
+    o = align_up(o + (size_t)L.n_tiles * 9 * sizeof(int64_t));
+    o = align_up(o + 64);
+    /* the reductions run when the list of rows_listed is done with: four bytes
+     * per row hold a record of each tile of RED_THREADS rows, and one more */
+    L.moments = L.listed;
+    L.metrics = L.spare;
     L.fixed = o;
     return L;
 }
@@ -157,10 +158,6 @@ void find_tag_hash(pk::TagMatch &tm)
     }
 }
 
-/* The tiers of the row automaton, in the grammar's strict or lenient form.
- * The deep tier is a launch of its own only when deep_launch is set (the
- * batch-wide statistics need every row first); otherwise group_reward runs
- * it. */
 /* A small batch takes rows_par, one wave per row: its waves are done in one or
  * two rounds of the chip, and a row's own chain of steps, shorter over 64 lanes
  * than over 16, sets the time.  A larger one takes rows_quad, four rows per
@@ -169,10 +166,11 @@ void find_tag_hash(pk::TagMatch &tm)
  * rows of 20,000 tokens 980 and 935). */
 bool rows_par_batch(int64_t n, int cus) { return n <= (int64_t)cus * PAR_ROWS_PER_CU; }
 
+/* The row kernels, in the grammar's strict or lenient form (the deep tier runs
+ * in the kernel that follows them). */
 template <bool LENIENT>
 void launch_rows(const pk::RowArgs &ra, int cus, uint8_t *mode, int32_t *counters, int32_t *listed,
-                 int32_t *deep_rows, int32_t *deep_frames, uint32_t *deep_bits, bool deep_launch,
-                 hipStream_t stream)
+                 int32_t *deep_rows, hipStream_t stream)
 {
     if (rows_par_batch(ra.n, cus)) {
         /* rows_par runs the rows it does not hold through the automaton
@@ -184,9 +182,35 @@ void launch_rows(const pk::RowArgs &ra, int cus, uint8_t *mode, int32_t *counter
         hipLaunchKernelGGL(pk::rows_listed<LENIENT>, dim3((unsigned)(cus * LISTED_WAVES_PER_CU)), dim3(64), 0, stream,
                            ra, mode, counters, listed, deep_rows);
     }
-    if (deep_launch)
-        hipLaunchKernelGGL(pk::rows_deep<LENIENT>, dim3(1), dim3(64), 0, stream, ra, mode, counters, deep_rows,
-                           deep_frames, deep_bits);
+}
+
+/* The rewards and, with `metrics`, the batch metrics. */
+template <bool LENIENT>
+void launch_reward(const pk::RewardArgs &rw, const pk::DeepArgs &da, bool batch_stats, pk::MomentRec *moments,
+                   pk::MetricRec *recs, double *metrics, hipStream_t stream)
+{
+    const bool single = rw.n <= pk::RED_SINGLE && (batch_stats || metrics);
+    const unsigned threads = single ? (unsigned)((rw.n + pk::WAVE - 1) / pk::WAVE * pk::WAVE) : pk::RED_THREADS;
+    const unsigned blocks = (unsigned)((rw.n + threads - 1) / threads);
+    if (!batch_stats && metrics) {
+        hipLaunchKernelGGL((pk::group_reward<LENIENT, true>), dim3(blocks), dim3(threads), 0, stream, rw, da, recs,
+                           metrics);
+    } else if (!batch_stats) {
+        hipLaunchKernelGGL((pk::group_reward<LENIENT, false>), dim3(blocks), dim3(threads), 0, stream, rw, da, recs,
+                           metrics);
+    } else if (single) {
+        hipLaunchKernelGGL(pk::batch_single<LENIENT>, dim3(1), dim3(threads), 0, stream, rw, da, metrics);
+    } else {
+        const int32_t rpt = rw.n <= pk::RED_ONE_ROW ? 1 : pk::ROWS_PER_THREAD;
+        const int64_t tiles = (rw.n + pk::RED_THREADS * rpt - 1) / (pk::RED_THREADS * rpt);
+        hipLaunchKernelGGL(pk::batch_moments<LENIENT>, dim3((unsigned)tiles), dim3(pk::RED_THREADS), 0, stream, rw, da,
+                           moments, rpt);
+        hipLaunchKernelGGL(pk::batch_reward, dim3(blocks), dim3(threads), 0, stream, rw, moments, (int32_t)tiles + 1, recs,
+                           metrics);
+    }
+    if (metrics && blocks > 1)
+        hipLaunchKernelGGL(pk::metrics_final, dim3(1), dim3(pk::RED_THREADS), 0, stream, recs, (int64_t)blocks, rw.n,
+                           metrics);
 }
 
 /* The scan's persistent grid: SCAN_BLOCKS_PER_CU blocks of SCAN_WAVES waves
@@ -332,16 +356,12 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     uint8_t *mode = (uint8_t *)(ws + L.mode);
     int32_t *listed = (int32_t *)(ws + L.listed);
     int32_t *deep_rows = (int32_t *)(ws + L.deep_rows);
-    double *red_d = (double *)(ws + L.red_d);
-    int64_t *red_i = (int64_t *)(ws + L.red_i);
-    pk::BatchStats *stats = (pk::BatchStats *)(ws + L.stats);
     const CapSections q = cap_sections(L, cap);
     int32_t *deep_frames = (int32_t *)(ws + q.frames);
     uint32_t *deep_bits = (uint32_t *)(ws + q.bits);
     pk::SegRec *seg = (pk::SegRec *)(ws + q.seg);
     uint32_t *slots = (uint32_t *)(ws + q.slots);
 
-    const unsigned tiles = (unsigned)L.n_tiles;
     /* a batch that fits one scan block's plan is planned by the scan blocks
      * themselves (one launch less, and the scan waves find their rows in LDS),
      * unless each block would plan many more rows than it scans */
@@ -388,12 +408,8 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     ra.out = row_out;
     const bool lenient = (h->cfg.flags & PARASON_CFG_LENIENT_GAPS) != 0;
     const bool batch_stats = (h->cfg.flags & PARASON_CFG_BATCH_STATS) != 0;
-    if (lenient)
-        launch_rows<true>(ra, cus, mode, counters, listed, deep_rows, deep_frames, deep_bits,
-                          batch_stats, stream);
-    else
-        launch_rows<false>(ra, cus, mode, counters, listed, deep_rows, deep_frames, deep_bits,
-                           batch_stats, stream);
+    if (lenient) launch_rows<true>(ra, cus, mode, counters, listed, deep_rows, stream);
+    else launch_rows<false>(ra, cus, mode, counters, listed, deep_rows, stream);
 
     pk::RewardArgs rw;
     rw.total = out->total;
@@ -416,28 +432,12 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     rw.eta = out->eta;
     rw.accel = out->accel;
     rw.saved = out->saved;
-    rw.batch = nullptr;
     rw.n = n_traj;
-    if (batch_stats) {
-        pk::StatsArgs st{out->total, out->latency, out->n_subtask, out->n_trial, out->flags, n_traj, red_d, red_i, stats};
-        hipLaunchKernelGGL(pk::batch_stats_tiles<1>, dim3(tiles), dim3(pk::RED_THREADS), 0, stream, st);
-        hipLaunchKernelGGL(pk::batch_stats_final<1>, dim3(1), dim3(pk::RED_THREADS), 0, stream, st, L.n_tiles);
-        hipLaunchKernelGGL(pk::batch_stats_tiles<2>, dim3(tiles), dim3(pk::RED_THREADS), 0, stream, st);
-        hipLaunchKernelGGL(pk::batch_stats_final<2>, dim3(1), dim3(pk::RED_THREADS), 0, stream, st, L.n_tiles);
-        rw.batch = stats;
-        hipLaunchKernelGGL(pk::batch_reward, dim3((unsigned)((n_traj + 255) / 256)), dim3(256), 0, stream, rw);
-    } else {
-        const pk::DeepArgs da{ra, mode, counters, deep_rows, deep_frames, deep_bits};
-        const dim3 grid((unsigned)((n_traj + 255) / 256));
-        if (lenient) hipLaunchKernelGGL(pk::group_reward<true>, grid, dim3(256), 0, stream, rw, da);
-        else hipLaunchKernelGGL(pk::group_reward<false>, grid, dim3(256), 0, stream, rw, da);
-    }
-    if (out->metrics) {
-        pk::MetricsArgs ma{out->total, out->latency, out->n_subtask, out->n_trial, out->flags, correct,
-                           out->reward, n_traj, red_i, red_d, out->metrics};
-        hipLaunchKernelGGL(pk::metrics_tiles, dim3(tiles), dim3(pk::RED_THREADS), 0, stream, ma);
-        hipLaunchKernelGGL(pk::metrics_final, dim3(1), dim3(pk::RED_THREADS), 0, stream, ma, L.n_tiles);
-    }
+    const pk::DeepArgs da{ra, mode, counters, deep_rows, deep_frames, deep_bits};
+    pk::MomentRec *moments = (pk::MomentRec *)(ws + L.moments);
+    pk::MetricRec *recs = (pk::MetricRec *)(ws + L.metrics);
+    if (lenient) launch_reward<true>(rw, da, batch_stats, moments, recs, out->metrics, stream);
+    else launch_reward<false>(rw, da, batch_stats, moments, recs, out->metrics, stream);
 
     return hipGetLastError() == hipSuccess ? PARASON_OK : PARASON_ERR_HIP;
 }

@@ -32,14 +32,18 @@
  *        The automaton with frames of open blocks in LDS (FAST_DEPTH per row,
  *        64 outline entries per block; MID_DEPTH for the rows that need more);
  *        a row that needs more still is handed to the deep tier.
- *   rows_deep  (one thread, only rows rows_listed or rows_par handed over)
- *        The same automaton with frames and entry types in global workspace.
- *        Only with batch-wide statistics is this a launch of its own; with
- *        per-group statistics the first block of group_reward runs these rows
- *        and then the rewards of their groups (mode[i] bit MODE_DEEP marks
- *        them, so every other block skips those groups).
  *   group_reward  (one thread per row)
- *        Statistics and Definition 3.1 in IEEE double, fixed order.
+ *        Statistics and Definition 3.1 in IEEE double, fixed order.  The deep
+ *        tier's rows, those rows_listed or rows_par handed over, are run first
+ *        by a thread of its first block, by the same automaton with frames and
+ *        entry types in global workspace, and then the rewards of their groups
+ *        (mode[i] bit MODE_DEEP marks them, so every other block skips those
+ *        groups).  With batch metrics each block also leaves its partial sums.
+ *   batch_moments, batch_reward  (batch-wide statistics, in place of it)
+ *        Mergeable moments per tile of rows (the deep tier's rows as one more
+ *        record), then the rewards, every block merging the records itself.
+ *   metrics_final  (batch metrics of more than one block)
+ *   batch_single  (batch-wide statistics of up to 1,024 rows: one block)
  *
  * Paper references: grammar -- figure "Context-Free Grammar for Parason"
  * (Sec. 3.2); latency -- Sec. 4 "Evaluation"; ratios, eta and the reward --
@@ -615,22 +619,10 @@ __device__ void run_deep_rows(const RowArgs &a, const uint8_t *__restrict__ mode
     }
 }
 
-/* The deep rows on a single thread, as a launch of its own: used when the
- * batch-wide statistics need every row before the reward. */
-template <bool LENIENT>
-__global__ void __launch_bounds__(64) rows_deep(RowArgs a, const uint8_t *__restrict__ mode,
-                                                const int32_t *__restrict__ counters,
-                                                const int32_t *__restrict__ deep_rows, int32_t *__restrict__ frames,
-                                                uint32_t *__restrict__ bits)
-{
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    run_deep_rows<LENIENT>(a, mode, counters[1], deep_rows, frames, bits);
-}
-
 /* ------------------------------------------------------------------ rows_par */
 
 constexpr int PAR_EVENTS = 512; /* events of a row rows_par holds in LDS */
-constexpr int PAR_LEVELS = 16;  /* nesting rows_par evaluates */
+constexpr int PAR_LEVELS = 64;  /* nesting rows_par evaluates */
 
 /* The classes that may follow state st (one bit per class). */
 constexpr uint32_t allowed_classes(uint32_t st)
@@ -2157,21 +2149,12 @@ __global__ void __launch_bounds__(WAVE * SCAN_WAVES) read_probe(const int4 *__re
 
 /* ------------------------------------------------------------------ reward */
 
-/* Batch-wide statistics (PARASON_CFG_BATCH_STATS), in workspace. */
-struct BatchStats {
-    double mu[3];    /* latency, Subtask ratio, Trial ratio */
-    double sigma[3];
-    int32_t all_equal[3];
-    int32_t not_evaluated; /* rows flagged not evaluated */
-};
-
 struct RewardArgs {
     const int32_t *total, *latency, *n_subtask, *n_trial;
     const uint32_t *flags;
     const uint8_t *correct;
     int64_t n_groups;
     int32_t G;
-    const BatchStats *batch; /* non-null: one normalisation group = the whole batch */
     int64_t n;
     double alpha, beta_s, beta_r, rho, rho_clip;
     uint32_t cfg_flags;
@@ -2234,8 +2217,9 @@ __device__ __forceinline__ RowVals row_vals(const RewardArgs &a, int64_t r)
     return RowVals{a.flags[r], a.latency[r], a.total[r], a.n_subtask[r], a.n_trial[r], a.correct[r]};
 }
 
-__device__ __forceinline__ void write_reward(const RewardArgs &a, int64_t r, const RowVals &v, double zT, double zs,
-                                             double zr, double xs, double xr)
+/* Stores row r's reward and ratios; returns the reward as stored. */
+__device__ __forceinline__ float write_reward(const RewardArgs &a, int64_t r, const RowVals &v, double zT, double zs,
+                                              double zr, double xs, double xr)
 {
     const int32_t tot = v.tot;
     const double e = tot > 0 ? __dsub_rn(1.0, __ddiv_rn((double)v.lat, (double)tot)) : 0.0;
@@ -2255,9 +2239,10 @@ __device__ __forceinline__ void write_reward(const RewardArgs &a, int64_t r, con
     /* a row with tokens has latency >= 1 (an invalid row's latency is its length) */
     if (a.accel) a.accel[r] = tot > 0 ? (float)__ddiv_rn((double)tot, (double)v.lat) : 1.0f;
     if (a.saved) a.saved[r] = tot - v.lat;
+    return (float)R;
 }
 
-__device__ __forceinline__ void write_nan(const RewardArgs &a, int64_t r, const RowVals &v)
+__device__ __forceinline__ float write_nan(const RewardArgs &a, int64_t r, const RowVals &v)
 {
     const float nan = __int_as_float(0x7fc00000);
     a.reward[r] = nan;
@@ -2266,6 +2251,7 @@ __device__ __forceinline__ void write_nan(const RewardArgs &a, int64_t r, const 
     if (a.eta) a.eta[r] = nan;
     if (a.accel) a.accel[r] = nan;
     if (a.saved) a.saved[r] = (v.fl & NOT_EVALUATED) ? 0 : v.tot - v.lat;
+    return nan;
 }
 
 /* A group of G rows (G a power of two up to 64) in G consecutive lanes of one
@@ -2274,7 +2260,7 @@ __device__ __forceinline__ void write_nan(const RewardArgs &a, int64_t r, const 
  * paper's G = 8), so that the group's shuffles are unrolled and issue
  * together instead of one sum step after another. */
 template <int GC>
-__device__ __forceinline__ void group_reward_lanes(const RewardArgs &a, int64_t r, int32_t G_run, const RowVals &v)
+__device__ __forceinline__ float group_reward_lanes(const RewardArgs &a, int64_t r, int32_t G_run, const RowVals &v)
 {
     const int32_t G = GC > 0 ? GC : G_run;
     const int lane = threadIdx.x & (WAVE - 1);
@@ -2283,8 +2269,7 @@ __device__ __forceinline__ void group_reward_lanes(const RewardArgs &a, int64_t 
     const uint32_t fl = v.fl;
     const int32_t lat = v.lat, tot = v.tot, ns = v.ns, nt = v.nt;
     if ((__ballot(!(fl & NOT_EVALUATED)) & gmask) != gmask) {
-        write_nan(a, r, v);
-        return; /* the whole group returns here */
+        return write_nan(a, r, v); /* the whole group returns here */
     }
     const bool lat_equal = (__ballot(lat == __shfl(lat, gl, WAVE)) & gmask) == gmask;
     /* exact equality of the ratios, cross-multiplied against the group's first row */
@@ -2297,12 +2282,13 @@ __device__ __forceinline__ void group_reward_lanes(const RewardArgs &a, int64_t 
     const Moments mT = moments([&](int32_t j) { return __shfl(xT, gl + j, WAVE); }, G);
     const Moments ms = moments([&](int32_t j) { return __shfl(xs, gl + j, WAVE); }, G);
     const Moments mr = moments([&](int32_t j) { return __shfl(xr, gl + j, WAVE); }, G);
-    write_reward(a, r, v, zscore(xT, mT, lat_equal), zscore(xs, ms, sub_equal), zscore(xr, mr, tri_equal), xs, xr);
+    return write_reward(a, r, v, zscore(xT, mT, lat_equal), zscore(xs, ms, sub_equal), zscore(xr, mr, tri_equal), xs,
+                        xr);
 }
 
 /* Row r's reward from its group's values in memory, in the group's row order
  * (any group size, any thread layout). */
-__device__ __forceinline__ void group_reward_memory(const RewardArgs &a, int64_t r)
+__device__ __forceinline__ float group_reward_memory(const RewardArgs &a, int64_t r)
 {
     const int32_t G = a.G;
     const int64_t r0 = r - r % G;
@@ -2313,10 +2299,7 @@ __device__ __forceinline__ void group_reward_memory(const RewardArgs &a, int64_t
         lat_equal = lat_equal && a.latency[r0 + i] == a.latency[r0];
     }
     const RowVals v = row_vals(a, r);
-    if (!evaluated) {
-        write_nan(a, r, v);
-        return;
-    }
+    if (!evaluated) return write_nan(a, r, v);
     const bool sub_equal = same_ratio(a.n_subtask, a.total, r0, G);
     const bool tri_equal = same_ratio(a.n_trial, a.total, r0, G);
     auto xT = [&](int32_t i) { return (double)a.latency[r0 + i]; };
@@ -2324,8 +2307,8 @@ __device__ __forceinline__ void group_reward_memory(const RewardArgs &a, int64_t
     auto xr = [&](int32_t i) { return ratio(a.n_trial[r0 + i], a.total[r0 + i]); };
     const Moments mT = moments(xT, G), ms = moments(xs, G), mr = moments(xr, G);
     const int32_t i = (int32_t)(r - r0);
-    write_reward(a, r, v, zscore(xT(i), mT, lat_equal), zscore(xs(i), ms, sub_equal), zscore(xr(i), mr, tri_equal),
-                 xs(i), xr(i));
+    return write_reward(a, r, v, zscore(xT(i), mT, lat_equal), zscore(xs(i), ms, sub_equal),
+                        zscore(xr(i), mr, tri_equal), xs(i), xr(i));
 }
 
 /* The deep tier's rows (listed by rows_par or rows_listed), run by the first
@@ -2339,194 +2322,77 @@ struct DeepArgs {
     uint32_t *bits;
 };
 
-/* One thread per row.  A group within one wave shares its values by shuffles
- * (group_reward_lanes); otherwise every thread of a group computes the group's
- * moments itself from memory.  Either way the sums run in the group's row
- * order, so every thread of a group holds the same values; a group takes G
- * threads instead of one, which keeps the GPU busy when a batch has few
- * groups (an RL step has 128).
- *
- * Rows listed for the deep tier (normally none) are evaluated here first, by
- * thread 0 of block 0; after a barrier that block computes the rewards of the
- * groups holding them (a group listed twice is written twice, with the same
- * values).  Every block skips those groups: it tells them by the MODE_DEEP
- * mark, which nothing writes during this launch, so no block reads a row
- * another block is writing. */
-template <bool LENIENT>
-__global__ void __launch_bounds__(256) group_reward(RewardArgs a, DeepArgs d)
-{
-    const int32_t G = a.G;
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    /* the row's values in the same round of loads as the deep count (rows of
-     * groups the deep tier writes during this launch are not read from v) */
-    const RowVals v = row_vals(a, min(r, a.n - 1));
-    const int32_t n_deep = d.counters[1]; /* the same for every thread */
-    if (n_deep > 0 && blockIdx.x == 0) {
-        if (threadIdx.x == 0) run_deep_rows<LENIENT>(d.rows, d.mode, n_deep, d.deep_rows, d.frames, d.bits);
-        __syncthreads();
-        for (int64_t k = threadIdx.x; k < (int64_t)n_deep * G; k += blockDim.x) {
-            const int64_t rd = d.deep_rows[k / G];
-            group_reward_memory(a, rd - rd % G + k % G);
-        }
-    }
-    if (r >= a.n) return; /* n is a multiple of G: whole groups only */
-    if (n_deep > 0) {
-        const int64_t r0 = r - r % G;
-        bool deep = false;
-        for (int32_t i = 0; i < G; ++i) deep = deep || (d.mode[r0 + i] & MODE_DEEP) != 0;
-        if (deep) return; /* the whole group returns here */
-    }
-    if (G == 8) group_reward_lanes<8>(a, r, G, v);
-    else if (G <= WAVE && (G & (G - 1)) == 0) group_reward_lanes<0>(a, r, G, v);
-    else group_reward_memory(a, r);
-}
-
-/* One thread per row; mu, sigma of the whole batch from batch_stats. */
-__global__ void __launch_bounds__(256) batch_reward(RewardArgs a)
-{
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= a.n) return;
-    const BatchStats &b = *a.batch;
-    const RowVals v = row_vals(a, r);
-    if (b.not_evaluated) {
-        write_nan(a, r, v);
-        return;
-    }
-    const double xT = (double)v.lat, xs = ratio(v.ns, v.tot), xr = ratio(v.nt, v.tot);
-    write_reward(a, r, v, zscore(xT, Moments{b.mu[0], b.sigma[0]}, b.all_equal[0] != 0),
-                 zscore(xs, Moments{b.mu[1], b.sigma[1]}, b.all_equal[1] != 0),
-                 zscore(xr, Moments{b.mu[2], b.sigma[2]}, b.all_equal[2] != 0), xs, xr);
-}
-
-/* ------------------------------------------------------------------ batch reductions */
-
-struct StatsArgs {
-    const int32_t *total, *latency, *n_subtask, *n_trial;
-    const uint32_t *flags;
-    int64_t n;
-    double *dpart;    /* [tiles][3] */
-    int64_t *ipart;   /* [tiles][4]: not evaluated, latency differs, Subtask ratio differs, Trial ratio differs */
-    BatchStats *stats;
-};
-
-/* PASS 1: sums of the three statistics and the equality checks; PASS 2: sums
- * of squared deviations from the batch means. */
-template <int PASS>
-__global__ void __launch_bounds__(RED_THREADS) batch_stats_tiles(StatsArgs a)
-{
-    __shared__ double dl[3 * RED_THREADS];
-    __shared__ int64_t il[4 * RED_THREADS];
-    const int64_t r0 = (int64_t)blockIdx.x * RED_TILE + (int64_t)threadIdx.x * ROWS_PER_THREAD;
-    double d[3] = {0.0, 0.0, 0.0};
-    int64_t c[4] = {0, 0, 0, 0};
-    const int64_t s0 = a.n_subtask[0], t0 = a.total[0] > 0 ? a.total[0] : 1, u0 = a.n_trial[0];
-    const int64_t n0s = a.total[0] > 0 ? s0 : 0, n0r = a.total[0] > 0 ? u0 : 0;
-    for (int j = 0; j < ROWS_PER_THREAD; ++j) {
-        const int64_t r = r0 + j;
-        if (r >= a.n) break;
-        const double x[3] = {(double)a.latency[r], ratio(a.n_subtask[r], a.total[r]), ratio(a.n_trial[r], a.total[r])};
-        if (PASS == 1) {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) d[k] = __dadd_rn(d[k], x[k]);
-            const int64_t tr = a.total[r] > 0 ? a.total[r] : 1;
-            const int64_t ns = a.total[r] > 0 ? a.n_subtask[r] : 0, nr = a.total[r] > 0 ? a.n_trial[r] : 0;
-            c[0] += (a.flags[r] & NOT_EVALUATED) != 0;
-            c[1] += a.latency[r] != a.latency[0];
-            c[2] += ns * t0 != n0s * tr;
-            c[3] += nr * t0 != n0r * tr;
-        } else {
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const double dv = __dsub_rn(x[k], a.stats->mu[k]);
-                d[k] = __dadd_rn(d[k], __dmul_rn(dv, dv));
-            }
-        }
-    }
-    block_tree_sum<double, 3>(d, dl);
-    if (PASS == 1) block_tree_sum<int64_t, 4>(c, il);
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 3; ++k) a.dpart[blockIdx.x * 3 + k] = d[k];
-        if (PASS == 1)
-            for (int k = 0; k < 4; ++k) a.ipart[blockIdx.x * 4 + k] = c[k];
-    }
-}
-
-template <int PASS>
-__global__ void __launch_bounds__(RED_THREADS) batch_stats_final(StatsArgs a, int64_t tiles)
-{
-    __shared__ double dl[3 * RED_THREADS];
-    __shared__ int64_t il[4 * RED_THREADS];
-    double d[3];
-    sum_partials<double, 3>(a.dpart, tiles, d, dl);
-    if (PASS == 1) {
-        int64_t c[4];
-        sum_partials<int64_t, 4>(a.ipart, tiles, c, il);
-        if (threadIdx.x == 0) {
-            for (int k = 0; k < 3; ++k) a.stats->mu[k] = __ddiv_rn(d[k], (double)a.n);
-            a.stats->not_evaluated = c[0] != 0;
-            for (int k = 0; k < 3; ++k) a.stats->all_equal[k] = c[k + 1] == 0;
-        }
-    } else if (threadIdx.x == 0) {
-        for (int k = 0; k < 3; ++k) a.stats->sigma[k] = __dsqrt_rn(__ddiv_rn(d[k], (double)a.n));
-    }
-}
-
-struct MetricsArgs {
-    const int32_t *total, *latency, *n_subtask, *n_trial;
-    const uint32_t *flags;
-    const uint8_t *correct;
-    const float *reward;
-    int64_t n;
-    int64_t *ipart; /* [tiles][9] */
-    double *dpart;  /* [tiles][1] */
-    double *metrics;
-};
+/* ------------------------------------------------------------------ batch metrics */
 
 constexpr int NMI = 9; /* valid, triggered, correct, truncated, mismatch, sum total, latency, Subtask, Trial */
 
-__global__ void __launch_bounds__(RED_THREADS) metrics_tiles(MetricsArgs a)
-{
-    __shared__ int64_t il[NMI * RED_THREADS];
-    __shared__ double dl[RED_THREADS];
-    const int64_t r0 = (int64_t)blockIdx.x * RED_TILE + (int64_t)threadIdx.x * ROWS_PER_THREAD;
+/* Sums over some rows of the batch. */
+struct MetricRec {
     int64_t c[NMI];
+    double reward;
+};
+
+constexpr int RED_SINGLE = 1024;     /* rows whose reductions one block does */
+constexpr int RED_ONE_ROW = 1 << 16; /* rows up to which a reduction's thread takes one row */
+constexpr int RED_WAVES = RED_SINGLE / WAVE;
+
+/* Sum over the wave of values below 2^32, exact, in every lane. */
+__device__ __forceinline__ int64_t wave_sum_u32(int32_t v)
+{
+    return (int64_t)wave_sum32((int32_t)((uint32_t)v & 0xffffu)) + ((int64_t)wave_sum32((int32_t)((uint32_t)v >> 16)) << 16);
+}
+
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
 #pragma unroll
-    for (int k = 0; k < NMI; ++k) c[k] = 0;
-    double d[1] = {0.0};
-    for (int j = 0; j < ROWS_PER_THREAD; ++j) {
-        const int64_t r = r0 + j;
-        if (r >= a.n) break;
-        const uint32_t f = a.flags[r];
-        c[0] += (f & PARASON_FLAG_VALID) != 0;
-        c[1] += (f & PARASON_FLAG_TRIGGERED) != 0;
-        c[2] += a.correct[r] != 0;
-        c[3] += (f & PARASON_FLAG_TRUNCATED) != 0;
-        c[4] += (f & PARASON_FLAG_COUNT_MISMATCH) != 0;
-        c[5] += a.total[r];
-        c[6] += a.latency[r];
-        c[7] += a.n_subtask[r];
-        c[8] += a.n_trial[r];
-        d[0] = __dadd_rn(d[0], (double)a.reward[r]);
-    }
-    block_tree_sum<int64_t, NMI>(c, il);
-    block_tree_sum<double, 1>(d, dl);
+    for (int d = 1; d < WAVE; d <<= 1) v = __dadd_rn(v, __shfl(v, lane ^ d, WAVE));
+    return v;
+}
+
+/* The block's rows (one per thread with `has`: its accounting v and its stored
+ * reward R) added to rec, which thread 0 holds: counts by ballots, token sums
+ * exactly, the rewards' sum in a fixed tree.  Every thread calls this. */
+__device__ __forceinline__ void block_metrics(bool has, const RowVals &v, float R, MetricRec *lds /* [RED_WAVES] */,
+                                              MetricRec &rec)
+{
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    const uint32_t f = has ? v.fl : 0u;
+    MetricRec w;
+    w.c[0] = __popcll(__ballot((f & PARASON_FLAG_VALID) != 0));
+    w.c[1] = __popcll(__ballot((f & PARASON_FLAG_TRIGGERED) != 0));
+    w.c[2] = __popcll(__ballot(has && v.correct != 0));
+    w.c[3] = __popcll(__ballot((f & PARASON_FLAG_TRUNCATED) != 0));
+    w.c[4] = __popcll(__ballot((f & PARASON_FLAG_COUNT_MISMATCH) != 0));
+    w.c[5] = wave_sum_u32(has ? v.tot : 0);
+    w.c[6] = wave_sum_u32(has ? v.lat : 0);
+    w.c[7] = wave_sum_u32(has ? v.ns : 0);
+    w.c[8] = wave_sum_u32(has ? v.nt : 0);
+    w.reward = wave_sum_f64(has ? (double)R : 0.0);
+    __syncthreads(); /* the records of a call before */
+    if (lane == 0) lds[wv] = w;
+    __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 0; k < NMI; ++k) a.ipart[blockIdx.x * NMI + k] = c[k];
-        a.dpart[blockIdx.x] = d[0];
+        for (int i = 0; i < (int)(blockDim.x / WAVE); ++i) {
+            for (int k = 0; k < NMI; ++k) rec.c[k] += lds[i].c[k];
+            rec.reward = __dadd_rn(rec.reward, lds[i].reward);
+        }
     }
 }
 
-__global__ void __launch_bounds__(RED_THREADS) metrics_final(MetricsArgs a, int64_t tiles)
+__device__ __forceinline__ MetricRec no_metrics()
 {
-    __shared__ int64_t il[NMI * RED_THREADS];
-    __shared__ double dl[RED_THREADS];
-    int64_t c[NMI];
-    double d[1];
-    sum_partials<int64_t, NMI>(a.ipart, tiles, c, il);
-    sum_partials<double, 1>(a.dpart, tiles, d, dl);
-    if (threadIdx.x != 0) return;
-    double *m = a.metrics;
-    const double n = (double)a.n;
+    MetricRec r;
+    for (int k = 0; k < NMI; ++k) r.c[k] = 0;
+    r.reward = 0.0;
+    return r;
+}
+
+/* The PARASON_METRIC_COUNT metrics from the sums over the batch's n rows. */
+__device__ __forceinline__ void write_metrics(const MetricRec &rec, int64_t n_rows, double *m)
+{
+    const int64_t *c = rec.c;
+    const double n = (double)n_rows;
     const int64_t st = c[5], sl = c[6];
     for (int k = 0; k < PARASON_METRIC_COUNT; ++k) m[k] = 0.0;
     m[PARASON_METRIC_ROWS] = n;
@@ -2539,19 +2405,326 @@ __global__ void __launch_bounds__(RED_THREADS) metrics_final(MetricsArgs a, int6
     m[PARASON_METRIC_SUM_LATENCY] = (double)sl;
     m[PARASON_METRIC_SUM_SUBTASK] = (double)c[7];
     m[PARASON_METRIC_SUM_TRIAL] = (double)c[8];
-    if (a.n > 0) {
+    if (n_rows > 0) {
         m[PARASON_METRIC_TRIGGER_RATIO] = __ddiv_rn((double)c[1], n);
         m[PARASON_METRIC_MEAN_LATENCY] = __ddiv_rn((double)sl, n);
         m[PARASON_METRIC_MEAN_TOTAL] = __ddiv_rn((double)st, n);
         m[PARASON_METRIC_MEAN_SAVED] = __ddiv_rn((double)(st - sl), n);
         m[PARASON_METRIC_ACCURACY] = __ddiv_rn((double)c[2], n);
-        m[PARASON_METRIC_MEAN_REWARD] = __ddiv_rn(d[0], n);
+        m[PARASON_METRIC_MEAN_REWARD] = __ddiv_rn(rec.reward, n);
     }
     if (sl > 0) m[PARASON_METRIC_ACCELERATION] = __ddiv_rn((double)st, (double)sl);
     if (st > 0) {
         m[PARASON_METRIC_SUBTASK_SHARE] = __ddiv_rn((double)c[7], (double)st);
         m[PARASON_METRIC_TRIAL_SHARE] = __ddiv_rn((double)c[8], (double)st);
     }
+}
+
+/* A block's metrics: the metrics themselves when it is the only one, else its
+ * record for metrics_final. */
+__device__ __forceinline__ void put_metrics(const MetricRec &rec, int64_t n_rows, MetricRec *recs, double *metrics)
+{
+    if (threadIdx.x != 0) return;
+    if (gridDim.x == 1) write_metrics(rec, n_rows, metrics);
+    else recs[blockIdx.x] = rec;
+}
+
+/* The metrics of a batch from its blocks' records, in one block: every thread
+ * adds a run of records in order, then the threads' sums in a fixed tree. */
+__global__ void __launch_bounds__(RED_THREADS) metrics_final(const MetricRec *__restrict__ recs, int64_t n_recs,
+                                                             int64_t n_rows, double *__restrict__ metrics)
+{
+    __shared__ int64_t il[NMI * RED_THREADS];
+    __shared__ double dl[RED_THREADS];
+    const int64_t per = (n_recs + RED_THREADS - 1) / RED_THREADS;
+    MetricRec t = no_metrics();
+    for (int64_t i = threadIdx.x * per; i < min(n_recs, (threadIdx.x + 1) * per); ++i) {
+        const MetricRec x = recs[i];
+        for (int k = 0; k < NMI; ++k) t.c[k] += x.c[k];
+        t.reward = __dadd_rn(t.reward, x.reward);
+    }
+    double d[1] = {t.reward};
+    block_tree_sum<int64_t, NMI>(t.c, il);
+    block_tree_sum<double, 1>(d, dl);
+    t.reward = d[0];
+    if (threadIdx.x == 0) write_metrics(t, n_rows, metrics);
+}
+
+/* ------------------------------------------------------------------ per-group rewards */
+
+/* One thread per row.  A group within one wave shares its values by shuffles
+ * (group_reward_lanes); otherwise every thread of a group computes the group's
+ * moments itself from memory.  Either way the sums run in the group's row
+ * order, so every thread of a group holds the same values; a group takes G
+ * threads instead of one, which keeps the GPU busy when a batch has few
+ * groups (an RL step has 128).
+ *
+ * Rows listed for the deep tier (normally none) are evaluated here first, by
+ * thread 0 of block 0; after a barrier that block computes the rewards of the
+ * groups holding them (a group listed twice is written twice, with the same
+ * values, and counted once).  Every block skips those groups: it tells them by
+ * the MODE_DEEP mark, which nothing writes during this launch, so no block
+ * reads a row another block is writing.
+ *
+ * With metrics the block sums them from the values it holds: a launch of its
+ * own that read every row again took 7.8 us at 1,024 rows (15 us at 8,192),
+ * and its combining launch 4 us more; up to RED_SINGLE rows one block does it
+ * all (1,024 rows: 16.2 us in three launches, 8.9 us in one). */
+template <bool LENIENT, bool METRICS>
+__global__ void __launch_bounds__(METRICS ? RED_SINGLE : RED_THREADS)
+group_reward(RewardArgs a, DeepArgs d, MetricRec *__restrict__ recs, double *__restrict__ metrics)
+{
+    __shared__ MetricRec lds[METRICS ? RED_WAVES : 1];
+    const int32_t G = a.G;
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    /* the row's values in the same round of loads as the deep count (rows of
+     * groups the deep tier writes during this launch are not read from v) */
+    const RowVals v = row_vals(a, min(r, a.n - 1));
+    const int32_t n_deep = d.counters[1]; /* the same for every thread */
+    MetricRec rec = no_metrics();
+    if (n_deep > 0 && blockIdx.x == 0) {
+        if (threadIdx.x == 0) run_deep_rows<LENIENT>(d.rows, d.mode, n_deep, d.deep_rows, d.frames, d.bits);
+        __syncthreads();
+        for (int64_t k0 = 0; k0 < (int64_t)n_deep * G; k0 += blockDim.x) {
+            const int64_t k = k0 + threadIdx.x;
+            bool count = k < (int64_t)n_deep * G;
+            RowVals w = v;
+            float R = 0.0f;
+            if (count) {
+                const int64_t rd = d.deep_rows[k / G], g0 = rd - rd % G, rk = g0 + k % G;
+                R = group_reward_memory(a, rk);
+                w = row_vals(a, rk);
+                /* a group counts with its first deep row */
+                for (int64_t i = g0; i < rd; ++i) count = count && (d.mode[i] & MODE_DEEP) == 0;
+            }
+            if (METRICS) block_metrics(count, w, R, lds, rec);
+        }
+    }
+    bool mine = r < a.n; /* n is a multiple of G: whole groups only */
+    if (n_deep > 0 && mine) {
+        const int64_t r0 = r - r % G;
+        for (int32_t i = 0; i < G; ++i) mine = mine && (d.mode[r0 + i] & MODE_DEEP) == 0; /* the same for a whole group */
+    }
+    float R = 0.0f;
+    if (mine) {
+        if (G == 8) R = group_reward_lanes<8>(a, r, G, v);
+        else if (G <= WAVE && (G & (G - 1)) == 0) R = group_reward_lanes<0>(a, r, G, v);
+        else R = group_reward_memory(a, r);
+    }
+    if (!METRICS) return;
+    block_metrics(mine, v, R, lds, rec);
+    put_metrics(rec, a.n, recs, metrics);
+}
+
+/* ------------------------------------------------------------------ batch-wide statistics */
+
+/* Mean and sum of squared deviations of latency, Subtask ratio and Trial ratio
+ * over some rows; two such sets merge by the pairwise update of Chan, Golub
+ * and LeVeque ("Updating Formulae and a Pairwise Algorithm for Computing
+ * Sample Variances", 1979), whose error is that of a two-pass sum. */
+struct Moms {
+    double n, mean[3], m2[3];
+};
+
+__device__ __forceinline__ Moms no_moms() { return Moms{0.0, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}; }
+
+__device__ __forceinline__ Moms merge_moms(const Moms &x, const Moms &y)
+{
+    if (y.n == 0.0) return x;
+    if (x.n == 0.0) return y;
+    Moms z;
+    z.n = __dadd_rn(x.n, y.n);
+    const double fy = __ddiv_rn(y.n, z.n), fxy = __dmul_rn(x.n, fy);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double d = __dsub_rn(y.mean[k], x.mean[k]);
+        z.mean[k] = __dadd_rn(x.mean[k], __dmul_rn(d, fy));
+        z.m2[k] = __dadd_rn(__dadd_rn(x.m2[k], y.m2[k]), __dmul_rn(__dmul_rn(d, d), fxy));
+    }
+    return z;
+}
+
+__device__ __forceinline__ Moms row_moms(const RowVals &v)
+{
+    return Moms{1.0, {(double)v.lat, ratio(v.ns, v.tot), ratio(v.nt, v.tot)}, {0.0, 0.0, 0.0}};
+}
+
+/* What of a row differs from another row: bit 0 latency, 1 Subtask ratio, 2
+ * Trial ratio (exact, cross-multiplied). */
+__device__ __forceinline__ uint32_t differs(const RowVals &v, const RowVals &w)
+{
+    const int64_t tv = v.tot > 0 ? v.tot : 1, tw = w.tot > 0 ? w.tot : 1;
+    const int64_t sv = v.tot > 0 ? v.ns : 0, sw = w.tot > 0 ? w.ns : 0;
+    const int64_t rv = v.tot > 0 ? v.nt : 0, rw = w.tot > 0 ? w.nt : 0;
+    return (v.lat != w.lat ? 1u : 0u) | (sv * tw != sw * tv ? 2u : 0u) | (rv * tw != rw * tv ? 4u : 0u);
+}
+
+constexpr uint32_t NOT_EVAL_BIT = 8u; /* next to the three bits of differs() */
+
+/* A tile of rows: its moments, one of its rows, and what differs between them. */
+struct MomentRec {
+    Moms m;
+    RowVals first;
+    uint32_t bits;
+};
+static_assert(2 * sizeof(MomentRec) <= 256, "a batch of one tile fits the smallest section");
+static_assert(2 * sizeof(MomentRec) <= RED_THREADS * sizeof(int32_t), "a record per tile and one more");
+static_assert(sizeof(MetricRec) <= 256, "a record per block of 256 rows");
+
+/* Moments over the block and the OR of bits, in every thread: a butterfly over
+ * the wave (lane 0's result counts), then the waves in order. */
+__device__ __forceinline__ Moms block_moms(Moms m, uint32_t &bits, Moms *lds /* [RED_WAVES] */, uint32_t *lds_bits)
+{
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    for (int d = 1; d < WAVE; d <<= 1) {
+        Moms o;
+        o.n = __shfl(m.n, lane ^ d, WAVE);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            o.mean[k] = __shfl(m.mean[k], lane ^ d, WAVE);
+            o.m2[k] = __shfl(m.m2[k], lane ^ d, WAVE);
+        }
+        m = merge_moms(m, o);
+    }
+    uint32_t b = 0;
+#pragma unroll
+    for (uint32_t k = 1; k <= NOT_EVAL_BIT; k <<= 1) b |= __ballot((bits & k) != 0) != 0 ? k : 0u;
+    __syncthreads(); /* the values of a call before */
+    if (lane == 0) {
+        lds[wv] = m;
+        lds_bits[wv] = b;
+    }
+    __syncthreads();
+    m = lds[0];
+    bits = lds_bits[0];
+    for (int i = 1; i < (int)(blockDim.x / WAVE); ++i) {
+        m = merge_moms(m, lds[i]);
+        bits |= lds_bits[i];
+    }
+    return m;
+}
+
+/* Row r's reward under the batch's moments. */
+__device__ __forceinline__ float batch_row(const RewardArgs &a, int64_t r, const RowVals &v, const Moms &m, uint32_t bits)
+{
+    if (bits & NOT_EVAL_BIT) return write_nan(a, r, v);
+    const Moms x = row_moms(v);
+    double z[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        z[k] = zscore(x.mean[k], Moments{m.mean[k], __dsqrt_rn(__ddiv_rn(m.m2[k], m.n))}, ((bits >> k) & 1u) == 0);
+    return write_reward(a, r, v, z[0], z[1], z[2], x.mean[1], x.mean[2]);
+}
+
+__device__ __forceinline__ uint32_t row_bits(const RowVals &v, const RowVals &first)
+{
+    return differs(v, first) | ((v.fl & NOT_EVALUATED) ? NOT_EVAL_BIT : 0u);
+}
+
+/* The moments of each tile of RED_THREADS * rpt rows (rpt rows per thread).
+ * The deep tier's rows (normally none) are left out of their tiles: block 0
+ * evaluates them, on one thread, and leaves their moments as the record after
+ * the last tile's (every other block skips them by their MODE_DEEP mark).  So
+ * the statistics take one launch where four read the rows twice, a thread's
+ * sixteen rows one after the other (8,192 rows: 40 us with the deep tier's own
+ * launch, 5.4 us now). */
+template <bool LENIENT>
+__global__ void __launch_bounds__(RED_THREADS) batch_moments(RewardArgs a, DeepArgs d, MomentRec *__restrict__ recs,
+                                                             int32_t rpt)
+{
+    __shared__ Moms lds[RED_WAVES];
+    __shared__ uint32_t lds_bits[RED_WAVES];
+    __shared__ int64_t first_row;
+    const int64_t t0 = (int64_t)blockIdx.x * RED_THREADS * rpt, t1 = min(a.n, t0 + (int64_t)RED_THREADS * rpt);
+    const int32_t n_deep = d.counters[1];
+    int64_t f = t0;
+    if (n_deep > 0) {
+        if (threadIdx.x == 0) {
+            if (blockIdx.x == 0) run_deep_rows<LENIENT>(d.rows, d.mode, n_deep, d.deep_rows, d.frames, d.bits);
+            while (f < t1 && (d.mode[f] & MODE_DEEP)) ++f;
+            first_row = f;
+        }
+        __syncthreads();
+        f = first_row;
+    }
+    Moms m = no_moms();
+    uint32_t bits = 0;
+    RowVals first = row_vals(a, min(f, t1 - 1)); /* not used when every row of the tile is a deep one */
+    for (int32_t j = 0; j < rpt; ++j) {
+        const int64_t r = t0 + (int64_t)j * RED_THREADS + threadIdx.x; /* coalesced */
+        if (r >= t1 || (n_deep > 0 && (d.mode[r] & MODE_DEEP))) continue;
+        const RowVals v = row_vals(a, r);
+        m = merge_moms(m, row_moms(v));
+        bits |= row_bits(v, first);
+    }
+    m = block_moms(m, bits, lds, lds_bits);
+    if (threadIdx.x == 0) recs[blockIdx.x] = MomentRec{m, first, bits};
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        MomentRec x{no_moms(), first, 0u};
+        for (int32_t i = 0; i < n_deep; ++i) {
+            const RowVals v = row_vals(a, d.deep_rows[i]);
+            if (i == 0) x.first = v;
+            x.m = merge_moms(x.m, row_moms(v));
+            x.bits |= row_bits(v, x.first);
+        }
+        recs[gridDim.x] = x;
+    }
+}
+
+/* One thread per row; every block merges the n_recs records of the batch itself. */
+__global__ void __launch_bounds__(RED_THREADS) batch_reward(RewardArgs a, const MomentRec *__restrict__ moments,
+                                                            int32_t n_recs, MetricRec *__restrict__ recs,
+                                                            double *__restrict__ metrics)
+{
+    __shared__ Moms lds[RED_WAVES];
+    __shared__ uint32_t lds_bits[RED_WAVES];
+    __shared__ MetricRec lds_m[RED_WAVES];
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const RowVals v = row_vals(a, min(r, a.n - 1));
+    int32_t f = 0; /* a record with rows */
+    while (moments[f].m.n == 0.0) ++f;
+    const RowVals first = moments[f].first;
+    Moms m = no_moms();
+    uint32_t bits = 0;
+    for (int32_t i = threadIdx.x; i < n_recs; i += blockDim.x) {
+        const MomentRec x = moments[i];
+        if (x.m.n == 0.0) continue;
+        m = merge_moms(m, x.m);
+        bits |= x.bits | differs(x.first, first);
+    }
+    m = block_moms(m, bits, lds, lds_bits);
+    float R = 0.0f;
+    if (r < a.n) R = batch_row(a, r, v, m, bits);
+    if (!metrics) return;
+    MetricRec rec = no_metrics();
+    block_metrics(r < a.n, v, R, lds_m, rec);
+    put_metrics(rec, a.n, recs, metrics);
+}
+
+/* Up to RED_SINGLE rows in one block: the deep tier, the moments, the rewards
+ * and the metrics. */
+template <bool LENIENT>
+__global__ void __launch_bounds__(RED_SINGLE) batch_single(RewardArgs a, DeepArgs d, double *__restrict__ metrics)
+{
+    __shared__ Moms lds[RED_WAVES];
+    __shared__ uint32_t lds_bits[RED_WAVES];
+    __shared__ MetricRec lds_m[RED_WAVES];
+    const int64_t r = threadIdx.x;
+    const int32_t n_deep = d.counters[1];
+    if (n_deep > 0) {
+        if (threadIdx.x == 0) run_deep_rows<LENIENT>(d.rows, d.mode, n_deep, d.deep_rows, d.frames, d.bits);
+        __syncthreads();
+    }
+    const RowVals v = row_vals(a, min(r, a.n - 1)), first = row_vals(a, 0);
+    const bool has = r < a.n;
+    uint32_t bits = has ? row_bits(v, first) : 0u;
+    const Moms m = block_moms(has ? row_moms(v) : no_moms(), bits, lds, lds_bits);
+    float R = 0.0f;
+    if (has) R = batch_row(a, r, v, m, bits);
+    if (!metrics) return;
+    MetricRec rec = no_metrics();
+    block_metrics(has, v, R, lds_m, rec);
+    put_metrics(rec, a.n, nullptr, metrics);
 }
 
 } /* namespace pk */

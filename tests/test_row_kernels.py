@@ -9,10 +9,12 @@ import subprocess
 import numpy as np
 import pytest
 
-from adversarial import adversarial_streams, pack
+import grammar_pins as GP
+from adversarial import adversarial_streams, deep_stream, pack
 from gpu_util import DEFAULT_COEF, compare, insert_gaps, oracle_expect
 from paper_2608_24658_amd import parason as PX
 from paper_2608_24658_amd.synth import synth as S
+from test_gpu_metrics import check_metrics
 from test_simt_emulation import CLANG, CSRC, FEW, MANY, ROOT, SIMT, TAGS, check
 
 G = 8
@@ -64,6 +66,14 @@ def test_unstored_segments_adversarial(emu_small_pool, cus):
     check(emu_small_pool, tokens, starts, lengths, correct, cus=cus, what="unstored adversarial")
 
 
+@pytest.mark.parametrize("n", [1024, 1032])
+def test_emulated_batch_statistics(emu_small_pool, n):
+    """One block and several, with rows of the deep tier among them."""
+    tokens, starts, lengths = with_deep_rows(n, n)
+    correct = (np.arange(n) % 3 != 0).astype(np.uint8)
+    check(emu_small_pool, tokens, starts, lengths, correct, flags=PX.CFG_BATCH_STATS, cus=MANY, what="batch stats")
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,lo,hi,kind", [(2048, 1750, 5250, 0), (2056, 350, 1050, 0), (8192, 1, 2100, 1),
                                           (16384, 350, 1050, 0), (16392, 350, 1050, 0), (40000, 300, 900, 0)])
@@ -98,3 +108,37 @@ def test_adversarial_rows_in_a_large_batch_on_the_gpu():
     compare(got, *oracle_expect(tokens, starts, lengths, correct, S.CONTIGUOUS_TAGS, G, DEFAULT_COEF),
             what="adversarial, large batch")
     assert got["max_depth"].max() >= 1000
+
+
+def with_deep_rows(n, seed):
+    """Short rows with a few the deep tier evaluates, two of them in one group and one in the last."""
+    rng = np.random.default_rng(seed)
+    valid = [list(x) for x in GP.enumerate_valid(14)]
+    streams = [valid[int(k)] for k in rng.integers(0, len(valid), n)]
+    for i in {0, 3, n // 2, n - 1}:
+        streams[i] = deep_stream(80)
+    return pack(streams, S.CONTIGUOUS_TAGS)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("deep", [False, True])
+@pytest.mark.parametrize("n", [8, 1024, 1032, 65536, 65544])
+def test_batch_reductions_on_the_gpu(n, deep):
+    """Metrics and batch-wide statistics where their blocks and records change:
+    one block up to 1,024 rows, one row per thread up to 65,536."""
+    import torch
+
+    if deep:
+        tok, st, ln = with_deep_rows(n, n)
+        co = (np.arange(n) % 3 != 0).astype(np.uint8)
+    else:
+        tok, st, ln, co = short_rows(n, 20, 120, n)
+    dev = [torch.as_tensor(x).cuda() for x in (tok, st, ln, co)]
+    for flags in (0, PX.CFG_BATCH_STATS):
+        px = PX.Parason(S.CONTIGUOUS_TAGS, group_size=G, flags=flags, **DEFAULT_COEF)
+        out = px.run(*dev, total_tokens=tok.size, metrics=True)
+        got = {k: v.cpu().numpy() for k, v in out.items()}
+        got["flags"] = got["flags"].view(np.uint32)
+        rows, R, rs, rt, eta = oracle_expect(tok, st, ln, co, S.CONTIGUOUS_TAGS, G, DEFAULT_COEF, flags)
+        compare(got, rows, R, rs, rt, eta, what="n %d flags %d" % (n, flags), exact_reward=not flags)
+        check_metrics(got["metrics"], rows, co, R)
