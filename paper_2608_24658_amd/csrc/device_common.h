@@ -51,9 +51,11 @@ struct SegRec {
 constexpr int32_t DENSE = 1 << 20;
 static_assert(SEG_VEC % WAVE == 0, "a segment is a whole number of wave-wide loads");
 static_assert(POOL_PER_SEG % 4 == 0, "stored events are read 16 bytes at a time");
-constexpr int PLAN_TILE = 4096;          /* rows per plan tile */
+constexpr int PLAN_TILE = 1024;          /* rows per plan tile */
 constexpr int PLAN_THREADS = 256;
-constexpr int ROWS_PER_THREAD = PLAN_TILE / PLAN_THREADS;
+constexpr int PLAN_RPT = PLAN_TILE / PLAN_THREADS;
+constexpr int64_t PLAN_TWO = 4096; /* tiles up to which plan_rows adds up the tiles before its own */
+constexpr int ROWS_PER_THREAD = 16; /* of the batch reductions of many rows */
 #ifndef PARASON_FAST_DEPTH
 #define PARASON_FAST_DEPTH 4
 #endif
@@ -149,6 +151,35 @@ __device__ __forceinline__ int64_t wave_inclusive_scan(int64_t v)
         if (lane >= d) v += o;
     }
     return v;
+}
+
+/* Sum over a block of PLAN_THREADS threads, in every thread (part: one value
+ * per wave; it may be reused after the next barrier). */
+__device__ __forceinline__ int64_t block_sum(int64_t v, int64_t *part)
+{
+    const int64_t inc = wave_inclusive_scan(v);
+    __syncthreads(); /* part's use before */
+    if ((threadIdx.x & (WAVE - 1)) == WAVE - 1) part[threadIdx.x / WAVE] = inc;
+    __syncthreads();
+    int64_t t = 0;
+    for (int w = 0; w < PLAN_THREADS / WAVE; ++w) t += part[w];
+    return t;
+}
+
+/* Segments of the rows [r0, r0 + PLAN_TILE) of a batch, in every thread of a
+ * block of PLAN_THREADS. */
+__device__ __forceinline__ int64_t tile_segments(const int64_t *starts, const int32_t *lengths, int64_t n, int64_t mis,
+                                                 int64_t r0, int64_t *part)
+{
+    int64_t s = 0;
+#pragma unroll
+    for (int j = 0; j < PLAN_RPT; ++j) {
+        /* unconditional, coalesced loads: a load under a condition would wait for the one before it */
+        const int64_t r = r0 + threadIdx.x + j * PLAN_THREADS, q = min(r, n - 1);
+        const int64_t c = row_segments(starts[q], lengths[q], mis);
+        s += r < n ? c : 0;
+    }
+    return block_sum(s, part);
 }
 
 /* Wave scans and reductions by DPP: shifts within rows of 16 lanes
@@ -323,14 +354,67 @@ struct SegCursor {
     }
 };
 
+/* ------------------------------------------------------------------ plan in LDS */
+
+constexpr int SCAN_PLAN_ROWS = 2048; /* rows up to which a block plans the batch itself */
+
+/* The segment plan of a batch of at most SCAN_PLAN_ROWS rows, made by one
+ * block of NW waves in LDS (off[r] = first segment of row r, off[n] = the
+ * total): the segment counts with coalesced loads (row t + THREADS * j for
+ * thread t), then an exclusive scan with each thread over SCAN_PLAN_ROWS /
+ * THREADS consecutive rows.  The rows' starts and lengths stay in LDS (st, ln)
+ * for the block's segment cursors.  Every thread of the block calls this; it
+ * ends with a barrier. */
+template <int NW>
+__device__ __forceinline__ void block_plan(const int64_t *starts, const int32_t *lengths, int64_t n, int64_t mis,
+                                           int64_t *off, int64_t *part /* [NW] */, int64_t *st, int32_t *ln)
+{
+    constexpr int THREADS = WAVE * NW;
+    constexpr int RPT = SCAN_PLAN_ROWS / THREADS;
+    static_assert(SCAN_PLAN_ROWS % THREADS == 0, "whole rows per thread");
+    const int t = (int)threadIdx.x, lane = t & (WAVE - 1), wv = t / WAVE;
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        const int64_t r = t + (int64_t)THREADS * j;
+        if (r < n) {
+            const int64_t start = starts[r];
+            const int32_t len = lengths[r];
+            st[r] = start;
+            ln[r] = len;
+            off[r] = row_segments(start, len, mis);
+        } else {
+            off[r] = 0;
+        }
+    }
+    __syncthreads();
+    int64_t c[RPT], sum = 0;
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        c[k] = off[t * RPT + k];
+        sum += c[k];
+    }
+    const int64_t inc = wave_inclusive_scan(sum);
+    if (lane == WAVE - 1) part[wv] = inc;
+    __syncthreads();
+    int64_t run = inc - sum, total = 0;
+    for (int w = 0; w < NW; ++w) {
+        run += w < wv ? part[w] : 0;
+        total += part[w];
+    }
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        if (t * RPT + k < n) off[t * RPT + k] = run;
+        run += c[k];
+    }
+    if (t == 0) off[n] = total; /* rows beyond n are not rewritten, so no other thread writes off[n] */
+    __syncthreads();
+}
+
 /* ------------------------------------------------------------------ batch reductions */
 
-/* Deterministic sums: every thread adds its ROWS_PER_THREAD consecutive rows in
- * index order, the block combines the threads in a fixed pairwise tree, and one
- * block adds the block partials in block order. */
+/* Deterministic sums: the block combines its threads in a fixed pairwise tree,
+ * and one block adds the block partials in block order. */
 constexpr int RED_THREADS = 256;
-constexpr int RED_TILE = RED_THREADS * ROWS_PER_THREAD;
-static_assert(RED_TILE == PLAN_TILE, "the reductions reuse the plan's tile count");
 
 template <class T, int K>
 __device__ __forceinline__ void block_tree_sum(T (&v)[K], T *lds /* [K][RED_THREADS] */)

@@ -41,41 +41,41 @@ constexpr int LISTED_WAVES_PER_CU = 20; /* rows_listed waves a CU holds (8 KB of
 
 /* Byte offsets of the workspace sections for n rows. */
 struct Layout {
-    size_t seg_off, tile_sum, tile_off, counters, mode, listed, deep_rows, spare;
-    size_t moments, metrics; /* the batch reductions' records */
-    size_t fixed;  /* bytes before the per-segment sections */
-    int64_t n_tiles;
+    size_t seg_off, counters, mode, listed, deep_rows;
+    size_t plan, moments, metrics; /* the plan's scratch and the batch reductions' records */
+    size_t fixed;                  /* bytes before the per-segment sections */
 };
 
 Layout layout_for(int64_t n)
 {
     Layout L;
-    L.n_tiles = n > 0 ? (n + pk::PLAN_TILE - 1) / pk::PLAN_TILE : 1;
+    const size_t rows = (size_t)(n > 0 ? n : 1);
+    /* sizes that some sections have outgrown or no longer need are kept, so
+     * that workspaces keep theirs: in units of 4096 rows */
+    const size_t units = (rows + 4095) / 4096;
     size_t o = 0;
     L.seg_off = o;
     o = align_up(o + (size_t)(n + 1) * sizeof(int64_t));
-    L.tile_sum = o;
-    o = align_up(o + (size_t)L.n_tiles * sizeof(int64_t));
-    L.tile_off = o;
-    o = align_up(o + (size_t)L.n_tiles * sizeof(int64_t));
+    o = align_up(o + units * sizeof(int64_t));
+    o = align_up(o + units * sizeof(int64_t));
     L.counters = o;
     o = align_up(o + 4 * sizeof(int32_t));
     L.mode = o;
-    o = align_up(o + (size_t)(n > 0 ? n : 1));
+    o = align_up(o + rows);
     L.listed = o;
-    o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
+    o = align_up(o + rows * sizeof(int32_t));
     L.deep_rows = o;
-    o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
-    L.spare = o;
-    o = align_up(o + (size_t)(n > 0 ? n : 1) * sizeof(int32_t));
-    /* no longer used; kept so that workspaces keep their sizes */
-    o = align_up(o + (size_t)L.n_tiles * 3 * sizeof(double));
-    o = align_up(o + (size_t)L.n_tiles * 9 * sizeof(int64_t));
+    o = align_up(o + rows * sizeof(int32_t));
+    L.metrics = o;
+    o = align_up(o + rows * sizeof(int32_t));
+    o = align_up(o + units * 3 * sizeof(double));
+    o = align_up(o + units * 9 * sizeof(int64_t));
     o = align_up(o + 64);
-    /* the reductions run when the list of rows_listed is done with: four bytes
-     * per row hold a record of each tile of RED_THREADS rows, and one more */
+    /* the plan is made before, and the reductions run after the row kernels
+     * use their list: four bytes per row hold 16 per PLAN_TILE rows, and a
+     * record per RED_THREADS rows and one more */
+    L.plan = L.listed;
     L.moments = L.listed;
-    L.metrics = L.spare;
     L.fixed = o;
     return L;
 }
@@ -231,21 +231,23 @@ void launch_scan(const pk::TagMatch &tm, const pk::ScanArgs &sa, int cus, hipStr
 
 }  // namespace
 
-void abi::launch_plan(const int64_t *starts, const int32_t *lengths, int64_t n, int64_t mis, int64_t n_tiles,
-                      int64_t *tile_sum, int64_t *tile_off, int64_t *seg_off, int32_t *counters, uint8_t *mode,
+void abi::launch_plan(const int64_t *starts, const int32_t *lengths, int64_t n, int64_t mis, void *scratch,
+                      int64_t *seg_off, int32_t *counters, uint8_t *mode, const int64_t *len_sum, int64_t *n_tokens,
                       hipStream_t stream)
 {
-    const unsigned tiles = (unsigned)n_tiles;
-    if (n_tiles == 1) {
-        hipLaunchKernelGGL(pk::plan_rows<true>, dim3(1), dim3(pk::PLAN_THREADS), 0, stream, starts, lengths, n, mis,
-                           nullptr, seg_off, mode, counters);
-        return;
+    const int64_t tiles = plan_tile_count(n);
+    int64_t *tile_sum = (int64_t *)scratch, *tile_off = tile_sum + tiles;
+    const dim3 grid((unsigned)tiles), block(pk::PLAN_THREADS);
+    if (tiles > 1 && !len_sum)
+        hipLaunchKernelGGL(pk::plan_tiles, grid, block, 0, stream, starts, lengths, n, mis, tile_sum);
+    if (tiles > pk::PLAN_TWO) {
+        hipLaunchKernelGGL(pk::plan_top, dim3(1), dim3(1024), 0, stream, tile_sum, tiles, tile_off, seg_off, n, counters);
+        hipLaunchKernelGGL(pk::plan_rows<true>, grid, block, 0, stream, starts, lengths, n, mis, tile_sum, tile_off,
+                           seg_off, mode, counters, len_sum, n_tokens);
+    } else {
+        hipLaunchKernelGGL(pk::plan_rows<false>, grid, block, 0, stream, starts, lengths, n, mis, tile_sum, tile_off,
+                           seg_off, mode, counters, len_sum, n_tokens);
     }
-    hipLaunchKernelGGL(pk::plan_tiles, dim3(tiles), dim3(pk::PLAN_THREADS), 0, stream, starts, lengths, n, mis,
-                       tile_sum);
-    hipLaunchKernelGGL(pk::plan_top, dim3(1), dim3(1024), 0, stream, tile_sum, n_tiles, tile_off, seg_off, n, counters);
-    hipLaunchKernelGGL(pk::plan_rows<false>, dim3(tiles), dim3(pk::PLAN_THREADS), 0, stream, starts, lengths, n, mis,
-                       tile_off, seg_off, mode, counters);
 }
 
 extern "C" {
@@ -350,8 +352,6 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
     Layout L = layout_for(n_traj);
     char *ws = (char *)workspace;
     int64_t *seg_off = (int64_t *)(ws + L.seg_off);
-    int64_t *tile_sum = (int64_t *)(ws + L.tile_sum);
-    int64_t *tile_off = (int64_t *)(ws + L.tile_off);
     int32_t *counters = (int32_t *)(ws + L.counters);
     uint8_t *mode = (uint8_t *)(ws + L.mode);
     int32_t *listed = (int32_t *)(ws + L.listed);
@@ -367,7 +367,7 @@ int parason_run_timed(const parason_handle *h, const int32_t *tokens, const int6
      * unless each block would plan many more rows than it scans */
     const bool plan_in_scan = n_traj <= pk::SCAN_PLAN_ROWS && n_traj < (int64_t)cus * PLAN_ROWS_PER_CU;
     if (!plan_in_scan)
-        abi::launch_plan(starts, lengths, n_traj, mis, L.n_tiles, tile_sum, tile_off, seg_off, counters, mode, stream);
+        abi::launch_plan(starts, lengths, n_traj, mis, ws + L.plan, seg_off, counters, mode, nullptr, nullptr, stream);
 
     const pk::RowOut row_out{out->total,    out->latency,   out->n_subtask,       out->n_trial,
                              out->n_blocks, out->max_depth, out->first_error_pos, out->flags};

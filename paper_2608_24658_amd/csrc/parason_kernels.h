@@ -3,10 +3,11 @@
  *
  * Data flow of one parason_run (all on the caller's stream):
  *
- *   plan_tiles / plan_top / plan_rows  (one plan_rows block for one tile)
+ *   plan_tiles / plan_rows  (one plan_rows block for one tile; plan_top between
+ *        them for more than PLAN_TWO tiles)
  *        Each row is cut into segments of SEG_VEC 16-byte vectors, starting at
- *        the 128-byte line that holds its first token.  A three-pass exclusive
- *        scan gives seg_off[i] (first segment of row i) and the segment count
+ *        the 128-byte line that holds its first token.  An exclusive scan over
+ *        the rows gives seg_off[i] (first segment of row i) and the segment count
  *        seg_off[n]; mode[i] is cleared.  A batch of at most SCAN_PLAN_ROWS
  *        rows skips these launches: every scan block makes the plan in LDS
  *        itself (scan_plan).
@@ -70,20 +71,8 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_tiles(const int64_t *__rest
                                                            int64_t mis, int64_t *__restrict__ tile_sum)
 {
     __shared__ int64_t part[PLAN_THREADS / WAVE];
-    int64_t r0 = (int64_t)blockIdx.x * PLAN_TILE;
-    int64_t s = 0;
-    for (int j = 0; j < ROWS_PER_THREAD; ++j) {
-        int64_t r = r0 + (int64_t)j * PLAN_THREADS + threadIdx.x; /* coalesced */
-        if (r < n) s += row_segments(starts[r], lengths[r], mis);
-    }
-    s = wave_inclusive_scan(s);
-    if ((threadIdx.x & (WAVE - 1)) == WAVE - 1) part[threadIdx.x / WAVE] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t t = 0;
-        for (int w = 0; w < PLAN_THREADS / WAVE; ++w) t += part[w];
-        tile_sum[blockIdx.x] = t;
-    }
+    const int64_t t = tile_segments(starts, lengths, n, mis, (int64_t)blockIdx.x * PLAN_TILE, part);
+    if (threadIdx.x == 0) tile_sum[blockIdx.x] = t;
 }
 
 /* tile_off = exclusive scan of tile_sum; seg_off[n] = total; clears counters. */
@@ -116,44 +105,75 @@ __global__ void __launch_bounds__(1024) plan_top(const int64_t *__restrict__ til
     if (threadIdx.x == 0) seg_off[n] = carry_s;
 }
 
-/* seg_off[i] = first segment of row i; mode[i] = 0 (events in per-segment lists). */
-/* SINGLE: the batch is one tile, and this one block also does plan_top's
- * work (seg_off[n], clearing the counters), so a small batch is planned with
- * one launch instead of three. */
-template <bool SINGLE>
+/* seg_off[i] = first segment of row i; mode[i] = 0 (events in per-segment
+ * lists).  The segments before a block's tile: tile_off (TOP, after plan_top), or
+ * the sum over the tiles before it, which each block adds up itself, so that a
+ * plan of up to PLAN_TWO tiles takes two launches (64,000 rows: 10.0 + 4.9 + 8.3
+ * us with plan_top and tiles of 4,096 rows, sixteen to a thread, 4.7 + 4.7 now);
+ * the last block then writes the total and clears the counters as plan_top
+ * does.  The block's rows are loaded coalesced and scanned through LDS, as a
+ * thread's rows are consecutive.  mode and the sum n_tokens of the tiles'
+ * len_sum are optional. */
+template <bool TOP>
 __global__ void __launch_bounds__(PLAN_THREADS) plan_rows(const int64_t *__restrict__ starts,
                                                           const int32_t *__restrict__ lengths, int64_t n,
-                                                          int64_t mis, const int64_t *__restrict__ tile_off,
+                                                          int64_t mis, const int64_t *__restrict__ tile_sum,
+                                                          const int64_t *__restrict__ tile_off,
                                                           int64_t *__restrict__ seg_off, uint8_t *__restrict__ mode,
-                                                          int32_t *__restrict__ counters)
+                                                          int32_t *__restrict__ counters,
+                                                          const int64_t *__restrict__ len_sum,
+                                                          int64_t *__restrict__ n_tokens)
 {
-    if (SINGLE && threadIdx.x < 4) counters[threadIdx.x] = 0;
     __shared__ int64_t part[PLAN_THREADS / WAVE];
-    /* thread t owns the ROWS_PER_THREAD consecutive rows starting at r0 + t*ROWS_PER_THREAD */
-    int64_t r0 = (int64_t)blockIdx.x * PLAN_TILE + (int64_t)threadIdx.x * ROWS_PER_THREAD;
-    int64_t cnt[ROWS_PER_THREAD];
-    int64_t s = 0;
-#pragma unroll
-    for (int j = 0; j < ROWS_PER_THREAD; ++j) {
-        int64_t r = r0 + j;
-        cnt[j] = r < n ? row_segments(starts[r], lengths[r], mis) : 0;
-        s += cnt[j];
+    __shared__ int64_t cnt[PLAN_TILE];
+    const int t = (int)threadIdx.x, wv = t / WAVE;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    const int64_t r0 = (int64_t)blockIdx.x * PLAN_TILE;
+    int64_t before = 0;
+    if (TOP) {
+        before = tile_off[blockIdx.x];
+    } else {
+        for (int64_t b = t; b < (int64_t)blockIdx.x; b += PLAN_THREADS) before += tile_sum[b];
+        if (last && t < 4) counters[t] = 0;
     }
-    int64_t inc = wave_inclusive_scan(s);
-    if ((threadIdx.x & (WAVE - 1)) == WAVE - 1) part[threadIdx.x / WAVE] = inc;
+#pragma unroll
+    for (int j = 0; j < PLAN_RPT; ++j) {
+        const int64_t r = r0 + t + j * PLAN_THREADS, q = min(r, n - 1);
+        const int64_t c = row_segments(starts[q], lengths[q], mis);
+        cnt[t + j * PLAN_THREADS] = r < n ? c : 0;
+        if (mode && r < n) mode[r] = 0;
+    }
+    if (!TOP) before = block_sum(before, part);
     __syncthreads();
-    int64_t off = (SINGLE ? 0 : tile_off[blockIdx.x]) + inc - s;
-    for (int w = 0; w < (int)(threadIdx.x / WAVE); ++w) off += part[w];
+    int64_t c[PLAN_RPT], s = 0;
 #pragma unroll
-    for (int j = 0; j < ROWS_PER_THREAD; ++j) {
-        int64_t r = r0 + j;
-        if (r < n) {
-            seg_off[r] = off;
-            mode[r] = 0;
-        }
-        off += cnt[j];
+    for (int k = 0; k < PLAN_RPT; ++k) {
+        c[k] = cnt[t * PLAN_RPT + k];
+        s += c[k];
     }
-    if (SINGLE && threadIdx.x == PLAN_THREADS - 1) seg_off[n] = off; /* the last thread ends at the total */
+    const int64_t inc = wave_inclusive_scan(s);
+    if ((t & (WAVE - 1)) == WAVE - 1) part[wv] = inc;
+    __syncthreads();
+    int64_t off = before + inc - s;
+    for (int w = 0; w < wv; ++w) off += part[w];
+#pragma unroll
+    for (int k = 0; k < PLAN_RPT; ++k) {
+        cnt[t * PLAN_RPT + k] = off;
+        off += c[k];
+    }
+    if (!TOP && last && t == PLAN_THREADS - 1) seg_off[n] = off; /* the last thread ends at the total */
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PLAN_RPT; ++j) {
+        const int64_t r = r0 + t + j * PLAN_THREADS;
+        if (r < n) seg_off[r] = cnt[t + j * PLAN_THREADS];
+    }
+    if (last && len_sum) {
+        int64_t s = 0;
+        for (int64_t b = t; b < (int64_t)gridDim.x; b += PLAN_THREADS) s += len_sum[b];
+        s = block_sum(s, part);
+        if (t == 0) n_tokens[0] = s;
+    }
 }
 
 /* ------------------------------------------------------------------ automaton */
@@ -1723,7 +1743,6 @@ struct RowCollect {
 constexpr int EVL = 1024;                 /* LDS events per wave */
 constexpr int SCAN_WAVES = 4;             /* waves per scan block */
 constexpr int SCAN_THREADS = WAVE * SCAN_WAVES;
-constexpr int SCAN_PLAN_ROWS = 2048;      /* rows up to which a scan block plans the batch itself */
 /* Waves per block of a scan that plans in LDS.  Every block plans the whole
  * batch before its first load, so half as many blocks of twice the size plan
  * it half as often and are all dispatched sooner (a 2,048-row step: 2.7 us
@@ -1801,64 +1820,22 @@ __device__ __forceinline__ bool collect_segment(const ScanArgs &a, const int4 (&
     return w.s == w.last && !rc.global;
 }
 
-/* The segment plan of a batch of at most SCAN_PLAN_ROWS rows, made by one
- * scan block in LDS (off[r] = first segment of row r, off[n] = the total):
- * the segment counts with coalesced loads (row t + SCAN_THREADS * j for thread
- * t), then an exclusive scan with each thread over SCAN_PLAN_ROWS /
- * SCAN_THREADS consecutive rows.  Block 0 also writes the plan to seg_off for
+/* block_plan by every scan block.  Block 0 also writes the plan to seg_off for
  * the row kernels, clears the mode of rows without segments (no scan wave
  * sees them; all rows when the batch overflows the workspace) and the
  * counters; every other row's mode is cleared by the wave holding its first
- * segment.  The rows' starts and lengths stay in LDS (st, ln) for the block's
- * segment cursors. */
+ * segment. */
 template <int NW>
 __device__ __forceinline__ void scan_plan(const ScanArgs &a, int64_t *off, int64_t *part, int64_t *st, int32_t *ln)
 {
-    constexpr int THREADS = WAVE * NW;
-    constexpr int RPT = SCAN_PLAN_ROWS / THREADS;
-    static_assert(SCAN_PLAN_ROWS % THREADS == 0, "whole rows per thread");
-    const int t = (int)threadIdx.x, lane = t & (WAVE - 1), wv = t / WAVE;
-#pragma unroll
-    for (int j = 0; j < RPT; ++j) {
-        const int64_t r = t + (int64_t)THREADS * j;
-        if (r < a.n) {
-            const int64_t start = a.starts[r];
-            const int32_t len = a.lengths[r];
-            st[r] = start;
-            ln[r] = len;
-            off[r] = row_segments(start, len, a.mis);
-        } else {
-            off[r] = 0;
-        }
-    }
-    __syncthreads();
-    int64_t c[RPT], sum = 0;
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-        c[k] = off[t * RPT + k];
-        sum += c[k];
-    }
-    const int64_t inc = wave_inclusive_scan(sum);
-    if (lane == WAVE - 1) part[wv] = inc;
-    __syncthreads();
-    int64_t run = inc - sum, total = 0;
-    for (int w = 0; w < NW; ++w) {
-        run += w < wv ? part[w] : 0;
-        total += part[w];
-    }
-#pragma unroll
-    for (int k = 0; k < RPT; ++k) {
-        if (t * RPT + k < a.n) off[t * RPT + k] = run;
-        run += c[k];
-    }
-    if (t == 0) off[a.n] = total; /* rows beyond n are not rewritten, so no other thread writes off[n] */
-    __syncthreads();
+    block_plan<NW>(a.starts, a.lengths, a.n, a.mis, off, part, st, ln);
+    const int t = (int)threadIdx.x;
     if (blockIdx.x == 0) {
         /* when the batch overflows the workspace no scan wave runs, so every
          * mode byte is cleared here */
         const bool overflow = off[a.n] > a.seg_cap;
         int64_t *seg_off = const_cast<int64_t *>(a.seg_off);
-        for (int64_t r = t; r <= a.n; r += THREADS) {
+        for (int64_t r = t; r <= a.n; r += WAVE * NW) {
             seg_off[r] = off[r];
             if (r < a.n && (overflow || off[r + 1] == off[r])) a.mode[r] = 0;
         }

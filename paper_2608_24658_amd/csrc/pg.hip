@@ -11,31 +11,30 @@ using abi::is_finite;
 
 namespace {
 
-constexpr int PG_BLOCKS_PER_CU = 4;
+constexpr int PG_WAVES_PER_CU = 16;
 constexpr int64_t PG_MAX_WAVES = 1 << 16;
 
 struct PgLayout {
-    size_t seg_off, tile_sum, tile_off, counters, mode, len_part, n_tokens, wsum, wcnt, end;
-    int64_t n_tiles;
+    size_t seg_off, counters, plan, n_tokens, wsum, wcnt, end;
 };
 
 PgLayout pg_layout_for(int64_t n)
 {
     PgLayout L;
-    L.n_tiles = n > 0 ? (n + pk::PLAN_TILE - 1) / pk::PLAN_TILE : 1;
+    const size_t rows = (size_t)(n > 0 ? n : 1);
+    /* sizes that are no longer needed are kept, so that workspaces keep theirs */
+    const size_t units = (rows + 4095) / 4096;
     size_t o = 0;
     L.seg_off = o;
     o = align_up(o + (size_t)(n + 1) * sizeof(int64_t));
-    L.tile_sum = o;
-    o = align_up(o + (size_t)L.n_tiles * sizeof(int64_t));
-    L.tile_off = o;
-    o = align_up(o + (size_t)L.n_tiles * sizeof(int64_t));
+    o = align_up(o + units * sizeof(int64_t));
+    o = align_up(o + units * sizeof(int64_t));
     L.counters = o;
     o = align_up(o + 4 * sizeof(int32_t));
-    L.mode = o;
-    o = align_up(o + (size_t)(n > 0 ? n : 1));
-    L.len_part = o;
-    o = align_up(o + (size_t)L.n_tiles * sizeof(int64_t));
+    /* a byte per row: 24 per PLAN_TILE rows, the plan's scratch and the tiles' token counts */
+    L.plan = o;
+    o = align_up(o + rows);
+    o = align_up(o + units * sizeof(int64_t));
     L.n_tokens = o;
     o = align_up(o + sizeof(int64_t));
     L.wsum = o;
@@ -79,29 +78,16 @@ int parason_pg_run(const parason_pg_config *cfg, const float *reward, const floa
     if (workspace_bytes < L.end) return PARASON_ERR_WORKSPACE;
     const int cus = cu_count();
     if (cus <= 0) return PARASON_ERR_DEVICE;
-    const int64_t waves = (int64_t)cus * PG_BLOCKS_PER_CU * 4;
+    const int64_t waves = (int64_t)cus * PG_WAVES_PER_CU;
     if (waves > PG_MAX_WAVES) return PARASON_ERR_DEVICE;
     hipStream_t stream = (hipStream_t)stream_ptr;
 
     const int64_t mis = (int64_t)((a0 & 15u) >> 2);
     char *ws = (char *)workspace;
-    int64_t *seg_off = (int64_t *)(ws + L.seg_off);
-    int64_t *tile_sum = (int64_t *)(ws + L.tile_sum);
-    int64_t *tile_off = (int64_t *)(ws + L.tile_off);
-    int32_t *counters = (int32_t *)(ws + L.counters);
-    uint8_t *mode = (uint8_t *)(ws + L.mode);
-    int64_t *len_part = (int64_t *)(ws + L.len_part);
     int64_t *n_tokens = (int64_t *)(ws + L.n_tokens);
     double *wsum = (double *)(ws + L.wsum);
     int64_t *wcnt = (int64_t *)(ws + L.wcnt);
 
-    const unsigned tiles = (unsigned)L.n_tiles;
-    abi::launch_plan(starts, lengths, n_traj, mis, L.n_tiles, tile_sum, tile_off, seg_off, counters, mode, stream);
-    pk::sum_lengths_tiles<<<dim3(tiles), dim3(pk::RED_THREADS), 0, stream>>>(lengths, n_traj, len_part);
-    pk::sum_lengths_final<<<dim3(1), dim3(pk::RED_THREADS), 0, stream>>>(len_part, L.n_tiles, n_tokens);
-    const int64_t n_groups = n_traj / cfg->group_size;
-    pk::pg_advantage<<<dim3((unsigned)((n_groups + 255) / 256)), dim3(256), 0, stream>>>(reward, n_groups,
-                                                                                          cfg->group_size, advantage);
     pk::PgArgs pa;
     pa.logp_base = logp - mis;
     pa.old_base = logp_old - mis;
@@ -110,7 +96,9 @@ int parason_pg_run(const parason_pg_config *cfg, const float *reward, const floa
     pa.starts = starts;
     pa.lengths = lengths;
     pa.n = n_traj;
-    pa.seg_off = seg_off;
+    pa.seg_off = (int64_t *)(ws + L.seg_off);
+    pa.reward = reward;
+    pa.G = cfg->group_size;
     pa.adv = advantage;
     pa.thr_low = (float)std::log1p(-cfg->clip_low);
     pa.thr_high = (float)std::log1p(cfg->clip_high);
@@ -119,8 +107,21 @@ int parason_pg_run(const parason_pg_config *cfg, const float *reward, const floa
     pa.n_tokens = n_tokens;
     pa.wsum = wsum;
     pa.wcnt = wcnt;
-    pk::pg_surrogate<<<dim3((unsigned)(cus * PG_BLOCKS_PER_CU)), dim3(256), 0, stream>>>(pa);
-    pk::pg_final<<<dim3(1), dim3(pk::RED_THREADS), 0, stream>>>(wsum, wcnt, waves, n_tokens, stats);
+    const bool plan = n_traj <= pk::SCAN_PLAN_ROWS;
+    const int64_t blocks = waves / (plan ? pk::PG_PLAN_WAVES : pk::PG_WAVES);
+    if (plan) {
+        pk::pg_surrogate<true><<<dim3((unsigned)blocks), dim3(pk::PG_PLAN_WAVES * pk::WAVE), 0, stream>>>(pa);
+    } else {
+        const int64_t tiles = abi::plan_tile_count(n_traj), n_groups = n_traj / cfg->group_size;
+        const int64_t group_blocks = (n_groups + pk::PLAN_THREADS - 1) / pk::PLAN_THREADS;
+        int64_t *scratch = (int64_t *)(ws + L.plan), *len_sum = scratch + 2 * tiles;
+        pk::pg_prepare<<<dim3((unsigned)(tiles > group_blocks ? tiles : group_blocks)), dim3(pk::PLAN_THREADS), 0, stream>>>(
+            pa, tiles, n_groups, scratch, len_sum);
+        abi::launch_plan(starts, lengths, n_traj, mis, scratch, (int64_t *)(ws + L.seg_off),
+                         (int32_t *)(ws + L.counters), nullptr, len_sum, n_tokens, stream);
+        pk::pg_surrogate<false><<<dim3((unsigned)blocks), dim3(pk::PG_WAVES * pk::WAVE), 0, stream>>>(pa);
+    }
+    pk::pg_final<<<dim3(1), dim3(pk::RED_THREADS), 0, stream>>>(wsum, wcnt, blocks, n_tokens, stats);
     return hipGetLastError() == hipSuccess ? PARASON_OK : PARASON_ERR_HIP;
 }
 

@@ -7,10 +7,12 @@
  * with DAPO-style clip-higher and a token-level mean, which the paper does not
  * restate).
  *
- *   pg_advantage   one thread per group: A_i = (R_i - mean) / std over the
- *                  group's float rewards (population std, IEEE double, index
- *                  order; A = 0 when all rewards of the group are equal).
- *   sum_lengths_*  exact token count N (deterministic block sums).
+ *   pg_prepare     (more than SCAN_PLAN_ROWS rows, then plan_rows; with fewer
+ *                  pg_surrogate's blocks do it) segments and tokens per tile of
+ *                  rows, exact, and the advantages, one thread per group: A_i =
+ *                  (R_i - mean) / std over the group's float rewards
+ *                  (population std, IEEE double, index order; A = 0 when all
+ *                  rewards of the group are equal).
  *   pg_surrogate   HBM-bound, one wave per segment of a row (the segment plan
  *                  of the accounting path, two segments in flight per wave):
  *                  d = logp - logp_old in float,
@@ -51,61 +53,63 @@ struct PgArgs {
     const int32_t *lengths;
     int64_t n;
     const int64_t *seg_off;
-    const float *adv;        /* per row */
+    const float *reward;
+    int32_t G;
+    float *adv;              /* per row */
     float thr_low, thr_high; /* ln(1 - eps_low), ln(1 + eps_high) */
     float lo_val, hi_val;    /* 1 - eps_low, 1 + eps_high */
-    const int64_t *n_tokens; /* computed on the device */
-    double *wsum;            /* [waves] sum of the objective terms */
-    int64_t *wcnt;           /* [waves][2] clipped high, clipped low */
+    int64_t *n_tokens;       /* computed on the device */
+    double *wsum;            /* [blocks] sum of the objective terms */
+    int64_t *wcnt;           /* [blocks][2] clipped high, clipped low */
 };
 
-__global__ void __launch_bounds__(256) pg_advantage(const float *__restrict__ reward, int64_t n_groups, int32_t G,
-                                                    float *__restrict__ adv)
+/* The advantages of a group from its rewards R[0 .. G) (adv may be R). */
+__device__ __forceinline__ void group_advantage(const float *R, int32_t G, float *adv)
 {
-    const int64_t grp = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (grp >= n_groups) return;
-    const int64_t r0 = grp * G;
     bool equal = true;
-    for (int32_t i = 1; i < G; ++i) equal = equal && reward[r0 + i] == reward[r0];
+    for (int32_t i = 1; i < G; ++i) equal = equal && R[i] == R[0];
     if (equal) {
-        for (int32_t i = 0; i < G; ++i) adv[r0 + i] = 0.0f;
+        for (int32_t i = 0; i < G; ++i) adv[i] = 0.0f;
         return;
     }
     double s = 0.0;
-    for (int32_t i = 0; i < G; ++i) s = __dadd_rn(s, (double)reward[r0 + i]);
+    for (int32_t i = 0; i < G; ++i) s = __dadd_rn(s, (double)R[i]);
     const double mu = __ddiv_rn(s, (double)G);
     double ss = 0.0;
     for (int32_t i = 0; i < G; ++i) {
-        const double d = __dsub_rn((double)reward[r0 + i], mu);
+        const double d = __dsub_rn((double)R[i], mu);
         ss = __dadd_rn(ss, __dmul_rn(d, d));
     }
     const double sigma = __dsqrt_rn(__ddiv_rn(ss, (double)G));
-    for (int32_t i = 0; i < G; ++i)
-        adv[r0 + i] = (float)__ddiv_rn(__dsub_rn((double)reward[r0 + i], mu), sigma);
+    for (int32_t i = 0; i < G; ++i) adv[i] = (float)__ddiv_rn(__dsub_rn((double)R[i], mu), sigma);
 }
 
-/* part[b] = sum of max(lengths, 0) over rows [b*RED_TILE, (b+1)*RED_TILE). */
-__global__ void __launch_bounds__(RED_THREADS) sum_lengths_tiles(const int32_t *__restrict__ lengths, int64_t n,
-                                                                 int64_t *__restrict__ part)
+/* What a batch of more than SCAN_PLAN_ROWS rows needs before its plan: block
+ * b's tile of PLAN_TILE rows (segments and tokens, exact), and the advantages
+ * of groups [b PLAN_THREADS, (b + 1) PLAN_THREADS), one thread per group. */
+__global__ void __launch_bounds__(PLAN_THREADS) pg_prepare(PgArgs a, int64_t n_tiles, int64_t n_groups,
+                                                           int64_t *__restrict__ tile_sum,
+                                                           int64_t *__restrict__ len_sum)
 {
-    __shared__ int64_t il[RED_THREADS];
-    const int64_t r0 = (int64_t)blockIdx.x * RED_TILE + (int64_t)threadIdx.x * ROWS_PER_THREAD;
-    int64_t v[1] = {0};
-    for (int j = 0; j < ROWS_PER_THREAD; ++j) {
-        const int64_t r = r0 + j;
-        if (r < n && lengths[r] > 0) v[0] += lengths[r];
+    __shared__ int64_t part[PLAN_THREADS / WAVE];
+    const int64_t grp = (int64_t)blockIdx.x * PLAN_THREADS + threadIdx.x;
+    if (blockIdx.x < n_tiles) {
+        const int64_t r0 = (int64_t)blockIdx.x * PLAN_TILE;
+        const int64_t segs = tile_segments(a.starts, a.lengths, a.n, a.mis, r0, part);
+        int64_t len = 0;
+#pragma unroll
+        for (int j = 0; j < PLAN_RPT; ++j) {
+            const int64_t r = r0 + threadIdx.x + j * PLAN_THREADS;
+            const int32_t l = a.lengths[min(r, a.n - 1)];
+            len += r < a.n && l > 0 ? l : 0;
+        }
+        len = block_sum(len, part);
+        if (threadIdx.x == 0) {
+            tile_sum[blockIdx.x] = segs;
+            len_sum[blockIdx.x] = len;
+        }
     }
-    block_tree_sum<int64_t, 1>(v, il);
-    if (threadIdx.x == 0) part[blockIdx.x] = v[0];
-}
-
-__global__ void __launch_bounds__(RED_THREADS) sum_lengths_final(const int64_t *__restrict__ part, int64_t tiles,
-                                                                 int64_t *__restrict__ n_tokens)
-{
-    __shared__ int64_t il[RED_THREADS];
-    int64_t v[1];
-    sum_partials<int64_t, 1>(part, tiles, v, il);
-    if (threadIdx.x == 0) n_tokens[0] = v[0];
+    if (grp < n_groups) group_advantage(a.reward + grp * a.G, a.G, a.adv + grp * a.G);
 }
 
 /* Wave-wide sums in a fixed order (butterfly over the 64 lanes). */
@@ -214,11 +218,11 @@ __device__ __forceinline__ void pg_tokens(const PgArgs &a, const SegView &w, int
 
 /* One loaded segment: the row's advantage decides the branch for the whole
  * wave. */
-__device__ __forceinline__ void pg_segment(const PgArgs &a, const SegView &w, int lane, const float4 (&xn)[LOADS],
-                                           const float4 (&xo)[LOADS], float inv_n, double &acc, uint32_t &clip_hi,
-                                           uint32_t &clip_lo)
+__device__ __forceinline__ void pg_segment(const PgArgs &a, const float *adv, const SegView &w, int lane,
+                                           const float4 (&xn)[LOADS], const float4 (&xo)[LOADS], float inv_n,
+                                           double &acc, uint32_t &clip_hi, uint32_t &clip_lo)
 {
-    const float A = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a.adv[w.row])));
+    const float A = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(adv[w.row])));
     if (A > 0.0f) {
         const float clipA = a.hi_val * A;
         if (w.edge) pg_tokens<1, true>(a, w, lane, xn, xo, A, a.thr_high, clipA, inv_n, acc, clip_hi);
@@ -235,24 +239,70 @@ __device__ __forceinline__ void pg_segment(const PgArgs &a, const SegView &w, in
 
 /* One wave per segment of the plan; the wave's segments are contiguous.  Two
  * register buffers alternate so that the next segment's loads are in flight
- * while the current one is evaluated. */
-__global__ void __launch_bounds__(256, 4) pg_surrogate(PgArgs a)
+ * while the current one is evaluated.
+ * PLAN (up to SCAN_PLAN_ROWS rows): every block makes the plan, the token count
+ * and the advantages itself in LDS, in blocks of 8 waves so that half as many
+ * blocks do; block 0 also writes the advantages and the count.  In place of
+ * launches for the plan, the count (two) and the advantages, which took 16 of
+ * the 27 us of 64 rows of 3,500 tokens (13.8 now) and 20 of the 89 us of 1,024
+ * rows of 26,800 (70 now). */
+constexpr int PG_WAVES = 4, PG_PLAN_WAVES = 8;
+template <bool PLAN>
+constexpr int pg_waves() { return PLAN ? PG_PLAN_WAVES : PG_WAVES; }
+
+template <bool PLAN>
+__global__ void __launch_bounds__(WAVE * pg_waves<PLAN>(), 4) pg_surrogate(PgArgs a)
 {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t wave = uniform64((int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE));
-    const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x / WAVE);
-    const int64_t S = a.seg_off[a.n];
+    constexpr int NW = pg_waves<PLAN>();
+    __shared__ int64_t plan_off[PLAN ? SCAN_PLAN_ROWS + 1 : 1];
+    __shared__ int64_t plan_st[PLAN ? SCAN_PLAN_ROWS : 1];
+    __shared__ int32_t plan_ln[PLAN ? SCAN_PLAN_ROWS : 1];
+    __shared__ float plan_adv[PLAN ? SCAN_PLAN_ROWS : 1];
+    __shared__ int64_t part[3][NW];
+    __shared__ double part_d[NW];
+    const int t = threadIdx.x, lane = t & (WAVE - 1);
+    const int wib = __builtin_amdgcn_readfirstlane(t / WAVE);
+    const int64_t wave = uniform64((int64_t)blockIdx.x * NW + wib);
+    const int64_t n_waves = (int64_t)gridDim.x * NW;
+    const int64_t *seg_off = a.seg_off, *starts = a.starts;
+    const int32_t *lengths = a.lengths;
+    const float *adv = a.adv;
+    int64_t N;
+    if (PLAN) {
+        for (int64_t r = t; r < a.n; r += WAVE * NW) plan_adv[r] = a.reward[r]; /* before block_plan's barriers */
+        block_plan<NW>(a.starts, a.lengths, a.n, a.mis, plan_off, part[0], plan_st, plan_ln);
+        int64_t len = 0;
+        for (int64_t r = t; r < a.n; r += WAVE * NW) len += plan_ln[r] > 0 ? plan_ln[r] : 0;
+        len = wave_inclusive_scan(len);
+        if (lane == WAVE - 1) part[1][wib] = len;
+        for (int64_t g = t; g < a.n / a.G; g += WAVE * NW) group_advantage(plan_adv + g * a.G, a.G, plan_adv + g * a.G);
+        __syncthreads();
+        N = 0;
+        for (int w = 0; w < NW; ++w) N += part[1][w];
+        if (blockIdx.x == 0) {
+            for (int64_t r = t; r < a.n; r += WAVE * NW) a.adv[r] = plan_adv[r];
+            if (t == 0) a.n_tokens[0] = N;
+        }
+        seg_off = plan_off;
+        starts = plan_st;
+        lengths = plan_ln;
+        adv = plan_adv;
+    } else {
+        N = a.n_tokens[0];
+    }
+    N = uniform64(N);
+    const int64_t S = uniform64(seg_off[a.n]);
     const int64_t s_begin = uniform64(S * wave / n_waves);
     const int64_t s_end = uniform64(S * (wave + 1) / n_waves);
     double acc = 0.0;
     /* per-lane clip counts: a lane sees at most a 64th of the batch's tokens */
     uint32_t clip_hi = 0, clip_lo = 0;
     if (s_begin < s_end) {
-        const float inv_n = (float)__ddiv_rn(1.0, (double)a.n_tokens[0]);
+        const float inv_n = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((float)__ddiv_rn(1.0, (double)N))));
         SegCursor cur;
-        cur.seg_off = a.seg_off;
-        cur.starts = a.starts;
-        cur.lengths = a.lengths;
+        cur.seg_off = seg_off;
+        cur.starts = starts;
+        cur.lengths = lengths;
         cur.mis = a.mis;
         cur.s_begin = s_begin;
         cur.s_end = s_end;
@@ -268,7 +318,7 @@ __global__ void __launch_bounds__(256, 4) pg_surrogate(PgArgs a)
                 wn = cur.view(s + 1);
                 pg_loads(a, wn, lane, nb, ob);
             }
-            pg_segment(a, w, lane, na, oa, inv_n, acc, clip_hi, clip_lo);
+            pg_segment(a, adv, w, lane, na, oa, inv_n, acc, clip_hi, clip_lo);
             if (!more) break;
             ++s;
             w = wn;
@@ -277,7 +327,7 @@ __global__ void __launch_bounds__(256, 4) pg_surrogate(PgArgs a)
                 wn = cur.view(s + 1);
                 pg_loads(a, wn, lane, na, oa);
             }
-            pg_segment(a, w, lane, nb, ob, inv_n, acc, clip_hi, clip_lo);
+            pg_segment(a, adv, w, lane, nb, ob, inv_n, acc, clip_hi, clip_lo);
             if (!more) break;
             ++s;
             w = wn;
@@ -287,29 +337,61 @@ __global__ void __launch_bounds__(256, 4) pg_surrogate(PgArgs a)
     const int64_t hi_sum = wave_sum((int64_t)clip_hi);
     const int64_t lo_sum = wave_sum((int64_t)clip_lo);
     if (lane == 0) {
-        a.wsum[wave] = acc;
-        a.wcnt[2 * wave] = hi_sum;
-        a.wcnt[2 * wave + 1] = lo_sum;
+        part_d[wib] = acc;
+        part[1][wib] = hi_sum;
+        part[2][wib] = lo_sum;
+    }
+    __syncthreads();
+    if (t == 0) { /* the block's waves in order */
+        double s = 0.0;
+        int64_t hi = 0, lo = 0;
+        for (int w = 0; w < NW; ++w) {
+            s += part_d[w];
+            hi += part[1][w];
+            lo += part[2][w];
+        }
+        a.wsum[blockIdx.x] = s;
+        a.wcnt[2 * blockIdx.x] = hi;
+        a.wcnt[2 * blockIdx.x + 1] = lo;
     }
 }
 
-/* stats = {loss, tokens, clipped high, clipped low}, sums over waves in order. */
+/* stats = {loss, tokens, clipped high, clipped low}, sums over the blocks in a
+ * fixed order. */
 __global__ void __launch_bounds__(RED_THREADS) pg_final(const double *__restrict__ wsum,
-                                                        const int64_t *__restrict__ wcnt, int64_t waves,
+                                                        const int64_t *__restrict__ wcnt, int64_t blocks,
                                                         const int64_t *__restrict__ n_tokens, double *__restrict__ stats)
 {
-    __shared__ double dl[RED_THREADS];
-    __shared__ int64_t il[2 * RED_THREADS];
-    double sv[1];
-    int64_t cv[2];
-    sum_partials<double, 1>(wsum, waves, sv, dl);
-    sum_partials<int64_t, 2>(wcnt, waves, cv, il);
-    if (threadIdx.x != 0) return;
+    __shared__ double part_d[RED_THREADS / WAVE];
+    __shared__ int64_t part[2][RED_THREADS / WAVE];
+    const int t = threadIdx.x, lane = t & (WAVE - 1), wv = t / WAVE;
     const int64_t N = n_tokens[0];
-    stats[PARASON_PG_STAT_LOSS] = N > 0 ? -__ddiv_rn(sv[0], (double)N) : 0.0;
+    double s = 0.0;
+    int64_t hi = 0, lo = 0;
+    for (int64_t b = t; b < blocks; b += RED_THREADS) { /* coalesced */
+        s += wsum[b];
+        hi += wcnt[2 * b];
+        lo += wcnt[2 * b + 1];
+    }
+    s = wave_sum(s);
+    hi = wave_sum(hi);
+    lo = wave_sum(lo);
+    if (lane == 0) {
+        part_d[wv] = s;
+        part[0][wv] = hi;
+        part[1][wv] = lo;
+    }
+    __syncthreads();
+    if (t != 0) return;
+    for (int w = 1; w < RED_THREADS / WAVE; ++w) {
+        s += part_d[w];
+        hi += part[0][w];
+        lo += part[1][w];
+    }
+    stats[PARASON_PG_STAT_LOSS] = N > 0 ? -__ddiv_rn(s, (double)N) : 0.0;
     stats[PARASON_PG_STAT_TOKENS] = (double)N;
-    stats[PARASON_PG_STAT_CLIP_HIGH] = (double)cv[0];
-    stats[PARASON_PG_STAT_CLIP_LOW] = (double)cv[1];
+    stats[PARASON_PG_STAT_CLIP_HIGH] = (double)hi;
+    stats[PARASON_PG_STAT_CLIP_LOW] = (double)lo;
 }
 
 } /* namespace pk */
