@@ -14,7 +14,8 @@
  *                  (population std, IEEE double, index order; A = 0 when all
  *                  rewards of the group are equal).
  *   pg_surrogate   HBM-bound, one wave per segment of a row (the segment plan
- *                  of the accounting path, two segments in flight per wave):
+ *                  of the accounting path, two segments in flight per wave,
+ *                  the waves taking them in turn):
  *                  d = logp - logp_old in float,
  *                  rho = exp(d) from the hardware exp2 (exp_ratio), the clip
  *                  decision on d against float thresholds ln(1 - eps_low),
@@ -237,15 +238,21 @@ __device__ __forceinline__ void pg_segment(const PgArgs &a, const float *adv, co
     }
 }
 
-/* One wave per segment of the plan; the wave's segments are contiguous.  Two
- * register buffers alternate so that the next segment's loads are in flight
- * while the current one is evaluated.
+/* One wave per segment of the plan.  The waves take chunks of segments in turn,
+ * so that all of them stream inside one window of the three arrays: with a
+ * contiguous range per wave (4,096 windows) 20,000 rows of 20,000 tokens took
+ * 976 us, in chunks of 2 segments 882-910, of 4 914, of 8 940 (4.8 GB; torch's
+ * sub of the same bytes 800).  A chunk is found by a search; where the plan is
+ * in LDS that is cheap enough for chunks of one segment, which leave the waves
+ * within one segment of each other (1,024 rows of 26,800 tokens: 67.4 us, 70.6
+ * as ranges).  Two register buffers alternate so that the next segment's loads
+ * are in flight while the current one is evaluated.
  * PLAN (up to SCAN_PLAN_ROWS rows): every block makes the plan, the token count
  * and the advantages itself in LDS, in blocks of 8 waves so that half as many
  * blocks do; block 0 also writes the advantages and the count.  In place of
  * launches for the plan, the count (two) and the advantages, which took 16 of
  * the 27 us of 64 rows of 3,500 tokens (13.8 now) and 20 of the 89 us of 1,024
- * rows of 26,800 (70 now). */
+ * rows of 26,800 (67 now). */
 constexpr int PG_WAVES = 4, PG_PLAN_WAVES = 8;
 template <bool PLAN>
 constexpr int pg_waves() { return PLAN ? PG_PLAN_WAVES : PG_WAVES; }
@@ -292,44 +299,51 @@ __global__ void __launch_bounds__(WAVE * pg_waves<PLAN>(), 4) pg_surrogate(PgArg
     }
     N = uniform64(N);
     const int64_t S = uniform64(seg_off[a.n]);
-    const int64_t s_begin = uniform64(S * wave / n_waves);
-    const int64_t s_end = uniform64(S * (wave + 1) / n_waves);
+    constexpr int64_t CHUNK = PLAN ? 1 : 2;
+    const int64_t hop = (n_waves - 1) * CHUNK + 1; /* from a chunk's last segment to the next chunk's first */
     double acc = 0.0;
     /* per-lane clip counts: a lane sees at most a 64th of the batch's tokens */
     uint32_t clip_hi = 0, clip_lo = 0;
-    if (s_begin < s_end) {
+    int64_t s = wave * CHUNK;
+    if (s < S) {
         const float inv_n = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((float)__ddiv_rn(1.0, (double)N))));
         SegCursor cur;
         cur.seg_off = seg_off;
         cur.starts = starts;
         cur.lengths = lengths;
         cur.mis = a.mis;
-        cur.s_begin = s_begin;
-        cur.s_end = s_end;
-        cur.seek(s_begin, a.n);
+        cur.s_begin = 0;
+        cur.s_end = S;
+        cur.seek(s, a.n);
         float4 na[LOADS], oa[LOADS], nb[LOADS], ob[LOADS];
-        SegView w = cur.view(s_begin);
+        SegView w = cur.view(s);
         pg_loads(a, w, lane, na, oa);
-        int64_t s = s_begin;
+        int32_t left = (int32_t)CHUNK - 1; /* segments left of the chunk after s */
         while (true) {
             SegView wn;
-            bool more = s + 1 < s_end;
+            int64_t sn = left > 0 ? s + 1 : s + hop;
+            bool more = sn < S;
             if (more) {
-                wn = cur.view(s + 1);
+                if (left == 0) cur.seek(sn, a.n);
+                wn = cur.view(sn);
                 pg_loads(a, wn, lane, nb, ob);
             }
+            left = left > 0 ? left - 1 : (int32_t)CHUNK - 1;
             pg_segment(a, adv, w, lane, na, oa, inv_n, acc, clip_hi, clip_lo);
             if (!more) break;
-            ++s;
+            s = sn;
             w = wn;
-            more = s + 1 < s_end;
+            sn = left > 0 ? s + 1 : s + hop;
+            more = sn < S;
             if (more) {
-                wn = cur.view(s + 1);
+                if (left == 0) cur.seek(sn, a.n);
+                wn = cur.view(sn);
                 pg_loads(a, wn, lane, na, oa);
             }
+            left = left > 0 ? left - 1 : (int32_t)CHUNK - 1;
             pg_segment(a, adv, w, lane, nb, ob, inv_n, acc, clip_hi, clip_lo);
             if (!more) break;
-            ++s;
+            s = sn;
             w = wn;
         }
     }
