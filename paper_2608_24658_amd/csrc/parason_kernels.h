@@ -1644,6 +1644,15 @@ __device__ __forceinline__ uint32_t tag_class(const TagMatch &tm, int32_t t)
     return classify(tm, t, false);
 }
 
+/* For hashed ids, the class the slot's lane holds (tab_class = the class of
+ * slot_id[lane]); every lane must call it, and only a tag's lane gets its
+ * class.  With twelve compares per token column instead, 8,192 rows of 3,500
+ * tokens took 75 us a call, 65 so. */
+__device__ __forceinline__ uint32_t slot_class(const TagMatch &tm, int32_t t, int32_t tab_class)
+{
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(tag_slot(tm, t) << 2), tab_class);
+}
+
 /* Tags of the LOADS vectors x[i] (vector v0 + i*WAVE + lane of this lane) are
  * appended to dst[0 .. cap) in position order as (q + bias) << 4 | class, where
  * q = 4*(i*WAVE + lane) + j is the position in the segment; cnt counts all of
@@ -1652,7 +1661,7 @@ __device__ __forceinline__ uint32_t tag_class(const TagMatch &tm, int32_t t)
 template <int MODE, bool EDGE>
 __device__ __forceinline__ void scan_vectors(const int4 (&x)[LOADS], int32_t q_lo, int32_t q_hi,
                                              uint32_t *__restrict__ dst, uint32_t cap, int32_t bias, uint32_t &cnt,
-                                             const TagMatch &tm, int32_t tab, int lane)
+                                             const TagMatch &tm, int32_t tab, int32_t tab_class, int lane)
 {
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
@@ -1667,26 +1676,32 @@ __device__ __forceinline__ void scan_vectors(const int4 (&x)[LOADS], int32_t q_l
         }
         const int32_t q0 = 4 * (i * WAVE + lane);
         uint64_t b[4];
-        uint32_t mine = 0; /* this lane's tags, bit j for token j */
+        bool hits[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             bool hit = is_tag<MODE>(tm, t[j], tab);
             if (EDGE) hit = hit && q0 + j >= q_lo && q0 + j < q_hi;
             b[j] = __ballot(hit);
-            mine |= hit ? 1u << j : 0u;
+            hits[j] = hit;
         }
         if ((b[0] | b[1] | b[2] | b[3]) == 0) continue; /* wave-uniform: most vectors hold no tag */
-        uint32_t pre = 0;
+        uint32_t idx = cnt;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            pre = __builtin_amdgcn_mbcnt_hi((uint32_t)(b[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[j], pre));
-        /* the lane's tags in position order, one store each (a lane almost
-         * never holds more than one tag of a vector) */
-        for (uint32_t idx = cnt + pre; mine != 0; ++idx) {
-            const uint32_t j = (uint32_t)__builtin_ctz(mine);
-            mine &= mine - 1u;
-            const int32_t tj = j == 0 ? t[0] : j == 1 ? t[1] : j == 2 ? t[2] : t[3];
-            if (idx < cap) dst[idx] = ((uint32_t)(q0 + (int32_t)j + bias) << 4) | tag_class<MODE>(tm, tj);
+            idx = __builtin_amdgcn_mbcnt_hi((uint32_t)(b[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b[j], idx));
+        /* one store per token column that holds a tag, in the lane's position
+         * order: with a loop over each lane's own tags every turn ran the whole
+         * wave through the selection of its token (outline-heavy rows, a tag in
+         * a hundred tokens: the scan of 8,192 rows of 3,500 32.4 us, 30.0 so) */
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (b[j] == 0) continue; /* wave-uniform */
+            uint32_t c = MODE == TM_HASH ? slot_class(tm, t[j], tab_class) : 0u;
+            if (hits[j]) {
+                if (MODE != TM_HASH) c = tag_class<MODE>(tm, t[j]);
+                if (idx < cap) dst[idx] = ((uint32_t)(q0 + j + bias) << 4) | c;
+                ++idx;
+            }
         }
         cnt += (uint32_t)(__popcll(b[0]) + __popcll(b[1]) + __popcll(b[2]) + __popcll(b[3]));
     }
@@ -1782,7 +1797,8 @@ __device__ __forceinline__ void flush_row(const ScanArgs &a, int64_t row, int64_
  * completes a row whose events are all in the LDS buffer (rc.lcnt of them). */
 template <int MODE, bool PLAN>
 __device__ __forceinline__ bool collect_segment(const ScanArgs &a, const int4 (&x)[LOADS], const SegView &w,
-                                                RowCollect &rc, uint32_t *lev, int32_t tab, int lane)
+                                                RowCollect &rc, uint32_t *lev, int32_t tab, int32_t tab_class,
+                                                int lane)
 {
     if (w.s == w.first) {
         rc.lcnt = 0;
@@ -1797,8 +1813,8 @@ __device__ __forceinline__ bool collect_segment(const ScanArgs &a, const int4 (&
     if (!rc.global) {
         const int32_t bias = (int32_t)(4 * w.v0 - w.g); /* row position of segment position 0 */
         const uint32_t cap = (uint32_t)EVL - rc.lcnt;
-        if (!w.edge) scan_vectors<MODE, false>(x, 0, SEG_TOK, lev + rc.lcnt, cap, bias, cnt, a.tm, tab, lane);
-        else scan_vectors<MODE, true>(x, w.q_lo, w.q_hi, lev + rc.lcnt, cap, bias, cnt, a.tm, tab, lane);
+        if (!w.edge) scan_vectors<MODE, false>(x, 0, SEG_TOK, lev + rc.lcnt, cap, bias, cnt, a.tm, tab, tab_class, lane);
+        else scan_vectors<MODE, true>(x, w.q_lo, w.q_hi, lev + rc.lcnt, cap, bias, cnt, a.tm, tab, tab_class, lane);
         if (cnt > cap) {
             /* the row's events overflow the LDS buffer: its segments so far are
              * classified again by the row kernel, the rest use per-segment lists */
@@ -1811,8 +1827,8 @@ __device__ __forceinline__ bool collect_segment(const ScanArgs &a, const int4 (&
         /* the segment's own list, in the wave's pool region */
         const uint32_t room = min(rc.p_end - rc.pc, (uint32_t)SEG_TOK); /* a multiple of 4 */
         uint32_t *dst = a.slots + rc.pc;
-        if (!w.edge) scan_vectors<MODE, false>(x, 0, SEG_TOK, dst, room, 0, cnt, a.tm, tab, lane);
-        else scan_vectors<MODE, true>(x, w.q_lo, w.q_hi, dst, room, 0, cnt, a.tm, tab, lane);
+        if (!w.edge) scan_vectors<MODE, false>(x, 0, SEG_TOK, dst, room, 0, cnt, a.tm, tab, tab_class, lane);
+        else scan_vectors<MODE, true>(x, w.q_lo, w.q_hi, dst, room, 0, cnt, a.tm, tab, tab_class, lane);
         const bool stored = cnt <= room;
         if (lane == 0) a.seg[w.s] = SegRec{stored ? (int32_t)cnt : DENSE, rc.pc};
         if (stored) rc.pc += (cnt + 3u) & ~3u;
@@ -1917,7 +1933,8 @@ struct ScanSched {
 template <int MODE, bool PLAN>
 __device__ __forceinline__ void scan_range(const ScanArgs &a, const int64_t *seg_off, const int64_t *starts,
                                            const int32_t *lengths, int64_t s_begin, int64_t s_end,
-                                           uint32_t pc, uint32_t p_end, uint32_t *lev, int32_t tab, int lane)
+                                           uint32_t pc, uint32_t p_end, uint32_t *lev, int32_t tab,
+                                           int32_t tab_class, int lane)
 {
     const int4 *src = reinterpret_cast<const int4 *>(a.tok_base);
     SegCursor cur;
@@ -1945,7 +1962,7 @@ __device__ __forceinline__ void scan_range(const ScanArgs &a, const int64_t *seg
             wn = cur.view(s + 1);
             issue_loads(xb, src, wn.v0, wn.v1, wn.edge, lane);
         }
-        if (collect_segment<MODE, PLAN>(a, xa, w, rc, lev, tab, lane))
+        if (collect_segment<MODE, PLAN>(a, xa, w, rc, lev, tab, tab_class, lane))
             flush_row(a, w.row, w.first, w.last, rc.lcnt, lev, rc, lane);
         if (!more) break;
         ++s;
@@ -1955,7 +1972,7 @@ __device__ __forceinline__ void scan_range(const ScanArgs &a, const int64_t *seg
             wn = cur.view(s + 1);
             issue_loads(xa, src, wn.v0, wn.v1, wn.edge, lane);
         }
-        if (collect_segment<MODE, PLAN>(a, xb, w, rc, lev, tab, lane))
+        if (collect_segment<MODE, PLAN>(a, xb, w, rc, lev, tab, tab_class, lane))
             flush_row(a, w.row, w.first, w.last, rc.lcnt, lev, rc, lane);
         if (!more) break;
         ++s;
@@ -1997,6 +2014,7 @@ __global__ void __launch_bounds__(WAVE * scan_waves<PLAN>(), PARASON_SCAN_WAVES_
     if (S > a.seg_cap) return; /* the row kernel reports PARASON_FLAG_WS_OVERFLOW */
     uint32_t *lev = lds_ev[wib];
     const int32_t tab = MODE == TM_HASH ? a.tm.slot_id[lane] : 0;
+    const int32_t tab_class = MODE == TM_HASH ? (int32_t)classify(a.tm, tab, false) : 0; /* of a slot in use */
     int64_t b, e, q, Bk = 0, Ek = 0, L1 = 0, Q = 0;
     bool blk_dyn = false;
     uint32_t extra;
@@ -2032,7 +2050,7 @@ __global__ void __launch_bounds__(WAVE * scan_waves<PLAN>(), PARASON_SCAN_WAVES_
             const uint32_t p_end =
                 __builtin_amdgcn_readfirstlane(POOL_PER_SEG * (uint32_t)e + extra * (uint32_t)(q + 1));
             scan_range<MODE, PLAN>(a, seg_off, PLAN ? plan_st : a.starts, PLAN ? plan_ln : a.lengths, b, e, pc, p_end,
-                                   lev, tab, lane);
+                                   lev, tab, tab_class, lane);
         }
         if (PLAN) {
             if (!blk_dyn) break;
