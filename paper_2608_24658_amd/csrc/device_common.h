@@ -230,37 +230,55 @@ __device__ __forceinline__ int32_t dpp_incl_scan(int32_t v, int lane)
     return row == 0 ? v : Op::f(row == 1 ? t0 : (row == 2 ? p2 : p3), v);
 }
 
-/* Segmented form: restarts at lanes with head set; lanes before the first
+/* The heads of a segmented scan, shared by the scans over the same heads:
+ * at[i], a head in the 2^i lanes up to this one of its row of 16 lanes; any, in
+ * those up to the row's first; f0 .. f2, whether rows 0 .. 2 hold one. */
+struct SegHeads {
+    bool at[4], any;
+    int32_t f0, f1, f2;
+};
+
+__device__ __forceinline__ SegHeads dpp_seg_heads(bool head)
+{
+    SegHeads h;
+    int32_t f = head ? 1 : 0;
+    h.at[0] = f != 0;
+    f |= row_shr<1>(f, 0);
+    h.at[1] = f != 0;
+    f |= row_shr<2>(f, 0);
+    h.at[2] = f != 0;
+    f |= row_shr<4>(f, 0);
+    h.at[3] = f != 0;
+    f |= row_shr<8>(f, 0);
+    h.any = f != 0;
+    h.f0 = __builtin_amdgcn_readlane(f, 15);
+    h.f1 = __builtin_amdgcn_readlane(f, 31);
+    h.f2 = __builtin_amdgcn_readlane(f, 47);
+    return h;
+}
+
+/* Segmented form: restarts at the heads; lanes before the first
  * head continue from carry.  Row r starts from C_r: C_0 = carry, and
  * C_{r+1} is row r's last lane if the row holds a head, else op(C_r, it). */
 template <class Op>
-__device__ __forceinline__ int32_t dpp_seg_scan(int32_t v, bool head, int32_t carry, int lane)
+__device__ __forceinline__ int32_t dpp_seg_scan(int32_t v, const SegHeads &h, int32_t carry, int lane)
 {
-    int32_t f = head ? 1 : 0;
-#define PARASON_SEG_STEP(N)                          \
-    {                                                \
-        const int32_t vo = row_shr<N>(v, Op::ident); \
-        const int32_t fo = row_shr<N>(f, 0);         \
-        if (!f) {                                    \
-            v = Op::f(vo, v);                        \
-            f = fo;                                  \
-        }                                            \
-    }
-    PARASON_SEG_STEP(1)
-    PARASON_SEG_STEP(2)
-    PARASON_SEG_STEP(4)
-    PARASON_SEG_STEP(8)
-#undef PARASON_SEG_STEP
+    int32_t o = Op::f(row_shr<1>(v, Op::ident), v);
+    v = h.at[0] ? v : o;
+    o = Op::f(row_shr<2>(v, Op::ident), v);
+    v = h.at[1] ? v : o;
+    o = Op::f(row_shr<4>(v, Op::ident), v);
+    v = h.at[2] ? v : o;
+    o = Op::f(row_shr<8>(v, Op::ident), v);
+    v = h.at[3] ? v : o;
     const int32_t v0 = __builtin_amdgcn_readlane(v, 15), v1 = __builtin_amdgcn_readlane(v, 31),
                   v2 = __builtin_amdgcn_readlane(v, 47);
-    const int32_t f0 = __builtin_amdgcn_readlane(f, 15), f1 = __builtin_amdgcn_readlane(f, 31),
-                  f2 = __builtin_amdgcn_readlane(f, 47);
-    const int32_t c1 = f0 ? v0 : Op::f(carry, v0);
-    const int32_t c2 = f1 ? v1 : Op::f(c1, v1);
-    const int32_t c3 = f2 ? v2 : Op::f(c2, v2);
+    const int32_t c1 = h.f0 ? v0 : Op::f(carry, v0);
+    const int32_t c2 = h.f1 ? v1 : Op::f(c1, v1);
+    const int32_t c3 = h.f2 ? v2 : Op::f(c2, v2);
     const int row = lane >> 4;
     const int32_t c = row == 0 ? carry : (row == 1 ? c1 : (row == 2 ? c2 : c3));
-    return f ? v : Op::f(c, v);
+    return h.any ? v : Op::f(c, v);
 }
 
 /* A segment as the scan wave sees it (all fields wave-uniform). */

@@ -19,7 +19,7 @@
  *        written out, coalesced, as one compact list (mode[i] = 1).  Other rows
  *        leave their events in per-segment lists (mode[i] = 0).  Every list the scan writes is in the wave's region of the
  *        slot pool; seg[s] holds its length and first slot.
- *   rows_par  (small batches: one wave per row, four events per lane)
+ *   rows_par  (small batches: one wave per row, one to four events per lane)
  *        Validity from local checks and a depth prefix sum; latency and branch
  *        tokens level by level with segmented scans (DPP).  A segment whose
  *        events the scan could not store (marked DENSE) is read again by the
@@ -719,12 +719,6 @@ __device__ __forceinline__ bool text_allowed(uint32_t st) { return (TEXT_STATES 
 __device__ __forceinline__ int32_t wave_incl_scan32(int32_t v, int lane) { return dpp_incl_scan<OpAdd>(v, lane); }
 __device__ __forceinline__ int32_t wave_incl_max32(int32_t v, int lane) { return dpp_incl_scan<OpMax>(v, lane); }
 
-template <bool MAX>
-__device__ __forceinline__ int32_t wave_seg_scan(int32_t v, bool head, int32_t carry, int lane)
-{
-    return MAX ? dpp_seg_scan<OpMax>(v, head, carry, lane) : dpp_seg_scan<OpAdd>(v, head, carry, lane);
-}
-
 /* Reductions over the wave, the result in every lane. */
 __device__ __forceinline__ int32_t wave_sum32(int32_t v)
 {
@@ -747,52 +741,85 @@ constexpr int PAR_K = 4;
 constexpr int PAR_PASS = PAR_K * WAVE;
 static_assert(PAR_EVENTS % PAR_PASS == 0, "passes end inside the LDS arrays");
 
-__device__ __forceinline__ void par_load(const int32_t *s, int32_t ib, int32_t (&v)[PAR_K])
+template <int K>
+__device__ __forceinline__ void par_load(const int32_t *s, int32_t ib, int32_t (&v)[K])
 {
-    const int4 x = *reinterpret_cast<const int4 *>(s + ib);
-    v[0] = x.x;
-    v[1] = x.y;
-    v[2] = x.z;
-    v[3] = x.w;
+    if constexpr (K == 4) {
+        const int4 x = *reinterpret_cast<const int4 *>(s + ib);
+        v[0] = x.x;
+        v[1] = x.y;
+        v[2] = x.z;
+        v[3] = x.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = s[ib + k];
+    }
 }
 
-__device__ __forceinline__ void par_store(int32_t *s, int32_t ib, const int32_t (&v)[PAR_K])
+template <int K>
+__device__ __forceinline__ void par_store(int32_t *s, int32_t ib, const int32_t (&v)[K])
 {
-    *reinterpret_cast<int4 *>(s + ib) = make_int4(v[0], v[1], v[2], v[3]);
+    if constexpr (K == 4) {
+        *reinterpret_cast<int4 *>(s + ib) = make_int4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k) s[ib + k] = v[k];
+    }
 }
 
-__device__ __forceinline__ int32_t par_pick(const int32_t (&v)[PAR_K], int32_t k)
+template <int K>
+__device__ __forceinline__ int32_t par_pick(const int32_t (&v)[K], int32_t k)
 {
-    return k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[2] : v[3];
+    int32_t x = v[0];
+#pragma unroll
+    for (int i = 1; i < K; ++i) x = k == i ? v[i] : x;
+    return x;
 }
 
 /* Inclusive scan over the wave's events in order, continuing from carry. */
-template <class Op>
-__device__ __forceinline__ void par_incl_scan(int32_t (&v)[PAR_K], int32_t carry, int lane)
+template <class Op, int K>
+__device__ __forceinline__ void par_incl_scan(int32_t (&v)[K], int32_t carry, int lane)
 {
 #pragma unroll
-    for (int k = 1; k < PAR_K; ++k) v[k] = Op::f(v[k - 1], v[k]);
-    const int32_t before = Op::f(carry, lane_before(dpp_incl_scan<Op>(v[PAR_K - 1], lane), Op::ident));
+    for (int k = 1; k < K; ++k) v[k] = Op::f(v[k - 1], v[k]);
+    const int32_t before = Op::f(carry, lane_before(dpp_incl_scan<Op>(v[K - 1], lane), Op::ident));
 #pragma unroll
-    for (int k = 0; k < PAR_K; ++k) v[k] = Op::f(before, v[k]);
+    for (int k = 0; k < K; ++k) v[k] = Op::f(before, v[k]);
+}
+
+/* The heads of segmented scans over the wave's events: seen[k], a head among
+ * the lane's events 0 .. k. */
+template <int K>
+struct ParHeads {
+    bool head[K], seen[K];
+    SegHeads lanes;
+};
+
+template <int K>
+__device__ __forceinline__ ParHeads<K> par_heads(const bool (&head)[K])
+{
+    ParHeads<K> h;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        h.head[k] = head[k];
+        h.seen[k] = k > 0 ? h.seen[k > 0 ? k - 1 : 0] | head[k] : head[k];
+    }
+    h.lanes = dpp_seg_heads(h.seen[K - 1]);
+    return h;
 }
 
 /* Segmented form: restarts at events with head set; events before the first
  * head continue from carry. */
-template <class Op>
-__device__ __forceinline__ void par_seg_scan(int32_t (&v)[PAR_K], const bool (&head)[PAR_K], int32_t carry, int lane)
+template <class Op, int K>
+__device__ __forceinline__ void par_seg_scan(int32_t (&v)[K], const ParHeads<K> &h, int32_t carry, int lane)
 {
-    bool any = head[0];
 #pragma unroll
-    for (int k = 1; k < PAR_K; ++k) {
-        if (!head[k]) v[k] = Op::f(v[k - 1], v[k]);
-        any = any || head[k];
-    }
-    const int32_t in = lane_before(dpp_seg_scan<Op>(v[PAR_K - 1], any, carry, lane), carry);
-    bool seen = false;
+    for (int k = 1; k < K; ++k)
+        if (!h.head[k]) v[k] = Op::f(v[k - 1], v[k]);
+    const int32_t in = lane_before(dpp_seg_scan<Op>(v[K - 1], h.lanes, carry, lane), carry);
 #pragma unroll
-    for (int k = 0; k < PAR_K; ++k) {
-        seen = seen || head[k];
+    for (int k = 0; k < K; ++k) {
+        const bool seen = h.seen[k];
         if (!seen) v[k] = Op::f(in, v[k]);
     }
 }
@@ -873,8 +900,182 @@ __device__ __forceinline__ void par_load_segment(const RowArgs &a, int64_t vrow0
     for (int i = 0; i < LOADS; ++i) x[i] = src[min(vrow0 + k * SEG_VEC + i * WAVE + lane, vend - 1)];
 }
 
-/* One row by one wave, its lanes over the row's events, four consecutive
- * events per lane.  The same results as the automaton, from the
+/* The two phases of par_row on the row's m events in LDS, K consecutive events
+ * per lane and pass; SINGLE: one pass holds them (the scans then carry nothing
+ * in).  One event per lane for rows of up to 64 (four of five of the
+ * generator's), two for up to 128 (99 of 100): a wave's steps per pass grow with
+ * K (8,192 rows of 3,500 tokens: 22.4 us with K = 4 for every row, 17.7 with 2
+ * and 4; 8 rows: 9.0 and 7.5). */
+template <bool LENIENT, int K, bool SINGLE>
+__device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r, int32_t len, int32_t m, int lane)
+{
+    constexpr int PASS = K * WAVE;
+    /* phase A: validity, first error, depth and open threads before each event */
+    int32_t prev_c = -1, prev_p = -1, depth = 0, threads = 0, err = INT32_MAX, max_depth = 0, n_blocks = 0;
+    for (int32_t i0 = 0; i0 < m && err == INT32_MAX; i0 += PASS) {
+        const int32_t ib = i0 + K * lane;
+        int32_t c[K], p[K], dd[K], dt[K];
+        par_load(l.X, ib, c);
+        par_load(l.P, ib, p);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (ib + k >= m) c[k] = p[k] = 0;
+            dd[k] = ib + k < m ? (c[k] == C_PAR) - (c[k] == C_END_PAR) : 0;
+            dt[k] = ib + k < m ? (c[k] == C_THR) - (c[k] == C_END_THR) : 0;
+        }
+        int32_t d_in[K], t_in[K]; /* depth and open threads after each event */
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            d_in[k] = dd[k];
+            t_in[k] = dt[k];
+        }
+        par_incl_scan<OpAdd>(d_in, depth, lane);
+        par_incl_scan<OpAdd>(t_in, threads, lane);
+        int32_t pc = lane_before(c[K - 1], prev_c), pp = lane_before(p[K - 1], prev_p);
+        int32_t e = INT32_MAX, open_depth = 0, pars = 0;
+        int32_t xv[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            /* the checks of one event, without branches (bitwise, not
+             * short-circuit: lanes hold different classes) */
+            const int32_t db = d_in[k] - dd[k], tb = t_in[k] - dt[k];
+            const int32_t ck = c[k];
+            const bool act = ib + k < m;
+            const uint32_t st = state_at(pc);
+            const int32_t gap = p[k] - pp - 1;
+            const bool text_ok = (gap == 0) | text_allowed(st) | (LENIENT & (st != S_START));
+            const bool closes_entry = (ck == C_END_SUB) | (ck == C_END_TRI);
+            const bool tag_ok = class_allowed(st, ck) & !((ck == C_END_THINK) & (db != 0)) &
+                                !((ck == C_END_THR) & (db == 0)) & !(closes_entry & ((ck != pc + 1) | (gap == 0)));
+            const int32_t ek = text_ok ? (tag_ok ? INT32_MAX : p[k]) : pp + 1;
+            const bool opens = act & (ck == C_PAR);
+            e = min(e, act ? ek : INT32_MAX);
+            open_depth = max(open_depth, opens ? db + 1 : 0);
+            pars += opens ? 1 : 0;
+            /* counts of a row that goes on to phase B are not negative */
+            xv[k] = par_key((uint32_t)ck, db, tb);
+            pc = c[k];
+            pp = p[k];
+        }
+        par_store(l.X, ib, xv);
+        err = wave_min32(e);
+        max_depth = max(max_depth, wave_max32(open_depth));
+        n_blocks += wave_sum32(pars);
+        /* the pass's last event: the one before the next pass's first */
+        const int32_t last = min(m - i0, PASS) - 1;
+        prev_c = __builtin_amdgcn_readlane(par_pick(c, last % K), last / K);
+        prev_p = __builtin_amdgcn_readlane(par_pick(p, last % K), last / K);
+        if (SINGLE) break;
+        depth = lane63(d_in[K - 1]);
+        threads = lane63(t_in[K - 1]);
+    }
+    if (err == INT32_MAX) {
+        /* the end of the row: the text after the last tag, then </think> must have come */
+        const uint32_t st = state_at(prev_c);
+        const int32_t gap = len - prev_p - 1;
+        const bool text_ok = gap == 0 || text_allowed(st) || (LENIENT && st != S_START);
+        if (!text_ok) err = prev_p + 1;
+        else if (st != S_TRAIL) err = len;
+    }
+    if (err != INT32_MAX) {
+        if (lane == 0) write_row(a.out, r, len, len, 0, 0, 0, 0, err, err == len ? PARASON_FLAG_TRUNCATED : 0u);
+        return true;
+    }
+    if (max_depth > PAR_LEVELS) return false;
+    __syncthreads();
+
+    /* phase B: level by level, deepest first */
+    int32_t my_sub = 0, my_tri = 0, my_saved = 0;
+    bool my_mismatch = false;
+    for (int32_t lev = max_depth; lev >= 1; --lev) {
+        /* one pass per level: the threads of level lev (tokens, latency, own
+         * tokens), then, from those values still in registers, the blocks of
+         * level lev (saved tokens, thread types, count mismatch) */
+        int32_t c_thr = -1, c_S = 0, c_CH = 0;
+        int32_t c_sum = 0, c_max = 0, c_n = 0, c_par = -1, c_eout = -1;
+        for (int32_t i0 = 0; i0 < m; i0 += PASS) {
+            const int32_t ib = i0 + K * lane;
+            int32_t x[K], sav[K], tk[K];
+            par_load(l.X, ib, x);
+            par_load(l.SAV, ib, sav);
+            par_load(l.TOK, ib, tk);
+            bool thr[K], ethr[K], par[K], epar[K];
+            int32_t ti[K], S[K], CH[K], pi[K], oi[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                /* phase A left class 0 in the places of the last pass past m */
+                thr[k] = x[k] == par_key(C_THR, lev, lev - 1);
+                ethr[k] = x[k] == par_key(C_END_THR, lev, lev);
+                par[k] = x[k] == par_key(C_PAR, lev - 1, lev - 1);
+                epar[k] = x[k] == par_key(C_END_PAR, lev, lev - 1);
+                ti[k] = thr[k] ? ib + k : -1;
+                S[k] = x[k] == par_key(C_END_PAR, lev + 1, lev) ? sav[k] : 0;
+                CH[k] = x[k] == par_key(C_END_THR, lev + 1, lev + 1) ? tk[k] : 0;
+                pi[k] = par[k] ? ib + k : -1;
+                oi[k] = x[k] == par_key(C_END_OUT, lev, lev - 1) ? ib + k : -1;
+            }
+            par_incl_scan<OpMax>(ti, c_thr, lane);  /* the thread each event is in */
+            const ParHeads<K> ht = par_heads(thr), hp = par_heads(par);
+            par_seg_scan<OpAdd>(S, ht, c_S, lane);
+            par_seg_scan<OpAdd>(CH, ht, c_CH, lane);
+            par_incl_scan<OpMax>(pi, c_par, lane);  /* the block each event is in ... */
+            par_incl_scan<OpMax>(oi, c_eout, lane); /* ... and its outline's end */
+            int32_t sum[K], mx[K], nt[K], own[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int32_t tok = ethr[k] ? l.P[ib + k] - l.P[max(ti[k], 0)] + 1 : 0;
+                if (ethr[k]) l.TOK[ib + k] = tok; /* read by the next level's threads */
+                sum[k] = tok;
+                mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
+                own[k] = tok - CH[k];
+                nt[k] = ethr[k] ? 1 : 0;
+            }
+            par_seg_scan<OpAdd>(sum, hp, c_sum, lane);
+            par_seg_scan<OpMax>(mx, hp, c_max, lane);
+            par_seg_scan<OpAdd>(nt, hp, c_n, lane);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
+                if (ethr[k]) {
+                    const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
+                    if (kk < n_e) {
+                        const int32_t t = l.X[pi[k] + 2 + 2 * kk] & 15;
+                        my_sub += t == C_SUB ? own[k] : 0;
+                        my_tri += t == C_TRI ? own[k] : 0;
+                    }
+                }
+                if (epar[k]) {
+                    const int32_t saved = sum[k] - mx[k];
+                    l.SAV[ib + k] = saved;
+                    my_mismatch = my_mismatch || nt[k] != n_e;
+                    my_saved += lev == 1 ? saved : 0;
+                }
+            }
+            if (SINGLE) break;
+            c_thr = lane63(ti[K - 1]);
+            c_S = lane63(S[K - 1]);
+            c_CH = lane63(CH[K - 1]);
+            c_sum = lane63(sum[K - 1]);
+            c_max = lane63(mx[K - 1]);
+            c_n = lane63(nt[K - 1]);
+            c_par = lane63(pi[K - 1]);
+            c_eout = lane63(oi[K - 1]);
+        }
+        __syncthreads();
+    }
+    const int32_t n_sub = wave_sum32(my_sub), n_tri = wave_sum32(my_tri), saved = wave_sum32(my_saved);
+    const bool mismatch = __ballot(my_mismatch) != 0;
+    if (lane == 0) {
+        uint32_t fl = PARASON_FLAG_VALID;
+        if (mismatch) fl |= PARASON_FLAG_COUNT_MISMATCH;
+        if (n_blocks > 0) fl |= PARASON_FLAG_TRIGGERED;
+        write_row(a.out, r, len, len - saved, n_sub, n_tri, n_blocks, max_depth, -1, fl);
+    }
+    return true;
+}
+
+/* One row by one wave, its lanes over the row's events, up to four consecutive
+ * events per lane and pass.  The same results as the automaton, from the
  * structure of the grammar:
  *   - the state before a tag is fixed by the class of the tag before it, and
  *     the nesting depth before it is a prefix sum, so every check of the
@@ -974,7 +1175,8 @@ __device__ bool par_row(const RowArgs &a, ParLds &l, int64_t r, int64_t start, i
             c0 += n_stored;
             held = m + total <= PAR_EVENTS;
             if (!held || total == 0) continue;
-            for (int32_t f0 = 0; f0 < total; f0 += PAR_PASS) par_store(map, f0 + jb, {-1, -1, -1, -1});
+            const int32_t none[PAR_K] = {-1, -1, -1, -1};
+            for (int32_t f0 = 0; f0 < total; f0 += PAR_PASS) par_store(map, f0 + jb, none);
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < PAR_K; ++k) {
@@ -1014,165 +1216,9 @@ __device__ bool par_row(const RowArgs &a, ParLds &l, int64_t r, int64_t start, i
     }
     if (!held) return false;
     __syncthreads();
-    /* phase A: validity, first error, depth and open threads before each event */
-    int32_t prev_c = -1, prev_p = -1, depth = 0, threads = 0, err = INT32_MAX, max_depth = 0, n_blocks = 0;
-    for (int32_t i0 = 0; i0 < m && err == INT32_MAX; i0 += PAR_PASS) {
-        const int32_t ib = i0 + PAR_K * lane;
-        int32_t c[PAR_K], p[PAR_K], dd[PAR_K], dt[PAR_K];
-        par_load(l.X, ib, c);
-        par_load(l.P, ib, p);
-#pragma unroll
-        for (int k = 0; k < PAR_K; ++k) {
-            if (ib + k >= m) c[k] = p[k] = 0;
-            dd[k] = ib + k < m ? (c[k] == C_PAR) - (c[k] == C_END_PAR) : 0;
-            dt[k] = ib + k < m ? (c[k] == C_THR) - (c[k] == C_END_THR) : 0;
-        }
-        int32_t d_in[PAR_K], t_in[PAR_K]; /* depth and open threads after each event */
-#pragma unroll
-        for (int k = 0; k < PAR_K; ++k) {
-            d_in[k] = dd[k];
-            t_in[k] = dt[k];
-        }
-        par_incl_scan<OpAdd>(d_in, depth, lane);
-        par_incl_scan<OpAdd>(t_in, threads, lane);
-        int32_t pc = lane_before(c[PAR_K - 1], prev_c), pp = lane_before(p[PAR_K - 1], prev_p);
-        int32_t e = INT32_MAX, open_depth = 0, pars = 0;
-        int32_t xv[PAR_K];
-#pragma unroll
-        for (int k = 0; k < PAR_K; ++k) {
-            /* the checks of one event, without branches (bitwise, not
-             * short-circuit: lanes hold different classes) */
-            const int32_t db = d_in[k] - dd[k], tb = t_in[k] - dt[k];
-            const int32_t ck = c[k];
-            const bool act = ib + k < m;
-            const uint32_t st = state_at(pc);
-            const int32_t gap = p[k] - pp - 1;
-            const bool text_ok = (gap == 0) | text_allowed(st) | (LENIENT & (st != S_START));
-            const bool closes_entry = (ck == C_END_SUB) | (ck == C_END_TRI);
-            const bool tag_ok = class_allowed(st, ck) & !((ck == C_END_THINK) & (db != 0)) &
-                                !((ck == C_END_THR) & (db == 0)) & !(closes_entry & ((ck != pc + 1) | (gap == 0)));
-            const int32_t ek = text_ok ? (tag_ok ? INT32_MAX : p[k]) : pp + 1;
-            const bool opens = act & (ck == C_PAR);
-            e = min(e, act ? ek : INT32_MAX);
-            open_depth = max(open_depth, opens ? db + 1 : 0);
-            pars += opens ? 1 : 0;
-            /* counts of a row that goes on to phase B are not negative */
-            xv[k] = par_key((uint32_t)ck, db, tb);
-            pc = c[k];
-            pp = p[k];
-        }
-        par_store(l.X, ib, xv);
-        err = wave_min32(e);
-        max_depth = max(max_depth, wave_max32(open_depth));
-        n_blocks += wave_sum32(pars);
-        /* the pass's last event: the one before the next pass's first */
-        const int32_t last = min(m - i0, PAR_PASS) - 1;
-        prev_c = __builtin_amdgcn_readlane(par_pick(c, last % PAR_K), last / PAR_K);
-        prev_p = __builtin_amdgcn_readlane(par_pick(p, last % PAR_K), last / PAR_K);
-        depth = lane63(d_in[PAR_K - 1]);
-        threads = lane63(t_in[PAR_K - 1]);
-    }
-    if (err == INT32_MAX) {
-        /* the end of the row: the text after the last tag, then </think> must have come */
-        const uint32_t st = state_at(prev_c);
-        const int32_t gap = len - prev_p - 1;
-        const bool text_ok = gap == 0 || text_allowed(st) || (LENIENT && st != S_START);
-        if (!text_ok) err = prev_p + 1;
-        else if (st != S_TRAIL) err = len;
-    }
-    if (err != INT32_MAX) {
-        if (lane == 0) write_row(a.out, r, len, len, 0, 0, 0, 0, err, err == len ? PARASON_FLAG_TRUNCATED : 0u);
-        return true;
-    }
-    if (max_depth > PAR_LEVELS) return false;
-    __syncthreads();
-
-    /* phase B: level by level, deepest first */
-    int32_t my_sub = 0, my_tri = 0, my_saved = 0;
-    bool my_mismatch = false;
-    for (int32_t lev = max_depth; lev >= 1; --lev) {
-        /* one pass per level: the threads of level lev (tokens, latency, own
-         * tokens), then, from those values still in registers, the blocks of
-         * level lev (saved tokens, thread types, count mismatch) */
-        int32_t c_thr = -1, c_S = 0, c_CH = 0;
-        int32_t c_sum = 0, c_max = 0, c_n = 0, c_par = -1, c_eout = -1;
-        for (int32_t i0 = 0; i0 < m; i0 += PAR_PASS) {
-            const int32_t ib = i0 + PAR_K * lane;
-            int32_t x[PAR_K], sav[PAR_K], tk[PAR_K];
-            par_load(l.X, ib, x);
-            par_load(l.SAV, ib, sav);
-            par_load(l.TOK, ib, tk);
-            bool thr[PAR_K], ethr[PAR_K], par[PAR_K], epar[PAR_K];
-            int32_t ti[PAR_K], S[PAR_K], CH[PAR_K], pi[PAR_K], oi[PAR_K];
-#pragma unroll
-            for (int k = 0; k < PAR_K; ++k) {
-                /* phase A left class 0 in the places of the last pass past m */
-                thr[k] = x[k] == par_key(C_THR, lev, lev - 1);
-                ethr[k] = x[k] == par_key(C_END_THR, lev, lev);
-                par[k] = x[k] == par_key(C_PAR, lev - 1, lev - 1);
-                epar[k] = x[k] == par_key(C_END_PAR, lev, lev - 1);
-                ti[k] = thr[k] ? ib + k : -1;
-                S[k] = x[k] == par_key(C_END_PAR, lev + 1, lev) ? sav[k] : 0;
-                CH[k] = x[k] == par_key(C_END_THR, lev + 1, lev + 1) ? tk[k] : 0;
-                pi[k] = par[k] ? ib + k : -1;
-                oi[k] = x[k] == par_key(C_END_OUT, lev, lev - 1) ? ib + k : -1;
-            }
-            par_incl_scan<OpMax>(ti, c_thr, lane);  /* the thread each event is in */
-            par_seg_scan<OpAdd>(S, thr, c_S, lane);
-            par_seg_scan<OpAdd>(CH, thr, c_CH, lane);
-            par_incl_scan<OpMax>(pi, c_par, lane);  /* the block each event is in ... */
-            par_incl_scan<OpMax>(oi, c_eout, lane); /* ... and its outline's end */
-            int32_t sum[PAR_K], mx[PAR_K], nt[PAR_K], own[PAR_K];
-#pragma unroll
-            for (int k = 0; k < PAR_K; ++k) {
-                const int32_t tok = ethr[k] ? l.P[ib + k] - l.P[max(ti[k], 0)] + 1 : 0;
-                if (ethr[k]) l.TOK[ib + k] = tok; /* read by the next level's threads */
-                sum[k] = tok;
-                mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
-                own[k] = tok - CH[k];
-                nt[k] = ethr[k] ? 1 : 0;
-            }
-            par_seg_scan<OpAdd>(sum, par, c_sum, lane);
-            par_seg_scan<OpMax>(mx, par, c_max, lane);
-            par_seg_scan<OpAdd>(nt, par, c_n, lane);
-#pragma unroll
-            for (int k = 0; k < PAR_K; ++k) {
-                const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
-                if (ethr[k]) {
-                    const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
-                    if (kk < n_e) {
-                        const int32_t t = l.X[pi[k] + 2 + 2 * kk] & 15;
-                        my_sub += t == C_SUB ? own[k] : 0;
-                        my_tri += t == C_TRI ? own[k] : 0;
-                    }
-                }
-                if (epar[k]) {
-                    const int32_t saved = sum[k] - mx[k];
-                    l.SAV[ib + k] = saved;
-                    my_mismatch = my_mismatch || nt[k] != n_e;
-                    my_saved += lev == 1 ? saved : 0;
-                }
-            }
-            c_thr = lane63(ti[PAR_K - 1]);
-            c_S = lane63(S[PAR_K - 1]);
-            c_CH = lane63(CH[PAR_K - 1]);
-            c_sum = lane63(sum[PAR_K - 1]);
-            c_max = lane63(mx[PAR_K - 1]);
-            c_n = lane63(nt[PAR_K - 1]);
-            c_par = lane63(pi[PAR_K - 1]);
-            c_eout = lane63(oi[PAR_K - 1]);
-        }
-        __syncthreads();
-    }
-    const int32_t n_sub = wave_sum32(my_sub), n_tri = wave_sum32(my_tri), saved = wave_sum32(my_saved);
-    const bool mismatch = __ballot(my_mismatch) != 0;
-    if (lane == 0) {
-        uint32_t fl = PARASON_FLAG_VALID;
-        if (mismatch) fl |= PARASON_FLAG_COUNT_MISMATCH;
-        if (n_blocks > 0) fl |= PARASON_FLAG_TRIGGERED;
-        write_row(a.out, r, len, len - saved, n_sub, n_tri, n_blocks, max_depth, -1, fl);
-    }
-    return true;
+    if (m <= WAVE) return par_eval<LENIENT, 1, true>(a, l, r, len, m, lane);
+    if (m <= 2 * WAVE) return par_eval<LENIENT, 2, true>(a, l, r, len, m, lane);
+    return par_eval<LENIENT, PAR_K, false>(a, l, r, len, m, lane);
 }
 
 /* One wave per row (a small batch).  A row par_row does not hold runs through
