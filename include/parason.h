@@ -409,6 +409,17 @@ int parason_fork(const parason_handle *h, const int32_t *tokens, const int64_t *
                  int64_t n_rows, uint32_t flags, const parason_fork_outputs *out, void *workspace,
                  size_t workspace_bytes, void *stream);
 
+/* parason_fork for a caller that has just sized its outputs: the call before on
+ * this stream with this workspace was parason_fork with the same handle, rows
+ * and flags, max_workers = ctx_capacity = 0 and the same worker_off, row_status
+ * and totals, and nothing has been written to any of these since.  The same
+ * results as parason_fork, without reading the rows' outlines a second time.
+ * (Nothing checks this: anything else in the workspace gives wrong results or
+ * writes out of bounds.) */
+int parason_fork_sized(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
+                       int64_t n_rows, uint32_t flags, const parason_fork_outputs *out, void *workspace,
+                       size_t workspace_bytes, void *stream);
+
 /* Join: rows as for parason_fork, worker_off[n_rows + 1] as parason_fork wrote
  * it, and the n_workers worker sequences (wtokens, wstarts, wlengths), each
  * beginning with its row (not checked) and continuing from its context. */
@@ -416,6 +427,14 @@ int parason_join(const parason_handle *h, const int32_t *tokens, const int64_t *
                  int64_t n_rows, const int64_t *worker_off, const int32_t *wtokens, const int64_t *wstarts,
                  const int32_t *wlengths, int64_t n_workers, uint32_t flags, const parason_join_outputs *out,
                  void *workspace, size_t workspace_bytes, void *stream);
+
+/* parason_join after a sizing call (parason_join with capacity = 0), as
+ * parason_fork_sized is to parason_fork: the same arguments, and the workspace,
+ * the outputs' starts, lengths and row_status as that call left them. */
+int parason_join_sized(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
+                       int64_t n_rows, const int64_t *worker_off, const int32_t *wtokens, const int64_t *wstarts,
+                       const int32_t *wlengths, int64_t n_workers, uint32_t flags, const parason_join_outputs *out,
+                       void *workspace, size_t workspace_bytes, void *stream);
 
 /* Static description of a status code. */
 const char *parason_strerror(int status);

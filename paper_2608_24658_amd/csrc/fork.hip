@@ -66,29 +66,11 @@ void launch_pack(const pk::PackScan<K> &ps, int64_t tiles, hipStream_t stream)
     hipLaunchKernelGGL(pk::pack_rows<K>, dim3((unsigned)tiles), dim3(pk::PACK_THREADS), 0, stream, ps);
 }
 
-}  // namespace
-
-extern "C" {
-
-int parason_fork_workspace_size(int64_t n_rows, size_t *bytes)
-{
-    if (!bytes) return PARASON_ERR_NULL;
-    if (n_rows < 0 || n_rows > INT32_MAX) return PARASON_ERR_SIZE;
-    *bytes = pack_layout(n_rows, 3).end;
-    return PARASON_OK;
-}
-
-int parason_join_workspace_size(int64_t n_rows, size_t *bytes)
-{
-    if (!bytes) return PARASON_ERR_NULL;
-    if (n_rows < 0 || n_rows > INT32_MAX) return PARASON_ERR_SIZE;
-    *bytes = pack_layout(n_rows, 1).end;
-    return PARASON_OK;
-}
-
-int parason_fork(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
+/* parason_fork; sized: the workspace holds what a call with the same rows and
+ * zero capacities left there, so the outlines are not walked again. */
+int fork_rows(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
                  int64_t n_rows, uint32_t flags, const parason_fork_outputs *out, void *workspace,
-                 size_t workspace_bytes, void *stream_ptr)
+                 size_t workspace_bytes, void *stream_ptr, bool sized)
 {
     if (!h || !out) return PARASON_ERR_NULL;
     if (n_rows < 0 || n_rows > INT32_MAX || out->max_workers < 0 || out->ctx_capacity < 0) return PARASON_ERR_SIZE;
@@ -148,7 +130,7 @@ int parason_fork(const parason_handle *h, const int32_t *tokens, const int64_t *
 
     const unsigned wave_blocks = (unsigned)std::min<int64_t>((n_rows + pk::OUTLINE_WAVES - 1) / pk::OUTLINE_WAVES,
                                                              (int64_t)cus * (32 / pk::OUTLINE_WAVES));
-    if (n_rows > 0) hipLaunchKernelGGL(pk::fork_outline<false>, dim3(wave_blocks), dim3(pk::OUTLINE_WAVES * pk::WAVE), 0, stream, fa);
+    if (n_rows > 0 && !sized) hipLaunchKernelGGL(pk::fork_outline<false>, dim3(wave_blocks), dim3(pk::OUTLINE_WAVES * pk::WAVE), 0, stream, fa);
     if (n_rows <= pk::FORK_SINGLE) {
         /* scans and records in one launch (at least one block: it writes the totals) */
         const unsigned blocks = (unsigned)std::max<int64_t>(1, (n_rows + pk::FORK_REC_WAVES - 1) / pk::FORK_REC_WAVES);
@@ -157,17 +139,19 @@ int parason_fork(const parason_handle *h, const int32_t *tokens, const int64_t *
         launch_pack(ps, L.tiles, stream);
         hipLaunchKernelGGL(pk::fork_outline<true>, dim3(wave_blocks), dim3(pk::OUTLINE_WAVES * pk::WAVE), 0, stream, fa);
     }
-    if (n_rows > 0) {
+    if (n_rows > 0 && out->ctx_capacity > 0) { /* without room for a token there is nothing to copy */
         const unsigned copy_blocks = (unsigned)(cus * COPY_BLOCKS_PER_CU); /* persistent, tiled over the output */
         hipLaunchKernelGGL(pk::fork_copy, dim3(copy_blocks), dim3(pk::PACK_THREADS), 0, stream, fa);
     }
     return hipGetLastError() == hipSuccess ? PARASON_OK : PARASON_ERR_HIP;
 }
 
-int parason_join(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
+/* parason_join; sized: the workspace and out hold what a call with the same
+ * arguments and no capacity left there, so the workers are not looked at again. */
+int join_rows(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
                  int64_t n_rows, const int64_t *worker_off, const int32_t *wtokens, const int64_t *wstarts,
                  const int32_t *wlengths, int64_t n_workers, uint32_t flags, const parason_join_outputs *out,
-                 void *workspace, size_t workspace_bytes, void *stream_ptr)
+                 void *workspace, size_t workspace_bytes, void *stream_ptr, bool sized)
 {
     if (!h || !out) return PARASON_ERR_NULL;
     if (n_rows < 0 || n_rows > INT32_MAX || n_workers < 0 || out->capacity < 0) return PARASON_ERR_SIZE;
@@ -219,17 +203,72 @@ int parason_join(const parason_handle *h, const int32_t *tokens, const int64_t *
     ps.report = 1;
     ps.over = (int32_t *)(ws + L.over);
 
-    if (n_rows > 0) hipLaunchKernelGGL(pk::join_size, dim3((unsigned)((n_rows + pk::JOIN_SIZE_THREADS - 1) / pk::JOIN_SIZE_THREADS)),
+    if (n_rows > 0 && !sized) hipLaunchKernelGGL(pk::join_size, dim3((unsigned)((n_rows + pk::JOIN_SIZE_THREADS - 1) / pk::JOIN_SIZE_THREADS)),
                                        dim3(pk::JOIN_SIZE_THREADS), 0, stream, ja);
-    const unsigned copy_blocks = n_rows > 0 ? (unsigned)(cus * COPY_BLOCKS_PER_CU) : 1u;
+    /* without room for a token only the offsets and totals are left to write */
+    const bool copies = n_rows > 0 && out->capacity > 0;
+    const unsigned copy_blocks = copies ? (unsigned)(cus * COPY_BLOCKS_PER_CU) : 1u;
     if (n_rows <= pk::JOIN_SINGLE) {
-        /* the scan inside the copy (no rows: one block, which writes the zero totals) */
+        /* the scan inside the copy */
         hipLaunchKernelGGL(pk::join_copy<true>, dim3(copy_blocks), dim3(pk::PACK_THREADS), 0, stream, ja, ps);
     } else {
         launch_pack(ps, L.tiles, stream);
-        hipLaunchKernelGGL(pk::join_copy<false>, dim3(copy_blocks), dim3(pk::PACK_THREADS), 0, stream, ja, ps);
+        if (copies)
+            hipLaunchKernelGGL(pk::join_copy<false>, dim3(copy_blocks), dim3(pk::PACK_THREADS), 0, stream, ja, ps);
     }
     return hipGetLastError() == hipSuccess ? PARASON_OK : PARASON_ERR_HIP;
+}
+
+}  // namespace
+
+extern "C" {
+
+int parason_fork_workspace_size(int64_t n_rows, size_t *bytes)
+{
+    if (!bytes) return PARASON_ERR_NULL;
+    if (n_rows < 0 || n_rows > INT32_MAX) return PARASON_ERR_SIZE;
+    *bytes = pack_layout(n_rows, 3).end;
+    return PARASON_OK;
+}
+
+int parason_join_workspace_size(int64_t n_rows, size_t *bytes)
+{
+    if (!bytes) return PARASON_ERR_NULL;
+    if (n_rows < 0 || n_rows > INT32_MAX) return PARASON_ERR_SIZE;
+    *bytes = pack_layout(n_rows, 1).end;
+    return PARASON_OK;
+}
+
+int parason_fork(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
+                 int64_t n_rows, uint32_t flags, const parason_fork_outputs *out, void *workspace,
+                 size_t workspace_bytes, void *stream_ptr)
+{
+    return fork_rows(h, tokens, starts, lengths, n_rows, flags, out, workspace, workspace_bytes, stream_ptr, false);
+}
+
+int parason_fork_sized(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
+                       int64_t n_rows, uint32_t flags, const parason_fork_outputs *out, void *workspace,
+                       size_t workspace_bytes, void *stream_ptr)
+{
+    return fork_rows(h, tokens, starts, lengths, n_rows, flags, out, workspace, workspace_bytes, stream_ptr, true);
+}
+
+int parason_join(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
+                 int64_t n_rows, const int64_t *worker_off, const int32_t *wtokens, const int64_t *wstarts,
+                 const int32_t *wlengths, int64_t n_workers, uint32_t flags, const parason_join_outputs *out,
+                 void *workspace, size_t workspace_bytes, void *stream_ptr)
+{
+    return join_rows(h, tokens, starts, lengths, n_rows, worker_off, wtokens, wstarts, wlengths, n_workers, flags, out,
+                     workspace, workspace_bytes, stream_ptr, false);
+}
+
+int parason_join_sized(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
+                       int64_t n_rows, const int64_t *worker_off, const int32_t *wtokens, const int64_t *wstarts,
+                       const int32_t *wlengths, int64_t n_workers, uint32_t flags, const parason_join_outputs *out,
+                       void *workspace, size_t workspace_bytes, void *stream_ptr)
+{
+    return join_rows(h, tokens, starts, lengths, n_rows, worker_off, wtokens, wstarts, wlengths, n_workers, flags, out,
+                     workspace, workspace_bytes, stream_ptr, true);
 }
 
 }  // extern "C"

@@ -44,7 +44,7 @@ MAX_OPEN_ENTRIES = 1 << 24
 EXPORTED = ("parason_create", "parason_workspace_size", "parason_run", "parason_run_timed", "parason_destroy",
             "parason_strerror", "parason_pg_workspace_size", "parason_pg_run", "parason_decode_init",
             "parason_decode_step", "parason_fork_workspace_size", "parason_join_workspace_size", "parason_fork",
-            "parason_join", "parason_read_probe", "parason_run_noalloc")
+            "parason_join", "parason_read_probe", "parason_run_noalloc", "parason_fork_sized", "parason_join_sized")
 
 FORK_SEED_ENTRY = 1 << 0
 JOIN_CLOSE_PARALLEL = 1 << 0
@@ -184,17 +184,19 @@ def lib():
         for name in ("parason_fork_workspace_size", "parason_join_workspace_size"):
             getattr(L, name).restype = ctypes.c_int
             getattr(L, name).argtypes = [ctypes.c_int64, ctypes.POINTER(ctypes.c_size_t)]
-        L.parason_fork.restype = ctypes.c_int
-        L.parason_fork.argtypes = [
-            ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_uint32,
-            ctypes.POINTER(ForkOutputs), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
-        ]
-        L.parason_join.restype = ctypes.c_int
-        L.parason_join.argtypes = [
-            ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p,
-            ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_uint32,
-            ctypes.POINTER(JoinOutputs), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
-        ]
+        for name in ("parason_fork", "parason_fork_sized"):
+            getattr(L, name).restype = ctypes.c_int
+            getattr(L, name).argtypes = [
+                ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_uint32,
+                ctypes.POINTER(ForkOutputs), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
+            ]
+        for name in ("parason_join", "parason_join_sized"):
+            getattr(L, name).restype = ctypes.c_int
+            getattr(L, name).argtypes = [
+                ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p,
+                ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_uint32,
+                ctypes.POINTER(JoinOutputs), ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
+            ]
         L.parason_read_probe.restype = ctypes.c_int
         L.parason_read_probe.argtypes = [ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p, ctypes.c_int64,
                                          ctypes.c_void_p]
@@ -340,15 +342,19 @@ class Parason:
         return logits
 
     def fork_raw(self, tokens_ptr, starts_ptr, lengths_ptr, n_rows, flags, out: ForkOutputs, ws_ptr, ws_bytes,
-                 stream) -> int:
-        return lib().parason_fork(self._h, tokens_ptr, starts_ptr, lengths_ptr, int(n_rows), int(flags),
-                                  ctypes.byref(out), ws_ptr, int(ws_bytes), stream)
+                 stream, sized: bool = False) -> int:
+        """parason_fork, or parason_fork_sized right after a sizing call."""
+        fn = lib().parason_fork_sized if sized else lib().parason_fork
+        return fn(self._h, tokens_ptr, starts_ptr, lengths_ptr, int(n_rows), int(flags), ctypes.byref(out), ws_ptr,
+                  int(ws_bytes), stream)
 
     def join_raw(self, tokens_ptr, starts_ptr, lengths_ptr, n_rows, worker_off_ptr, wtokens_ptr, wstarts_ptr,
-                 wlengths_ptr, n_workers, flags, out: JoinOutputs, ws_ptr, ws_bytes, stream) -> int:
-        return lib().parason_join(self._h, tokens_ptr, starts_ptr, lengths_ptr, int(n_rows), worker_off_ptr,
-                                  wtokens_ptr, wstarts_ptr, wlengths_ptr, int(n_workers), int(flags),
-                                  ctypes.byref(out), ws_ptr, int(ws_bytes), stream)
+                 wlengths_ptr, n_workers, flags, out: JoinOutputs, ws_ptr, ws_bytes, stream,
+                 sized: bool = False) -> int:
+        """parason_join, or parason_join_sized right after a sizing call."""
+        fn = lib().parason_join_sized if sized else lib().parason_join
+        return fn(self._h, tokens_ptr, starts_ptr, lengths_ptr, int(n_rows), worker_off_ptr, wtokens_ptr, wstarts_ptr,
+                  wlengths_ptr, int(n_workers), int(flags), ctypes.byref(out), ws_ptr, int(ws_bytes), stream)
 
     def fork(self, tokens, starts, lengths, seed: bool = True, max_workers=None, ctx_capacity=None) -> dict:
         """Worker contexts of a batch of rows (device tensors).  Without
@@ -365,7 +371,7 @@ class Parason:
         res = dict(worker_off=torch.empty(n + 1, **i64), row_status=torch.empty(max(n, 1), **i32)[:n],
                    totals=torch.empty(3, **i64))
 
-        def call(W, T):
+        def call(W, T, sized=False):
             res.update(ctx_tokens=torch.empty(max(T, 1), **i32)[:T], ctx_starts=torch.empty(max(W, 1), **i64)[:W],
                        ctx_lengths=torch.empty(max(W, 1), **i32)[:W], ctx_row=torch.empty(max(W, 1), **i32)[:W],
                        ctx_entry=torch.empty(max(W, 1), **i32)[:W], ctx_kind=torch.empty(max(W, 1), **i32)[:W])
@@ -373,16 +379,17 @@ class Parason:
                 "ctx_tokens", "ctx_starts", "ctx_lengths", "ctx_row", "ctx_entry", "ctx_kind", "worker_off",
                 "row_status", "totals")])
             rc = self.fork_raw(_ptr(tokens, starts), starts.data_ptr(), lengths.data_ptr(), n, flags, o,
-                               ws.data_ptr(), ws.numel(), stream)
+                               ws.data_ptr(), ws.numel(), stream, sized)
             if rc != OK:
                 raise ParasonError(rc, "parason_fork")
 
-        if max_workers is None or ctx_capacity is None:
+        sizing = max_workers is None or ctx_capacity is None
+        if sizing:
             call(0, 0)
-            W, T, _ = (int(x) for x in res["totals"].cpu())
+            W, T, _ = res["totals"].tolist()
             max_workers = W if max_workers is None else max_workers
             ctx_capacity = T if ctx_capacity is None else ctx_capacity
-        call(max_workers, ctx_capacity)
+        call(max_workers, ctx_capacity, sizing)
         return res
 
     def join(self, tokens, starts, lengths, worker_off, wtokens, wstarts, wlengths, close: bool = True,
@@ -401,20 +408,21 @@ class Parason:
                    row_status=torch.empty(max(n, 1), dtype=torch.int32, device=dev)[:n],
                    totals=torch.empty(2, dtype=torch.int64, device=dev))
 
-        def call(T):
+        def call(T, sized=False):
             res["tokens"] = torch.empty(max(T, 1), dtype=torch.int32, device=dev)[:T]
             o = JoinOutputs(int(T), *[res[k].data_ptr() for k in ("tokens", "starts", "lengths", "row_status",
                                                                    "totals")])
             rc = self.join_raw(_ptr(tokens, starts), starts.data_ptr(), lengths.data_ptr(), n,
                                worker_off.data_ptr(), _ptr(wtokens, wstarts), wstarts.data_ptr(),
-                               wlengths.data_ptr(), nw, flags, o, ws.data_ptr(), ws.numel(), stream)
+                               wlengths.data_ptr(), nw, flags, o, ws.data_ptr(), ws.numel(), stream, sized)
             if rc != OK:
                 raise ParasonError(rc, "parason_join")
 
-        if capacity is None:
+        sizing = capacity is None
+        if sizing:
             call(0)
             capacity = int(res["totals"][0].item())
-        call(capacity)
+        call(capacity, sizing)
         return res
 
     def run(self, tokens, starts, lengths, correct, out: dict | None = None, workspace=None, total_tokens=None,
