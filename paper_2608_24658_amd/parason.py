@@ -8,6 +8,7 @@ is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -132,7 +133,26 @@ INT_FIELDS = ("total", "latency", "n_subtask", "n_trial", "n_blocks", "max_depth
 FLOAT_FIELDS = ("reward", "r_subtask", "r_trial", "eta", "accel")
 OPTIONAL_FIELDS = ("r_subtask", "r_trial", "eta", "metrics", "accel", "saved")
 
+_OUT_FIELDS = INT_FIELDS + ("flags", "reward")  # required, in the order of Outputs
+
 _lib = None
+
+
+def _stream(device) -> int:
+    """The raw handle of torch's current stream on `device`.  (A Stream object
+    for every call would cost more than the rest of its arguments.)"""
+    import torch
+
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+def _outputs(out: dict) -> Outputs:
+    get = out.get
+    ptrs = [out[k].data_ptr() for k in _OUT_FIELDS]
+    for k in ("r_subtask", "r_trial", "eta", "metrics", "accel", "saved"):
+        t = get(k)
+        ptrs.append(t.data_ptr() if t is not None else None)
+    return Outputs(*ptrs)
 
 
 class ParasonError(RuntimeError):
@@ -281,33 +301,21 @@ class Parason:
     def run_raw(self, tokens_ptr, starts_ptr, lengths_ptr, correct_ptr, n_traj, out: dict, ws_ptr, ws_bytes,
                 stream) -> int:
         """Direct C-ABI call with raw device pointers; returns the status."""
-        o = Outputs()
-        for k in INT_FIELDS + ("flags", "reward"):
-            setattr(o, k, out[k].data_ptr())
-        for k in OPTIONAL_FIELDS:
-            setattr(o, k, out[k].data_ptr() if k in out and out[k] is not None else None)
+        o = _outputs(out)
         return lib().parason_run(self._h, tokens_ptr, starts_ptr, lengths_ptr, correct_ptr, int(n_traj),
                                  ctypes.byref(o), ws_ptr, int(ws_bytes), stream)
 
     def run_noalloc_raw(self, tokens_ptr, starts_ptr, lengths_ptr, correct_ptr, n_traj, total_tokens, out: dict,
                         stream) -> int:
         """parason_run_noalloc (no workspace: the library's static scratch); returns the status."""
-        o = Outputs()
-        for k in INT_FIELDS + ("flags", "reward"):
-            setattr(o, k, out[k].data_ptr())
-        for k in OPTIONAL_FIELDS:
-            setattr(o, k, out[k].data_ptr() if k in out and out[k] is not None else None)
+        o = _outputs(out)
         return lib().parason_run_noalloc(self._h, tokens_ptr, starts_ptr, lengths_ptr, correct_ptr, int(n_traj),
                                          int(total_tokens), ctypes.byref(o), stream)
 
     def run_timed_raw(self, tokens_ptr, starts_ptr, lengths_ptr, correct_ptr, n_traj, out: dict, ws_ptr, ws_bytes,
                       stream, scan_events) -> int:
         """parason_run_timed: scan_events is a ctypes array of two hipEvent_t (or None)."""
-        o = Outputs()
-        for k in INT_FIELDS + ("flags", "reward"):
-            setattr(o, k, out[k].data_ptr())
-        for k in OPTIONAL_FIELDS:
-            setattr(o, k, out[k].data_ptr() if k in out and out[k] is not None else None)
+        o = _outputs(out)
         ev = ctypes.cast(scan_events, ctypes.c_void_p) if scan_events is not None else None
         return lib().parason_run_timed(self._h, tokens_ptr, starts_ptr, lengths_ptr, correct_ptr, int(n_traj),
                                        ctypes.byref(o), ws_ptr, int(ws_bytes), stream, ev)
@@ -324,8 +332,10 @@ class Parason:
         along the vocabulary) in place, on the current stream."""
         import torch
 
-        dtypes = {torch.float32: DTYPE_F32, torch.bfloat16: DTYPE_BF16, torch.float16: DTYPE_F16}
-        if logits.dtype not in dtypes or logits.dim() != 2 or logits.stride(1) != 1 or not logits.is_cuda:
+        dtype = logits.dtype
+        code = (DTYPE_BF16 if dtype is torch.bfloat16 else DTYPE_F32 if dtype is torch.float32
+                else DTYPE_F16 if dtype is torch.float16 else None)
+        if code is None or logits.dim() != 2 or logits.stride(1) != 1 or not logits.is_cuda:
             raise TypeError("logits must be a [batch, vocab] float32/bfloat16/float16 device tensor, unit stride")
         batch, vocab = logits.shape
         if states.dtype != torch.uint8 or states.numel() != batch * DECODE_STATE_BYTES or not states.is_contiguous():
@@ -333,10 +343,9 @@ class Parason:
         if tokens is not None and (tokens.dtype != torch.int32 or tokens.numel() != batch
                                    or not tokens.is_contiguous()):
             raise TypeError("tokens must be a contiguous int32 device tensor of batch entries")
-        stream = torch.cuda.current_stream(logits.device).cuda_stream
-        rc = self.decode_step_raw(states.data_ptr(), tokens.data_ptr() if tokens is not None else None, batch,
-                                  logits.data_ptr(), vocab, logits.stride(0) if batch > 1 else vocab,
-                                  dtypes[logits.dtype], eos_id, stream)
+        rc = (_lib or lib()).parason_decode_step(
+            self._h, states.data_ptr(), tokens.data_ptr() if tokens is not None else None, batch, logits.data_ptr(),
+            vocab, logits.stride(0) if batch > 1 else vocab, code, int(eos_id), _stream(logits.device))
         if rc != OK:
             raise ParasonError(rc, "parason_decode_step")
         return logits
@@ -362,24 +371,26 @@ class Parason:
         import torch
 
         _check_rows(tokens, starts, lengths)
-        dev, n = starts.device, int(starts.numel())
+        dev, n = starts.device, starts.numel()
         flags = FORK_SEED_ENTRY if seed else 0
         ws = torch.empty(_ws_size("parason_fork_workspace_size", n), dtype=torch.uint8, device=dev)
-        stream = torch.cuda.current_stream(dev).cuda_stream
-        i64 = dict(dtype=torch.int64, device=dev)
-        i32 = dict(dtype=torch.int32, device=dev)
-        res = dict(worker_off=torch.empty(n + 1, **i64), row_status=torch.empty(max(n, 1), **i32)[:n],
-                   totals=torch.empty(3, **i64))
+        stream = _stream(dev)
+        i64, i32 = starts.new_empty, lengths.new_empty  # int64, int32 on the rows' device
+        worker_off, row_status, totals = i64(n + 1), i32(n), i64(3)
+        rows = (_ptr(tokens, starts), starts.data_ptr(), lengths.data_ptr(), n, flags)
+        res = dict(worker_off=worker_off, row_status=row_status, totals=totals)
+        tail = (worker_off.data_ptr(), row_status.data_ptr() if n else None, totals.data_ptr())
 
         def call(W, T, sized=False):
-            res.update(ctx_tokens=torch.empty(max(T, 1), **i32)[:T], ctx_starts=torch.empty(max(W, 1), **i64)[:W],
-                       ctx_lengths=torch.empty(max(W, 1), **i32)[:W], ctx_row=torch.empty(max(W, 1), **i32)[:W],
-                       ctx_entry=torch.empty(max(W, 1), **i32)[:W], ctx_kind=torch.empty(max(W, 1), **i32)[:W])
-            o = ForkOutputs(int(W), int(T), *[res[k].data_ptr() for k in (
-                "ctx_tokens", "ctx_starts", "ctx_lengths", "ctx_row", "ctx_entry", "ctx_kind", "worker_off",
-                "row_status", "totals")])
-            rc = self.fork_raw(_ptr(tokens, starts), starts.data_ptr(), lengths.data_ptr(), n, flags, o,
-                               ws.data_ptr(), ws.numel(), stream, sized)
+            if W or T:
+                res.update(ctx_tokens=i32(T), ctx_starts=i64(W), ctx_lengths=i32(W), ctx_row=i32(W), ctx_entry=i32(W),
+                           ctx_kind=i32(W))
+            elif sized or not sizing:
+                res.update(ctx_tokens=i32(0), ctx_starts=i64(0), ctx_lengths=i32(0), ctx_row=i32(0), ctx_entry=i32(0),
+                           ctx_kind=i32(0))
+            ctx = [res[k].data_ptr() or None for k in (
+                "ctx_tokens", "ctx_starts", "ctx_lengths", "ctx_row", "ctx_entry", "ctx_kind")] if W or T else [None] * 6
+            rc = self.fork_raw(*rows, ForkOutputs(W, T, *ctx, *tail), ws.data_ptr(), ws.numel(), stream, sized)
             if rc != OK:
                 raise ParasonError(rc, "parason_fork")
 
@@ -389,7 +400,7 @@ class Parason:
             W, T, _ = res["totals"].tolist()
             max_workers = W if max_workers is None else max_workers
             ctx_capacity = T if ctx_capacity is None else ctx_capacity
-        call(max_workers, ctx_capacity, sizing)
+        call(int(max_workers), int(ctx_capacity), sizing)
         return res
 
     def join(self, tokens, starts, lengths, worker_off, wtokens, wstarts, wlengths, close: bool = True,
@@ -399,30 +410,29 @@ class Parason:
 
         _check_rows(tokens, starts, lengths)
         _check_rows(wtokens, wstarts, wlengths)
-        dev, n, nw = starts.device, int(starts.numel()), int(wstarts.numel())
+        dev, n, nw = starts.device, starts.numel(), wstarts.numel()
         flags = (JOIN_CLOSE_PARALLEL if close else 0) | (JOIN_APPEND_ONLY if append_only else 0)
         ws = torch.empty(_ws_size("parason_join_workspace_size", n), dtype=torch.uint8, device=dev)
-        stream = torch.cuda.current_stream(dev).cuda_stream
-        res = dict(starts=torch.empty(n + 1, dtype=torch.int64, device=dev),
-                   lengths=torch.empty(max(n, 1), dtype=torch.int32, device=dev)[:n],
-                   row_status=torch.empty(max(n, 1), dtype=torch.int32, device=dev)[:n],
-                   totals=torch.empty(2, dtype=torch.int64, device=dev))
+        stream = _stream(dev)
+        i64, i32 = starts.new_empty, lengths.new_empty  # int64, int32 on the rows' device
+        res = dict(starts=i64(n + 1), lengths=i32(n), row_status=i32(n), totals=i64(2))
+        args = (_ptr(tokens, starts), starts.data_ptr(), lengths.data_ptr(), n, worker_off.data_ptr(),
+                _ptr(wtokens, wstarts), wstarts.data_ptr(), wlengths.data_ptr(), nw, flags)
+        tail = [res[k].data_ptr() or None for k in ("starts", "lengths", "row_status", "totals")]
 
         def call(T, sized=False):
-            res["tokens"] = torch.empty(max(T, 1), dtype=torch.int32, device=dev)[:T]
-            o = JoinOutputs(int(T), *[res[k].data_ptr() for k in ("tokens", "starts", "lengths", "row_status",
-                                                                   "totals")])
-            rc = self.join_raw(_ptr(tokens, starts), starts.data_ptr(), lengths.data_ptr(), n,
-                               worker_off.data_ptr(), _ptr(wtokens, wstarts), wstarts.data_ptr(),
-                               wlengths.data_ptr(), nw, flags, o, ws.data_ptr(), ws.numel(), stream, sized)
+            if T or sized or not sizing:
+                res["tokens"] = i32(T)
+            o = JoinOutputs(T, res["tokens"].data_ptr() if T else None, *tail)
+            rc = self.join_raw(*args, o, ws.data_ptr(), ws.numel(), stream, sized)
             if rc != OK:
                 raise ParasonError(rc, "parason_join")
 
         sizing = capacity is None
         if sizing:
             call(0)
-            capacity = int(res["totals"][0].item())
-        call(capacity, sizing)
+            capacity = res["totals"].tolist()[0]
+        call(int(capacity), sizing)
         return res
 
     def run(self, tokens, starts, lengths, correct, out: dict | None = None, workspace=None, total_tokens=None,
@@ -443,7 +453,7 @@ class Parason:
             if total_tokens is None:
                 total_tokens = int(lengths.to(torch.int64).clamp_min(0).sum().item()) if n else 0
             workspace = self.alloc_workspace(n, total_tokens, tokens.device)
-        stream = torch.cuda.current_stream(tokens.device).cuda_stream
+        stream = _stream(tokens.device)
         tok_ptr = tokens.data_ptr() if tokens.numel() else starts.data_ptr()
         rc = self.run_raw(tok_ptr, starts.data_ptr(), lengths.data_ptr(), correct.data_ptr(), n, out,
                           workspace.data_ptr(), workspace.numel(), stream)
@@ -471,6 +481,7 @@ def _ptr(tokens, fallback):
     return tokens.data_ptr() if tokens.numel() else fallback.data_ptr()
 
 
+@functools.lru_cache(maxsize=256)
 def _ws_size(name: str, n: int) -> int:
     b = ctypes.c_size_t()
     rc = getattr(lib(), name)(int(n), ctypes.byref(b))
@@ -485,7 +496,7 @@ def decode_init(batch: int, device, states=None):
 
     if states is None:
         states = torch.empty(int(batch) * DECODE_STATE_BYTES, dtype=torch.uint8, device=device)
-    stream = torch.cuda.current_stream(states.device).cuda_stream
+    stream = _stream(states.device)
     rc = lib().parason_decode_init(states.data_ptr(), int(batch), stream)
     if rc != OK:
         raise ParasonError(rc, "parason_decode_init")
@@ -500,11 +511,7 @@ def decode_fields(states):
 
 
 def pg_workspace_size(n_traj: int) -> int:
-    b = ctypes.c_size_t()
-    rc = lib().parason_pg_workspace_size(int(n_traj), ctypes.byref(b))
-    if rc != OK:
-        raise ParasonError(rc, "parason_pg_workspace_size")
-    return b.value
+    return _ws_size("parason_pg_workspace_size", int(n_traj))
 
 
 def pg_run_raw(cfg: PgConfig, reward_ptr, logp_ptr, old_ptr, starts_ptr, lengths_ptr, n_traj, adv_ptr, grad_ptr,
@@ -527,13 +534,13 @@ def pg_run(reward, logp, logp_old, starts, lengths, group_size=8, clip_low=0.2, 
             raise TypeError("expected contiguous %s device tensors" % dt)
     dev = logp.device
     cfg = PgConfig(int(group_size), float(clip_low), float(clip_high))
-    adv = torch.empty(n, dtype=torch.float32, device=dev)
+    adv = reward.new_empty(n)
     if grad is None:
         grad = torch.empty_like(logp)
     stats = torch.empty(len(PG_STATS), dtype=torch.float64, device=dev)
     if workspace is None:
         workspace = torch.empty(pg_workspace_size(n), dtype=torch.uint8, device=dev)
-    stream = torch.cuda.current_stream(dev).cuda_stream
+    stream = _stream(dev)
     rc = pg_run_raw(cfg, reward.data_ptr(), logp.data_ptr(), logp_old.data_ptr(), starts.data_ptr(),
                     lengths.data_ptr(), n, adv.data_ptr(), grad.data_ptr(), stats.data_ptr(), workspace.data_ptr(),
                     workspace.numel(), stream)
