@@ -633,10 +633,22 @@ __global__ void __launch_bounds__(FORK_REC_THREADS) fork_records(ForkArgs a, Pac
 #endif
 constexpr int WV = PARASON_COPY_WV;      /* 16-byte vectors per lane per wave step */
 constexpr int64_t WTILE = 4 * WV * WAVE; /* output positions per wave step */
+constexpr int64_t WTILE_MIN = 4 * WAVE;  /* the least: a vector, or four dwords, per lane */
 constexpr int TAIL_U = 16;               /* elements per lane per step of a context's tail */
 constexpr int COPY_WAVES = PACK_THREADS / WAVE;
 
 typedef int v4i_t __attribute__((ext_vector_type(4)));
+
+/* Positions per wave step of a copy of n positions by n_waves: WTILE, or
+ * WTILE_MIN where that still leaves every wave at most one step, so that a
+ * small copy is spread over the waves there are (the contexts of 48 rows of
+ * 12,000 tokens, 260 tiles of 1,024 for 8,192 waves: 15.5 us, and 11.3 in tiles
+ * of 256).  Beyond that the longer steps win: 512 rows of 26,800 tokens 34.5 us a
+ * call, 37.6 in tiles of 512. */
+__device__ __forceinline__ int64_t copy_tile(int64_t n, int64_t n_waves)
+{
+    return n <= WTILE_MIN * n_waves ? WTILE_MIN : WTILE;
+}
 
 /* 16 bytes from a 4-byte aligned address (global memory takes unaligned
  * 16-byte loads at dword granularity). */
@@ -783,9 +795,9 @@ __global__ void __launch_bounds__(PACK_THREADS) fork_copy(ForkArgs a)
     const int wv = threadIdx.x / WAVE;
     if (a.over[0]) return;
     const int64_t UT = a.unit_off[a.n];
-    const int64_t NW = (int64_t)gridDim.x * COPY_WAVES;
-    for (int64_t t = (int64_t)blockIdx.x * COPY_WAVES + wv; t * WTILE < UT; t += NW) {
-        const int64_t lo = t * WTILE, hi = min(lo + WTILE, UT);
+    const int64_t NW = (int64_t)gridDim.x * COPY_WAVES, tile = copy_tile(UT, NW);
+    for (int64_t t = (int64_t)blockIdx.x * COPY_WAVES + wv; t * tile < UT; t += NW) {
+        const int64_t lo = t * tile, hi = min(lo + tile, UT);
         for (int64_t r = wave_find(a.unit_off, a.n, lo, lane); r < a.n; ++r) {
             /* the row's records in one round of loads, before any branch */
             const int64_t uo = a.unit_off[r], ue = a.unit_off[r + 1];
@@ -974,9 +986,9 @@ __global__ void __launch_bounds__(PACK_THREADS) join_copy(JoinArgs a, PackScan<1
         return;
     }
     const int64_t T = out_starts[a.n];
-    const int64_t NW = (int64_t)gridDim.x * COPY_WAVES;
-    for (int64_t t = (int64_t)blockIdx.x * COPY_WAVES + wv; t * WTILE < T; t += NW) {
-        const int64_t lo = t * WTILE, hi = min(lo + WTILE, T);
+    const int64_t NW = (int64_t)gridDim.x * COPY_WAVES, tile = copy_tile(T, NW);
+    for (int64_t t = (int64_t)blockIdx.x * COPY_WAVES + wv; t * tile < T; t += NW) {
+        const int64_t lo = t * tile, hi = min(lo + tile, T);
         for (int64_t i = wave_find(out_starts, a.n, lo, lane); i < a.n; ++i) {
             /* the row's records in one round of loads, before any branch */
             const int64_t os = out_starts[i], len = a.out_len64[i];
