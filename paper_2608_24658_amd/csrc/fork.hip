@@ -134,7 +134,10 @@ int fork_rows(const parason_handle *h, const int32_t *tokens, const int64_t *sta
     if (n_rows <= pk::FORK_SINGLE) {
         /* scans and records in one launch (at least one block: it writes the totals) */
         const unsigned blocks = (unsigned)std::max<int64_t>(1, (n_rows + pk::FORK_REC_WAVES - 1) / pk::FORK_REC_WAVES);
-        hipLaunchKernelGGL(pk::fork_records, dim3(blocks), dim3(pk::FORK_REC_THREADS), 0, stream, fa, ps);
+        if (n_rows <= pk::FORK_REC_FEW * pk::FORK_REC_THREADS)
+            hipLaunchKernelGGL(pk::fork_records<pk::FORK_REC_FEW>, dim3(blocks), dim3(pk::FORK_REC_THREADS), 0, stream, fa, ps);
+        else
+            hipLaunchKernelGGL(pk::fork_records<pk::FORK_REC_MANY>, dim3(blocks), dim3(pk::FORK_REC_THREADS), 0, stream, fa, ps);
     } else {
         launch_pack(ps, L.tiles, stream);
         hipLaunchKernelGGL(pk::fork_outline<true>, dim3(wave_blocks), dim3(pk::OUTLINE_WAVES * pk::WAVE), 0, stream, fa);

@@ -547,7 +547,8 @@ __global__ void __launch_bounds__(OUTLINE_WAVES * WAVE) fork_outline(ForkArgs a)
         outline_row<WRITE>(a, i, WRITE ? a.worker_off[i] : 0, WRITE ? a.tok_off[i] : 0, ev_all[wv], lane);
 }
 
-/* Up to FORK_SINGLE rows: the scans of the three counts and the worker
+/* Up to FORK_SINGLE rows (2,000 rows of 3,000 tokens: 39.7 us a call with
+ * pack_single and fork_outline<true>, 36.3 so; at 4,000 rows both take 60): the scans of the three counts and the worker
  * records in one launch instead of pack_single and fork_outline<true>.  Every
  * block scans the counts of all rows (24 bytes per row, read from L2; each
  * thread FORK_REC_RPT consecutive rows), then its FORK_REC_WAVES waves write
@@ -555,11 +556,13 @@ __global__ void __launch_bounds__(OUTLINE_WAVES * WAVE) fork_outline(ForkArgs a)
  * row in the scan writes its offsets (in the row's own block); the block
  * holding the last row writes the totals and the capacity flag, which every
  * block computes alike. */
-constexpr int FORK_SINGLE = 1024;
+constexpr int FORK_SINGLE = 2048;
 constexpr int FORK_REC_WAVES = 8; /* 16: 1.3 us slower at 1,024 rows; 4: as fast */
 constexpr int FORK_REC_THREADS = FORK_REC_WAVES * WAVE;
-constexpr int FORK_REC_RPT = FORK_SINGLE / FORK_REC_THREADS;
+constexpr int FORK_REC_FEW = 2; /* rows per thread of the scan up to FORK_REC_FEW * FORK_REC_THREADS rows ... */
+constexpr int FORK_REC_MANY = FORK_SINGLE / FORK_REC_THREADS; /* ... and up to FORK_SINGLE */
 
+template <int FORK_REC_RPT>
 __global__ void __launch_bounds__(FORK_REC_THREADS) fork_records(ForkArgs a, PackScan<3> ps)
 {
     __shared__ int64_t part[3][FORK_REC_WAVES];

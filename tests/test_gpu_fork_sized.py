@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 TAGS = S.CONTIGUOUS_TAGS
 
 
-@pytest.mark.parametrize("n,forks", [(1, True), (48, True), (1024, True), (1025, True), (4104, True), (64, False)])
+@pytest.mark.parametrize("n,forks", [(1, True), (48, True), (1024, True), (1025, True), (2048, True), (2049, True), (4104, True), (64, False)])
 def test_sized_by_the_call(n, forks):
     P = S.make_params(dict(seed=n, len_kind=0, len_lo=300, len_hi=900))
     tok, st, ln, _ = S.host_batch(P, n)
