@@ -53,8 +53,8 @@ inline int cu_count()
 
 inline bool is_finite(double x) { return std::isfinite(x); }
 
-/* The segment plan of n >= 1 rows (two launches on `stream` for up to PLAN_TWO
- * tiles, one for a single tile, else three; defined with the plan kernels):
+/* The segment plan of n >= 1 rows (one launch on `stream` for up to PLAN_ONE
+ * tiles, two for up to PLAN_TWO, else three; defined with the plan kernels):
  * seg_off[0 .. n] and, when given, mode[0 .. n) as the token scan uses them,
  * counters[0 .. 4) cleared.  scratch holds plan_scratch(n) bytes.  With len_sum
  * (every tile's token count) the caller has filled in the tiles' segment counts

@@ -54,6 +54,7 @@ static_assert(POOL_PER_SEG % 4 == 0, "stored events are read 16 bytes at a time"
 constexpr int PLAN_TILE = 1024;          /* rows per plan tile */
 constexpr int PLAN_THREADS = 256;
 constexpr int PLAN_RPT = PLAN_TILE / PLAN_THREADS;
+constexpr int64_t PLAN_ONE = 16;   /* tiles planned in one launch */
 constexpr int64_t PLAN_TWO = 4096; /* tiles up to which plan_rows adds up the tiles before its own */
 constexpr int ROWS_PER_THREAD = 16; /* of the batch reductions of many rows */
 #ifndef PARASON_FAST_DEPTH

@@ -238,7 +238,12 @@ void abi::launch_plan(const int64_t *starts, const int32_t *lengths, int64_t n, 
     const int64_t tiles = plan_tile_count(n);
     int64_t *tile_sum = (int64_t *)scratch, *tile_off = tile_sum + tiles;
     const dim3 grid((unsigned)tiles), block(pk::PLAN_THREADS);
-    if (tiles > 1 && !len_sum)
+    if (tiles <= pk::PLAN_ONE && !len_sum) {
+        hipLaunchKernelGGL(pk::plan_direct, grid, dim3(pk::PLAN_TILE), 0, stream, starts, lengths, n, mis, seg_off, mode,
+                           counters);
+        return;
+    }
+    if (!len_sum)
         hipLaunchKernelGGL(pk::plan_tiles, grid, block, 0, stream, starts, lengths, n, mis, tile_sum);
     if (tiles > pk::PLAN_TWO) {
         hipLaunchKernelGGL(pk::plan_top, dim3(1), dim3(1024), 0, stream, tile_sum, tiles, tile_off, seg_off, n, counters);

@@ -3,8 +3,8 @@
  *
  * Data flow of one parason_run (all on the caller's stream):
  *
- *   plan_tiles / plan_rows  (one plan_rows block for one tile; plan_top between
- *        them for more than PLAN_TWO tiles)
+ *   plan_direct, or plan_tiles / plan_rows  (more than PLAN_ONE tiles of rows;
+ *        plan_top between them for more than PLAN_TWO)
  *        Each row is cut into segments of SEG_VEC 16-byte vectors, starting at
  *        the 128-byte line that holds its first token.  An exclusive scan over
  *        the rows gives seg_off[i] (first segment of row i) and the segment count
@@ -174,6 +174,41 @@ __global__ void __launch_bounds__(PLAN_THREADS) plan_rows(const int64_t *__restr
         s = block_sum(s, part);
         if (t == 0) n_tokens[0] = s;
     }
+}
+
+/* The plan of up to PLAN_ONE tiles in one launch: each block, one row per
+ * thread, adds up the rows before its tile itself, from the rows' records in
+ * the caches (a call on 2,056 rows of 700 tokens 26.9 us with plan_tiles and
+ * plan_rows, 24.1 so; 8,192 rows of 3,500 58.4 and 56.3, 16,384 of 500 56.4 and
+ * 55.6). */
+__global__ void __launch_bounds__(PLAN_TILE) plan_direct(const int64_t *__restrict__ starts,
+                                                         const int32_t *__restrict__ lengths, int64_t n, int64_t mis,
+                                                         int64_t *__restrict__ seg_off, uint8_t *__restrict__ mode,
+                                                         int32_t *__restrict__ counters)
+{
+    constexpr int NW = PLAN_TILE / WAVE;
+    __shared__ int64_t part[2][NW];
+    const int t = (int)threadIdx.x, wv = t / WAVE;
+    const int64_t r = (int64_t)blockIdx.x * PLAN_TILE + t, q = min(r, n - 1);
+    const int64_t c_own = row_segments(starts[q], lengths[q], mis), c = r < n ? c_own : 0;
+    int64_t before = 0;
+#pragma unroll 4
+    for (int64_t b = t; b < (int64_t)blockIdx.x * PLAN_TILE; b += PLAN_TILE) before += row_segments(starts[b], lengths[b], mis);
+    const int64_t inc = wave_inclusive_scan(c);
+    before = wave_inclusive_scan(before);
+    if ((t & (WAVE - 1)) == WAVE - 1) {
+        part[0][wv] = inc;
+        part[1][wv] = before;
+    }
+    __syncthreads();
+    int64_t off = inc - c;
+    for (int w = 0; w < NW; ++w) off += part[1][w] + (w < wv ? part[0][w] : 0);
+    if (r < n) {
+        seg_off[r] = off;
+        mode[r] = 0;
+        if (r == n - 1) seg_off[n] = off + c;
+    }
+    if (blockIdx.x == 0 && t < 4) counters[t] = 0;
 }
 
 /* ------------------------------------------------------------------ automaton */
