@@ -130,7 +130,10 @@ int fork_rows(const parason_handle *h, const int32_t *tokens, const int64_t *sta
 
     const unsigned wave_blocks = (unsigned)std::min<int64_t>((n_rows + pk::OUTLINE_WAVES - 1) / pk::OUTLINE_WAVES,
                                                              (int64_t)cus * (32 / pk::OUTLINE_WAVES));
-    if (n_rows > 0 && !sized) hipLaunchKernelGGL(pk::fork_outline<false>, dim3(wave_blocks), dim3(pk::OUTLINE_WAVES * pk::WAVE), 0, stream, fa);
+    if (n_rows > pk::WIN_ROWS && !sized)
+        hipLaunchKernelGGL(pk::fork_outline<false>, dim3(wave_blocks), dim3(pk::OUTLINE_WAVES * pk::WAVE), 0, stream, fa);
+    else if (n_rows > 0 && !sized)
+        hipLaunchKernelGGL(pk::fork_window, dim3((unsigned)n_rows), dim3(pk::WIN_THREADS), 0, stream, fa);
     if (n_rows <= pk::FORK_SINGLE) {
         /* scans and records in one launch (at least one block: it writes the totals) */
         const unsigned blocks = (unsigned)std::max<int64_t>(1, (n_rows + pk::FORK_REC_WAVES - 1) / pk::FORK_REC_WAVES);
