@@ -431,8 +431,7 @@ __device__ __forceinline__ void block_plan(const int64_t *starts, const int32_t 
 
 /* ------------------------------------------------------------------ batch reductions */
 
-/* Deterministic sums: the block combines its threads in a fixed pairwise tree,
- * and one block adds the block partials in block order. */
+/* Deterministic sums: the block combines its threads in a fixed pairwise tree. */
 constexpr int RED_THREADS = 256;
 
 template <class T, int K>
@@ -452,24 +451,6 @@ __device__ __forceinline__ void block_tree_sum(T (&v)[K], T *lds /* [K][RED_THRE
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = lds[k * RED_THREADS];
     __syncthreads();
-}
-
-/* Sum of part[0 .. m) (each of K values) in index order by one block. */
-template <class T, int K>
-__device__ __forceinline__ void sum_partials(const T *part, int64_t m, T (&out)[K], T *lds)
-{
-    T v[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = 0;
-    const int64_t per = (m + RED_THREADS - 1) / RED_THREADS;
-    const int64_t b0 = threadIdx.x * per, b1 = min(m, b0 + per);
-    for (int64_t b = b0; b < b1; ++b) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) v[k] += part[b * K + k];
-    }
-    block_tree_sum<T, K>(v, lds);
-#pragma unroll
-    for (int k = 0; k < K; ++k) out[k] = v[k];
 }
 
 } /* namespace pk */

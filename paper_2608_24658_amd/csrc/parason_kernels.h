@@ -750,10 +750,6 @@ __device__ __forceinline__ bool class_allowed(uint32_t st, int32_t c)
 }
 __device__ __forceinline__ bool text_allowed(uint32_t st) { return (TEXT_STATES >> st) & 1u; }
 
-/* Inclusive prefix sum and running maximum over the wave's lanes. */
-__device__ __forceinline__ int32_t wave_incl_scan32(int32_t v, int lane) { return dpp_incl_scan<OpAdd>(v, lane); }
-__device__ __forceinline__ int32_t wave_incl_max32(int32_t v, int lane) { return dpp_incl_scan<OpMax>(v, lane); }
-
 /* Reductions over the wave, the result in every lane. */
 __device__ __forceinline__ int32_t wave_sum32(int32_t v)
 {
@@ -1838,7 +1834,6 @@ struct RowCollect {
 
 constexpr int EVL = 1024;                 /* LDS events per wave */
 constexpr int SCAN_WAVES = 4;             /* waves per scan block */
-constexpr int SCAN_THREADS = WAVE * SCAN_WAVES;
 /* Waves per block of a scan that plans in LDS.  Every block plans the whole
  * batch before its first load, so half as many blocks of twice the size plan
  * it half as often and are all dispatched sooner (a 2,048-row step: 2.7 us
