@@ -73,7 +73,10 @@ int parason_decode_step(const parason_handle *h, parason_decode_state *states, c
     da.lenient = (h->cfg.flags & PARASON_CFG_LENIENT_GAPS) != 0;
     const int64_t max_blocks = (int64_t)cus * DECODE_BLOCKS_PER_CU;
     const unsigned blocks = (unsigned)(batch < max_blocks ? batch : max_blocks);
-    pk::decode_step<<<dim3(blocks), dim3(pk::DECODE_THREADS), 0, stream>>>(da);
+    if (batch <= (int64_t)cus * pk::DECODE_WIDE_ROWS_PER_CU)
+        pk::decode_step<pk::DECODE_WIDE_THREADS><<<dim3(blocks), dim3(pk::DECODE_WIDE_THREADS), 0, stream>>>(da);
+    else
+        pk::decode_step<pk::DECODE_THREADS><<<dim3(blocks), dim3(pk::DECODE_THREADS), 0, stream>>>(da);
     return hipGetLastError() == hipSuccess ? PARASON_OK : PARASON_ERR_HIP;
 }
 

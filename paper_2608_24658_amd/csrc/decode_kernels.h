@@ -140,15 +140,18 @@ __device__ __forceinline__ void store_ninf(char *row, int64_t i, const DecodeArg
 /* Threads of a row's block.  Most rows take a handful of stores, but a row that
  * forbids Text is rewritten by its block alone, and the step lasts as long as
  * that block: 16 rows of 151,936 float32 logits 14.8 us at 256 threads, 11.2 at
- * 512; eight draft steps of 256 rows 59.2 and 50.5; 1,000 rows of 50,257 float32
- * logits, all of them rewritten, 43.5 and 44.5. */
-#ifndef PARASON_DECODE_THREADS
-#define PARASON_DECODE_THREADS 512
-#endif
-constexpr int DECODE_THREADS = PARASON_DECODE_THREADS;
+ * 512; eight draft steps of 256 rows 59.2 and 50.5, four of 512 rows 35.2 and
+ * 28.3.  Beyond two rows per CU the rows fill the chip either way and dispatching
+ * twice the waves costs more: 1,024 rows of 151,936 bf16 logits, all rewritten,
+ * 48.8 us at 256 threads and 49.6 at 512, their 64 draft steps replayed as a
+ * graph 4.6 and 5.9 us each. */
+constexpr int DECODE_THREADS = 256;
+constexpr int DECODE_WIDE_THREADS = 512;
+constexpr int DECODE_WIDE_ROWS_PER_CU = 2;
 
 /* One block per row, grid-stride over the rows. */
-__global__ void __launch_bounds__(DECODE_THREADS) decode_step(DecodeArgs a)
+template <int NT>
+__global__ void __launch_bounds__(NT) decode_step(DecodeArgs a)
 {
     __shared__ uint32_t allow_s;
     for (int64_t r = blockIdx.x; r < a.batch; r += gridDim.x) {
@@ -203,14 +206,14 @@ __global__ void __launch_bounds__(DECODE_THREADS) decode_step(DecodeArgs a)
 #endif
         constexpr int U = PARASON_DECODE_UNROLL;
         int32_t v = (int32_t)threadIdx.x;
-        for (; v + (U - 1) * DECODE_THREADS < nv; v += U * DECODE_THREADS) {
+        for (; v + (U - 1) * NT < nv; v += U * NT) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int32_t vv = v + u * DECODE_THREADS;
+                const int32_t vv = v + u * NT;
                 if (vv != kv0 && vv != kv1 && vv != kv2) vrow[vv] = ninf4;
             }
         }
-        for (; v < nv; v += DECODE_THREADS)
+        for (; v < nv; v += NT)
             if (v != kv0 && v != kv1 && v != kv2) vrow[v] = ninf4;
         if (threadIdx.x < 3) {
             const int32_t kv = threadIdx.x == 0 ? kv0 : (threadIdx.x == 1 ? kv1 : kv2);
@@ -221,9 +224,9 @@ __global__ void __launch_bounds__(DECODE_THREADS) decode_step(DecodeArgs a)
                     if (e != keep0 && e != keep1 && e != keep2) store_ninf(row, e, a);
             }
         }
-        for (int64_t e = threadIdx.x; e < head; e += DECODE_THREADS)
+        for (int64_t e = threadIdx.x; e < head; e += NT)
             if (e != keep0 && e != keep1 && e != keep2) store_ninf(row, e, a);
-        for (int64_t e = tail0 + threadIdx.x; e < a.vocab; e += DECODE_THREADS)
+        for (int64_t e = tail0 + threadIdx.x; e < a.vocab; e += NT)
             if (e != keep0 && e != keep1 && e != keep2) store_ninf(row, e, a);
     }
 }

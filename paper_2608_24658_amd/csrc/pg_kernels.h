@@ -245,7 +245,12 @@ __device__ __forceinline__ void pg_segment(const PgArgs &a, const float *adv, co
  * sub of the same bytes 800).  A chunk is found by a search; where the plan is
  * in LDS that is cheap enough for chunks of one segment, which leave the waves
  * within one segment of each other (1,024 rows of 26,800 tokens: 67.4 us, 70.6
- * as ranges).  Two register buffers alternate so that the next segment's loads
+ * as ranges).  Arrays of tens of GB are the exception: there a range per wave is
+ * within 1 % of the chunks where the buffers' placement is bad for it and 9 %
+ * ahead where it is good (17.9e9 tokens, 4,270 segments per wave: ranges 39.8 and
+ * chunks 39.4 ms in three processes, 36.5 and 39.8 in a fourth; 5.0e9 tokens,
+ * 1,200 per wave: 11.9 and 11.6 in all of them), so from PG_RANGE_SEGS segments per
+ * wave each wave takes one chunk, its share of them.  Two register buffers alternate so that the next segment's loads
  * are in flight while the current one is evaluated.
  * PLAN (up to SCAN_PLAN_ROWS rows): every block makes the plan, the token count
  * and the advantages itself in LDS, in blocks of 8 waves so that half as many
@@ -254,6 +259,7 @@ __device__ __forceinline__ void pg_segment(const PgArgs &a, const float *adv, co
  * the 27 us of 64 rows of 3,500 tokens (13.8 now) and 20 of the 89 us of 1,024
  * rows of 26,800 (67 now). */
 constexpr int PG_WAVES = 4, PG_PLAN_WAVES = 8;
+constexpr int PG_RANGE_SEGS = 2048; /* segments per wave from which a wave takes one range */
 template <bool PLAN>
 constexpr int pg_waves() { return PLAN ? PG_PLAN_WAVES : PG_WAVES; }
 
@@ -299,12 +305,14 @@ __global__ void __launch_bounds__(WAVE * pg_waves<PLAN>(), 4) pg_surrogate(PgArg
     }
     N = uniform64(N);
     const int64_t S = uniform64(seg_off[a.n]);
-    constexpr int64_t CHUNK = PLAN ? 1 : 2;
-    const int64_t hop = (n_waves - 1) * CHUNK + 1; /* from a chunk's last segment to the next chunk's first */
+    const int32_t chunk =
+        PLAN ? 1 : __builtin_amdgcn_readfirstlane(
+                       S < n_waves * PG_RANGE_SEGS ? 2 : (int32_t)min((S + n_waves - 1) / n_waves, (int64_t)INT32_MAX));
+    const int64_t hop = (n_waves - 1) * chunk + 1; /* from a chunk's last segment to the next chunk's first */
     double acc = 0.0;
     /* per-lane clip counts: a lane sees at most a 64th of the batch's tokens */
     uint32_t clip_hi = 0, clip_lo = 0;
-    int64_t s = wave * CHUNK;
+    int64_t s = wave * chunk;
     if (s < S) {
         const float inv_n = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int((float)__ddiv_rn(1.0, (double)N))));
         SegCursor cur;
@@ -318,7 +326,7 @@ __global__ void __launch_bounds__(WAVE * pg_waves<PLAN>(), 4) pg_surrogate(PgArg
         float4 na[LOADS], oa[LOADS], nb[LOADS], ob[LOADS];
         SegView w = cur.view(s);
         pg_loads(a, w, lane, na, oa);
-        int32_t left = (int32_t)CHUNK - 1; /* segments left of the chunk after s */
+        int32_t left = chunk - 1; /* segments left of the chunk after s */
         while (true) {
             SegView wn;
             int64_t sn = left > 0 ? s + 1 : s + hop;
@@ -328,7 +336,7 @@ __global__ void __launch_bounds__(WAVE * pg_waves<PLAN>(), 4) pg_surrogate(PgArg
                 wn = cur.view(sn);
                 pg_loads(a, wn, lane, nb, ob);
             }
-            left = left > 0 ? left - 1 : (int32_t)CHUNK - 1;
+            left = left > 0 ? left - 1 : chunk - 1;
             pg_segment(a, adv, w, lane, na, oa, inv_n, acc, clip_hi, clip_lo);
             if (!more) break;
             s = sn;
@@ -340,7 +348,7 @@ __global__ void __launch_bounds__(WAVE * pg_waves<PLAN>(), 4) pg_surrogate(PgArg
                 wn = cur.view(sn);
                 pg_loads(a, wn, lane, na, oa);
             }
-            left = left > 0 ? left - 1 : (int32_t)CHUNK - 1;
+            left = left > 0 ? left - 1 : chunk - 1;
             pg_segment(a, adv, w, lane, nb, ob, inv_n, acc, clip_hi, clip_lo);
             if (!more) break;
             s = sn;

@@ -17,16 +17,30 @@ def test_plan_boundaries(n, G):
     lengths, _ = S.host_rows(P, n)
     if n > 1:
         lengths[n // 2] = 0
+    check(P, lengths, n, G)
+
+
+@pytest.mark.parametrize("more", [-8, 0, 4008])
+def test_range_per_wave(more):
+    # one segment per row of at most 3 tokens: 2,048 segments per wave (16 waves
+    # per CU) and beyond, where a wave takes one range in place of chunks
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 16 * 2048 + more
+    lengths = np.random.default_rng(n).integers(1, 4, n).astype(np.int32)
+    check(S.make_params(dict(seed=7, len_kind=1, len_lo=1, len_hi=3)), lengths, n, 8)
+
+
+def check(P, lengths, n, G):
     N = int(lengths.astype(np.int64).sum())
     starts = np.concatenate([[0], np.cumsum(lengths[:-1].astype(np.int64))])
     old, new = S.host_logp(P, 0, N)
     reward = np.random.default_rng(n).choice(np.array([-1.0, 1.0, 1.25, 0.8], np.float32), n)
     dev = [torch.as_tensor(x).cuda() for x in (reward, new, old, starts, lengths)]
     got = PX.pg_run(*dev, group_size=G)
-    adv = PO.advantages(reward, G)
+    some = min(n, 16384 // G * G)
+    adv = PO.advantages(reward[:some], G)
     a32 = got["advantage"].cpu().numpy()
     # the same double expression in the same order, stored as float
-    assert np.all(np.abs(a32 - adv) <= 2.0 ** -24 * np.abs(adv))
+    assert np.all(np.abs(a32[:some] - adv) <= 2.0 ** -24 * np.abs(adv))
     A = np.repeat(a32.astype(np.float64), lengths)
     d = new.astype(np.float64) - old.astype(np.float64)
     d32 = new - old
