@@ -1,5 +1,8 @@
 /*
  * pg.hip -- C-ABI of the policy-gradient step (kernels in pg_kernels.h).
+ *
+ * Launches use hipLaunchKernelGGL, as in parason.hip, so that the same source
+ * also compiles against a host-side stand-in for the HIP runtime.
  */
 #include "abi_common.h"
 #include "pg_kernels.h"
@@ -110,18 +113,20 @@ int parason_pg_run(const parason_pg_config *cfg, const float *reward, const floa
     const bool plan = n_traj <= pk::SCAN_PLAN_ROWS;
     const int64_t blocks = waves / (plan ? pk::PG_PLAN_WAVES : pk::PG_WAVES);
     if (plan) {
-        pk::pg_surrogate<true><<<dim3((unsigned)blocks), dim3(pk::PG_PLAN_WAVES * pk::WAVE), 0, stream>>>(pa);
+        hipLaunchKernelGGL(pk::pg_surrogate<true>, dim3((unsigned)blocks), dim3(pk::PG_PLAN_WAVES * pk::WAVE), 0,
+                           stream, pa);
     } else {
         const int64_t tiles = abi::plan_tile_count(n_traj), n_groups = n_traj / cfg->group_size;
         const int64_t group_blocks = (n_groups + pk::PLAN_THREADS - 1) / pk::PLAN_THREADS;
         int64_t *scratch = (int64_t *)(ws + L.plan), *len_sum = scratch + 2 * tiles;
-        pk::pg_prepare<<<dim3((unsigned)(tiles > group_blocks ? tiles : group_blocks)), dim3(pk::PLAN_THREADS), 0, stream>>>(
-            pa, tiles, n_groups, scratch, len_sum);
+        hipLaunchKernelGGL(pk::pg_prepare, dim3((unsigned)(tiles > group_blocks ? tiles : group_blocks)),
+                           dim3(pk::PLAN_THREADS), 0, stream, pa, tiles, n_groups, scratch, len_sum);
         abi::launch_plan(starts, lengths, n_traj, mis, scratch, (int64_t *)(ws + L.seg_off),
                          (int32_t *)(ws + L.counters), nullptr, len_sum, n_tokens, stream);
-        pk::pg_surrogate<false><<<dim3((unsigned)blocks), dim3(pk::PG_WAVES * pk::WAVE), 0, stream>>>(pa);
+        hipLaunchKernelGGL(pk::pg_surrogate<false>, dim3((unsigned)blocks), dim3(pk::PG_WAVES * pk::WAVE), 0, stream,
+                           pa);
     }
-    pk::pg_final<<<dim3(1), dim3(pk::RED_THREADS), 0, stream>>>(wsum, wcnt, blocks, n_tokens, stats);
+    hipLaunchKernelGGL(pk::pg_final, dim3(1), dim3(pk::RED_THREADS), 0, stream, wsum, wcnt, blocks, n_tokens, stats);
     return hipGetLastError() == hipSuccess ? PARASON_OK : PARASON_ERR_HIP;
 }
 

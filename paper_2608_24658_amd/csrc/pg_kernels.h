@@ -287,11 +287,13 @@ __global__ void __launch_bounds__(WAVE * pg_waves<PLAN>(), 4) pg_surrogate(PgArg
         int64_t len = 0;
         for (int64_t r = t; r < a.n; r += WAVE * NW) len += plan_ln[r] > 0 ? plan_ln[r] : 0;
         len = wave_inclusive_scan(len);
-        if (lane == WAVE - 1) part[1][wib] = len;
+        /* part[0], which block_plan is done with and nothing writes again: no
+         * barrier lies between the reads of N below and the kernel's last sums */
+        if (lane == WAVE - 1) part[0][wib] = len;
         for (int64_t g = t; g < a.n / a.G; g += WAVE * NW) group_advantage(plan_adv + g * a.G, a.G, plan_adv + g * a.G);
         __syncthreads();
         N = 0;
-        for (int w = 0; w < NW; ++w) N += part[1][w];
+        for (int w = 0; w < NW; ++w) N += part[0][w];
         if (blockIdx.x == 0) {
             for (int64_t r = t; r < a.n; r += WAVE * NW) a.adv[r] = plan_adv[r];
             if (t == 0) a.n_tokens[0] = N;

@@ -1,8 +1,8 @@
 /*
- * CPU SIMT emulation of the subset of HIP used by the accounting kernels.
+ * CPU SIMT emulation of the subset of HIP used by the library's kernels.
  *
  * TEST INFRASTRUCTURE.  The test suite compiles the library's own sources
- * (csrc/parason.hip and the headers it includes) for the host with this file
+ * (csrc/*.hip and the headers they include) for the host with this file
  * in place of the HIP runtime header, so that the device code runs on the CPU
  * under AddressSanitizer and UndefinedBehaviorSanitizer.  Nothing in the
  * library includes or knows about this file.
@@ -26,6 +26,14 @@
  * lane reads a lane that has exited, or when nothing can proceed.
  * __shared__ arrays become function-scope statics: one copy, which is what a
  * block sees since blocks never run at the same time.
+ *
+ * Order: the GPU promises none between the waves of a block, beyond its
+ * barriers, or between blocks.  By default the waves advance together, one wave
+ * operation each in turn, and blocks run in index order.  SIMT_WAVES=ahead (or
+ * ahead-reverse) in the environment runs each wave to its next barrier before
+ * the wave after (before) it, so that a barrier missing between one wave's
+ * read and another's write shows; SIMT_BLOCKS=reverse runs the blocks from the
+ * last to the first, so that results which depend on the order of atomics show.
  */
 #pragma once
 #include <stdint.h>
@@ -64,6 +72,10 @@ struct alignas(16) int4 {
 struct alignas(16) uint4 {
     unsigned x, y, z, w;
 };
+struct alignas(16) float4 {
+    float x, y, z, w;
+};
+inline float4 make_float4(float x, float y, float z, float w) { return float4{x, y, z, w}; }
 inline int4 make_int4(int x, int y, int z, int w) { return int4{x, y, z, w}; }
 inline uint4 make_uint4(unsigned x, unsigned y, unsigned z, unsigned w) { return uint4{x, y, z, w}; }
 
@@ -122,6 +134,14 @@ struct State {
     std::function<void()> body;
     int cur = -1;
     uint64_t collectives = 0;
+    bool waves_ahead = false, waves_reverse = false, blocks_reverse = false;
+    State()
+    {
+        const char *w = std::getenv("SIMT_WAVES"), *b = std::getenv("SIMT_BLOCKS");
+        waves_ahead = w && strncmp(w, "ahead", 5) == 0;
+        waves_reverse = w && strcmp(w, "ahead-reverse") == 0;
+        blocks_reverse = b && strcmp(b, "reverse") == 0;
+    }
 };
 
 inline State &st()
@@ -258,6 +278,34 @@ inline void resolve_wave(int w0, int nl)
     ++S.collectives;
 }
 
+/* Run the wave's threads to their next operation.  Resolves it and returns
+ * true, or returns false when they wait at __syncthreads or none is left. */
+inline bool wave_step(int w0, int nl, bool &any_alive)
+{
+    State &S = st();
+    int op = OP_NONE;
+    uintptr_t site = 0;
+    bool live = false, mixed = false;
+    for (int i = 0; i < nl; ++i) {
+        const Lane &L = S.lanes[w0 + i];
+        if (L.alive && !L.waiting) run_lane(w0 + i);
+        if (!L.alive) continue;
+        if (!live) {
+            op = L.op;
+            site = L.site;
+            live = true;
+        } else if (L.op != op || L.site != site) {
+            mixed = true;
+        }
+    }
+    if (!live) return false;
+    any_alive = true;
+    if (mixed) fail("the live lanes of a wave wait at different wave operations", w0);
+    if (op == OP_SYNC) return false;
+    resolve_wave(w0, nl);
+    return true;
+}
+
 inline void run_block()
 {
     State &S = st();
@@ -279,47 +327,25 @@ inline void run_block()
         for (int k = 0; k < 6; ++k) sp[k] = nullptr;
         L.sp = sp;
     }
+    const int waves = (n + WAVE - 1) / WAVE;
     for (;;) {
-        bool any_alive = false;
-        for (int i = 0; i < n; ++i) {
-            if (S.lanes[i].alive && !S.lanes[i].waiting) run_lane(i);
-            any_alive = any_alive || S.lanes[i].alive;
+        bool any_alive = false, progressed = false;
+        for (int k = 0; k < waves; ++k) {
+            const int w0 = WAVE * (S.waves_reverse ? waves - 1 - k : k);
+            const int nl = n - w0 < WAVE ? n - w0 : WAVE;
+            /* the wave's next operation; with waves_ahead all of them up to a barrier or its end */
+            while (wave_step(w0, nl, any_alive)) {
+                progressed = true;
+                if (!S.waves_ahead) break;
+            }
         }
         if (!any_alive) return;
-        /* every live thread now waits at a wave operation or at __syncthreads */
-        bool progressed = false, at_sync_everywhere = true;
-        for (int w0 = 0; w0 < n; w0 += WAVE) {
-            const int nl = n - w0 < WAVE ? n - w0 : WAVE;
-            int op = OP_NONE;
-            uintptr_t site = 0;
-            bool live = false, mixed = false;
-            for (int i = 0; i < nl; ++i) {
-                const Lane &L = S.lanes[w0 + i];
-                if (!L.alive) continue;
-                if (!live) {
-                    op = L.op;
-                    site = L.site;
-                    live = true;
-                } else if (L.op != op || L.site != site) {
-                    mixed = true;
-                }
-            }
-            if (!live) continue;
-            if (mixed) fail("the live lanes of a wave wait at different wave operations", w0);
-            if (op != OP_SYNC) {
-                at_sync_everywhere = false;
-                resolve_wave(w0, nl);
-                progressed = true;
-            }
-        }
-        if (!progressed) {
-            if (!at_sync_everywhere) fail("no thread can proceed", -1);
+        if (!progressed) /* every live thread waits at __syncthreads */
             for (int i = 0; i < n; ++i)
                 if (S.lanes[i].alive) {
                     S.lanes[i].waiting = false;
                     S.lanes[i].op = OP_NONE;
                 }
-        }
     }
 }
 
@@ -336,7 +362,7 @@ inline void launch(dim3 grid, dim3 block, std::function<void()> body)
     if (S.lanes.size() < block.x) S.lanes.resize(block.x);
     if (S.stacks.size() < (size_t)block.x * S.stack_size) S.stacks.assign((size_t)block.x * S.stack_size, 0);
     for (uint32_t b = 0; b < grid.x; ++b) {
-        S.bidx = dim3(b);
+        S.bidx = dim3(S.blocks_reverse ? grid.x - 1 - b : b);
         run_block();
     }
     S.body = nullptr;
@@ -413,6 +439,7 @@ inline uint32_t mbcnt_hi(uint32_t m, uint32_t acc)
 #define __ballot(p) simt::ballot((p), SIMT_SITE)
 #define __shfl(v, src, ...) simt::shfl((v), (src), SIMT_SITE)
 #define __shfl_up(v, d, ...) simt::shfl_up((v), (d), SIMT_SITE)
+#define __shfl_xor(v, d, ...) simt::shfl((v), simt::lane_id() ^ (d), SIMT_SITE)
 #define __builtin_amdgcn_readfirstlane(v) simt::readfirstlane((int)(v), SIMT_SITE)
 #define __builtin_amdgcn_readlane(v, l) simt::readlane((int)(v), (l), SIMT_SITE)
 #define __builtin_amdgcn_update_dpp(o, s, c, r, b, bc) simt::update_dpp((o), (s), (c), (r), (b), (bc), SIMT_SITE)
@@ -426,6 +453,9 @@ inline uint32_t mbcnt_hi(uint32_t m, uint32_t acc)
 
 inline int __popcll(unsigned long long x) { return __builtin_popcountll(x); }
 inline float __int_as_float(int x) { return simt::from_bits<float>((uint32_t)x); }
+inline int __float_as_int(float x) { return (int)(uint32_t)simt::bits(x); }
+inline float __fsub_rn(float a, float b) { return a - b; }
+inline float __builtin_amdgcn_exp2f(float x) { return std::exp2(x); }
 inline double __dadd_rn(double a, double b) { return a + b; }
 inline double __dsub_rn(double a, double b) { return a - b; }
 inline double __dmul_rn(double a, double b) { return a * b; }
