@@ -281,7 +281,7 @@ int parason_pg_workspace_size(int64_t n_traj, size_t *bytes);
  *   logp, logp_old  float log-probabilities of the generated tokens; row i is
  *              [starts[i], starts[i] + lengths[i]) as for parason_run; the
  *              three float arrays must share their position modulo 16 bytes
- *   advantage  float[n_traj] out: A_i
+ *   advantage  float[n_traj] out: A_i (may be the array reward)
  *   grad       float out, same layout as logp: d loss / d logp on every row
  *              position (other positions are not written)
  *   stats      double[PARASON_PG_STAT_COUNT] out

@@ -110,7 +110,12 @@ int parason_pg_run(const parason_pg_config *cfg, const float *reward, const floa
     pa.n_tokens = n_tokens;
     pa.wsum = wsum;
     pa.wcnt = wcnt;
-    const bool plan = n_traj <= pk::SCAN_PLAN_ROWS;
+    /* Blocks that plan the batch themselves all read the rewards while the
+     * first of them writes the advantages: a caller's advantages over the
+     * rewards take the launches, where each group's thread reads its rewards
+     * before it writes. */
+    const bool in_place = advantage < reward + n_traj && reward < advantage + n_traj;
+    const bool plan = n_traj <= pk::SCAN_PLAN_ROWS && !in_place;
     const int64_t blocks = waves / (plan ? pk::PG_PLAN_WAVES : pk::PG_WAVES);
     if (plan) {
         hipLaunchKernelGGL(pk::pg_surrogate<true>, dim3((unsigned)blocks), dim3(pk::PG_PLAN_WAVES * pk::WAVE), 0,

@@ -55,3 +55,23 @@ def check(P, lengths, n, G):
     terms = np.where(clipped, np.where(clip_hi, 1.28, 0.8) * A, A * np.exp(d))
     assert st[1] == N and st[2] == clip_hi.sum() and st[3] == clip_lo.sum()
     assert abs(st[0] + terms.sum() / max(N, 1)) <= 2.0 ** -20 * np.abs(terms).sum() / max(N, 1)
+
+
+@pytest.mark.parametrize("n", [64, 2048, 2056])
+def test_advantages_over_the_rewards(n):
+    """The advantages written over the rewards: the same advantages and gradients."""
+    P = S.make_params(dict(seed=n, len_kind=1, len_lo=1, len_hi=2500))
+    lengths, _ = S.host_rows(P, n)
+    starts = np.concatenate([[0], np.cumsum(lengths[:-1].astype(np.int64))])
+    old, new = S.host_logp(P, 0, int(lengths.astype(np.int64).sum()))
+    reward = np.random.default_rng(n).choice(np.array([-1.0, 1.0, 1.25, 0.8], np.float32), n)
+    r, lp, lo, st, ln = (torch.as_tensor(x).cuda() for x in (reward, new, old, starts, lengths))
+    want = PX.pg_run(r, lp, lo, st, ln, group_size=8)
+    grad, stats = torch.empty_like(lp), torch.empty(4, dtype=torch.float64, device="cuda")
+    ws = torch.empty(PX.pg_workspace_size(n), dtype=torch.uint8, device="cuda")
+    rc = PX.pg_run_raw(PX.PgConfig(8, 0.2, 0.28), r.data_ptr(), lp.data_ptr(), lo.data_ptr(), st.data_ptr(), ln.data_ptr(),
+                       n, r.data_ptr(), grad.data_ptr(), stats.data_ptr(), ws.data_ptr(), ws.numel(),
+                       torch.cuda.current_stream().cuda_stream)
+    assert rc == PX.OK
+    assert torch.equal(r, want["advantage"]) and torch.equal(grad, want["grad"])
+    assert torch.equal(stats[1:], want["stats"][1:])

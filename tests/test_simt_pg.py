@@ -91,3 +91,16 @@ BATCHES = [(8, 1, 40, 8, 2), (64, 300, 1500, 8, 2), (600, 0, 300, 3, 2), (2048, 
 @pytest.mark.parametrize("n,lo,hi,G,cus", BATCHES)
 def test_emulated_step(emu, n, lo, hi, G, cus, waves):
     check(emu, batch(n, lo, hi, n), G, cus, "n %d, %s" % (n, waves), shift=n % 4, waves=waves)
+
+
+@pytest.mark.parametrize("n", [64, 2048, 2056])
+def test_advantages_over_the_rewards(emu, n):
+    """The advantages may be written over the rewards, at any batch size: the
+    same advantages and gradients, bit for bit.  (A block that reads rewards
+    another one has written over normalises advantages a second time, which
+    changes their last bits.)"""
+    args = batch(n, 1, 60, n + 1)
+    apart, over = (run_emu(emu, *args, 8, 2, in_place=x) for x in (False, True))
+    assert np.array_equal(over[0], apart[0]) and np.array_equal(over[1], apart[1])
+    assert np.array_equal(over[2][1:], apart[2][1:])
+    assert abs(over[2][0] - apart[2][0]) <= 1e-12 * abs(apart[2][0])  # the same terms in double, in another order
