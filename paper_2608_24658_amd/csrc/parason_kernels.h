@@ -2388,10 +2388,43 @@ struct DeepArgs {
     RowArgs rows;
     const uint8_t *mode;
     const int32_t *counters; /* counters[1]: rows in deep_rows */
-    const int32_t *deep_rows;
+    int32_t *deep_rows;
     int32_t *frames;
     uint32_t *bits;
 };
+
+/* deep_rows in row order, by one block (part: a word per wave).  The list is
+ * filled through an atomic counter, so its order is the scheduler's, and sums in
+ * list order would differ in their last bits from call to call.  It is written
+ * again from the rows' MODE_DEEP marks: sixteen rows per thread and step,
+ * whatever the number of deep rows (a batch with two or more only). */
+__device__ __forceinline__ void order_deep_rows(const DeepArgs &d, int64_t n, int32_t *part)
+{
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    int32_t found = 0;
+    for (int64_t r0 = 0; r0 < n; r0 += 16 * (int64_t)blockDim.x) {
+        const int64_t r = r0 + 16 * (int64_t)threadIdx.x;
+        uint32_t hit = 0; /* bit j: row r + j */
+        if (r < n) {      /* the section is padded to whole quads */
+            const uint4 q = *reinterpret_cast<const uint4 *>(d.mode + r);
+            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) hit |= ((w[j / 4] >> (8 * (j % 4))) & MODE_DEEP) != 0 ? 1u << j : 0u;
+            if (n - r < 16) hit &= (1u << (n - r)) - 1u;
+        }
+        const int32_t cnt = __popcll(hit), incl = dpp_incl_scan<OpAdd>(cnt, lane);
+        __syncthreads(); /* part's use before */
+        if (lane == WAVE - 1) part[wv] = incl;
+        __syncthreads();
+        int32_t at = found + incl - cnt;
+        for (int w = 0; w < (int)(blockDim.x / WAVE); ++w) {
+            at += w < wv ? part[w] : 0;
+            found += part[w];
+        }
+        for (; hit != 0; hit &= hit - 1) d.deep_rows[at++] = (int32_t)(r + __builtin_ctz(hit));
+    }
+    __syncthreads();
+}
 
 /* ------------------------------------------------------------------ batch metrics */
 
@@ -2546,6 +2579,7 @@ __global__ void __launch_bounds__(METRICS ? RED_SINGLE : RED_THREADS)
 group_reward(RewardArgs a, DeepArgs d, MetricRec *__restrict__ recs, double *__restrict__ metrics)
 {
     __shared__ MetricRec lds[METRICS ? RED_WAVES : 1];
+    __shared__ int32_t part[METRICS ? RED_WAVES : 1];
     const int32_t G = a.G;
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     /* the row's values in the same round of loads as the deep count (rows of
@@ -2554,6 +2588,7 @@ group_reward(RewardArgs a, DeepArgs d, MetricRec *__restrict__ recs, double *__r
     const int32_t n_deep = d.counters[1]; /* the same for every thread */
     MetricRec rec = no_metrics();
     if (n_deep > 0 && blockIdx.x == 0) {
+        if (METRICS && n_deep > 1) order_deep_rows(d, a.n, part); /* their rewards' sum in row order */
         if (threadIdx.x == 0) run_deep_rows<LENIENT>(d.rows, d.mode, n_deep, d.deep_rows, d.frames, d.bits);
         __syncthreads();
         for (int64_t k0 = 0; k0 < (int64_t)n_deep * G; k0 += blockDim.x) {
@@ -2705,11 +2740,13 @@ __global__ void __launch_bounds__(RED_THREADS) batch_moments(RewardArgs a, DeepA
 {
     __shared__ Moms lds[RED_WAVES];
     __shared__ uint32_t lds_bits[RED_WAVES];
+    __shared__ int32_t part[RED_WAVES];
     __shared__ int64_t first_row;
     const int64_t t0 = (int64_t)blockIdx.x * RED_THREADS * rpt, t1 = min(a.n, t0 + (int64_t)RED_THREADS * rpt);
     const int32_t n_deep = d.counters[1];
     int64_t f = t0;
     if (n_deep > 0) {
+        if (blockIdx.x == 0 && n_deep > 1) order_deep_rows(d, a.n, part); /* their moments merge in row order */
         if (threadIdx.x == 0) {
             if (blockIdx.x == 0) run_deep_rows<LENIENT>(d.rows, d.mode, n_deep, d.deep_rows, d.frames, d.bits);
             while (f < t1 && (d.mode[f] & MODE_DEEP)) ++f;

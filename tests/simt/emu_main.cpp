@@ -11,11 +11,12 @@
  * Input (little endian): int64 n, int64 n_tok, int64 ws_tokens (the
  * total_tokens given to parason_workspace_size), int32 tag_ids[12],
  * int32 group_size, uint32 cfg_flags, int32 cus, int32 shift, int32 noalloc,
- * double coef[5], then int32 tokens[n_tok], int64 starts[n], int32
+ * int32 metrics (asked for or not), double coef[5], then int32 tokens[n_tok], int64 starts[n], int32
  * lengths[n], uint8 correct[n].
  * Output: int32 total, latency, n_subtask, n_trial, n_blocks, max_depth,
  * first_error_pos, flags [n each], float reward, r_subtask, r_trial, eta,
- * accel [n each], int32 saved [n], int32 status.
+ * accel [n each], int32 saved [n], int32 status, double metrics
+ * [PARASON_METRIC_COUNT] (-77 when not asked for).
  */
 #include <cstdio>
 #include <cstdlib>
@@ -43,7 +44,7 @@ int main(int argc, char **argv)
     FILE *f = fopen(argv[1], "rb");
     if (!f) return 2;
     int64_t n, n_tok, ws_tokens;
-    int32_t tags[12], G, cus, shift, noalloc;
+    int32_t tags[12], G, cus, shift, noalloc, want_metrics;
     uint32_t flags;
     double coef[5];
     rd(f, &n, 8);
@@ -55,6 +56,7 @@ int main(int argc, char **argv)
     rd(f, &cus, 4);
     rd(f, &shift, 4);
     rd(f, &noalloc, 4);
+    rd(f, &want_metrics, 4);
     rd(f, coef, sizeof coef);
     /* tokens at `shift` elements past a 256-byte boundary, in an allocation
      * that ends at the 16-byte vector holding the last token (the scan reads
@@ -87,6 +89,7 @@ int main(int argc, char **argv)
     std::vector<int32_t> I[8];
     std::vector<float> F[5];
     std::vector<int32_t> saved(n > 0 ? n : 1);
+    std::vector<double> metrics(PARASON_METRIC_COUNT, -77.0);
     for (auto &v : I) v.assign(n > 0 ? n : 1, -77);
     for (auto &v : F) v.assign(n > 0 ? n : 1, -77.0f);
     if (rc == PARASON_OK) {
@@ -106,6 +109,7 @@ int main(int argc, char **argv)
         out.eta = F[3].data();
         out.accel = F[4].data();
         out.saved = saved.data();
+        if (want_metrics) out.metrics = metrics.data();
         if (noalloc) {
             rc = parason_run_noalloc(h, tokens, starts.data(), lengths.data(), correct.data(), n, ws_tokens, &out,
                                      nullptr);
@@ -130,6 +134,7 @@ int main(int argc, char **argv)
     for (auto &v : F) fwrite(v.data(), 4, (size_t)n, o);
     fwrite(saved.data(), 4, (size_t)n, o);
     fwrite(&rc, 4, 1, o);
+    fwrite(metrics.data(), 8, metrics.size(), o);
     fclose(o);
     free(tok_mem);
     fprintf(stderr, "simt: %llu wave operations\n", (unsigned long long)simt::st().collectives);

@@ -2,7 +2,7 @@
  * CPU SIMT emulation of the subset of HIP used by the library's kernels.
  *
  * TEST INFRASTRUCTURE.  The test suite compiles the library's own sources
- * (csrc/*.hip and the headers they include) for the host with this file
+ * (csrc, the .hip files and the headers they include) for the host with this file
  * in place of the HIP runtime header, so that the device code runs on the CPU
  * under AddressSanitizer and UndefinedBehaviorSanitizer.  Nothing in the
  * library includes or knows about this file.
@@ -34,6 +34,10 @@
  * the wave after (before) it, so that a barrier missing between one wave's
  * read and another's write shows; SIMT_BLOCKS=reverse runs the blocks from the
  * last to the first, so that results which depend on the order of atomics show.
+ *
+ * Divergence: with SIMT_DIVERGENT set, lanes of a wave that wait at different
+ * wave operations are no error: those at the earliest source line go first, as
+ * the branch they are in does on the GPU, and the others wait for them.
  */
 #pragma once
 #include <stdint.h>
@@ -134,13 +138,14 @@ struct State {
     std::function<void()> body;
     int cur = -1;
     uint64_t collectives = 0;
-    bool waves_ahead = false, waves_reverse = false, blocks_reverse = false;
+    bool waves_ahead = false, waves_reverse = false, blocks_reverse = false, divergent = false;
     State()
     {
         const char *w = std::getenv("SIMT_WAVES"), *b = std::getenv("SIMT_BLOCKS");
         waves_ahead = w && strncmp(w, "ahead", 5) == 0;
         waves_reverse = w && strcmp(w, "ahead-reverse") == 0;
         blocks_reverse = b && strcmp(b, "reverse") == 0;
+        divergent = std::getenv("SIMT_DIVERGENT") != nullptr;
     }
 };
 
@@ -216,35 +221,30 @@ inline uint64_t meet(int op, uintptr_t site, uint64_t a, uint64_t b)
 
 inline int lane_id() { return st().cur & (WAVE - 1); }
 
-/* Resolve the wave [w0, w0 + 64) whose live lanes all wait at one wave operation. */
-inline void resolve_wave(int w0, int nl)
+/* Resolve the wave operation `op` at `site` for the lanes of the wave
+ * [w0, w0 + 64) that wait there: all live ones, or those of a divergent branch. */
+inline void resolve_wave(int w0, int nl, int op, uintptr_t site)
 {
     State &S = st();
     Lane *W = &S.lanes[w0];
-    const int op = [&] {
-        for (int i = 0; i < nl; ++i)
-            if (W[i].alive) return W[i].op;
-        return (int)OP_NONE;
-    }();
-    uint64_t mask = 0;
-    for (int i = 0; i < nl; ++i)
-        if (W[i].alive) mask |= 1ull << i;
+    bool in[WAVE];
+    for (int i = 0; i < nl; ++i) in[i] = W[i].alive && W[i].op == op && W[i].site == site;
     auto src = [&](int i, int j) -> uint64_t {
-        if (j < 0 || j >= nl || !W[j].alive) fail("a wave operation reads a lane that has exited", w0 + i);
+        if (j < 0 || j >= nl || !in[j]) fail("a wave operation reads a lane that has exited or is elsewhere", w0 + i);
         return W[j].a;
     };
     int first = -1;
     for (int i = 0; i < nl && first < 0; ++i)
-        if (W[i].alive) first = i;
+        if (in[i]) first = i;
     for (int i = 0; i < nl; ++i) {
-        if (!W[i].alive) continue;
+        if (!in[i]) continue;
         Lane &L = W[i];
         switch (op) {
         case OP_WAVE_BARRIER: L.result = 0; break;
         case OP_BALLOT: {
             uint64_t m = 0;
             for (int j = 0; j < nl; ++j)
-                if (W[j].alive && W[j].a) m |= 1ull << j;
+                if (in[j] && W[j].a) m |= 1ull << j;
             L.result = m;
             break;
         }
@@ -274,7 +274,6 @@ inline void resolve_wave(int w0, int nl)
         L.waiting = false;
         L.op = OP_NONE;
     }
-    (void)mask;
     ++S.collectives;
 }
 
@@ -300,9 +299,19 @@ inline bool wave_step(int w0, int nl, bool &any_alive)
     }
     if (!live) return false;
     any_alive = true;
-    if (mixed) fail("the live lanes of a wave wait at different wave operations", w0);
+    if (mixed) {
+        if (!S.divergent) fail("the live lanes of a wave wait at different wave operations", w0);
+        op = OP_SYNC;
+        for (int i = 0; i < nl; ++i) {
+            const Lane &L = S.lanes[w0 + i];
+            if (L.alive && L.op != OP_SYNC && (op == OP_SYNC || L.site < site)) {
+                op = L.op;
+                site = L.site;
+            }
+        }
+    }
     if (op == OP_SYNC) return false;
-    resolve_wave(w0, nl);
+    resolve_wave(w0, nl, op, site);
     return true;
 }
 

@@ -12,10 +12,11 @@ import pytest
 import grammar_pins as GP
 from adversarial import adversarial_streams, deep_stream, pack
 from gpu_util import DEFAULT_COEF, compare, insert_gaps, oracle_expect
+from oracle import oracle as O
 from paper_2608_24658_amd import parason as PX
 from paper_2608_24658_amd.synth import synth as S
 from test_gpu_metrics import check_metrics
-from test_simt_emulation import CLANG, CSRC, FEW, MANY, ROOT, SIMT, TAGS, check
+from test_simt_emulation import CLANG, CSRC, FEW, MANY, ROOT, SIMT, TAGS, check, run_emu
 
 G = 8
 
@@ -69,9 +70,44 @@ def test_unstored_segments_adversarial(emu_small_pool, cus):
 @pytest.mark.parametrize("n", [1024, 1032])
 def test_emulated_batch_statistics(emu_small_pool, n):
     """One block and several, with rows of the deep tier among them."""
-    tokens, starts, lengths = with_deep_rows(n, n)
+    tokens, starts, lengths = pack(with_deep_rows(n, n), S.CONTIGUOUS_TAGS)
     correct = (np.arange(n) % 3 != 0).astype(np.uint8)
     check(emu_small_pool, tokens, starts, lengths, correct, flags=PX.CFG_BATCH_STATS, cus=MANY, what="batch stats")
+
+
+@pytest.mark.parametrize("flags", [0, PX.CFG_BATCH_STATS])
+@pytest.mark.parametrize("n,cus", [(1024, MANY), (1032, MANY), (2056, FEW)])
+def test_emulated_deep_rows_in_any_order(emu_small_pool, n, cus, flags):
+    """The deep tier's list is filled by atomics, so its order is the
+    scheduler's.  The rewards, the batch statistics and the metrics of blocks run
+    in index order and from the last to the first: bit for bit the same.  So that
+    an order shows, the mean latency is a whole number that one row has, and a
+    weight of 1e18 makes that row's reward under batch statistics the rounding
+    error of the mean; without them a weight of 1e15 next to the -1 of wrong
+    answers makes the sum of the rewards inexact."""
+    streams = with_deep_rows(n, n, [int(x) for x in np.random.default_rng(n).integers(66, 130, 200)])
+    rest = int(oracle_latency(streams[2:]).sum())
+    mean = rest // (n - 2) + 2
+    streams[1:3] = [[GP.THINK] + [GP.TEXT] * (k - 2) + [GP.END_THINK] for k in (mean, 2)]
+    fill = n * mean - int(oracle_latency(streams).sum()) + 2
+    assert fill >= 2
+    streams[2] = [GP.THINK] + [GP.TEXT] * (fill - 2) + [GP.END_THINK]
+    tokens, starts, lengths = pack(streams, TAGS)
+    correct = (np.arange(n) % 3 != 0).astype(np.uint8)
+    coef = dict(alpha=1e18 if flags else 1e15, beta_subtask=0.0, beta_trial=0.0, rho=0.5, rho_clip=0.25)
+    got, back = (run_emu(emu_small_pool, tokens, starts, lengths, correct, flags=flags, cus=cus, coef=coef, metrics=True,
+                         blocks=x, divergent=True)[0] for x in ("forward", "reverse"))
+    for k in got:
+        assert np.array_equal(got[k], back[k], equal_nan=True), k
+    rows, R, rs, rt, eta = oracle_expect(tokens, starts, lengths, correct, TAGS, G, coef, flags)
+    if not flags:
+        compare(got, rows, R, rs, rt, eta, what="deep rows")
+        check_metrics(got["metrics"], rows, correct, R)
+
+
+def oracle_latency(streams):
+    tokens, starts, lengths = pack(streams, TAGS)
+    return O.eval_rows(tokens, starts, lengths, TAGS)["latency"]
 
 
 @pytest.mark.gpu
@@ -110,14 +146,15 @@ def test_adversarial_rows_in_a_large_batch_on_the_gpu():
     assert got["max_depth"].max() >= 1000
 
 
-def with_deep_rows(n, seed):
+def with_deep_rows(n, seed, depths=(80, 80, 80, 80)):
     """Short rows with a few the deep tier evaluates, two of them in one group and one in the last."""
     rng = np.random.default_rng(seed)
     valid = [list(x) for x in GP.enumerate_valid(14)]
     streams = [valid[int(k)] for k in rng.integers(0, len(valid), n)]
-    for i in {0, 3, n // 2, n - 1}:
-        streams[i] = deep_stream(80)
-    return pack(streams, S.CONTIGUOUS_TAGS)
+    rows = sorted({0, 3, n // 2, n - 1} | {int(i) for i in rng.integers(0, n, max(0, len(depths) - 4))})
+    for i, depth in zip(rows, depths):
+        streams[i] = deep_stream(depth)
+    return streams
 
 
 @pytest.mark.gpu
@@ -129,7 +166,7 @@ def test_batch_reductions_on_the_gpu(n, deep):
     import torch
 
     if deep:
-        tok, st, ln = with_deep_rows(n, n)
+        tok, st, ln = pack(with_deep_rows(n, n), S.CONTIGUOUS_TAGS)
         co = (np.arange(n) % 3 != 0).astype(np.uint8)
     else:
         tok, st, ln, co = short_rows(n, 20, 120, n)

@@ -61,14 +61,14 @@ def emu(tmp_path_factory):
 
 
 def run_emu(binary, tokens, starts, lengths, correct, tags=TAGS, flags=0, cus=2, shift=0, noalloc=False,
-            ws_tokens=None, coef=DEFAULT_COEF, tmp="/tmp"):
+            ws_tokens=None, coef=DEFAULT_COEF, metrics=False, blocks="forward", divergent=False, tmp="/tmp"):
     n = len(starts)
     tokens = np.ascontiguousarray(tokens, np.int32)
     if ws_tokens is None:
         ws_tokens = int(np.maximum(np.asarray(lengths), 0).astype(np.int64).sum())
     hdr = (np.array([n, tokens.size, ws_tokens], np.int64).tobytes() + np.asarray(tags, np.int32).tobytes()
            + np.array([G], np.int32).tobytes() + np.array([flags], np.uint32).tobytes()
-           + np.array([cus, shift, int(noalloc)], np.int32).tobytes()
+           + np.array([cus, shift, int(noalloc), int(metrics)], np.int32).tobytes()
            + np.array([coef[k] for k in ("alpha", "beta_subtask", "beta_trial", "rho", "rho_clip")],
                       np.float64).tobytes())
     body = (tokens.tobytes() + np.asarray(starts, np.int64).tobytes() + np.asarray(lengths, np.int32).tobytes()
@@ -78,7 +78,8 @@ def run_emu(binary, tokens, starts, lengths, correct, tags=TAGS, flags=0, cus=2,
     with open(fin, "wb") as f:
         f.write(hdr + body)
     env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1:abort_on_error=1",
-               UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1")
+               UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1", SIMT_BLOCKS=blocks,
+               **({"SIMT_DIVERGENT": "1"} if divergent else {}))
     r = subprocess.run([binary, fin, fout], env=env, capture_output=True, text=True, timeout=600)
     if r.returncode != 0:
         raise RuntimeError("emulation failed (%d):\n%s" % (r.returncode, r.stderr[-4000:]))
@@ -95,6 +96,7 @@ def run_emu(binary, tokens, starts, lengths, correct, tags=TAGS, flags=0, cus=2,
         off += 4 * n
     out["saved"] = np.frombuffer(b, np.int32, n, off).copy()
     off += 4 * n
+    out["metrics"] = np.frombuffer(b, np.float64, len(PX.METRICS), off + 4).copy()
     return out, int(np.frombuffer(b, np.int32, 1, off)[0])
 
 
