@@ -385,7 +385,7 @@ typedef struct parason_fork_outputs {
     int32_t *ctx_kind;        /* [max_workers] 1 = Subtask, 2 = Trial */
     int64_t *worker_off;      /* [n_rows + 1] first worker of each row; [n_rows] = workers */
     uint32_t *row_status;     /* [n_rows] PARASON_PACK_* (0: dispatched) */
-    int64_t *totals;          /* [3] workers, context tokens, over capacity (0/1) */
+    int64_t *totals;          /* [3] workers, context tokens, over capacity (0/1; 2: parason_fork_sized) */
 } parason_fork_outputs;
 
 typedef struct parason_join_outputs {
@@ -394,7 +394,7 @@ typedef struct parason_join_outputs {
     int64_t *starts;          /* [n_rows + 1]; [n_rows] = total tokens */
     int32_t *lengths;         /* [n_rows] */
     uint32_t *row_status;     /* [n_rows] PARASON_PACK_* */
-    int64_t *totals;          /* [2] tokens, over capacity (0/1) */
+    int64_t *totals;          /* [2] tokens, over capacity (0/1; 2: parason_join_sized) */
 } parason_join_outputs;
 
 /* Bytes of device workspace parason_fork / parason_join need for n_rows rows. */
@@ -412,10 +412,12 @@ int parason_fork(const parason_handle *h, const int32_t *tokens, const int64_t *
 /* parason_fork for a caller that has just sized its outputs: the call before on
  * this stream with this workspace was parason_fork with the same handle, rows
  * and flags, max_workers = ctx_capacity = 0 and the same worker_off, row_status
- * and totals, and nothing has been written to any of these since.  The same
- * results as parason_fork, without reading the rows' outlines a second time.
- * (Nothing checks this: anything else in the workspace gives wrong results or
- * writes out of bounds.) */
+ * and totals, and nothing has been written to any of these or to the rows since.
+ * The same results as parason_fork, without reading the rows' outlines a second
+ * time.  A workspace that no such call left (another fork or join has used it
+ * since, or the pointers, the rows' number, the flags or the handle's tag ids differ)
+ * gives totals {0, 0, 2} and no other output.  (Contents that changed in place
+ * are not seen, as in any call whose inputs change while it runs.) */
 int parason_fork_sized(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
                        int64_t n_rows, uint32_t flags, const parason_fork_outputs *out, void *workspace,
                        size_t workspace_bytes, void *stream);
@@ -430,7 +432,8 @@ int parason_join(const parason_handle *h, const int32_t *tokens, const int64_t *
 
 /* parason_join after a sizing call (parason_join with capacity = 0), as
  * parason_fork_sized is to parason_fork: the same arguments, and the workspace,
- * the outputs' starts, lengths and row_status as that call left them. */
+ * the outputs' starts, lengths and row_status as that call left them.  Totals
+ * {0, 2} and no other output when the workspace is not that call's. */
 int parason_join_sized(const parason_handle *h, const int32_t *tokens, const int64_t *starts, const int32_t *lengths,
                        int64_t n_rows, const int64_t *worker_off, const int32_t *wtokens, const int64_t *wstarts,
                        const int32_t *wlengths, int64_t n_workers, uint32_t flags, const parason_join_outputs *out,

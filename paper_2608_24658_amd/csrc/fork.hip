@@ -6,6 +6,7 @@
  * also compiles against a host-side stand-in for the HIP runtime.
  */
 #include <algorithm>
+#include <initializer_list>
 
 #include "abi_common.h"
 #include "fork_kernels.h"
@@ -20,7 +21,8 @@ constexpr int COPY_BLOCKS_PER_CU = 8;
 /* Workspace of fork (K = 3 counts per row: workers, context tokens, copy
  * units) or join (K = 1). */
 struct PackLayout {
-    size_t counts, outl, tile_sum, tile_off, tok_off, unit_off, summ, over, end;
+    size_t over, mark; /* first, where every call finds them whatever its rows */
+    size_t counts, outl, tile_sum, tile_off, tok_off, unit_off, summ, end;
     int64_t tiles;
 };
 
@@ -29,6 +31,9 @@ PackLayout pack_layout(int64_t n, int K)
     PackLayout L;
     L.tiles = n > 0 ? (n + pk::PACK_TILE - 1) / pk::PACK_TILE : 1;
     size_t o = 0;
+    L.over = o;
+    L.mark = o + sizeof(uint64_t);
+    o = align_up(o + 2 * sizeof(uint64_t));
     L.counts = o;
     o = align_up(o + (size_t)(n > 0 ? n : 1) * K * sizeof(int64_t));
     L.outl = o;
@@ -43,11 +48,28 @@ PackLayout pack_layout(int64_t n, int K)
     if (K == 3) o = align_up(o + (size_t)(n + 1) * sizeof(int64_t));
     L.summ = o;
     if (K == 3) o = align_up(o + (size_t)(n > 0 ? n : 1) * pk::SUMM_ENTRIES * sizeof(uint64_t));
-    L.over = o;
-    o = align_up(o + sizeof(int32_t));
     L.end = o;
     return L;
 }
+
+/* The mark a call leaves in its workspace for a sized one, from everything the
+ * two must have in common: a word the memory holds by chance once in 2^64. */
+uint64_t call_key(const parason_handle *h, std::initializer_list<uint64_t> args)
+{
+    uint64_t x = 0x9e3779b97f4a7c15ull;
+    const auto mix = [&x](uint64_t v) { /* the finaliser of splitmix64 (Steele, Lea and Flood 2014) */
+        x += v + 0x9e3779b97f4a7c15ull;
+        x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+        x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+        x ^= x >> 31;
+    };
+    for (int32_t id : h->cfg.tag_ids) mix((uint64_t)(uint32_t)id);
+    mix(h->cfg.flags & PARASON_CFG_LENIENT_GAPS);
+    for (uint64_t v : args) mix(v);
+    return x;
+}
+
+uint64_t addr(const void *p) { return (uint64_t)(uintptr_t)p; }
 
 bool aligned(const void *p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
@@ -127,6 +149,10 @@ int fork_rows(const parason_handle *h, const int32_t *tokens, const int64_t *sta
     ps.totals = out->totals;
     ps.report = 2; /* totals = workers, context tokens, over */
     ps.over = (int32_t *)(ws + L.over);
+    ps.mark = (uint64_t *)(ws + L.mark);
+    ps.key = call_key(h, {3u, (uint64_t)n_rows, flags, addr(tokens), addr(starts), addr(lengths), addr(out->worker_off),
+                          addr(out->row_status), addr(out->totals)});
+    ps.sized = sized;
 
     const unsigned wave_blocks = (unsigned)std::min<int64_t>((n_rows + pk::OUTLINE_WAVES - 1) / pk::OUTLINE_WAVES,
                                                              (int64_t)cus * (32 / pk::OUTLINE_WAVES));
@@ -208,6 +234,11 @@ int join_rows(const parason_handle *h, const int32_t *tokens, const int64_t *sta
     ps.totals = out->totals;
     ps.report = 1;
     ps.over = (int32_t *)(ws + L.over);
+    ps.mark = (uint64_t *)(ws + L.mark);
+    ps.key = call_key(h, {1u, (uint64_t)n_rows, flags, addr(tokens), addr(starts), addr(lengths), addr(worker_off),
+                          addr(wtokens), addr(wstarts), addr(wlengths), (uint64_t)n_workers, addr(out->starts),
+                          addr(out->lengths), addr(out->row_status), addr(out->totals)});
+    ps.sized = sized;
 
     if (n_rows > 0 && !sized) hipLaunchKernelGGL(pk::join_size, dim3((unsigned)((n_rows + pk::JOIN_SIZE_THREADS - 1) / pk::JOIN_SIZE_THREADS)),
                                        dim3(pk::JOIN_SIZE_THREADS), 0, stream, ja);

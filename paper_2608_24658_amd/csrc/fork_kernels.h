@@ -102,7 +102,44 @@ struct PackScan {
     int64_t *totals;       /* optional: totals[0 .. report) and then the over flag, for the caller */
     int report;            /* totals reported (the first `report` of the K) */
     int32_t *over;         /* workspace copy of the over flag */
+    uint64_t *mark;        /* workspace: the key of the call that left vals there */
+    uint64_t key;
+    bool sized;            /* vals are an earlier call's, which mark must show */
 };
+
+constexpr int32_t PACK_STALE = 2; /* over flag of a sized call whose workspace holds no such call's results */
+
+/* A sized call whose workspace does not show its key: vals may be anything, so
+ * nothing is read from them and only the over flag is written.  Loads that do not
+ * depend on vals' contents belong before this check, so that they are in flight
+ * together. */
+template <int K>
+__device__ __forceinline__ bool pack_stale(const PackScan<K> &a)
+{
+    return a.sized && a.mark[0] != a.key;
+}
+
+/* The totals and the flag, by one thread of the launch; the mark stays as it is
+ * in a sized call. */
+template <int K>
+__device__ __forceinline__ void pack_report(const PackScan<K> &a, const int64_t (&total)[K], int32_t over)
+{
+    if (a.totals) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (k < a.report) a.totals[k] = total[k];
+        a.totals[a.report] = over;
+    }
+    a.over[0] = over;
+    if (!a.sized) a.mark[0] = a.key;
+}
+
+template <int K>
+__device__ __forceinline__ void pack_report_stale(const PackScan<K> &a)
+{
+    const int64_t none[K] = {};
+    pack_report(a, none, PACK_STALE);
+}
 
 template <int K>
 __global__ void __launch_bounds__(PACK_THREADS) pack_tiles(PackScan<K> a)
@@ -110,6 +147,7 @@ __global__ void __launch_bounds__(PACK_THREADS) pack_tiles(PackScan<K> a)
     __shared__ int64_t lds[K * PACK_THREADS];
     const int64_t r0 = (int64_t)blockIdx.x * PACK_TILE + (int64_t)threadIdx.x * PACK_ROWS_PER_THREAD;
     int64_t v[K];
+    if (pack_stale(a)) return;
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = 0;
     for (int j = 0; j < PACK_ROWS_PER_THREAD; ++j) {
@@ -131,6 +169,10 @@ __global__ void __launch_bounds__(1024) pack_top(PackScan<K> a, int64_t tiles)
 {
     __shared__ int64_t part[K][1024 / WAVE];
     __shared__ int64_t carry[K];
+    if (pack_stale(a)) {
+        if (threadIdx.x == 0) pack_report_stale(a);
+        return;
+    }
     if (threadIdx.x < K) carry[threadIdx.x] = 0;
     __syncthreads();
     for (int64_t base = 0; base < tiles; base += 1024) {
@@ -159,14 +201,14 @@ __global__ void __launch_bounds__(1024) pack_top(PackScan<K> a, int64_t tiles)
     }
     if (threadIdx.x == 0) {
         int32_t over = 0;
+        int64_t total[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            a.out[k][a.n] = carry[k];
-            over |= carry[k] > a.cap[k] ? 1 : 0;
-            if (a.totals && k < a.report) a.totals[k] = carry[k];
+            total[k] = carry[k];
+            a.out[k][a.n] = total[k];
+            over |= total[k] > a.cap[k] ? 1 : 0;
         }
-        if (a.totals) a.totals[a.report] = over;
-        a.over[0] = over;
+        pack_report(a, total, over);
     }
 }
 
@@ -176,6 +218,7 @@ __global__ void __launch_bounds__(PACK_THREADS) pack_rows(PackScan<K> a)
     __shared__ int64_t part[K][PACK_THREADS / WAVE];
     const int64_t r0 = (int64_t)blockIdx.x * PACK_TILE + (int64_t)threadIdx.x * PACK_ROWS_PER_THREAD;
     int64_t s[K], off[K];
+    if (pack_stale(a)) return;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         s[k] = 0;
@@ -217,7 +260,11 @@ __global__ void __launch_bounds__(PACK_THREADS) pack_single(PackScan<K> a)
 #pragma unroll
         for (int k = 0; k < K; ++k) v[j][k] = r0 + j < a.n ? a.vals[(r0 + j) * K + k] : 0;
     }
-    int64_t off[K];
+    if (pack_stale(a)) {
+        if (threadIdx.x == 0) pack_report_stale(a);
+        return;
+    }
+    int64_t off[K], total[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         int64_t s = 0;
@@ -231,26 +278,20 @@ __global__ void __launch_bounds__(PACK_THREADS) pack_single(PackScan<K> a)
     int32_t over = 0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        int64_t total = 0;
+        total[k] = 0;
         for (int w = 0; w < PACK_THREADS / WAVE; ++w) {
             if (w < wv) off[k] += part[k][w];
-            total += part[k][w];
+            total[k] += part[k][w];
         }
 #pragma unroll
         for (int j = 0; j < PACK_ROWS_PER_THREAD; ++j) {
             if (r0 + j < a.n) a.out[k][r0 + j] = off[k];
             off[k] += v[j][k];
         }
-        over |= total > a.cap[k] ? 1 : 0;
-        if (threadIdx.x == 0) {
-            a.out[k][a.n] = total;
-            if (a.totals && k < a.report) a.totals[k] = total;
-        }
+        over |= total[k] > a.cap[k] ? 1 : 0;
+        if (threadIdx.x == 0) a.out[k][a.n] = total[k];
     }
-    if (threadIdx.x == 0) {
-        if (a.totals) a.totals[a.report] = over;
-        a.over[0] = over;
-    }
+    if (threadIdx.x == 0) pack_report(a, total, over);
 }
 
 /* ---- fork --------------------------------------------------------------- */
@@ -345,7 +386,7 @@ __device__ __forceinline__ void outline_row(const ForkArgs &a, int64_t i, int64_
     int64_t o;
     if (WRITE) {
         const int64_t n_e = a.counts[3 * i];
-        if (a.status[i] != 0 || n_e == 0) return;
+        if (n_e == 0) return; /* also of a row whose status is not 0 */
         if (n_e <= SUMM_ENTRIES) {
             /* the first walk kept every entry of this outline: the records
              * without a second walk (lane k: entry k) */
@@ -711,6 +752,10 @@ __global__ void __launch_bounds__(FORK_REC_THREADS) fork_records(ForkArgs a, Pac
 #pragma unroll
         for (int k = 0; k < 3; ++k) v[j][k] = q0 + j < a.n ? a.counts[3 * (q0 + j) + k] : 0;
     }
+    if (pack_stale(ps)) {
+        if (blockIdx.x == gridDim.x - 1 && t == 0) pack_report_stale(ps);
+        return;
+    }
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         int64_t sum = 0;
@@ -747,10 +792,7 @@ __global__ void __launch_bounds__(FORK_REC_THREADS) fork_records(ForkArgs a, Pac
     if (blockIdx.x == gridDim.x - 1 && t == 0) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) ps.out[k][a.n] = total[k];
-        ps.totals[0] = total[0];
-        ps.totals[1] = total[1];
-        ps.totals[2] = over;
-        ps.over[0] = over;
+        pack_report(ps, total, over);
     }
     __syncthreads();
     const int64_t i = r0 + wv;
@@ -1089,8 +1131,13 @@ __global__ void __launch_bounds__(PACK_THREADS) join_copy(JoinArgs a, PackScan<1
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
             v[j] = r0 + j < a.n ? a.out_len64[r0 + j] : 0;
-            sum += v[j];
         }
+        if (pack_stale(ps)) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) pack_report_stale(ps);
+            return;
+        }
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) sum += v[j];
         const int64_t inc = wave_inclusive_scan(sum);
         if (lane == WAVE - 1) part[wv] = inc;
         __syncthreads();
@@ -1111,10 +1158,9 @@ __global__ void __launch_bounds__(PACK_THREADS) join_copy(JoinArgs a, PackScan<1
         if (threadIdx.x == 0) {
             soff[a.n] = total;
             if (blockIdx.x == 0) {
+                const int64_t totals[1] = {total};
                 ps.out[0][a.n] = total;
-                ps.totals[0] = total;
-                ps.totals[1] = over;
-                ps.over[0] = over;
+                pack_report(ps, totals, over);
             }
         }
         __syncthreads();

@@ -11,7 +11,8 @@
  * pattern first, so reliance on their contents or access past their ends
  * fails.
  *
- * Input (little endian): int32 mode (0 fork, 1 join), int32 tag_ids[12],
+ * Input (little endian): int32 mode (0 fork, 1 join; 2, 3: the same, then the
+ * sized calls, see sized_checks), int32 tag_ids[12],
  * uint32 cfg_flags, uint32 call_flags, int32 cus, int64 n, int64 n_tok, then
  * int32 tokens[n_tok], int64 starts[n], int32 lengths[n]; for a join also
  * int64 n_workers, int64 n_wtok, int64 worker_off[n + 1], int32
@@ -21,7 +22,8 @@
  * workers and T context tokens int64 ctx_starts[W], int32 ctx_lengths[W],
  * ctx_row[W], ctx_entry[W], ctx_kind[W], ctx_tokens[T]; join: int64
  * totals[2], uint32 row_status[n], int32 lengths[n], int64 starts[n + 1],
- * int32 tokens[totals[0]].
+ * int32 tokens[totals[0]].  In modes 2 and 3 the second status is
+ * sized_checks' result, and nothing follows it.
  */
 #include <cstdio>
 #include <cstdlib>
@@ -57,6 +59,67 @@ static void wr(FILE *o, const void *p, size_t n)
     if (n) fwrite(p, 1, n, o);
 }
 
+/* Sized calls (mode 2: fork, 3: join) on a workspace that holds a sizing call's
+ * results, another call's, or none; outs: every array a call writes, with its
+ * bytes.  A stale workspace gives the totals 0, ..., 2 and writes nothing else.
+ * Returns the first check that failed, 0 for none. */
+template <class Sizing, class Full, class Sized>
+static int sized_checks(Sizing sizing, Full full, Sized sized, size_t wsb, int64_t *totals, int report,
+                        const std::vector<std::pair<void *, size_t>> &outs)
+{
+    const auto snap = [&] {
+        std::vector<char> s;
+        for (const auto &o : outs) s.insert(s.end(), (char *)o.first, (char *)o.first + o.second);
+        return s;
+    };
+    const auto fill = [&](int c) {
+        for (const auto &o : outs) memset(o.first, c, o.second);
+    };
+    const auto stale = [&](void *ws, uint32_t other) {
+        const std::vector<char> before = snap();
+        for (int k = 0; k < report; ++k) totals[k] = -1;
+        totals[report] = -1;
+        if (sized(ws, other) != PARASON_OK) return false;
+        bool ok = totals[report] == 2;
+        for (int k = 0; k < report; ++k) ok = ok && totals[k] == 0;
+        return ok && before == snap();
+    };
+    int bad = 0;
+    char *ws = pattern<char>((int64_t)wsb);
+    if (full(ws) != PARASON_OK) bad = 1;
+    const std::vector<char> ref = snap();
+    free(ws);
+    /* a workspace no call has used */
+    ws = pattern<char>((int64_t)wsb);
+    if (!bad && !stale(ws, 0u)) bad = 2;
+    /* a sizing call's, with other flags; then with the same ones, twice */
+    fill(0x5a);
+    if (!bad && sizing(ws) != PARASON_OK) bad = 3;
+    if (!bad && !stale(ws, 1u)) bad = 4;
+    for (int k = 0; k < 2; ++k)
+        if (!bad && (sized(ws, 0u) != PARASON_OK || totals[report] != 0 || snap() != ref)) bad = 5;
+    /* an unrelated call in between, on rows of its own */
+    if (!bad) {
+        memset(ws + 16, 0xee, wsb - 16);
+        parason_config cfg;
+        memset(&cfg, 0, sizeof cfg);
+        for (int k = 0; k < 12; ++k) cfg.tag_ids[k] = 100 + k;
+        cfg.group_size = 1;
+        parason_handle *h = nullptr;
+        int64_t off[1] = {0}, t[3];
+        parason_fork_outputs o;
+        memset(&o, 0, sizeof o);
+        o.worker_off = off;
+        o.totals = t;
+        if (parason_create(&cfg, &h) != PARASON_OK ||
+            parason_fork(h, nullptr, nullptr, nullptr, 0, 0, &o, ws, wsb, nullptr) != PARASON_OK || !stale(ws, 0u))
+            bad = 6;
+        parason_destroy(h);
+    }
+    free(ws);
+    return bad;
+}
+
 int main(int argc, char **argv)
 {
     if (argc != 3) {
@@ -84,6 +147,8 @@ int main(int argc, char **argv)
     int64_t n_workers = 0, n_wtok = 0;
     int64_t *worker_off = nullptr, *wstarts = nullptr;
     int32_t *wtokens = nullptr, *wlengths = nullptr;
+    const bool sized = mode >= 2;
+    mode &= 1;
     if (mode == 1) {
         rd(f, &n_workers, 8);
         rd(f, &n_wtok, 8);
@@ -142,10 +207,23 @@ int main(int argc, char **argv)
             out.ctx_tokens = T ? ctok : nullptr;
             rc1 = parason_fork(h, tokens, starts, lengths, n, call_flags, &out, ws, wsb, nullptr);
             free(ws);
+            if (sized) {
+                parason_fork_outputs none = out;
+                none.max_workers = none.ctx_capacity = 0;
+                rc1 = sized_checks(
+                    [&](void *p) { return parason_fork(h, tokens, starts, lengths, n, call_flags, &none, p, wsb, nullptr); },
+                    [&](void *p) { return parason_fork(h, tokens, starts, lengths, n, call_flags, &out, p, wsb, nullptr); },
+                    [&](void *p, uint32_t x) {
+                        return parason_fork_sized(h, tokens, starts, lengths, n, call_flags ^ x, &out, p, wsb, nullptr);
+                    },
+                    wsb, totals, 2,
+                    {{status, (size_t)n * 4}, {woff, (size_t)(n + 1) * 8}, {cst, (size_t)W * 8}, {cln, (size_t)W * 4},
+                     {crow, (size_t)W * 4}, {cent, (size_t)W * 4}, {ckind, (size_t)W * 4}, {ctok, (size_t)T * 4}});
+            }
         }
         wr(o, &rc0, 4);
         wr(o, &rc1, 4);
-        wr(o, totals, sizeof totals);
+        if (!sized) wr(o, totals, sizeof totals);
         wr(o, status, (size_t)n * 4);
         wr(o, woff, (size_t)(n + 1) * 8);
         wr(o, cst, (size_t)W * 8);
@@ -186,10 +264,29 @@ int main(int argc, char **argv)
             rc1 = parason_join(h, tokens, starts, lengths, n, worker_off, wtokens, wstarts, wlengths, n_workers,
                                call_flags, &out, ws, wsb, nullptr);
             free(ws);
+            if (sized) {
+                parason_join_outputs none = out;
+                none.capacity = 0;
+                rc1 = sized_checks(
+                    [&](void *p) {
+                        return parason_join(h, tokens, starts, lengths, n, worker_off, wtokens, wstarts, wlengths,
+                                            n_workers, call_flags, &none, p, wsb, nullptr);
+                    },
+                    [&](void *p) {
+                        return parason_join(h, tokens, starts, lengths, n, worker_off, wtokens, wstarts, wlengths,
+                                            n_workers, call_flags, &out, p, wsb, nullptr);
+                    },
+                    [&](void *p, uint32_t x) {
+                        return parason_join_sized(h, tokens, starts, lengths, n, worker_off, wtokens, wstarts, wlengths,
+                                                  n_workers, call_flags ^ x, &out, p, wsb, nullptr);
+                    },
+                    wsb, totals, 1,
+                    {{status, (size_t)n * 4}, {olen, (size_t)n * 4}, {ost, (size_t)(n + 1) * 8}, {otok, (size_t)T * 4}});
+            }
         }
         wr(o, &rc0, 4);
         wr(o, &rc1, 4);
-        wr(o, totals, sizeof totals);
+        if (!sized) wr(o, totals, sizeof totals);
         wr(o, status, (size_t)n * 4);
         wr(o, olen, (size_t)n * 4);
         wr(o, ost, (size_t)(n + 1) * 8);

@@ -216,6 +216,27 @@ def test_emulated_fork_join_edges(emu):
     assert g["row_status"][1] & PX.PACK_BAD_ROW and g["lengths"][1] == 0
 
 
+@pytest.mark.parametrize("n", [200, 1032, 2056, 4200])
+def test_emulated_sized_calls(emu, n):
+    """parason_fork_sized and parason_join_sized, on both sides of the sizes
+    where their launches change: the outputs of a plain call after a sizing call,
+    and a status, with nothing else written, on a workspace that no call, a call
+    with other flags or another fork has left."""
+    rng = np.random.default_rng(n)
+    rows = short_rows(CONTIG, n, rng)
+    tok, st, ln = layout(rows, rng)
+    res, _, _, _ = oracle_fork(rows, CONTIG, True)
+    r = Reader(_run(emu, _header(2, CONTIG, 0, PX.FORK_SEED_ENTRY, 2, tok, st, ln), "/tmp"))
+    assert list(r.take(np.int32, 2)) == [PX.OK, 0]
+    wtok, wst, wln = layout(worker_sequences(res, CONTIG, rng, p_bad=0.05), rng)
+    payload = (_header(3, CONTIG, 0, F.JOIN_CLOSE_PARALLEL, 2, tok, st, ln)
+               + np.array([len(wst), wtok.size], np.int64).tobytes() + np.asarray(res["worker_off"], np.int64).tobytes()
+               + np.ascontiguousarray(wtok, np.int32).tobytes() + np.asarray(wst, np.int64).tobytes()
+               + np.asarray(wln, np.int32).tobytes())
+    r = Reader(_run(emu, payload, "/tmp"))
+    assert list(r.take(np.int32, 2)) == [PX.OK, 0]
+
+
 # ---------------------------------------------------------------- planted mistakes
 
 MUTANTS = {
