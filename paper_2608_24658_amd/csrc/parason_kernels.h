@@ -678,6 +678,12 @@ __device__ void run_deep_rows(const RowArgs &a, const uint8_t *__restrict__ mode
 
 constexpr int PAR_EVENTS = 512; /* events of a row rows_par holds in LDS */
 constexpr int PAR_LEVELS = 64;  /* nesting rows_par evaluates */
+/* Levels up to which par_row takes no lists of a level's events.  A list costs a
+ * pass over the row's events, the scans over them eight: 60,000 rows of 162 events
+ * in one level 226 us a call without and 241 with lists, of 502 events 345 and 376;
+ * 60,000 different rows of up to 10 levels 397 and 304, of up to 30 2,315 and 980,
+ * 60,000 equal rows nested 30 deep 1,495 and 902. */
+constexpr int PAR_DIRECT = 2;
 
 /* The classes that may follow state st (one bit per class). */
 constexpr uint32_t allowed_classes(uint32_t st)
@@ -855,31 +861,50 @@ __device__ __forceinline__ void par_seg_scan(int32_t (&v)[K], const ParHeads<K> 
     }
 }
 
+/* In X and in rows_quad an event is its class and, for a structural tag of a
+ * block (<Parallel>, </Outlines>, <Thread>, </Thread>, </Parallel>), that block's
+ * level (1 = top level; 0 for other tags), so that one compare finds the tags of
+ * a level.  depth: open blocks before the event. */
+__device__ __forceinline__ int32_t par_word(uint32_t c, int32_t depth)
+{
+    const bool own = (c == C_THR) | (c == C_END_THR) | (c == C_END_PAR) | (c == C_END_OUT);
+    const int32_t lev = c == C_PAR ? depth + 1 : (own ? depth : 0);
+    return (int32_t)(c | ((uint32_t)lev & 0xfffu) << 4);
+}
+__device__ __forceinline__ int32_t par_tag(uint32_t c, int32_t lev) { return (int32_t)c + lev * 16; }
+
+/* A level's list: the numbers of the events that are its tags, and, with
+ * PAR_INNER, of the </Parallel> of the blocks directly inside it. */
+constexpr uint32_t PAR_INNER = 1u << 15;
+typedef uint16_t __attribute__((may_alias)) half_t;
+
 /* The LDS of a wave that evaluates a row with its lanes over the row's events:
- * per event its position, its class with the depth and the open threads before
- * it (one word), and, while the levels are evaluated, a thread's tokens and a
- * block's saved tokens.  Until phase A the last two hold the map from event to
- * segment of the split-row gather.  8 KB per wave, so that 20 waves (rows) fit
- * a compute unit; with a word per quantity (16 KB) it was 10. */
+ * per event its position, its word (in the lower half of X; the upper halves
+ * hold a level's list), and, while the levels are evaluated, at a </Parallel> its
+ * block's saved tokens and the tokens of its threads.  Until phase A the last
+ * two hold the map from event to segment of the split-row gather.  8 KB per wave,
+ * so that 20 waves (rows) fit a compute unit; with a word per quantity (16 KB)
+ * it was 10. */
 struct ParLds {
     int32_t P[PAR_EVENTS];
-    int32_t X[PAR_EVENTS]; /* class | depth before << 4 | threads before << 16 */
+    int32_t X[PAR_EVENTS];
     int32_t TOK[PAR_EVENTS];
     int32_t SAV[PAR_EVENTS];
+    __device__ uint32_t entry(int32_t j) const { return reinterpret_cast<const half_t *>(X)[2 * j + 1]; }
+    __device__ void set_entry(int32_t j, uint32_t v) { reinterpret_cast<half_t *>(X)[2 * j + 1] = (half_t)v; }
+    __device__ int32_t pos(int32_t i) const { return P[i]; }
+    __device__ uint32_t cls(int32_t i) const { return (uint32_t)X[i] & 15u; }
 };
-constexpr int PAR_LDS = 4 * PAR_EVENTS; /* words */
-static_assert(PAR_EVENTS < (1 << 12), "depths and thread counts of a held row fit their fields");
+static_assert(PAR_EVENTS <= (int)PAR_INNER, "an event's number and the flag fit a half word");
+static_assert(PAR_LEVELS + 1 < (1 << 12), "a level fits its field");
 static_assert(PAR_EVENTS >= 2 * PAR_PASS, "the gather of a split row keeps two words per segment of a chunk in SAV");
 static_assert(MID_DEPTH * FRAME_WORDS <= PAR_EVENTS, "the automaton's frames fit TOK");
 
-/* The word of X.  In a valid row the depth and the open threads before a
- * structural tag of level lev are fixed (an outline and a <Thread> of a block
- * of level lev stand in lev blocks and lev - 1 threads, a </Thread> in lev of
- * both), so one compare with such a word finds the tags of a level. */
-__device__ __forceinline__ int32_t par_key(uint32_t c, int32_t depth, int32_t threads)
-{
-    return (int32_t)(c | ((uint32_t)depth & 0xfffu) << 4 | (uint32_t)threads << 16);
-}
+/* What a lane has found of its row so far. */
+struct ParSums {
+    int32_t sub, tri, saved;
+    bool mismatch;
+};
 
 /* The tags of one segment of the row at g, read again by the whole wave: the
  * vectors x (vector v0 + i * WAVE + lane), of which the positions inside the
@@ -893,6 +918,7 @@ __device__ __forceinline__ int32_t par_classify(const RowArgs &a, const int4 (&x
     for (int i = 0; i < LOADS; ++i) {
         const int32_t t[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
         const int32_t p0 = bias + 4 * (i * WAVE + lane); /* row position of the vector's first token */
+        if (bias + 4 * i * WAVE >= len) break;           /* wave-uniform: a short row's other vectors */
         uint32_t c[4];
         uint64_t b[4];
 #pragma unroll
@@ -931,6 +957,241 @@ __device__ __forceinline__ void par_load_segment(const RowArgs &a, int64_t vrow0
     for (int i = 0; i < LOADS; ++i) x[i] = src[min(vrow0 + k * SEG_VEC + i * WAVE + lane, vend - 1)];
 }
 
+/* The widths of rows_quad (and of a small level in par_row): QUAD_W lanes (one DPP row) per row, QUAD_K
+ * consecutive events per lane. */
+constexpr int QUAD_W = 16;
+constexpr int QUAD_K = 8;
+constexpr int QUAD_ROWS = WAVE / QUAD_W;
+constexpr int QUAD_EVENTS = QUAD_W * QUAD_K;
+
+/* Scans over the QUAD_W lanes of a row stay inside a DPP row: four shifts and
+ * no carries between rows of lanes. */
+template <class Op>
+__device__ __forceinline__ int32_t quad_lane_scan(int32_t v)
+{
+    v = Op::f(v, row_shr<1>(v, Op::ident));
+    v = Op::f(v, row_shr<2>(v, Op::ident));
+    v = Op::f(v, row_shr<4>(v, Op::ident));
+    return Op::f(v, row_shr<8>(v, Op::ident));
+}
+
+/* Value of the row's last lane, in all of its lanes. */
+__device__ __forceinline__ int32_t quad_last(int32_t v, int lane) { return __shfl(v, lane | (QUAD_W - 1), WAVE); }
+
+/* Inclusive scan over a row's events in order. */
+template <class Op, int K>
+__device__ __forceinline__ void quad_incl_scan(int32_t (&v)[K])
+{
+#pragma unroll
+    for (int k = 1; k < K; ++k) v[k] = Op::f(v[k - 1], v[k]);
+    const int32_t before = row_shr<1>(quad_lane_scan<Op>(v[K - 1]), Op::ident);
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = Op::f(before, v[k]);
+}
+
+/* Segment heads of a row's events, shared by the segmented scans over the
+ * same heads: seen[k], a head among the lane's events 0 .. k; at[i], a head in
+ * the 2^i lanes up to this one. */
+template <int K>
+struct QuadHeads {
+    bool seen[K];
+    bool at[4];
+};
+
+template <int K>
+__device__ __forceinline__ QuadHeads<K> quad_heads(const bool (&head)[K])
+{
+    QuadHeads<K> h;
+    h.seen[0] = head[0];
+#pragma unroll
+    for (int k = 1; k < K; ++k) h.seen[k] = h.seen[k - 1] | head[k];
+    int32_t f = h.seen[K - 1] ? 1 : 0;
+    h.at[0] = f != 0;
+    f |= row_shr<1>(f, 0);
+    h.at[1] = f != 0;
+    f |= row_shr<2>(f, 0);
+    h.at[2] = f != 0;
+    f |= row_shr<4>(f, 0);
+    h.at[3] = f != 0;
+    return h;
+}
+
+/* Segmented inclusive scan: restarts at heads; events before the first head
+ * hold what precedes it (unused).  Op::ident must be Op's identity on v. */
+template <class Op, int K>
+__device__ __forceinline__ void quad_seg_scan(int32_t (&v)[K], const bool (&head)[K], const QuadHeads<K> &h)
+{
+#pragma unroll
+    for (int k = 1; k < K; ++k) v[k] = head[k] ? v[k] : Op::f(v[k - 1], v[k]);
+    int32_t t = v[K - 1];
+    int32_t o = Op::f(row_shr<1>(t, Op::ident), t);
+    t = h.at[0] ? t : o;
+    o = Op::f(row_shr<2>(t, Op::ident), t);
+    t = h.at[1] ? t : o;
+    o = Op::f(row_shr<4>(t, Op::ident), t);
+    t = h.at[2] ? t : o;
+    o = Op::f(row_shr<8>(t, Op::ident), t);
+    t = h.at[3] ? t : o;
+    const int32_t in = row_shr<1>(t, Op::ident);
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = h.seen[k] ? v[k] : Op::f(in, v[k]);
+}
+
+/* A row's LDS in rows_quad: its events (row position << 4 | class), a level's list
+ * and, as in ParLds, what is kept at a </Parallel>. */
+struct QuadLds {
+    uint32_t ev[QUAD_EVENTS], list[QUAD_EVENTS];
+    int32_t SAV[QUAD_EVENTS], TOK[QUAD_EVENTS];
+    __device__ uint32_t entry(int32_t j) const { return list[j]; }
+    __device__ void set_entry(int32_t j, uint32_t v) { list[j] = v; }
+    __device__ int32_t pos(int32_t i) const { return (int32_t)(ev[i] >> 4); }
+    __device__ uint32_t cls(int32_t i) const { return ev[i] & 15u; }
+};
+static_assert(QUAD_ROWS * sizeof(QuadLds) <= sizeof(ParLds), "rows_quad keeps its events in par_row's LDS");
+
+/* One level of a row from its list of n <= K * QUAD_W entries, K consecutive ones
+ * per lane of a DPP row: its threads (tokens, latency, own tokens), then, from
+ * those values still in registers, its blocks (saved tokens, thread types, count
+ * mismatch).  l16: the lane among the row's; LDS is QuadLds or ParLds. */
+template <int K, class Lds>
+__device__ __forceinline__ void quad_level(Lds &l, int32_t n, bool top, int l16, ParSums &out)
+{
+    bool thr[K], ethr[K], par[K], epar[K];
+    int32_t id[K], at[K], S[K], CH[K], pi[K], oi[K], pos[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int32_t j = K * l16 + k;
+        const uint32_t q = j < n ? l.entry(j) : 0u;
+        const bool inner = (q & PAR_INNER) != 0;
+        id[k] = (int32_t)(q & (PAR_INNER - 1u));
+        const uint32_t c = j < n && !inner ? l.cls(id[k]) : 0u;
+        pos[k] = l.pos(id[k]);
+        thr[k] = c == C_THR;
+        ethr[k] = c == C_END_THR;
+        par[k] = c == C_PAR;
+        epar[k] = c == C_END_PAR;
+        at[k] = thr[k] ? pos[k] : -1;
+        S[k] = inner ? l.SAV[id[k]] : 0;
+        CH[k] = inner ? l.TOK[id[k]] : 0;
+        pi[k] = par[k] ? id[k] : -1;
+        oi[k] = c == C_END_OUT ? id[k] : -1;
+    }
+    quad_incl_scan<OpMax>(at); /* where the thread each entry is in begins */
+    const QuadHeads<K> ht = quad_heads(thr);
+    quad_seg_scan<OpAdd>(S, thr, ht);
+    quad_seg_scan<OpAdd>(CH, thr, ht);
+    quad_incl_scan<OpMax>(pi); /* the block each entry is in ... */
+    quad_incl_scan<OpMax>(oi); /* ... and its outline's end */
+    int32_t sum[K], mx[K], nt[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int32_t tok = ethr[k] ? pos[k] - at[k] + 1 : 0;
+        sum[k] = tok;
+        mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
+        CH[k] = tok - CH[k];              /* its own tokens */
+        nt[k] = ethr[k] ? 1 : 0;
+    }
+    const QuadHeads<K> hp = quad_heads(par);
+    quad_seg_scan<OpAdd>(sum, par, hp);
+    quad_seg_scan<OpMax>(mx, par, hp);
+    quad_seg_scan<OpAdd>(nt, par, hp);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
+        if (ethr[k]) {
+            const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
+            if (kk < n_e) {
+                const uint32_t t = l.cls(pi[k] + 2 + 2 * kk);
+                out.sub += t == C_SUB ? CH[k] : 0;
+                out.tri += t == C_TRI ? CH[k] : 0;
+            }
+        }
+        if (epar[k]) {
+            const int32_t saved = sum[k] - mx[k];
+            l.SAV[id[k]] = saved;
+            l.TOK[id[k]] = sum[k];
+            out.mismatch = out.mismatch || nt[k] != n_e;
+            out.saved += top ? saved : 0;
+        }
+    }
+}
+
+/* quad_level over the whole wave, in passes of K consecutive entries per lane. */
+template <int K>
+__device__ __forceinline__ void par_level(ParLds &l, int32_t n, bool top, int lane, ParSums &out)
+{
+    int32_t c_thr = -1, c_S = 0, c_CH = 0;
+    int32_t c_sum = 0, c_max = 0, c_n = 0, c_par = -1, c_eout = -1;
+    for (int32_t j0 = 0; j0 < n; j0 += K * WAVE) {
+        bool thr[K], ethr[K], par[K], epar[K];
+        int32_t id[K], at[K], S[K], CH[K], pi[K], oi[K], pos[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int32_t j = j0 + K * lane + k;
+            const uint32_t q = j < n ? l.entry(j) : 0u;
+            const bool inner = (q & PAR_INNER) != 0;
+            id[k] = (int32_t)(q & (PAR_INNER - 1u));
+            const uint32_t c = j < n && !inner ? l.cls(id[k]) : 0u;
+            pos[k] = l.pos(id[k]);
+            thr[k] = c == C_THR;
+            ethr[k] = c == C_END_THR;
+            par[k] = c == C_PAR;
+            epar[k] = c == C_END_PAR;
+            at[k] = thr[k] ? pos[k] : -1;
+            S[k] = inner ? l.SAV[id[k]] : 0;
+            CH[k] = inner ? l.TOK[id[k]] : 0;
+            pi[k] = par[k] ? id[k] : -1;
+            oi[k] = c == C_END_OUT ? id[k] : -1;
+        }
+        par_incl_scan<OpMax>(at, c_thr, lane); /* where the thread each entry is in begins */
+        const ParHeads<K> ht = par_heads(thr), hp = par_heads(par);
+        par_seg_scan<OpAdd>(S, ht, c_S, lane);
+        par_seg_scan<OpAdd>(CH, ht, c_CH, lane);
+        par_incl_scan<OpMax>(pi, c_par, lane);  /* the block each entry is in ... */
+        par_incl_scan<OpMax>(oi, c_eout, lane); /* ... and its outline's end */
+        int32_t sum[K], mx[K], nt[K], own[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int32_t tok = ethr[k] ? pos[k] - at[k] + 1 : 0;
+            sum[k] = tok;
+            mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
+            own[k] = tok - CH[k];
+            nt[k] = ethr[k] ? 1 : 0;
+        }
+        par_seg_scan<OpAdd>(sum, hp, c_sum, lane);
+        par_seg_scan<OpMax>(mx, hp, c_max, lane);
+        par_seg_scan<OpAdd>(nt, hp, c_n, lane);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
+            if (ethr[k]) {
+                const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
+                if (kk < n_e) {
+                    const uint32_t t = l.cls(pi[k] + 2 + 2 * kk);
+                    out.sub += t == C_SUB ? own[k] : 0;
+                    out.tri += t == C_TRI ? own[k] : 0;
+                }
+            }
+            if (epar[k]) {
+                const int32_t saved = sum[k] - mx[k];
+                l.SAV[id[k]] = saved;
+                l.TOK[id[k]] = sum[k];
+                out.mismatch = out.mismatch || nt[k] != n_e;
+                out.saved += top ? saved : 0;
+            }
+        }
+        if (n <= K * WAVE) break;
+        c_thr = lane63(at[K - 1]);
+        c_S = lane63(S[K - 1]);
+        c_CH = lane63(CH[K - 1]);
+        c_sum = lane63(sum[K - 1]);
+        c_max = lane63(mx[K - 1]);
+        c_n = lane63(nt[K - 1]);
+        c_par = lane63(pi[K - 1]);
+        c_eout = lane63(oi[K - 1]);
+    }
+}
+
 /* The two phases of par_row on the row's m events in LDS, K consecutive events
  * per lane and pass; SINGLE: one pass holds them (the scans then carry nothing
  * in).  One event per lane for rows of up to 64 (four of five of the
@@ -941,27 +1202,22 @@ template <bool LENIENT, int K, bool SINGLE>
 __device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r, int32_t len, int32_t m, int lane)
 {
     constexpr int PASS = K * WAVE;
-    /* phase A: validity, first error, depth and open threads before each event */
-    int32_t prev_c = -1, prev_p = -1, depth = 0, threads = 0, err = INT32_MAX, max_depth = 0, n_blocks = 0;
+    /* phase A: validity, first error, depth before each event */
+    int32_t prev_c = -1, prev_p = -1, depth = 0, err = INT32_MAX, max_depth = 0, n_blocks = 0;
     for (int32_t i0 = 0; i0 < m && err == INT32_MAX; i0 += PASS) {
         const int32_t ib = i0 + K * lane;
-        int32_t c[K], p[K], dd[K], dt[K];
+        int32_t c[K], p[K], dd[K];
         par_load(l.X, ib, c);
         par_load(l.P, ib, p);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             if (ib + k >= m) c[k] = p[k] = 0;
             dd[k] = ib + k < m ? (c[k] == C_PAR) - (c[k] == C_END_PAR) : 0;
-            dt[k] = ib + k < m ? (c[k] == C_THR) - (c[k] == C_END_THR) : 0;
         }
-        int32_t d_in[K], t_in[K]; /* depth and open threads after each event */
+        int32_t d_in[K]; /* depth after each event */
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            d_in[k] = dd[k];
-            t_in[k] = dt[k];
-        }
+        for (int k = 0; k < K; ++k) d_in[k] = dd[k];
         par_incl_scan<OpAdd>(d_in, depth, lane);
-        par_incl_scan<OpAdd>(t_in, threads, lane);
         int32_t pc = lane_before(c[K - 1], prev_c), pp = lane_before(p[K - 1], prev_p);
         int32_t e = INT32_MAX, open_depth = 0, pars = 0;
         int32_t xv[K];
@@ -969,7 +1225,7 @@ __device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r,
         for (int k = 0; k < K; ++k) {
             /* the checks of one event, without branches (bitwise, not
              * short-circuit: lanes hold different classes) */
-            const int32_t db = d_in[k] - dd[k], tb = t_in[k] - dt[k];
+            const int32_t db = d_in[k] - dd[k];
             const int32_t ck = c[k];
             const bool act = ib + k < m;
             const uint32_t st = state_at(pc);
@@ -983,8 +1239,7 @@ __device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r,
             e = min(e, act ? ek : INT32_MAX);
             open_depth = max(open_depth, opens ? db + 1 : 0);
             pars += opens ? 1 : 0;
-            /* counts of a row that goes on to phase B are not negative */
-            xv[k] = par_key((uint32_t)ck, db, tb);
+            xv[k] = par_word((uint32_t)ck, db);
             pc = c[k];
             pp = p[k];
         }
@@ -998,7 +1253,6 @@ __device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r,
         prev_p = __builtin_amdgcn_readlane(par_pick(p, last % K), last / K);
         if (SINGLE) break;
         depth = lane63(d_in[K - 1]);
-        threads = lane63(t_in[K - 1]);
     }
     if (err == INT32_MAX) {
         /* the end of the row: the text after the last tag, then </think> must have come */
@@ -1016,86 +1270,115 @@ __device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r,
     __syncthreads();
 
     /* phase B: level by level, deepest first */
-    int32_t my_sub = 0, my_tri = 0, my_saved = 0;
-    bool my_mismatch = false;
+    ParSums t{0, 0, 0, false};
     for (int32_t lev = max_depth; lev >= 1; --lev) {
-        /* one pass per level: the threads of level lev (tokens, latency, own
-         * tokens), then, from those values still in registers, the blocks of
-         * level lev (saved tokens, thread types, count mismatch) */
-        int32_t c_thr = -1, c_S = 0, c_CH = 0;
-        int32_t c_sum = 0, c_max = 0, c_n = 0, c_par = -1, c_eout = -1;
-        for (int32_t i0 = 0; i0 < m; i0 += PASS) {
-            const int32_t ib = i0 + K * lane;
-            int32_t x[K], sav[K], tk[K];
-            par_load(l.X, ib, x);
-            par_load(l.SAV, ib, sav);
-            par_load(l.TOK, ib, tk);
-            bool thr[K], ethr[K], par[K], epar[K];
-            int32_t ti[K], S[K], CH[K], pi[K], oi[K];
+        if (K == 1 || max_depth <= PAR_DIRECT) {
+            /* all of the row's events, as in par_level */
+            int32_t c_thr = -1, c_S = 0, c_CH = 0;
+            int32_t c_sum = 0, c_max = 0, c_n = 0, c_par = -1, c_eout = -1;
+            for (int32_t i0 = 0; i0 < m; i0 += PASS) {
+                const int32_t ib = i0 + K * lane;
+                int32_t x[K], sav[K], tk[K];
+                par_load(l.X, ib, x);
+                par_load(l.SAV, ib, sav);
+                par_load(l.TOK, ib, tk);
+                bool thr[K], ethr[K], par[K], epar[K];
+                int32_t ti[K], S[K], CH[K], pi[K], oi[K];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                /* phase A left class 0 in the places of the last pass past m */
-                thr[k] = x[k] == par_key(C_THR, lev, lev - 1);
-                ethr[k] = x[k] == par_key(C_END_THR, lev, lev);
-                par[k] = x[k] == par_key(C_PAR, lev - 1, lev - 1);
-                epar[k] = x[k] == par_key(C_END_PAR, lev, lev - 1);
-                ti[k] = thr[k] ? ib + k : -1;
-                S[k] = x[k] == par_key(C_END_PAR, lev + 1, lev) ? sav[k] : 0;
-                CH[k] = x[k] == par_key(C_END_THR, lev + 1, lev + 1) ? tk[k] : 0;
-                pi[k] = par[k] ? ib + k : -1;
-                oi[k] = x[k] == par_key(C_END_OUT, lev, lev - 1) ? ib + k : -1;
-            }
-            par_incl_scan<OpMax>(ti, c_thr, lane);  /* the thread each event is in */
-            const ParHeads<K> ht = par_heads(thr), hp = par_heads(par);
-            par_seg_scan<OpAdd>(S, ht, c_S, lane);
-            par_seg_scan<OpAdd>(CH, ht, c_CH, lane);
-            par_incl_scan<OpMax>(pi, c_par, lane);  /* the block each event is in ... */
-            par_incl_scan<OpMax>(oi, c_eout, lane); /* ... and its outline's end */
-            int32_t sum[K], mx[K], nt[K], own[K];
+                for (int k = 0; k < K; ++k) {
+                    /* phase A left class 0 in the places of the last pass past m */
+                    const int32_t w = x[k]; /* the upper halves are 0: no lists */
+                    const bool inner = w == par_tag(C_END_PAR, lev + 1);
+                    thr[k] = w == par_tag(C_THR, lev);
+                    ethr[k] = w == par_tag(C_END_THR, lev);
+                    par[k] = w == par_tag(C_PAR, lev);
+                    epar[k] = w == par_tag(C_END_PAR, lev);
+                    ti[k] = thr[k] ? ib + k : -1;
+                    S[k] = inner ? sav[k] : 0;
+                    CH[k] = inner ? tk[k] : 0;
+                    pi[k] = par[k] ? ib + k : -1;
+                    oi[k] = w == par_tag(C_END_OUT, lev) ? ib + k : -1;
+                }
+                par_incl_scan<OpMax>(ti, c_thr, lane); /* the thread each event is in */
+                const ParHeads<K> ht = par_heads(thr), hp = par_heads(par);
+                par_seg_scan<OpAdd>(S, ht, c_S, lane);
+                par_seg_scan<OpAdd>(CH, ht, c_CH, lane);
+                par_incl_scan<OpMax>(pi, c_par, lane); /* the block each event is in ... */
+                par_incl_scan<OpMax>(oi, c_eout, lane); /* ... and its outline's end */
+                int32_t sum[K], mx[K], nt[K], own[K];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int32_t tok = ethr[k] ? l.P[ib + k] - l.P[max(ti[k], 0)] + 1 : 0;
-                if (ethr[k]) l.TOK[ib + k] = tok; /* read by the next level's threads */
-                sum[k] = tok;
-                mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
-                own[k] = tok - CH[k];
-                nt[k] = ethr[k] ? 1 : 0;
-            }
-            par_seg_scan<OpAdd>(sum, hp, c_sum, lane);
-            par_seg_scan<OpMax>(mx, hp, c_max, lane);
-            par_seg_scan<OpAdd>(nt, hp, c_n, lane);
+                for (int k = 0; k < K; ++k) {
+                    const int32_t tok = ethr[k] ? l.P[ib + k] - l.P[max(ti[k], 0)] + 1 : 0;
+                    sum[k] = tok;
+                    mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
+                    own[k] = tok - CH[k];
+                    nt[k] = ethr[k] ? 1 : 0;
+                }
+                par_seg_scan<OpAdd>(sum, hp, c_sum, lane);
+                par_seg_scan<OpMax>(mx, hp, c_max, lane);
+                par_seg_scan<OpAdd>(nt, hp, c_n, lane);
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
-                if (ethr[k]) {
-                    const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
-                    if (kk < n_e) {
-                        const int32_t t = l.X[pi[k] + 2 + 2 * kk] & 15;
-                        my_sub += t == C_SUB ? own[k] : 0;
-                        my_tri += t == C_TRI ? own[k] : 0;
+                for (int k = 0; k < K; ++k) {
+                    const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
+                    if (ethr[k]) {
+                        const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
+                        if (kk < n_e) {
+                            const int32_t ty = l.X[pi[k] + 2 + 2 * kk] & 15;
+                            t.sub += ty == C_SUB ? own[k] : 0;
+                            t.tri += ty == C_TRI ? own[k] : 0;
+                        }
+                    }
+                    if (epar[k]) {
+                        const int32_t saved = sum[k] - mx[k];
+                        l.SAV[ib + k] = saved;
+                        l.TOK[ib + k] = sum[k];
+                        t.mismatch = t.mismatch || nt[k] != n_e;
+                        t.saved += lev == 1 ? saved : 0;
                     }
                 }
-                if (epar[k]) {
-                    const int32_t saved = sum[k] - mx[k];
-                    l.SAV[ib + k] = saved;
-                    my_mismatch = my_mismatch || nt[k] != n_e;
-                    my_saved += lev == 1 ? saved : 0;
-                }
+                if (SINGLE) break;
+                c_thr = lane63(ti[K - 1]);
+                c_S = lane63(S[K - 1]);
+                c_CH = lane63(CH[K - 1]);
+                c_sum = lane63(sum[K - 1]);
+                c_max = lane63(mx[K - 1]);
+                c_n = lane63(nt[K - 1]);
+                c_par = lane63(pi[K - 1]);
+                c_eout = lane63(oi[K - 1]);
             }
-            if (SINGLE) break;
-            c_thr = lane63(ti[K - 1]);
-            c_S = lane63(S[K - 1]);
-            c_CH = lane63(CH[K - 1]);
-            c_sum = lane63(sum[K - 1]);
-            c_max = lane63(mx[K - 1]);
-            c_n = lane63(nt[K - 1]);
-            c_par = lane63(pi[K - 1]);
-            c_eout = lane63(oi[K - 1]);
+        } else {
+            /* the level's events first, as a list, so that a level costs what it
+             * holds and not what the row holds */
+            int32_t n = 0;
+            for (int32_t i0 = 0; i0 < m; i0 += PASS) {
+                const int32_t ib = i0 + K * lane;
+                int32_t x[K], cnt = 0;
+                bool own[K], inner[K];
+                par_load(l.X, ib, x);
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    /* phase A left class 0 in the places of the last pass past m */
+                    const int32_t w = x[k] & 0xffff;
+                    own[k] = w >> 4 == lev;
+                    inner[k] = w == par_tag(C_END_PAR, lev + 1);
+                    cnt += own[k] | inner[k] ? 1 : 0;
+                }
+                const int32_t incl = dpp_incl_scan<OpAdd>(cnt, lane);
+                int32_t j = n + incl - cnt;
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+                    if (own[k] | inner[k]) l.set_entry(j++, (uint32_t)(ib + k) | (inner[k] ? PAR_INNER : 0u));
+                n += lane63(incl);
+            }
+            __syncthreads();
+            if (n <= QUAD_W) quad_level<1>(l, n, lev == 1, lane, t); /* in the first DPP row */
+            else if (n <= WAVE) par_level<1>(l, n, lev == 1, lane, t);
+            else par_level<PAR_K>(l, n, lev == 1, lane, t);
         }
         __syncthreads();
     }
-    const int32_t n_sub = wave_sum32(my_sub), n_tri = wave_sum32(my_tri), saved = wave_sum32(my_saved);
-    const bool mismatch = __ballot(my_mismatch) != 0;
+    const int32_t n_sub = wave_sum32(t.sub), n_tri = wave_sum32(t.tri), saved = wave_sum32(t.saved);
+    const bool mismatch = __ballot(t.mismatch) != 0;
     if (lane == 0) {
         uint32_t fl = PARASON_FLAG_VALID;
         if (mismatch) fl |= PARASON_FLAG_COUNT_MISMATCH;
@@ -1118,8 +1401,8 @@ __device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r,
  *     length less the saved tokens of its top-level blocks; a thread's own
  *     tokens (its tokens less those of the threads nested in it) take the
  *     type of the outline entry it pairs with.  Evaluated level by level,
- *     deepest first, with segmented scans, one pass over the events per
- *     level (phase B).
+ *     deepest first, with segmented scans (phase B): over the row's events where
+ *     it has few levels, else over a list of the level's own.
  * Returns false, with nothing written, for a row of more than PAR_EVENTS
  * events or nested deeper than PAR_LEVELS.  Split rows are read from their
  * segments' lists directly, and a segment whose list the scan could not store
@@ -1297,85 +1580,6 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
 
 /* ------------------------------------------------------------------ rows_quad */
 
-/* The widths of rows_quad: QUAD_W lanes (one DPP row) per row, QUAD_K
- * consecutive events per lane. */
-constexpr int QUAD_W = 16;
-constexpr int QUAD_K = 8;
-constexpr int QUAD_ROWS = WAVE / QUAD_W;
-constexpr int QUAD_EVENTS = QUAD_W * QUAD_K;
-static_assert(QUAD_ROWS * QUAD_EVENTS <= PAR_LDS, "rows_quad keeps its events in par_row's LDS");
-
-/* Scans over the QUAD_W lanes of a row stay inside a DPP row: four shifts and
- * no carries between rows of lanes. */
-template <class Op>
-__device__ __forceinline__ int32_t quad_lane_scan(int32_t v)
-{
-    v = Op::f(v, row_shr<1>(v, Op::ident));
-    v = Op::f(v, row_shr<2>(v, Op::ident));
-    v = Op::f(v, row_shr<4>(v, Op::ident));
-    return Op::f(v, row_shr<8>(v, Op::ident));
-}
-
-/* Value of the row's last lane, in all of its lanes. */
-__device__ __forceinline__ int32_t quad_last(int32_t v, int lane) { return __shfl(v, lane | (QUAD_W - 1), WAVE); }
-
-/* Inclusive scan over a row's events in order. */
-template <class Op>
-__device__ __forceinline__ void quad_incl_scan(int32_t (&v)[QUAD_K])
-{
-#pragma unroll
-    for (int k = 1; k < QUAD_K; ++k) v[k] = Op::f(v[k - 1], v[k]);
-    const int32_t before = row_shr<1>(quad_lane_scan<Op>(v[QUAD_K - 1]), Op::ident);
-#pragma unroll
-    for (int k = 0; k < QUAD_K; ++k) v[k] = Op::f(before, v[k]);
-}
-
-/* Segment heads of a row's events, shared by the segmented scans over the
- * same heads: seen[k], a head among the lane's events 0 .. k; at[i], a head in
- * the 2^i lanes up to this one. */
-struct QuadHeads {
-    bool seen[QUAD_K];
-    bool at[4];
-};
-
-__device__ __forceinline__ QuadHeads quad_heads(const bool (&head)[QUAD_K])
-{
-    QuadHeads h;
-    h.seen[0] = head[0];
-#pragma unroll
-    for (int k = 1; k < QUAD_K; ++k) h.seen[k] = h.seen[k - 1] | head[k];
-    int32_t f = h.seen[QUAD_K - 1] ? 1 : 0;
-    h.at[0] = f != 0;
-    f |= row_shr<1>(f, 0);
-    h.at[1] = f != 0;
-    f |= row_shr<2>(f, 0);
-    h.at[2] = f != 0;
-    f |= row_shr<4>(f, 0);
-    h.at[3] = f != 0;
-    return h;
-}
-
-/* Segmented inclusive scan: restarts at heads; events before the first head
- * hold what precedes it (unused).  Op::ident must be Op's identity on v. */
-template <class Op>
-__device__ __forceinline__ void quad_seg_scan(int32_t (&v)[QUAD_K], const bool (&head)[QUAD_K], const QuadHeads &h)
-{
-#pragma unroll
-    for (int k = 1; k < QUAD_K; ++k) v[k] = head[k] ? v[k] : Op::f(v[k - 1], v[k]);
-    int32_t t = v[QUAD_K - 1];
-    int32_t o = Op::f(row_shr<1>(t, Op::ident), t);
-    t = h.at[0] ? t : o;
-    o = Op::f(row_shr<2>(t, Op::ident), t);
-    t = h.at[1] ? t : o;
-    o = Op::f(row_shr<4>(t, Op::ident), t);
-    t = h.at[2] ? t : o;
-    o = Op::f(row_shr<8>(t, Op::ident), t);
-    t = h.at[3] ? t : o;
-    const int32_t in = row_shr<1>(t, Op::ident);
-#pragma unroll
-    for (int k = 0; k < QUAD_K; ++k) v[k] = h.seen[k] ? v[k] : Op::f(in, v[k]);
-}
-
 /* A larger batch: four rows per wave, sixteen lanes per row, eight consecutive
  * events per lane, so that a row of up to QUAD_EVENTS events (99 of 100 of the
  * generator's; the median row holds 38) stays in registers from its list to its
@@ -1393,7 +1597,8 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
 {
     __shared__ __align__(16) ParLds l;
     const int lane = threadIdx.x, l16 = lane & (QUAD_W - 1);
-    uint32_t *ev = reinterpret_cast<uint32_t *>(&l) + (lane / QUAD_W) * QUAD_EVENTS; /* the row's events */
+    QuadLds &ql = reinterpret_cast<QuadLds *>(&l)[lane / QUAD_W];
+    uint32_t *ev = ql.ev; /* the row's events */
     const int64_t r0 = (int64_t)blockIdx.x * QUAD_ROWS;
     const int64_t r = min(r0 + lane / QUAD_W, a.n - 1);
     /* the row's records in one round of loads, before any branch */
@@ -1477,16 +1682,15 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
     }
     __syncthreads();
 
-    /* phase A: validity, first error, depth and open threads before each event */
+    /* phase A: validity, first error, depth before each event */
     const int32_t ib = QUAD_K * l16;
-    int32_t key[QUAD_K], d_in[QUAD_K];
+    int32_t word[QUAD_K], d_in[QUAD_K], dd[QUAD_K];
 #pragma unroll
     for (int k = 0; k < QUAD_K; ++k) {
         if (ib + k >= m) e[k] = 0;
         const uint32_t c = e[k] & 15u;
-        /* depth in the low half, open threads in the high half */
-        d_in[k] = (c == C_PAR ? 1 : 0) - (c == C_END_PAR ? 1 : 0) + (c == C_THR ? 0x10000 : 0) - (c == C_END_THR ? 0x10000 : 0);
-        key[k] = d_in[k];
+        dd[k] = (c == C_PAR ? 1 : 0) - (c == C_END_PAR ? 1 : 0);
+        d_in[k] = dd[k];
     }
     quad_incl_scan<OpAdd>(d_in);
     int32_t err = INT32_MAX, max_depth = 0, n_blocks = 0;
@@ -1496,8 +1700,7 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
         int32_t pc = l16 == 0 ? -1 : (int32_t)(e_prev & 15u), pp = l16 == 0 ? -1 : (int32_t)(e_prev >> 4);
 #pragma unroll
         for (int k = 0; k < QUAD_K; ++k) {
-            const int32_t before = d_in[k] - key[k];
-            const int32_t db = (int32_t)(int16_t)before, tb = (before - db) >> 16;
+            const int32_t db = d_in[k] - dd[k];
             const int32_t ck = (int32_t)(e[k] & 15u), p = (int32_t)(e[k] >> 4);
             const bool act = ib + k < m;
             const uint32_t st = state_at(pc);
@@ -1511,7 +1714,7 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
             err = min(err, act ? ek : INT32_MAX);
             max_depth = max(max_depth, opens ? db + 1 : 0);
             n_blocks += opens ? 1 : 0;
-            key[k] = par_key((uint32_t)ck, db, tb);
+            word[k] = par_word((uint32_t)ck, db);
             pc = ck;
             pp = p;
         }
@@ -1532,72 +1735,39 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
     const bool valid = held && err == INT32_MAX;
     if (!valid) {
 #pragma unroll
-        for (int k = 0; k < QUAD_K; ++k) key[k] = 0; /* no structural tag of any level */
+        for (int k = 0; k < QUAD_K; ++k) word[k] = 0; /* no structural tag of any level */
         max_depth = 0;
     }
 
-    /* phase B: level by level, deepest first, as many as the wave's deepest row has */
-    int32_t my_sub = 0, my_tri = 0, my_saved = 0;
-    bool my_mismatch = false;
-    int32_t val[QUAD_K]; /* at a </Thread> its thread's tokens, at a </Parallel> its block's saved tokens */
-#pragma unroll
-    for (int k = 0; k < QUAD_K; ++k) val[k] = 0;
+    /* phase B: level by level, deepest first, as many as the wave's deepest row
+     * has; the level's events as a list first, so that a level costs what it holds
+     * and not what the row holds */
+    ParSums t{0, 0, 0, false};
     for (int32_t lev = wave_max32(max_depth); lev >= 1; --lev) {
-        bool thr[QUAD_K], par[QUAD_K];
-        int32_t at[QUAD_K], S[QUAD_K], CH[QUAD_K], pi[QUAD_K], oi[QUAD_K];
+        bool own[QUAD_K], inner[QUAD_K];
+        int32_t cnt = 0;
 #pragma unroll
         for (int k = 0; k < QUAD_K; ++k) {
-            thr[k] = key[k] == par_key(C_THR, lev, lev - 1);
-            par[k] = key[k] == par_key(C_PAR, lev - 1, lev - 1);
-            at[k] = thr[k] ? (int32_t)(e[k] >> 4) : -1;
-            S[k] = key[k] == par_key(C_END_PAR, lev + 1, lev) ? val[k] : 0;
-            CH[k] = key[k] == par_key(C_END_THR, lev + 1, lev + 1) ? val[k] : 0;
-            pi[k] = par[k] ? ib + k : -1;
-            oi[k] = key[k] == par_key(C_END_OUT, lev, lev - 1) ? ib + k : -1;
+            own[k] = word[k] >> 4 == lev;
+            inner[k] = word[k] == par_tag(C_END_PAR, lev + 1);
+            cnt += own[k] | inner[k] ? 1 : 0;
         }
-        quad_incl_scan<OpMax>(at); /* where the thread each event is in begins */
-        const QuadHeads ht = quad_heads(thr);
-        quad_seg_scan<OpAdd>(S, thr, ht);
-        quad_seg_scan<OpAdd>(CH, thr, ht);
-        quad_incl_scan<OpMax>(pi); /* the block each event is in ... */
-        quad_incl_scan<OpMax>(oi); /* ... and its outline's end */
-        int32_t sum[QUAD_K], mx[QUAD_K], nt[QUAD_K];
+        const int32_t incl = quad_lane_scan<OpAdd>(cnt);
+        int32_t j = incl - cnt;
 #pragma unroll
-        for (int k = 0; k < QUAD_K; ++k) {
-            const bool ethr = key[k] == par_key(C_END_THR, lev, lev);
-            const int32_t tok = ethr ? (int32_t)(e[k] >> 4) - at[k] + 1 : 0;
-            if (ethr) val[k] = tok; /* read by the next level's threads */
-            sum[k] = tok;
-            mx[k] = ethr ? tok - S[k] : 0; /* the thread's latency */
-            CH[k] = tok - CH[k];           /* its own tokens */
-            nt[k] = ethr ? 1 : 0;
-        }
-        const QuadHeads hp = quad_heads(par);
-        quad_seg_scan<OpAdd>(sum, par, hp);
-        quad_seg_scan<OpMax>(mx, par, hp);
-        quad_seg_scan<OpAdd>(nt, par, hp);
-#pragma unroll
-        for (int k = 0; k < QUAD_K; ++k) {
-            const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
-            if (key[k] == par_key(C_END_THR, lev, lev)) {
-                const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
-                if (kk < n_e) {
-                    const uint32_t t = ev[pi[k] + 2 + 2 * kk] & 15u;
-                    my_sub += t == C_SUB ? CH[k] : 0;
-                    my_tri += t == C_TRI ? CH[k] : 0;
-                }
-            }
-            if (key[k] == par_key(C_END_PAR, lev, lev - 1)) {
-                val[k] = sum[k] - mx[k];
-                my_mismatch = my_mismatch || nt[k] != n_e;
-                my_saved += lev == 1 ? val[k] : 0;
-            }
-        }
+        for (int k = 0; k < QUAD_K; ++k)
+            if (own[k] | inner[k]) ql.set_entry(j++, (uint32_t)(ib + k) | (inner[k] ? PAR_INNER : 0u));
+        const int32_t n = quad_last(incl, lane);
+        __syncthreads();
+        if (__ballot(n > QUAD_W) == 0) quad_level<1>(ql, n, lev == 1, l16, t);
+        else if (__ballot(n > 2 * QUAD_W) == 0) quad_level<2>(ql, n, lev == 1, l16, t);
+        else quad_level<QUAD_K>(ql, n, lev == 1, l16, t);
+        __syncthreads();
     }
-    const int32_t n_sub = quad_last(quad_lane_scan<OpAdd>(my_sub), lane);
-    const int32_t n_tri = quad_last(quad_lane_scan<OpAdd>(my_tri), lane);
-    const int32_t saved = quad_last(quad_lane_scan<OpAdd>(my_saved), lane);
-    const bool mismatch = ((uint32_t)(__ballot(my_mismatch) >> (lane & ~(QUAD_W - 1))) & 0xffffu) != 0;
+    const int32_t n_sub = quad_last(quad_lane_scan<OpAdd>(t.sub), lane);
+    const int32_t n_tri = quad_last(quad_lane_scan<OpAdd>(t.tri), lane);
+    const int32_t saved = quad_last(quad_lane_scan<OpAdd>(t.saved), lane);
+    const bool mismatch = ((uint32_t)(__ballot(t.mismatch) >> (lane & ~(QUAD_W - 1))) & 0xffffu) != 0;
     if (held && l16 == 0) {
         if (valid) {
             uint32_t fl = PARASON_FLAG_VALID;

@@ -105,6 +105,65 @@ def test_emulated_deep_rows_in_any_order(emu_small_pool, n, cus, flags):
         check_metrics(got["metrics"], rows, correct, R)
 
 
+def nested_stream(rng, k, depth, per_level=1):
+    """depth levels of blocks with k entries (and k threads, or one more or less
+    now and then), per_level of a block's threads holding a block of the next
+    level, so that a level's list holds 2 k + 3 tags per block and one more per
+    block directly inside."""
+    def block(d):
+        s = [GP.PAR, GP.OUT]
+        for _ in range(k):
+            o, c = (GP.SUB, GP.END_SUB) if rng.random() < 0.5 else (GP.TRI, GP.END_TRI)
+            s += [o] + [GP.TEXT] * int(rng.integers(1, 3)) + [c]
+        s += [GP.END_OUT]
+        n = max(1, k + int(rng.choice([0, 0, 0, 0, 1, -1])))
+        inside = set(rng.choice(n, min(n, per_level), replace=False).tolist()) if d > 1 else set()
+        for j in range(n):
+            s += [GP.THR] + [GP.TEXT] * int(rng.integers(0, 4)) + (block(d - 1) if j in inside else [])
+            s += [GP.TEXT] * int(rng.integers(0, 3)) + [GP.END_THR]
+        return s + [GP.END_PAR]
+    return [GP.THINK] + block(depth) + [GP.END_THINK]
+
+
+def list_streams():
+    """Rows whose levels' lists end at 16, 32, 64 and 128 entries and more, over
+    every number of events per lane and up to the deepest row a wave holds."""
+    rng = np.random.default_rng(17)
+    shapes = [(6, 3, 1), (7, 3, 1), (14, 3, 1), (15, 3, 1), (30, 3, 1), (31, 3, 1), (62, 3, 1), (1, 20, 1), (1, 21, 1),
+              (1, 62, 1), (1, 64, 1), (1, 65, 1), (2, 5, 2), (3, 4, 3), (2, 6, 2), (4, 3, 4), (5, 3, 4), (40, 2, 1),
+              (60, 2, 1), (9, 2, 9), (2, 3, 1), (2, 12, 1), (3, 8, 1), (4, 13, 1)]
+    return [nested_stream(rng, *x) for x in shapes for _ in range(4)]
+
+
+@pytest.mark.parametrize("cus", [MANY, FEW])
+def test_emulated_level_lists(emu_small_pool, cus):
+    """With most lists of the scan unstored and with all of them stored."""
+    streams = list_streams()
+    for gap in (0, 60):  # text after each row, so that its segments' share of the pool holds its tags
+        tokens, starts, lengths = pack([s + [GP.TEXT] * (gap * len(s)) for s in streams], TAGS)
+        correct = (np.arange(lengths.size) % 3 != 0).astype(np.uint8)
+        check(emu_small_pool, tokens, starts, lengths, correct, cus=cus, what="level lists cus %d" % cus)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1024, 20000])
+def test_level_lists_on_the_gpu(n):
+    import torch
+
+    streams = list_streams()
+    for gap in (0, 20):
+        tokens, starts, lengths = pack([s + [GP.TEXT] * (gap * len(s)) for s in streams], S.CONTIGUOUS_TAGS)
+        m = lengths.size
+        pick = np.arange(n) % m
+        co = (np.arange(n) % 3 != 0).astype(np.uint8)
+        px = PX.Parason(S.CONTIGUOUS_TAGS, group_size=G, **DEFAULT_COEF)
+        dev = [torch.as_tensor(x).cuda() for x in (tokens, starts[pick], lengths[pick], co)]
+        got = {k: v.cpu().numpy() for k, v in px.run(*dev, total_tokens=int(lengths[pick].astype(np.int64).sum())).items()}
+        got["flags"] = got["flags"].view(np.uint32)
+        compare(got, *oracle_expect(tokens, starts[pick], lengths[pick], co, S.CONTIGUOUS_TAGS, G, DEFAULT_COEF, 0),
+                what="level lists %d gap %d" % (n, gap))
+
+
 def oracle_latency(streams):
     tokens, starts, lengths = pack(streams, TAGS)
     return O.eval_rows(tokens, starts, lengths, TAGS)["latency"]
