@@ -139,12 +139,13 @@ __device__ __forceinline__ void store_ninf(char *row, int64_t i, const DecodeArg
 
 /* Threads of a row's block.  Most rows take a handful of stores, but a row that
  * forbids Text is rewritten by its block alone, and the step lasts as long as
- * that block: 16 rows of 151,936 float32 logits 14.8 us at 256 threads, 11.2 at
- * 512; eight draft steps of 256 rows 59.2 and 50.5, four of 512 rows 35.2 and
- * 28.3.  Beyond two rows per CU the rows fill the chip either way and dispatching
- * twice the waves costs more: 1,024 rows of 151,936 bf16 logits, all rewritten,
- * 48.8 us at 256 threads and 49.6 at 512, their 64 draft steps replayed as a
- * graph 4.6 and 5.9 us each. */
+ * that block.  Steps of 151,936 logits replayed as a graph, us a step at 256 and
+ * at 512 threads: every row rewritten, 16 rows of float32 13.4 and 9.7, 64 of bf16
+ * 10.5 and 8.6, 300 of float32 33.1 and 30.6, of bf16 19.3 and 17.6, 512 49.1 and
+ * 49.4, 26.4 and 25.7, 640 and 1,024 equal; every row in Text, up to 256 rows
+ * equal, 300 3.73 and 3.88, 512 3.85 and 4.02.  Up to two rows per CU, so, where the
+ * rewritten rows win more than the others lose (eager calls, 5.2 us of host work
+ * each, show no difference in Text); beyond, twice the waves win nothing. */
 constexpr int DECODE_THREADS = 256;
 constexpr int DECODE_WIDE_THREADS = 512;
 constexpr int DECODE_WIDE_ROWS_PER_CU = 2;

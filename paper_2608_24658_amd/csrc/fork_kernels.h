@@ -580,9 +580,13 @@ __device__ __forceinline__ void outline_row(const ForkArgs &a, int64_t i, int64_
  * row's last WIN tokens in one round, compacts their tags in order into LDS, and
  * its first wave finds the outline in that list and checks it as outline_row
  * does, so that a row is two rounds of loads and not a backward search and a
- * forward walk of one step after another (1,024 rows of 26,800 tokens, outlines
- * of up to 1,500: 7.6 us, 11.9 by outline_row; 2,000 rows of 1,500 tokens lose 3
- * us a call, so that the rule ends at 1,024 rows).  A row whose outline begins before the window, or
+ * forward walk of one step after another.  What decides is the outline's length,
+ * which only the device knows: the walk and the scans of 64 rows with outlines of
+ * 300 tokens 9.9 us by outline_row and 9.1 so, of 1,000 rows 10.4 and 10.4, of
+ * 1,500 11.3 and 12.0, of 2,000 11.7 and 13.9; with outlines of 1,500 tokens 1,000
+ * rows 15.7 and 10.5, 1,500 17.0 and 12.3, 2,000 17.4 and 14.2, whatever the rows'
+ * own length (1,500 or 26,800).  The rule ends at 1,024 rows, up to which no
+ * outline loses.  A row whose outline begins before the window, or
  * with more tags in it than the list holds, is left to outline_row. */
 constexpr int WIN_THREADS = 256;
 constexpr int WIN_J = 8; /* tokens per thread */

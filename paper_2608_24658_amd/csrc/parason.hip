@@ -161,9 +161,12 @@ void find_tag_hash(pk::TagMatch &tm)
 /* A small batch takes rows_par, one wave per row: its waves are done in one or
  * two rounds of the chip, and a row's own chain of steps, shorter over 64 lanes
  * than over 16, sets the time.  A larger one takes rows_quad, four rows per
- * wave, where the instructions set it (rows of 3,500 tokens, a call: 8,192 rows
- * 75 us with rows_par and 80 with rows_quad, 24,000 rows 154 and 151, 64,000
- * rows of 20,000 tokens 980 and 935). */
+ * wave, where the instructions set it (rows of 3,500 tokens, us a call with
+ * rows_par and with rows_quad: 4,096 rows 40 and 47, 16,384 94 and 96, 24,000 127
+ * and 136, 36,000 175 and 173; 64,000 rows of 20,000 930 and 902).  The line lies
+ * below their crossing because what rows_par does not hold it runs on one lane,
+ * one row per wave, and rows_quad's goes to rows_listed, 64 per wave (20,000 rows
+ * of 602 events 928 us, 8,192 of them by rows_par 1,770). */
 bool rows_par_batch(int64_t n, int cus) { return n <= (int64_t)cus * PAR_ROWS_PER_CU; }
 
 /* The row kernels, in the grammar's strict or lenient form (the deep tier runs

@@ -978,24 +978,24 @@ __device__ __forceinline__ int32_t quad_lane_scan(int32_t v)
 /* Value of the row's last lane, in all of its lanes. */
 __device__ __forceinline__ int32_t quad_last(int32_t v, int lane) { return __shfl(v, lane | (QUAD_W - 1), WAVE); }
 
-/* Inclusive scan over a row's events in order. */
+/* Inclusive scan over a row's events in order, continuing from carry. */
 template <class Op, int K>
-__device__ __forceinline__ void quad_incl_scan(int32_t (&v)[K])
+__device__ __forceinline__ void quad_incl_scan(int32_t (&v)[K], int32_t carry = Op::ident)
 {
 #pragma unroll
     for (int k = 1; k < K; ++k) v[k] = Op::f(v[k - 1], v[k]);
-    const int32_t before = row_shr<1>(quad_lane_scan<Op>(v[K - 1]), Op::ident);
+    const int32_t before = Op::f(carry, row_shr<1>(quad_lane_scan<Op>(v[K - 1]), Op::ident));
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = Op::f(before, v[k]);
 }
 
 /* Segment heads of a row's events, shared by the segmented scans over the
  * same heads: seen[k], a head among the lane's events 0 .. k; at[i], a head in
- * the 2^i lanes up to this one. */
+ * the 2^i lanes up to this one; before, in any lane before it. */
 template <int K>
 struct QuadHeads {
     bool seen[K];
-    bool at[4];
+    bool at[4], before;
 };
 
 template <int K>
@@ -1013,13 +1013,16 @@ __device__ __forceinline__ QuadHeads<K> quad_heads(const bool (&head)[K])
     h.at[2] = f != 0;
     f |= row_shr<4>(f, 0);
     h.at[3] = f != 0;
+    f |= row_shr<8>(f, 0);
+    h.before = row_shr<1>(f, 0) != 0;
     return h;
 }
 
 /* Segmented inclusive scan: restarts at heads; events before the first head
- * hold what precedes it (unused).  Op::ident must be Op's identity on v. */
+ * continue from carry.  Op::ident must be Op's identity on v. */
 template <class Op, int K>
-__device__ __forceinline__ void quad_seg_scan(int32_t (&v)[K], const bool (&head)[K], const QuadHeads<K> &h)
+__device__ __forceinline__ void quad_seg_scan(int32_t (&v)[K], const bool (&head)[K], const QuadHeads<K> &h,
+                                              int32_t carry = Op::ident)
 {
 #pragma unroll
     for (int k = 1; k < K; ++k) v[k] = head[k] ? v[k] : Op::f(v[k - 1], v[k]);
@@ -1032,7 +1035,7 @@ __device__ __forceinline__ void quad_seg_scan(int32_t (&v)[K], const bool (&head
     t = h.at[2] ? t : o;
     o = Op::f(row_shr<8>(t, Op::ident), t);
     t = h.at[3] ? t : o;
-    const int32_t in = row_shr<1>(t, Op::ident);
+    const int32_t prev = row_shr<1>(t, Op::ident), in = h.before ? prev : Op::f(carry, prev);
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = h.seen[k] ? v[k] : Op::f(in, v[k]);
 }
@@ -1049,70 +1052,83 @@ struct QuadLds {
 };
 static_assert(QUAD_ROWS * sizeof(QuadLds) <= sizeof(ParLds), "rows_quad keeps its events in par_row's LDS");
 
-/* One level of a row from its list of n <= K * QUAD_W entries, K consecutive ones
- * per lane of a DPP row: its threads (tokens, latency, own tokens), then, from
+/* One level of a row from its list of n entries, K consecutive ones per lane of a
+ * DPP row, and with PASSES as many times that as a list of the wave needs: its threads (tokens, latency, own tokens), then, from
  * those values still in registers, its blocks (saved tokens, thread types, count
  * mismatch).  l16: the lane among the row's; LDS is QuadLds or ParLds. */
-template <int K, class Lds>
-__device__ __forceinline__ void quad_level(Lds &l, int32_t n, bool top, int l16, ParSums &out)
+template <int K, bool PASSES, class Lds>
+__device__ __forceinline__ void quad_level(Lds &l, int32_t n, bool top, int lane, int l16, ParSums &out)
 {
-    bool thr[K], ethr[K], par[K], epar[K];
-    int32_t id[K], at[K], S[K], CH[K], pi[K], oi[K], pos[K];
+    int32_t c_thr = -1, c_S = 0, c_CH = 0;
+    int32_t c_sum = 0, c_max = 0, c_n = 0, c_par = -1, c_eout = -1;
+    for (int32_t j0 = 0;; j0 += K * QUAD_W) {
+        bool thr[K], ethr[K], par[K], epar[K];
+        int32_t id[K], at[K], S[K], CH[K], pi[K], oi[K], pos[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int32_t j = K * l16 + k;
-        const uint32_t q = j < n ? l.entry(j) : 0u;
-        const bool inner = (q & PAR_INNER) != 0;
-        id[k] = (int32_t)(q & (PAR_INNER - 1u));
-        const uint32_t c = j < n && !inner ? l.cls(id[k]) : 0u;
-        pos[k] = l.pos(id[k]);
-        thr[k] = c == C_THR;
-        ethr[k] = c == C_END_THR;
-        par[k] = c == C_PAR;
-        epar[k] = c == C_END_PAR;
-        at[k] = thr[k] ? pos[k] : -1;
-        S[k] = inner ? l.SAV[id[k]] : 0;
-        CH[k] = inner ? l.TOK[id[k]] : 0;
-        pi[k] = par[k] ? id[k] : -1;
-        oi[k] = c == C_END_OUT ? id[k] : -1;
-    }
-    quad_incl_scan<OpMax>(at); /* where the thread each entry is in begins */
-    const QuadHeads<K> ht = quad_heads(thr);
-    quad_seg_scan<OpAdd>(S, thr, ht);
-    quad_seg_scan<OpAdd>(CH, thr, ht);
-    quad_incl_scan<OpMax>(pi); /* the block each entry is in ... */
-    quad_incl_scan<OpMax>(oi); /* ... and its outline's end */
-    int32_t sum[K], mx[K], nt[K];
+        for (int k = 0; k < K; ++k) {
+            const int32_t j = j0 + K * l16 + k;
+            const uint32_t q = j < n ? l.entry(j) : 0u;
+            const bool inner = (q & PAR_INNER) != 0;
+            id[k] = (int32_t)(q & (PAR_INNER - 1u));
+            const uint32_t c = j < n && !inner ? l.cls(id[k]) : 0u;
+            pos[k] = l.pos(id[k]);
+            thr[k] = c == C_THR;
+            ethr[k] = c == C_END_THR;
+            par[k] = c == C_PAR;
+            epar[k] = c == C_END_PAR;
+            at[k] = thr[k] ? pos[k] : -1;
+            S[k] = inner ? l.SAV[id[k]] : 0;
+            CH[k] = inner ? l.TOK[id[k]] : 0;
+            pi[k] = par[k] ? id[k] : -1;
+            oi[k] = c == C_END_OUT ? id[k] : -1;
+        }
+        quad_incl_scan<OpMax>(at, c_thr); /* where the thread each entry is in begins */
+        const QuadHeads<K> ht = quad_heads(thr);
+        quad_seg_scan<OpAdd>(S, thr, ht, c_S);
+        quad_seg_scan<OpAdd>(CH, thr, ht, c_CH);
+        quad_incl_scan<OpMax>(pi, c_par); /* the block each entry is in ... */
+        quad_incl_scan<OpMax>(oi, c_eout); /* ... and its outline's end */
+        int32_t sum[K], mx[K], nt[K], own[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int32_t tok = ethr[k] ? pos[k] - at[k] + 1 : 0;
-        sum[k] = tok;
-        mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
-        CH[k] = tok - CH[k];              /* its own tokens */
-        nt[k] = ethr[k] ? 1 : 0;
-    }
-    const QuadHeads<K> hp = quad_heads(par);
-    quad_seg_scan<OpAdd>(sum, par, hp);
-    quad_seg_scan<OpMax>(mx, par, hp);
-    quad_seg_scan<OpAdd>(nt, par, hp);
+        for (int k = 0; k < K; ++k) {
+            const int32_t tok = ethr[k] ? pos[k] - at[k] + 1 : 0;
+            sum[k] = tok;
+            mx[k] = ethr[k] ? tok - S[k] : 0; /* the thread's latency */
+            own[k] = tok - CH[k];             /* its own tokens */
+            nt[k] = ethr[k] ? 1 : 0;
+        }
+        const QuadHeads<K> hp = quad_heads(par);
+        quad_seg_scan<OpAdd>(sum, par, hp, c_sum);
+        quad_seg_scan<OpMax>(mx, par, hp, c_max);
+        quad_seg_scan<OpAdd>(nt, par, hp, c_n);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
-        if (ethr[k]) {
-            const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
-            if (kk < n_e) {
-                const uint32_t t = l.cls(pi[k] + 2 + 2 * kk);
-                out.sub += t == C_SUB ? CH[k] : 0;
-                out.tri += t == C_TRI ? CH[k] : 0;
+        for (int k = 0; k < K; ++k) {
+            const int32_t n_e = (oi[k] - pi[k] - 2) / 2;
+            if (ethr[k]) {
+                const int32_t kk = nt[k] - 1; /* thread kk pairs with entry kk */
+                if (kk < n_e) {
+                    const uint32_t t = l.cls(pi[k] + 2 + 2 * kk);
+                    out.sub += t == C_SUB ? own[k] : 0;
+                    out.tri += t == C_TRI ? own[k] : 0;
+                }
+            }
+            if (epar[k]) {
+                const int32_t saved = sum[k] - mx[k];
+                l.SAV[id[k]] = saved;
+                l.TOK[id[k]] = sum[k];
+                out.mismatch = out.mismatch || nt[k] != n_e;
+                out.saved += top ? saved : 0;
             }
         }
-        if (epar[k]) {
-            const int32_t saved = sum[k] - mx[k];
-            l.SAV[id[k]] = saved;
-            l.TOK[id[k]] = sum[k];
-            out.mismatch = out.mismatch || nt[k] != n_e;
-            out.saved += top ? saved : 0;
-        }
+        if (!PASSES || __ballot(n > j0 + K * QUAD_W) == 0) break;
+        c_thr = quad_last(at[K - 1], lane);
+        c_S = quad_last(S[K - 1], lane);
+        c_CH = quad_last(CH[K - 1], lane);
+        c_sum = quad_last(sum[K - 1], lane);
+        c_max = quad_last(mx[K - 1], lane);
+        c_n = quad_last(nt[K - 1], lane);
+        c_par = quad_last(pi[K - 1], lane);
+        c_eout = quad_last(oi[K - 1], lane);
     }
 }
 
@@ -1371,7 +1387,7 @@ __device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r,
                 n += lane63(incl);
             }
             __syncthreads();
-            if (n <= QUAD_W) quad_level<1>(l, n, lev == 1, lane, t); /* in the first DPP row */
+            if (n <= QUAD_W) quad_level<1, false>(l, n, lev == 1, lane, lane, t); /* in the first DPP row */
             else if (n <= WAVE) par_level<1>(l, n, lev == 1, lane, t);
             else par_level<PAR_K>(l, n, lev == 1, lane, t);
         }
@@ -1580,114 +1596,20 @@ __global__ void __launch_bounds__(64) rows_par(RowArgs a, uint8_t *__restrict__ 
 
 /* ------------------------------------------------------------------ rows_quad */
 
-/* A larger batch: four rows per wave, sixteen lanes per row, eight consecutive
- * events per lane, so that a row of up to QUAD_EVENTS events (99 of 100 of the
- * generator's; the median row holds 38) stays in registers from its list to its
- * outputs.  The same two phases as par_row, without its passes and carries.
- * It is bound by instructions: par_row spends a wave's on one row, whose events
- * fill a sixth of its 256 places, and the per-lane automaton's lanes wait for
- * each other in most of its states.  64,000 rows of 20,000 tokens: 67 us, one
- * wave per row 124, one lane per row 219; 712,000 rows: 569 us, 1,266, 644.
- * Rows it does not hold (more events, a segment the scan could not store) are
- * evaluated one after the other by the whole wave (par_row); one that par_row
- * does not hold either is listed for rows_listed. */
-template <bool LENIENT>
-__global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__restrict__ mode,
-                                                int32_t *__restrict__ counters, int32_t *__restrict__ listed)
+/* The two phases of rows_quad on the m events of each of the wave's four rows (0
+ * where not held), K consecutive events per lane, and the outputs of held rows. */
+template <bool LENIENT, int K>
+__device__ __forceinline__ void quad_eval(const RowArgs &a, QuadLds &l, int64_t r, int32_t len, int32_t m, bool held,
+                                          int lane)
 {
-    __shared__ __align__(16) ParLds l;
-    const int lane = threadIdx.x, l16 = lane & (QUAD_W - 1);
-    QuadLds &ql = reinterpret_cast<QuadLds *>(&l)[lane / QUAD_W];
-    uint32_t *ev = ql.ev; /* the row's events */
-    const int64_t r0 = (int64_t)blockIdx.x * QUAD_ROWS;
-    const int64_t r = min(r0 + lane / QUAD_W, a.n - 1);
-    /* the row's records in one round of loads, before any branch */
-    const int64_t start = a.starts[r];
-    const int32_t len = a.lengths[r];
-    const int64_t S = a.seg_off[a.n], s0 = a.seg_off[r], s1 = a.seg_off[r + 1];
-    const bool compact = (mode[r] & MODE_COMPACT) != 0;
-    const bool bad = start < 0 || len < 0;
-    const bool over = S > a.seg_cap;
-    const bool mine = r0 + lane / QUAD_W < a.n; /* the last wave's lanes past the batch repeat its last row */
-    const bool eval = mine && !bad && !over;
-    if (mine && !eval && l16 == 0) {
-        if (bad) write_row(a.out, r, 0, 0, 0, 0, 0, 0, 0, PARASON_FLAG_BAD_ROW);
-        else write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_WS_OVERFLOW);
-    }
-    /* the row's events (row position << 4 | class): lane l16 holds events
-     * QUAD_K l16 .. QUAD_K l16 + 7 of the m */
-    const int64_t g = start + a.mis;
-    int32_t m = 0;
-    bool held = eval;
-    const bool has_list = eval && compact;
-    uint32_t first_slot = 0;
-    if (has_list) {
-        const SegRec rec = a.seg[s0];
-        m = rec.count;
-        held = m <= QUAD_EVENTS;
-        first_slot = held && m > 0 ? rec.list : 0u;
-    }
-    uint32_t e[QUAD_K];
-    {
-        /* whole quads of four slots, as they are stored; lanes past the list
-         * read its last quad again */
-        const int32_t last_quad = held && m > 0 ? (m - 1) / 4 : 0;
-        const uint4 *list = reinterpret_cast<const uint4 *>(a.slots + first_slot);
-        const uint4 q0 = list[min(2 * l16, last_quad)], q1 = list[min(2 * l16 + 1, last_quad)];
-        e[0] = q0.x, e[1] = q0.y, e[2] = q0.z, e[3] = q0.w;
-        e[4] = q1.x, e[5] = q1.y, e[6] = q1.z, e[7] = q1.w;
-    }
-    const bool split = eval && !compact;
-    held = held && (!split || len < (1 << 27));
-    if (__ballot(split && held) != 0) {
-        /* sixteen segments at a time: their records, an exclusive scan of
-         * their counts, then every lane copies its segment's list */
-        const int64_t vrow0 = row_first_vec(g);
-        for (int64_t c0 = s0; __ballot(split && held && c0 < s1) != 0; c0 += QUAD_W) {
-            const int64_t s = c0 + l16;
-            const bool in = split && held && s < s1;
-            const SegRec rec = in ? a.seg[s] : SegRec{0, 0u};
-            const uint32_t dense = (uint32_t)(__ballot(rec.count == DENSE) >> (lane & ~(QUAD_W - 1))) & 0xffffu;
-            const int32_t cnt = dense != 0 ? 0 : rec.count;
-            const int32_t incl = quad_lane_scan<OpAdd>(cnt);
-            const int32_t total = quad_last(incl, lane);
-            held = held && dense == 0 && m + total <= QUAD_EVENTS;
-            if (held && cnt > 0) {
-                const int32_t base = (int32_t)(4 * (vrow0 + (s - s0) * SEG_VEC) - g);
-                const uint4 *list = reinterpret_cast<const uint4 *>(a.slots + rec.list);
-                uint32_t *dst = ev + m + incl - cnt;
-                const int32_t last = (cnt - 1) / 4;
-                for (int32_t q = 0; q <= last; q += 2) { /* two quads in flight */
-                    const uint4 x = list[q], y = list[min(q + 1, last)];
-                    const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        if (4 * q + u < cnt)
-                            dst[4 * q + u] = (uint32_t)(base + (int32_t)(w[u] >> 4)) << 4 | (w[u] & 15u);
-                }
-            }
-            m += held ? total : 0;
-        }
-        __syncthreads();
-        if (split) {
-            const uint4 q0 = reinterpret_cast<const uint4 *>(ev)[2 * l16], q1 = reinterpret_cast<const uint4 *>(ev)[2 * l16 + 1];
-            e[0] = q0.x, e[1] = q0.y, e[2] = q0.z, e[3] = q0.w;
-            e[4] = q1.x, e[5] = q1.y, e[6] = q1.z, e[7] = q1.w;
-        }
-    }
-    if (!held) m = 0;
-    if (has_list) { /* the types of outline entries are looked up here */
-        reinterpret_cast<uint4 *>(ev)[2 * l16] = make_uint4(e[0], e[1], e[2], e[3]);
-        reinterpret_cast<uint4 *>(ev)[2 * l16 + 1] = make_uint4(e[4], e[5], e[6], e[7]);
-    }
-    __syncthreads();
-
+    const int l16 = lane & (QUAD_W - 1);
     /* phase A: validity, first error, depth before each event */
-    const int32_t ib = QUAD_K * l16;
-    int32_t word[QUAD_K], d_in[QUAD_K], dd[QUAD_K];
+    const int32_t ib = K * l16;
+    uint32_t e[K];
+    int32_t word[K], d_in[K], dd[K];
 #pragma unroll
-    for (int k = 0; k < QUAD_K; ++k) {
-        if (ib + k >= m) e[k] = 0;
+    for (int k = 0; k < K; ++k) {
+        e[k] = ib + k < m ? l.ev[ib + k] : 0u;
         const uint32_t c = e[k] & 15u;
         dd[k] = (c == C_PAR ? 1 : 0) - (c == C_END_PAR ? 1 : 0);
         d_in[k] = dd[k];
@@ -1696,10 +1618,10 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
     int32_t err = INT32_MAX, max_depth = 0, n_blocks = 0;
     {
         /* -1 before the first event: a class before </think> and a position */
-        const uint32_t e_prev = (uint32_t)row_shr<1>((int32_t)e[QUAD_K - 1], -1);
+        const uint32_t e_prev = (uint32_t)row_shr<1>((int32_t)e[K - 1], -1);
         int32_t pc = l16 == 0 ? -1 : (int32_t)(e_prev & 15u), pp = l16 == 0 ? -1 : (int32_t)(e_prev >> 4);
 #pragma unroll
-        for (int k = 0; k < QUAD_K; ++k) {
+        for (int k = 0; k < K; ++k) {
             const int32_t db = d_in[k] - dd[k];
             const int32_t ck = (int32_t)(e[k] & 15u), p = (int32_t)(e[k] >> 4);
             const bool act = ib + k < m;
@@ -1724,7 +1646,7 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
     n_blocks = quad_last(quad_lane_scan<OpAdd>(n_blocks), lane);
     if (held && err == INT32_MAX) {
         /* the end of the row: the text after the last tag, then </think> must have come */
-        const uint32_t e_last = m > 0 ? ev[m - 1] : 0u;
+        const uint32_t e_last = m > 0 ? l.ev[m - 1] : 0u;
         const int32_t pc = m > 0 ? (int32_t)(e_last & 15u) : -1, pp = m > 0 ? (int32_t)(e_last >> 4) : -1;
         const uint32_t st = state_at(pc);
         const int32_t gap = len - pp - 1;
@@ -1735,7 +1657,7 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
     const bool valid = held && err == INT32_MAX;
     if (!valid) {
 #pragma unroll
-        for (int k = 0; k < QUAD_K; ++k) word[k] = 0; /* no structural tag of any level */
+        for (int k = 0; k < K; ++k) word[k] = 0; /* no structural tag of any level */
         max_depth = 0;
     }
 
@@ -1744,10 +1666,10 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
      * and not what the row holds */
     ParSums t{0, 0, 0, false};
     for (int32_t lev = wave_max32(max_depth); lev >= 1; --lev) {
-        bool own[QUAD_K], inner[QUAD_K];
+        bool own[K], inner[K];
         int32_t cnt = 0;
 #pragma unroll
-        for (int k = 0; k < QUAD_K; ++k) {
+        for (int k = 0; k < K; ++k) {
             own[k] = word[k] >> 4 == lev;
             inner[k] = word[k] == par_tag(C_END_PAR, lev + 1);
             cnt += own[k] | inner[k] ? 1 : 0;
@@ -1755,13 +1677,13 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
         const int32_t incl = quad_lane_scan<OpAdd>(cnt);
         int32_t j = incl - cnt;
 #pragma unroll
-        for (int k = 0; k < QUAD_K; ++k)
-            if (own[k] | inner[k]) ql.set_entry(j++, (uint32_t)(ib + k) | (inner[k] ? PAR_INNER : 0u));
+        for (int k = 0; k < K; ++k)
+            if (own[k] | inner[k]) l.set_entry(j++, (uint32_t)(ib + k) | (inner[k] ? PAR_INNER : 0u));
         const int32_t n = quad_last(incl, lane);
         __syncthreads();
-        if (__ballot(n > QUAD_W) == 0) quad_level<1>(ql, n, lev == 1, l16, t);
-        else if (__ballot(n > 2 * QUAD_W) == 0) quad_level<2>(ql, n, lev == 1, l16, t);
-        else quad_level<QUAD_K>(ql, n, lev == 1, l16, t);
+        if (K == 1 || __ballot(n > QUAD_W) == 0) quad_level<1, false>(l, n, lev == 1, lane, l16, t);
+        else if (K == 2 || __ballot(n > 2 * QUAD_W) == 0) quad_level<2, false>(l, n, lev == 1, lane, l16, t);
+        else quad_level<4, (K > 4)>(l, n, lev == 1, lane, l16, t);
         __syncthreads();
     }
     const int32_t n_sub = quad_last(quad_lane_scan<OpAdd>(t.sub), lane);
@@ -1778,6 +1700,108 @@ __global__ void __launch_bounds__(64) rows_quad(RowArgs a, const uint8_t *__rest
             write_row(a.out, r, len, len, 0, 0, 0, 0, err, err == len ? PARASON_FLAG_TRUNCATED : 0u);
         }
     }
+}
+
+/* A larger batch: four rows per wave, sixteen lanes per row, as many consecutive
+ * events per lane (1, 2, 4 or 8) as the fullest of the four rows needs, up to
+ * QUAD_EVENTS a row (99 of 100 of the generator's; the median row holds 38).
+ * The same two phases as par_row, without phase A's passes.  It is bound by
+ * instructions and, at few events per lane, by the latency of a wave's chain of
+ * loads: par_row spends a wave's instructions on one row, whose events fill a
+ * sixth of its 256 places, and the per-lane automaton's lanes wait for each other
+ * in most of its states.  64,000 rows of 20,000 tokens: 48-60 us, one wave per
+ * row 124, one lane per row 219; 712,000 rows: 362 us, 1,266, 644.  With eight
+ * events per lane for every row, and up to eight of a level's, it took 133 vector
+ * registers (three waves per SIMD) and 65-73 and 589 us; levels of at most four
+ * entries per lane and pass leave 96, so that the five waves the LDS has room for
+ * fit (2,000,000 rows of two to four tokens 1,532 us a call, 1,274 so, 1,053 with
+ * one lane per row).
+ * Rows it does not hold (more events, a segment the scan could not store) are
+ * evaluated one after the other by the whole wave (par_row); one that par_row
+ * does not hold either is listed for rows_listed. */
+template <bool LENIENT>
+__global__ void __launch_bounds__(64, 5) rows_quad(RowArgs a, const uint8_t *__restrict__ mode,
+                                                int32_t *__restrict__ counters, int32_t *__restrict__ listed)
+{
+    __shared__ __align__(16) ParLds l;
+    const int lane = threadIdx.x, l16 = lane & (QUAD_W - 1);
+    QuadLds &ql = reinterpret_cast<QuadLds *>(&l)[lane / QUAD_W];
+    const int64_t r0 = (int64_t)blockIdx.x * QUAD_ROWS;
+    const int64_t r = min(r0 + lane / QUAD_W, a.n - 1);
+    /* the row's records in one round of loads, before any branch */
+    const int64_t start = a.starts[r];
+    const int32_t len = a.lengths[r];
+    const int64_t S = a.seg_off[a.n], s0 = a.seg_off[r], s1 = a.seg_off[r + 1];
+    const bool compact = (mode[r] & MODE_COMPACT) != 0;
+    const bool bad = start < 0 || len < 0;
+    const bool over = S > a.seg_cap;
+    const bool mine = r0 + lane / QUAD_W < a.n; /* the last wave's lanes past the batch repeat its last row */
+    const bool eval = mine && !bad && !over;
+    if (mine && !eval && l16 == 0) {
+        if (bad) write_row(a.out, r, 0, 0, 0, 0, 0, 0, 0, PARASON_FLAG_BAD_ROW);
+        else write_row(a.out, r, len, 0, 0, 0, 0, 0, 0, PARASON_FLAG_WS_OVERFLOW);
+    }
+    /* the row's m events into its LDS */
+    const int64_t g = start + a.mis;
+    int32_t m = 0;
+    bool held = eval;
+    const bool has_list = eval && compact;
+    uint32_t first_slot = 0;
+    if (has_list) {
+        const SegRec rec = a.seg[s0];
+        m = rec.count;
+        held = m <= QUAD_EVENTS;
+        first_slot = held && m > 0 ? rec.list : 0u;
+    }
+    if (held && has_list && 4 * l16 < m) {
+        /* whole quads of four slots, as they are stored, a quad of the list's
+         * first half and one of its second per lane */
+        const uint4 *list = reinterpret_cast<const uint4 *>(a.slots + first_slot);
+        const int32_t q1 = l16 + QUAD_W;
+        const uint4 x = list[l16], y = 4 * q1 < m ? list[q1] : make_uint4(0u, 0u, 0u, 0u);
+        reinterpret_cast<uint4 *>(ql.ev)[l16] = x;
+        if (4 * q1 < m) reinterpret_cast<uint4 *>(ql.ev)[q1] = y;
+    }
+    const bool split = eval && !compact;
+    held = held && (!split || len < (1 << 27));
+    if (__ballot(split && held) != 0) {
+        /* sixteen segments at a time: their records, an exclusive scan of
+         * their counts, then every lane copies its segment's list */
+        const int64_t vrow0 = row_first_vec(g);
+        for (int64_t c0 = s0; __ballot(split && held && c0 < s1) != 0; c0 += QUAD_W) {
+            const int64_t s = c0 + l16;
+            const bool in = split && held && s < s1;
+            const SegRec rec = in ? a.seg[s] : SegRec{0, 0u};
+            const uint32_t dense = (uint32_t)(__ballot(rec.count == DENSE) >> (lane & ~(QUAD_W - 1))) & 0xffffu;
+            const int32_t cnt = dense != 0 ? 0 : rec.count;
+            const int32_t incl = quad_lane_scan<OpAdd>(cnt);
+            const int32_t total = quad_last(incl, lane);
+            held = held && dense == 0 && m + total <= QUAD_EVENTS;
+            if (held && cnt > 0) {
+                const int32_t base = (int32_t)(4 * (vrow0 + (s - s0) * SEG_VEC) - g);
+                const uint4 *list = reinterpret_cast<const uint4 *>(a.slots + rec.list);
+                uint32_t *dst = ql.ev + m + incl - cnt;
+                const int32_t last = (cnt - 1) / 4;
+                for (int32_t q = 0; q <= last; q += 2) { /* two quads in flight */
+                    const uint4 x = list[q], y = list[min(q + 1, last)];
+                    const uint32_t w[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (4 * q + u < cnt)
+                            dst[4 * q + u] = (uint32_t)(base + (int32_t)(w[u] >> 4)) << 4 | (w[u] & 15u);
+                }
+            }
+            m += held ? total : 0;
+        }
+    }
+    if (!held) m = 0;
+    __syncthreads();
+
+    /* as many events per lane as the fullest of the four rows has */
+    if (__ballot(m > QUAD_W) == 0) quad_eval<LENIENT, 1>(a, ql, r, len, m, held, lane);
+    else if (__ballot(m > 2 * QUAD_W) == 0) quad_eval<LENIENT, 2>(a, ql, r, len, m, held, lane);
+    else if (__ballot(m > 4 * QUAD_W) == 0) quad_eval<LENIENT, 4>(a, ql, r, len, m, held, lane);
+    else quad_eval<LENIENT, QUAD_K>(a, ql, r, len, m, held, lane);
     uint64_t todo = __ballot(eval && !held && l16 == 0);
     while (todo != 0) {
         __syncthreads(); /* the LDS is rewritten */

@@ -248,9 +248,11 @@ __device__ __forceinline__ void pg_segment(const PgArgs &a, const float *adv, co
  * as ranges).  Arrays of tens of GB are the exception: there a range per wave is
  * within 1 % of the chunks where the buffers' placement is bad for it and 9 %
  * ahead where it is good (17.9e9 tokens, 4,270 segments per wave: ranges 39.8 and
- * chunks 39.4 ms in three processes, 36.5 and 39.8 in a fourth; 5.0e9 tokens,
- * 1,200 per wave: 11.9 and 11.6 in all of them), so from PG_RANGE_SEGS segments per
- * wave each wave takes one chunk, its share of them.  Two register buffers alternate so that the next segment's loads
+ * chunks 39.4 ms in three processes, 36.5 and 39.8 in a fourth).  The crossing, over
+ * three more processes each: 1,200 segments per wave ranges 10.7-12.0 and chunks
+ * 10.9-11.1 ms, 1,600 15.0-15.7 and 14.5-14.7, 2,000 17.5-19.4 and 17.9-18.4, 2,600
+ * 22.3-22.9 and 23.7-24.1, 3,200 27.0-27.9 and 29.3-29.9.  So from PG_RANGE_SEGS
+ * segments per wave each wave takes one chunk, its share of them.  Two register buffers alternate so that the next segment's loads
  * are in flight while the current one is evaluated.
  * PLAN (up to SCAN_PLAN_ROWS rows): every block makes the plan, the token count
  * and the advantages itself in LDS, in blocks of 8 waves so that half as many
