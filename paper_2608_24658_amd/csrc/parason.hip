@@ -72,8 +72,8 @@ Layout layout_for(int64_t n)
     o = align_up(o + units * 9 * sizeof(int64_t));
     o = align_up(o + 64);
     /* the plan is made before, and the reductions run after the row kernels
-     * use their list: four bytes per row hold 16 per PLAN_TILE rows, and a
-     * record per RED_THREADS rows and one more */
+     * use their list: four bytes per row hold 16 per PLAN_TILE rows (the plan's
+     * scratch), and a record per RED_THREADS rows and one more */
     L.plan = L.listed;
     L.moments = L.listed;
     L.fixed = o;
@@ -204,7 +204,11 @@ void launch_reward(const pk::RewardArgs &rw, const pk::DeepArgs &da, bool batch_
     } else if (single) {
         hipLaunchKernelGGL(pk::batch_single<LENIENT>, dim3(1), dim3(threads), 0, stream, rw, da, metrics);
     } else {
-        const int32_t rpt = rw.n <= pk::RED_ONE_ROW ? 1 : pk::ROWS_PER_THREAD;
+        const int64_t rows_per_tile = (rw.n + pk::RED_TILES - 1) / pk::RED_TILES; /* at least, in a batch of millions */
+        const int32_t rpt = rw.n <= pk::RED_ONE_ROW
+                                ? 1
+                                : (int32_t)std::max<int64_t>(pk::ROWS_PER_THREAD,
+                                                             (rows_per_tile + pk::RED_THREADS - 1) / pk::RED_THREADS);
         const int64_t tiles = (rw.n + pk::RED_THREADS * rpt - 1) / (pk::RED_THREADS * rpt);
         hipLaunchKernelGGL(pk::batch_moments<LENIENT>, dim3((unsigned)tiles), dim3(pk::RED_THREADS), 0, stream, rw, da,
                            moments, rpt);

@@ -26,7 +26,7 @@
  *        wave.  A row it cannot hold runs through the grammar's pushdown
  *        automaton on one lane, with MID_DEPTH frames in LDS: Text runs are the
  *        gaps between event positions.
- *   rows_quad  (larger batches: four rows per wave, eight events per lane)
+ *   rows_quad  (larger batches: four rows per wave, one to eight events per lane)
  *        The same, for rows of up to QUAD_EVENTS events; others by the whole
  *        wave as in rows_par.  A row that does not fit that either is listed.
  *   rows_listed  (after rows_quad: one thread per listed row)
@@ -2632,6 +2632,7 @@ struct MetricRec {
 
 constexpr int RED_SINGLE = 1024;     /* rows whose reductions one block does */
 constexpr int RED_ONE_ROW = 1 << 16; /* rows up to which a reduction's thread takes one row */
+constexpr int64_t RED_TILES = 1024;  /* at most so many moment records: every block of the rewards merges them all */
 constexpr int RED_WAVES = RED_SINGLE / WAVE;
 
 /* Sum over the wave of values below 2^32, exact, in every lane. */

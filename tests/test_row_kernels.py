@@ -238,3 +238,27 @@ def test_batch_reductions_on_the_gpu(n, deep):
         rows, R, rs, rt, eta = oracle_expect(tok, st, ln, co, S.CONTIGUOUS_TAGS, G, DEFAULT_COEF, flags)
         compare(got, rows, R, rs, rt, eta, what="n %d flags %d" % (n, flags), exact_reward=not flags)
         check_metrics(got["metrics"], rows, co, R)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("flags", [0, PX.CFG_BATCH_STATS])
+def test_millions_of_rows_on_the_gpu(flags):
+    """Past 4,194,304 rows: the plan's own launch over the tiles (plan_top), and
+    batch statistics whose number of records no longer grows with the batch.  Rows
+    of two to four tokens (some cut off), every output and the metrics."""
+    import torch
+
+    n = (1 << 22) + 1032
+    t = S.CONTIGUOUS_TAGS
+    tok = np.tile(np.array([t[0], 5, 6, t[1]], np.int32), n)
+    rng = np.random.default_rng(4)
+    ln = np.where(rng.random(n) < 0.8, 4, rng.integers(0, 4, n)).astype(np.int32)
+    st = np.arange(n, dtype=np.int64) * 4
+    co = (rng.random(n) < 0.5).astype(np.uint8)
+    px = PX.Parason(t, group_size=G, flags=flags, **DEFAULT_COEF)
+    dev = [torch.as_tensor(x).cuda() for x in (tok, st, ln, co)]
+    got = {k: v.cpu().numpy() for k, v in px.run(*dev, total_tokens=int(ln.sum()), metrics=True).items()}
+    got["flags"] = got["flags"].view(np.uint32)
+    rows, R, rs, rt, eta = oracle_expect(tok, st, ln, co, t, G, DEFAULT_COEF, flags)
+    compare(got, rows, R, rs, rt, eta, what="millions", exact_reward=not flags)
+    check_metrics(got["metrics"], rows, co, R)
