@@ -56,11 +56,10 @@ inline bool is_finite(double x) { return std::isfinite(x); }
 /* The segment plan of n >= 1 rows (one launch on `stream` for up to PLAN_ONE
  * tiles, two for up to PLAN_TWO, else three; defined with the plan kernels):
  * seg_off[0 .. n] and, when given, mode[0 .. n) as the token scan uses them,
- * counters[0 .. 4) cleared.  scratch holds plan_scratch(n) bytes.  With len_sum
+ * counters[0 .. 4) cleared.  scratch holds two int64 per tile.  With len_sum
  * (every tile's token count) the caller has filled in the tiles' segment counts
  * at the start of scratch, and n_tokens receives the sum of len_sum. */
 inline int64_t plan_tile_count(int64_t n) { return (n + pk::PLAN_TILE - 1) / pk::PLAN_TILE; }
-inline size_t plan_scratch(int64_t n) { return (size_t)plan_tile_count(n) * 2 * sizeof(int64_t); }
 void launch_plan(const int64_t *starts, const int32_t *lengths, int64_t n, int64_t mis, void *scratch,
                  int64_t *seg_off, int32_t *counters, uint8_t *mode, const int64_t *len_sum, int64_t *n_tokens,
                  hipStream_t stream);

@@ -131,7 +131,7 @@ class JoinOutputs(ctypes.Structure):
 
 INT_FIELDS = ("total", "latency", "n_subtask", "n_trial", "n_blocks", "max_depth", "first_error_pos")
 FLOAT_FIELDS = ("reward", "r_subtask", "r_trial", "eta", "accel")
-OPTIONAL_FIELDS = ("r_subtask", "r_trial", "eta", "metrics", "accel", "saved")
+OPTIONAL_FIELDS = ("r_subtask", "r_trial", "eta", "metrics", "accel", "saved")  # in the order of Outputs
 
 _OUT_FIELDS = INT_FIELDS + ("flags", "reward")  # required, in the order of Outputs
 
@@ -149,7 +149,7 @@ def _stream(device) -> int:
 def _outputs(out: dict) -> Outputs:
     get = out.get
     ptrs = [out[k].data_ptr() for k in _OUT_FIELDS]
-    for k in ("r_subtask", "r_trial", "eta", "metrics", "accel", "saved"):
+    for k in OPTIONAL_FIELDS:
         t = get(k)
         ptrs.append(t.data_ptr() if t is not None else None)
     return Outputs(*ptrs)
