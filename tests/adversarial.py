@@ -70,8 +70,8 @@ def adversarial_streams():
         streams.append(s[: int(rng.integers(0, len(s) + 1))])
     # empty rows, single tokens
     streams += [[], [GP.THINK], [GP.TEXT], [GP.END_THINK]]
-    # nesting across the three tiers: LDS frames for 5 levels (rows_fast), for
-    # 33 (rows_mid), then global frames (rows_deep)
+    # nesting around the automaton's LDS frames (for 5 and for 33 levels) and
+    # beyond the 64 levels a wave evaluates (global frames)
     streams += [deep_stream(d) for d in (1, 2, 4, 5, 6, 9, 10, 32, 33, 34, 40, 1000)]
     streams.append(deep_stream(300, GP.TRI)[:-5])  # truncated deep
     # fan-out beyond the 64 entries of the fast path, with a thread-count mismatch

@@ -25,7 +25,7 @@ def test_traffic_summary(tmp_path, monkeypatch):
     scan = "void pk::scan_rows<0>(pk::ScanArgs)"
     # the read probe reads each of the run's 262,144 tokens once: 1 MiB, FETCH_SIZE 512 KiB
     _counters(os.path.join(d, "prof_fetch"), "FETCH_SIZE",
-              [(scan, 1000.0), (scan, 1002.0), ("pk::rows_fast<false>(pk::RowArgs)", 10.0),
+              [(scan, 1000.0), (scan, 1002.0), ("void pk::rows_quad<false>(pk::RowArgs)", 10.0),
                ("pk::read_probe(HIP_vector_type<int, 4u> const*, long)", 512.0)])
     _counters(os.path.join(d, "prof_write"), "WRITE_SIZE", [(scan, 7.0), (scan, 9.0)])
     with open(os.path.join(d, "prof_fetch.log"), "w") as f:

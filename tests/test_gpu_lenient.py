@@ -149,7 +149,7 @@ def test_hand_streams_with_gaps(dev, tags):
 
 def test_many_rows_with_gaps(dev):
     """24,576 rows (more than the one-wave-per-row kernel takes): the lenient
-    form of the per-lane automaton, several rows per wave."""
+    form of rows_quad, four rows per wave."""
     log("case lenient many rows")
     tag_ids = S.CONTIGUOUS_TAGS
     P = S.make_params("small", tag_ids=tag_ids)

@@ -137,21 +137,21 @@ def test_metrics_on_large_workload_properties(dev):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("n_rows", [64, 12288])
+@pytest.mark.parametrize("n_rows", [64, 12288, 20480])
 @pytest.mark.parametrize("batch_stats", [False, True])
 def test_deep_rows_with_metrics(dev, n_rows, batch_stats):
-    """Rows nested beyond the LDS tiers (34-60 deep) mixed with shallow ones,
-    under both normalisations and with the batch metrics: the deep tier runs
-    inside the per-group reward launch, or as a launch of its own before the
-    batch-wide statistics.  64 rows take the one-wave row kernel, 12,288 the
-    per-lane one."""
+    """Rows nested 34-60 deep and 70-90 deep (beyond what a wave holds: the deep
+    tier, inside the per-group reward launch or the batch-wide statistics') mixed
+    with shallow ones, under both normalisations and with the batch metrics.  64
+    and 12,288 rows take the one-wave row kernel, 20,480 four rows per wave."""
     from adversarial import deep_stream, pack
     import grammar_pins as GP
 
     log("case deep rows n=%d batch_stats=%s" % (n_rows, batch_stats))
     rng = np.random.default_rng(n_rows + batch_stats)
-    depths = np.concatenate([rng.integers(34, 61, size=6), rng.integers(6, 34, size=n_rows // 4),
-                             rng.integers(1, 6, size=n_rows - 6 - n_rows // 4)])
+    depths = np.concatenate([rng.integers(34, 61, size=6), rng.integers(70, 91, size=4),
+                             rng.integers(6, 34, size=n_rows // 4),
+                             rng.integers(1, 6, size=n_rows - 10 - n_rows // 4)])
     rng.shuffle(depths)
     streams = [deep_stream(int(d), GP.TRI if d % 2 else GP.SUB) for d in depths]
     tokens, starts, lengths = pack(streams, TAGS)
@@ -167,4 +167,4 @@ def test_deep_rows_with_metrics(dev, n_rows, batch_stats):
                                          O.CFG_BATCH_STATS if batch_stats else 0)
     compare(got, rows, R, rs, rt, eta, what="deep rows", exact_reward=not batch_stats)
     check_metrics(got["metrics"], rows, co, R)
-    assert int(np.max(got["max_depth"])) >= 34
+    assert int(np.max(got["max_depth"])) >= 70

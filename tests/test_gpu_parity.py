@@ -88,19 +88,19 @@ def test_adversarial_streams(dev, tags):
     log("adversarial: %d rows ok" % n)
 
 
-@pytest.mark.parametrize("reps", [4, 18])
+@pytest.mark.parametrize("reps", [4, 18, 28])
 @pytest.mark.parametrize("tags", ["scattered", "scattered-compare", "low-ids"])
 def test_tag_lookups_on_the_larger_batch_paths(dev, tags, reps):
     """The hashed and the twelve-compare tag tests in the scan instances and row
     kernels of batches the scan does not plan itself: the adversarial rows
-    repeated 4 times (2,392 rows: the plan launch, then rows_par) and 18 times
-    (10,768 rows with the padding to whole groups: the per-lane row tiers,
-    their gather and the deep tier)."""
+    repeated 4 and 18 times (2,392 and 10,768 rows with the padding to whole
+    groups: the plan launch, then rows_par) and 28 times (more than the 16,384
+    rows of rows_par: rows_quad, rows_listed and the deep tier)."""
     log("case tag lookups tags=%s reps=%d" % (tags, reps))
     tag_ids = {"low-ids": LOW_IDS}.get(tags, S.SCATTERED_TAGS)
     tokens, starts, lengths = pack(adversarial_streams() * reps, tag_ids)
     n = lengths.size
-    assert (n > 2048) and ((n >= 10240) == (reps == 18))
+    assert (n > 2048) and ((n > 16384) == (reps == 28))
     correct = (np.arange(n) % 3 != 2).astype(np.uint8)
     px, coef = px_for(tag_ids, flags=PX.CFG_TAG_COMPARE if tags == "scattered-compare" else 0)
     got = run_gpu(px, to_dev(tokens, torch.int32, dev), to_dev(starts, torch.int64, dev),
@@ -110,22 +110,24 @@ def test_tag_lookups_on_the_larger_batch_paths(dev, tags, reps):
     log("tag lookups: %d rows ok" % n)
 
 
-@pytest.mark.parametrize("n", [0, 8, 2056, 10240])
-def test_batches_without_tokens(dev, n):
+@pytest.mark.parametrize("tags", ["contiguous", "scattered", "scattered-compare"])
+@pytest.mark.parametrize("n", [0, 8, 2056, 10240, 16392])
+def test_batches_without_tokens(dev, n, tags):
     """Degenerate batches: no rows, and rows that are all empty (not one token
     in the batch) on each batch path: the scan's own plan (8 rows), the plan
-    launch with rows_par (2,056), the per-lane row tiers (10,240)."""
-    log("case batch without tokens n=%d" % n)
+    launch with rows_par (2,056 and 10,240), rows_quad (16,392)."""
+    log("case batch without tokens n=%d tags=%s" % (n, tags))
+    tag_ids = TAGS if tags == "contiguous" else S.SCATTERED_TAGS
     tokens = np.zeros(0, np.int32)
     starts = np.zeros(n, np.int64)
     lengths = np.zeros(n, np.int32)
     correct = (np.arange(n) % 2).astype(np.uint8)
-    px, coef = px_for()
+    px, coef = px_for(tag_ids, flags=PX.CFG_TAG_COMPARE if tags == "scattered-compare" else 0)
     got = run_gpu(px, to_dev(tokens, torch.int32, dev), to_dev(starts, torch.int64, dev),
                   to_dev(lengths, torch.int32, dev), to_dev(correct, torch.uint8, dev))
     assert all(v.size == n for v in got.values())
     if n:
-        compare(got, *oracle_expect(tokens, starts, lengths, correct, TAGS, G, coef), what="no tokens")
+        compare(got, *oracle_expect(tokens, starts, lengths, correct, tag_ids, G, coef), what="no tokens")
         assert np.all(got["total"] == 0)
 
 
@@ -156,10 +158,10 @@ def test_text_ids_over_the_whole_int32_range(dev, tags):
 
 @pytest.mark.parametrize("n", [2040, 2048, 2056, 4104])
 def test_plan_boundaries(dev, n):
-    """Around the batch sizes where the plan changes: up to 2,048 rows (that
-    take rows_par) the scan blocks plan the batch themselves; 2,056 rows take
-    the one-block plan launch; 4,104 rows two plan tiles.  Rows of the small
-    workload, every output compared with the oracle."""
+    """Around the batch sizes where the plan changes: up to 2,048 rows the scan
+    blocks plan the batch themselves; 2,056 and 4,104 rows take one plan launch
+    of three and five tiles.  Rows of the small workload, every output compared
+    with the oracle."""
     log("case plan boundary n=%d" % n)
     P = S.make_params("small")
     tok_h, st_h, ln_h, co_h = S.host_batch(P, n)
@@ -170,9 +172,8 @@ def test_plan_boundaries(dev, n):
 
 
 def test_many_rows_beyond_the_first_tier(dev):
-    """40,000 rows nested 6-33 deep (more than the second tier has threads, so
-    its threads stride over the handed-over list) and 48 rows nested 34-60
-    deep (the single-thread tier), mixed with shallow rows."""
+    """40,000 rows nested 6-33 deep and 48 rows nested 34-60 deep (up to as many
+    levels as a wave holds 64), mixed with shallow rows."""
     log("case tiers")
     rng = np.random.default_rng(12)
     depths = np.concatenate([rng.integers(6, 34, size=40000), rng.integers(34, 61, size=48),

@@ -9,16 +9,16 @@ driver tests/simt/emu_main.cpp runs batches through the C-ABI (parason_run and
 parason_run_noalloc) with host memory as device memory.  The emulated device
 reports a chosen number of compute units, which picks the kernels a batch
 takes: with many units every batch here is small (plan, scan_rows, rows_par,
-group_reward); with one or two, rows_fast after gather_rows, then rows_mid and
-the single-thread deep tier.  The workspace is handed over filled with a byte
+group_reward); with one, a batch of more than 64 rows takes rows_quad,
+rows_listed and the single-thread deep tier.  The workspace is handed over filled with a byte
 pattern and sized exactly, so reliance on its contents or reads past it fail.
 
 Planted mistakes in copies of the kernel sources (an off-by-one in a DPP
 segmented scan, a carry lost inside a lane's events of rows_par's segmented
 scan, a lost carry in the scan's compaction, a dropped row-edge mask, an
-unreserved pool part, a tag class read from the wrong table nibble, a
-dynamic scan chunk that ends a segment early, a block pool chunk that starts
-a segment late)
+unreserved pool part, a tag class read from the wrong table nibble, a level's
+list without the blocks inside it, a dynamic scan chunk that ends a segment
+early, a block pool chunk that starts a segment late)
 must each be caught by these comparisons."""
 import os
 import shutil
@@ -108,9 +108,9 @@ def check(binary, tokens, starts, lengths, correct, tags=TAGS, flags=0, cus=2, w
     return got
 
 
-# rows_par for every batch here (fewer rows than 20 waves per emulated unit x 2)
+# rows_par for every batch here (up to 64 rows per emulated unit)
 MANY = 64
-# rows_fast (one row per lane), gather_rows, rows_mid, deep tier
+# rows_quad (four rows per wave), rows_listed, deep tier past 64 rows
 FEW = 1
 
 
@@ -148,11 +148,11 @@ def stretch(stream, total, rng):
     return out + stream[last:]
 
 
-@pytest.mark.parametrize("n,cus", [(8, MANY), (2056, MANY), (64, FEW)])
+@pytest.mark.parametrize("n,cus", [(8, MANY), (2056, MANY), (64, FEW), (72, FEW)])
 def test_emulated_rows_without_tokens(emu, n, cus):
     """Batches of empty rows only (not one token): the scan has no segment to
     read, and each batch path (the scan's own plan, the plan launch with
-    rows_par, the per-lane row tiers) still writes every row's outputs."""
+    rows_par, rows_quad past 64 rows of one unit) still writes every row's outputs."""
     tokens = np.zeros(0, np.int32)
     starts = np.zeros(n, np.int64)
     lengths = np.zeros(n, np.int32)
@@ -234,10 +234,10 @@ def test_emulated_adversarial(emu, tags, cus):
 def test_emulated_lenient_gaps(emu):
     rng = np.random.default_rng(21)
     P = S.make_params("small")
-    tok, st, ln, co = S.host_batch(P, 64)
-    rows = [insert_gaps(tok[st[i]: st[i] + ln[i]], TAGS, rng) for i in range(64)]
+    tok, st, ln, co = S.host_batch(P, 72)
+    rows = [insert_gaps(tok[st[i]: st[i] + ln[i]], TAGS, rng) for i in range(72)]
     lengths = np.array([r.size for r in rows], np.int32)
-    starts = np.zeros(64, np.int64)
+    starts = np.zeros(72, np.int64)
     starts[1:] = np.cumsum(lengths[:-1])
     tokens = np.concatenate(rows)
     for cus in (MANY, FEW):
@@ -246,14 +246,14 @@ def test_emulated_lenient_gaps(emu):
 
 def test_emulated_layouts_noalloc_batch_stats(emu):
     P = S.make_params("small")
-    tok, st, ln, co = S.host_batch(P, 64)
+    tok, st, ln, co = S.host_batch(P, 72)
     for shift in (1, 2, 3):
         check(emu, tok, st, ln, co, cus=MANY, shift=shift, what="shift %d" % shift)
     lmax = int(ln.max()) + 3
-    padded = np.full((64, lmax), 11, np.int32)
-    for i in range(64):
+    padded = np.full((72, lmax), 11, np.int32)
+    for i in range(72):
         padded[i, : ln[i]] = tok[st[i]: st[i] + ln[i]]
-    check(emu, padded.ravel(), (np.arange(64) * lmax).astype(np.int64), ln, co, cus=FEW, what="padded")
+    check(emu, padded.ravel(), (np.arange(72) * lmax).astype(np.int64), ln, co, cus=FEW, what="padded")
     check(emu, tok, st, ln, co, cus=MANY, noalloc=True, what="noalloc")
     check(emu, tok, st, ln, co, flags=PX.CFG_BATCH_STATS, cus=FEW, what="batch stats")
 
@@ -290,6 +290,8 @@ MUTANTS = {
     # second to fourth events (rows_par, four events per lane)
     "lane-carry": ("parason_kernels.h", "if (!seen) v[k] = Op::f(in, v[k]);",
                    "if (!seen && k == 0) v[k] = Op::f(in, v[k]);"),
+    # a level's list in rows_quad leaves out the blocks directly inside it
+    "level-list": ("parason_kernels.h", "inner[k] = word[k] == par_tag(C_END_PAR, lev + 1);", "inner[k] = false;"),
     # a row's edge segments keep tags of the neighbouring rows
     "edge-mask": ("parason_kernels.h",
                   "if (EDGE) hit = hit && q0 + j >= q_lo && q0 + j < q_hi;",
@@ -319,7 +321,7 @@ def test_planted_mistakes_are_caught(tmp_path):
     for name, (p, _) in procs.items():
         assert p.wait() == 0, name
     P = S.make_params("small")
-    tok, st, ln, co = S.host_batch(P, 64)
+    tok, st, ln, co = S.host_batch(P, 72)
     tokens, starts, lengths = pack(adversarial_streams(), TAGS)
     correct = (np.arange(lengths.size) % 3 != 0).astype(np.uint8)
     dyn = dynamic_batch()
