@@ -32,6 +32,13 @@ def test_exports_every_declared_function():
         assert hasattr(L, n), n
 
 
+def test_binding_finds_torchs_stream_call():
+    """The binding reads the current stream's handle through this function of
+    torch, which is not part of its documented interface."""
+    torch = pytest.importorskip("torch")
+    assert callable(torch._C._cuda_getCurrentRawStream)
+
+
 def test_strerror_covers_codes():
     for rc in range(0, -11, -1):
         assert P.strerror(rc) != "unknown status"

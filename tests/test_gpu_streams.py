@@ -38,6 +38,13 @@ def packed(rows):
     return np.concatenate([np.asarray(r, np.int32) for r in rows]), starts, lengths
 
 
+def test_binding_uses_the_current_stream(dev):
+    assert PX._stream(dev) == torch.cuda.current_stream(dev).cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert PX._stream(dev) == side.cuda_stream != 0
+
+
 def test_accounting_on_four_streams(dev):
     log("case four streams")
     strict = PX.Parason(TAGS, group_size=G, **DEFAULT_COEF)
