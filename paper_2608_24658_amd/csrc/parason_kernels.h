@@ -867,9 +867,10 @@ __device__ __forceinline__ void par_seg_scan(int32_t (&v)[K], const ParHeads<K> 
  * a level.  depth: open blocks before the event. */
 __device__ __forceinline__ int32_t par_word(uint32_t c, int32_t depth)
 {
-    const bool own = (c == C_THR) | (c == C_END_THR) | (c == C_END_PAR) | (c == C_END_OUT);
-    const int32_t lev = c == C_PAR ? depth + 1 : (own ? depth : 0);
-    return (int32_t)(c | ((uint32_t)lev & 0xfffu) << 4);
+    constexpr uint32_t BLOCK_TAGS = 1u << C_PAR | 1u << C_END_OUT | 1u << C_THR | 1u << C_END_THR | 1u << C_END_PAR;
+    const uint32_t own = (uint32_t)((int32_t)(BLOCK_TAGS << (31u - c)) >> 31); /* all ones for these, else 0 */
+    const uint32_t lev = (uint32_t)depth + (c == C_PAR ? 1u : 0u);
+    return (int32_t)(c | (lev & own & 0xfffu) << 4);
 }
 __device__ __forceinline__ int32_t par_tag(uint32_t c, int32_t lev) { return (int32_t)c + lev * 16; }
 
@@ -1377,7 +1378,7 @@ __device__ __forceinline__ bool par_eval(const RowArgs &a, ParLds &l, int64_t r,
                     const int32_t w = x[k] & 0xffff;
                     own[k] = w >> 4 == lev;
                     inner[k] = w == par_tag(C_END_PAR, lev + 1);
-                    cnt += own[k] | inner[k] ? 1 : 0;
+                    cnt += (own[k] | inner[k]) ? 1 : 0;
                 }
                 const int32_t incl = dpp_incl_scan<OpAdd>(cnt, lane);
                 int32_t j = n + incl - cnt;
@@ -1672,7 +1673,7 @@ __device__ __forceinline__ void quad_eval(const RowArgs &a, QuadLds &l, int64_t 
         for (int k = 0; k < K; ++k) {
             own[k] = word[k] >> 4 == lev;
             inner[k] = word[k] == par_tag(C_END_PAR, lev + 1);
-            cnt += own[k] | inner[k] ? 1 : 0;
+            cnt += (own[k] | inner[k]) ? 1 : 0;
         }
         const int32_t incl = quad_lane_scan<OpAdd>(cnt);
         int32_t j = incl - cnt;
@@ -1710,7 +1711,7 @@ __device__ __forceinline__ void quad_eval(const RowArgs &a, QuadLds &l, int64_t 
  * loads: par_row spends a wave's instructions on one row, whose events fill a
  * sixth of its 256 places, and the per-lane automaton's lanes wait for each other
  * in most of its states.  64,000 rows of 20,000 tokens: 48-60 us, one wave per
- * row 124, one lane per row 219; 712,000 rows: 362 us, 1,266, 644.  With eight
+ * row 124, one lane per row 219; 712,000 rows: 352 us, 1,266, 644.  With eight
  * events per lane for every row, and up to eight of a level's, it took 133 vector
  * registers (three waves per SIMD) and 65-73 and 589 us; levels of at most four
  * entries per lane and pass leave 96, so that the five waves the LDS has room for
